@@ -392,6 +392,50 @@ qgtc_status qgtc_layer_static(const qgtc_bits* A, const qgtc_tile_map* map,
                               void* out, int64_t ld_out, void* stream);
 
 /* ---------------------------------------------------------------------------
+ * A stack of layers on one adjacency in one call (the driver loop of Section 4.5: every
+ * hidden layer hands low-bit codes to the next one, the last emits fp32 or int32).  The
+ * same integers as qgtc_pack_bits followed by qgtc_layer per layer; the activations between
+ * the layers stay in two buffers of the caller in a form only the library reads (the codes
+ * as bytes in the operand order of the int8 matrix instruction), which saves forming bit
+ * planes and putting them back together.
+ *   first, second   the epilogues of the layer's two products, as agg_ep and upd_ep of
+ *                   qgtc_layer: first is QGTC_OUT_BITS with at most 8 bits; second is
+ *                   QGTC_OUT_BITS with s bits for a hidden layer, QGTC_OUT_F32 or _I32 for the
+ *                   last (tuning: second's)
+ *   W               RIGHT_BYTES
+ *   buffer[2]       device, 16-byte aligned, buffer_bytes each: at least
+ *                   qgtc_stack_buffer_bytes(rows, columns) of every layer's input
+ * Limits: s and t at most 8 bits, at most 1024 input and 256 output columns per layer, A
+ * square or block-diagonal (else QGTC_ERR_UNSUPPORTED / _SHAPE).
+ *
+ * qgtc_stack_input    Eq. (2) of fp32 features into `buffer` (buffer[0] of the pass to come)
+ * qgtc_stack_forward  the pass.  Features: src != NULL - fp32, quantized first with q; else
+ *                     X != NULL - packed planes (RIGHT, s bits); else what
+ *                     qgtc_stack_input left in buffer[0]. */
+typedef struct qgtc_stack_layer {
+  qgtc_bits W;
+  qgtc_epilogue first;
+  qgtc_epilogue second;
+} qgtc_stack_layer;
+
+typedef struct qgtc_stack {
+  const qgtc_bits* A;
+  const qgtc_tile_map* map;           /* or NULL */
+  const qgtc_stack_layer* layers;     /* HOST array */
+  int32_t n_layers;
+  int32_t s;
+  void* buffer[2];
+  size_t buffer_bytes;
+} qgtc_stack;
+
+size_t qgtc_stack_buffer_bytes(int32_t rows, int32_t cols);
+qgtc_status qgtc_stack_input(const float* src, int32_t rows, int32_t cols, int64_t ld_src,
+                             const qgtc_quant* q, void* buffer, size_t buffer_bytes, void* stream);
+qgtc_status qgtc_stack_forward(const qgtc_stack* stack, const float* src, int64_t ld_src,
+                               const qgtc_quant* q, const qgtc_bits* X, void* out, int64_t ld_out,
+                               void* stream);
+
+/* ---------------------------------------------------------------------------
  * Non-zero tiles of A at the three tile widths qgtc_aggregate takes, in one pass over
  * the packed adjacency (the second kind of zero tiles of the paper's Section 6.3, gaps
  * inside a subgraph, shows as fewer non-zero tiles at narrower widths):

@@ -63,6 +63,15 @@ class _EpilogueC(C.Structure):
                 ("tuning", C.POINTER(_TuningC))]
 
 
+class _StackLayerC(C.Structure):
+    _fields_ = [("W", _BitsC), ("first", _EpilogueC), ("second", _EpilogueC)]
+
+
+class _StackC(C.Structure):
+    _fields_ = [("A", C.POINTER(_BitsC)), ("map", C.POINTER(_TileMapC)), ("layers", C.POINTER(_StackLayerC)),
+                ("n_layers", C.c_int32), ("s", C.c_int32), ("buffer", C.c_void_p * 2), ("buffer_bytes", C.c_size_t)]
+
+
 class _PlanInC(C.Structure):
     _fields_ = [("rows", C.c_int32), ("in_cols", C.c_int32), ("out_cols", C.c_int32),
                 ("s", C.c_int32), ("t", C.c_int32), ("n_tile_rows", C.c_int32),
@@ -129,6 +138,9 @@ def lib():
                                  P(_EpilogueC), vp, sz, vp, i64, vp]),
         "qgtc_layer_static": (C.c_int, [P(_BitsC), P(_TileMapC), P(_BitsC), P(_BitsC), P(_EpilogueC),
                                         P(_EpilogueC), vp, i64, vp]),
+        "qgtc_stack_buffer_bytes": (sz, [i32, i32]),
+        "qgtc_stack_input": (C.c_int, [vp, i32, i32, i64, P(_QuantC), vp, sz, vp]),
+        "qgtc_stack_forward": (C.c_int, [P(_StackC), vp, i64, P(_QuantC), P(_BitsC), vp, i64, vp]),
         "qgtc_tile_stats": (C.c_int, [P(_BitsC), vp, vp]),
         "qgtc_plan_layer": (C.c_int, [P(_PlanInC), P(_PlanOutC)]),
         "qgtc_quant_inv_scale": (C.c_float, [C.c_double, C.c_double, i32]),
@@ -399,6 +411,48 @@ def qgtc_layer_static(A: Bits, tmap: TileMap | None, X: Bits, W: Bits, agg_ep: E
     _check(lib().qgtc_layer_static(C.byref(A.c), m, C.byref(X.c), C.byref(W.c), C.byref(a),
                                    C.byref(u), ptr, ld, _stream()), "qgtc_layer_static")
     return res
+
+
+class Stack:
+    """A stack of layers ready to run (qgtc_stack): adjacency, map, one (W, first epilogue,
+    second epilogue) per layer, and the two activation buffers.  Holds on to every tensor it
+    points at."""
+
+    def __init__(self, A: Bits, tmap: TileMap | None, layers, s: int, buffers):
+        self.keep = (A, tmap, layers, buffers)
+        self.rows, self.in_cols = A.rows, layers[0][0].rows
+        self._layers = (_StackLayerC * len(layers))()
+        for dst, (W, first, second) in zip(self._layers, layers):
+            dst.W, dst.first, dst.second = W.c, first.to_c(), second.to_c()
+        nbytes = buffers[0].numel() * buffers[0].element_size()
+        self.c = _StackC(C.pointer(A.c), C.pointer(tmap.c) if tmap is not None else None, self._layers, len(layers), s,
+                         (C.c_void_p * 2)(*[b.data_ptr() for b in buffers]), nbytes)
+
+
+def qgtc_stack_input(src: torch.Tensor, nbits: int, quant, buffer: torch.Tensor):
+    """Eq. (2) of fp32 features into an activation buffer."""
+    assert src.dim() == 2 and src.dtype == torch.float32 and src.is_cuda and src.stride(1) == 1
+    rows, cols = src.shape
+    q = _QuantC(float(quant[0]), float(quant[1]), nbits)
+    _check(lib().qgtc_stack_input(src.data_ptr(), rows, cols, src.stride(0) if rows > 1 else max(cols, 1), C.byref(q),
+                                  buffer.data_ptr(), buffer.numel() * buffer.element_size(), _stream()), "qgtc_stack_input")
+
+
+def qgtc_stack_forward(stack: Stack, out: torch.Tensor, src: torch.Tensor | None = None, quant=None,
+                       X: Bits | None = None):
+    """One pass: from fp32 features (src, quant), from packed planes (X), or from what
+    qgtc_stack_input left in the stack's first buffer."""
+    q = ptr = None
+    ld = 0
+    if src is not None:
+        assert src.dtype == torch.float32 and src.is_cuda and src.stride(1) == 1
+        assert tuple(src.shape) == (stack.rows, stack.in_cols)
+        q = C.byref(_QuantC(float(quant[0]), float(quant[1]), stack.c.s))
+        ptr, ld = src.data_ptr(), src.stride(0) if src.shape[0] > 1 else max(src.shape[1], 1)
+    assert out.stride(1) == 1
+    _check(lib().qgtc_stack_forward(C.byref(stack.c), ptr, ld, q, C.byref(X.c) if X is not None else None, out.data_ptr(),
+                                    out.stride(0) if out.shape[0] > 1 else max(out.shape[1], 1), _stream()),
+           "qgtc_stack_forward")
 
 
 LAYER_FUSED, LAYER_TWO_KERNELS = 0, 1

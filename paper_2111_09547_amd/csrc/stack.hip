@@ -1,0 +1,219 @@
+// A stack of layers with its activations kept as codes in operand order (layer.h): the
+// quantizer writes the first layer's, every hidden layer the next one's, so that staging X
+// is a plain copy and no bit plane is formed or put back together between the layers.
+#include "layer.h"
+
+namespace qgtc {
+namespace {
+
+struct CodesParams {
+  const float* src;
+  int64_t ld_src;
+  int32_t rows, cols;
+  int32_t ct;                // 16-column tiles per column group
+  int64_t cg_bytes;
+  uint8_t* dst;
+  float lo, inv, qmaxf;
+  uint32_t flip;             // 0x80808080 for 8-bit codes
+  int32_t n_quads;           // groups of four columns, padding of the last column group included
+  uint32_t quad_magic;
+};
+
+// Eq. (2) for at most 8 bits: the clamp on the float (a NaN gives 0), truncation of a
+// non-negative value is its floor.
+__device__ __forceinline__ uint32_t quantize_small(float x, float lo, float inv, float qmaxf) {
+  return (uint32_t)__builtin_amdgcn_fmed3f((x - lo) * inv, 0.0f, qmaxf);
+}
+
+// Thread (word row kw, half h, four columns): the 16 rows 32 kw + 4 h + {0..3} + 8 {0..3}, four
+// columns each, become four code words of four columns: 64 consecutive bytes.  HBM-bound; all
+// 16 loads of a thread are in flight together.  VEC: rows are read 16 bytes at a time.
+template <bool VEC>
+__global__ __launch_bounds__(256) void pack_codes_kernel(const CodesParams p) {
+  const unsigned idx = blockIdx.x * 256u + threadIdx.x;
+  const unsigned rest = p.quad_magic ? __umulhi(idx, p.quad_magic) : idx;
+  const int quad = (int)(idx - rest * (unsigned)p.n_quads);
+  const int h = (int)(rest & 1u);
+  const int kw = (int)(rest >> 1);
+  const int r0 = kw * 32 + 4 * h;
+  if (kw * 32 >= p.rows) return;
+  const int c0 = quad * 4;
+  float v[4][4][4];                                  // [byte][word][column]
+#pragma unroll
+  for (int b = 0; b < 4; ++b)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float* row = p.src + (int64_t)min(r0 + 8 * b + r, p.rows - 1) * p.ld_src;
+      if (VEC) {
+        const float4 q = *reinterpret_cast<const float4*>(row + min(c0, p.cols - 4));
+        v[b][r][0] = q.x; v[b][r][1] = q.y; v[b][r][2] = q.z; v[b][r][3] = q.w;
+      } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[b][r][k] = row[min(c0 + k, p.cols - 1)];
+      }
+    }
+  const bool whole = kw * 32 + 32 <= p.rows;
+  uint8_t* dst = p.dst + codes_offset(c0, p.ct, p.cg_bytes, kw) + h * 256 * p.ct;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    uint32_t w[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      w[r] = 0u;
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {
+        uint32_t q = quantize_small(v[b][r][k], p.lo, p.inv, p.qmaxf);
+        if (!whole && r0 + 8 * b + r >= p.rows) q = 0u;
+        w[r] |= q << (8 * b);
+      }
+      w[r] = (c0 + k < p.cols ? w[r] : 0u) ^ p.flip;
+    }
+    *reinterpret_cast<uint4*>(dst + 16 * k) = make_uint4(w[0], w[1], w[2], w[3]);
+  }
+}
+
+int64_t codes_cg_bytes(int rows, int ct) { return (int64_t)cdiv(rows, 32) * (512 * ct); }
+
+qgtc_status pack_codes(const float* src, int64_t ld_src, int rows, int cols, const qgtc_quant* q, uint8_t* dst,
+                       hipStream_t stream) {
+  CodesParams p{};
+  p.src = src;
+  p.ld_src = ld_src;
+  p.rows = rows;
+  p.cols = cols;
+  p.ct = agg_col_tiles(cols);
+  p.cg_bytes = codes_cg_bytes(rows, p.ct);
+  p.dst = dst;
+  p.lo = (float)q->lo;
+  p.inv = qgtc_quant_inv_scale(q->lo, q->hi, q->nbits);
+  p.qmaxf = (float)((1u << q->nbits) - 1u);
+  p.flip = q->nbits == 8 ? 0x80808080u : 0u;
+  p.n_quads = cdiv(cols, 16 * p.ct) * 4 * p.ct;
+  p.quad_magic = div_magic(p.n_quads);
+  const int64_t items = (int64_t)cdiv(rows, 32) * 2 * p.n_quads;
+  const dim3 grid((unsigned)cdiv(items, 256));
+  ProfScope prof(QGTC_KERNEL_PACK, stream);
+  if (cols % 4 == 0 && ld_src % 4 == 0 && ((uintptr_t)src & 15u) == 0)
+    hipLaunchKernelGGL(pack_codes_kernel<true>, grid, dim3(256), 0, stream, p);
+  else
+    hipLaunchKernelGGL(pack_codes_kernel<false>, grid, dim3(256), 0, stream, p);
+  return launch_status();
+}
+
+}  // namespace
+
+qgtc_status layer_codes(const qgtc_bits* A, const qgtc_tile_map* map, const qgtc_bits* X, const uint8_t* x_codes,
+                        int x_cols, int s, const qgtc_bits* W, const qgtc_epilogue* agg_ep, const qgtc_epilogue* upd_ep,
+                        uint8_t* out_codes, void* out, int64_t ld_out, hipStream_t stream) {
+  LayerParams p{};
+  qgtc_bits x{};                                     // codes: the shape only
+  if (X) {
+    x = *X;
+  } else {
+    qgtc_describe(&x, A->block_rows > 0 ? A->rows : A->cols, x_cols, s, QGTC_RIGHT, 0);
+    x.data = reinterpret_cast<uint32_t*>(const_cast<uint8_t*>(x_codes));
+  }
+  qgtc_status st = agg_fill_params(A, map, &x, &p.a);
+  if (st != QGTC_OK) return st;
+  if (W->rows != x.cols || !plan_fused_applies(x.cols, W->cols, s, W->nbits)) return QGTC_ERR_SHAPE;
+  if (!X) {
+    const int64_t bytes = codes_cg_bytes(x.rows, agg_col_tiles(x.cols));
+    if (bytes >= (int64_t)1 << 32) return QGTC_ERR_UNSUPPORTED;
+    p.a.x_bytes = (uint32_t)bytes;
+  }
+  if (out_codes) {
+    EpiParams& u = p.up;
+    u.mode = kOutCodes;
+    u.relu = upd_ep->relu ? 1 : 0;
+    u.rq_nbits = upd_ep->rq_nbits;
+    u.rq_lo = upd_ep->rq_lo;
+    u.rq_inv_scale = upd_ep->rq_inv_scale;
+    u.col_a = upd_ep->col_scale;
+    u.col_b = upd_ep->col_shift;
+    u.out = out_codes;
+    const int ct = agg_col_tiles(W->cols);
+    u.ld_out = ct >> 1;                              // (1, 2, 4: 0, 1, 2)
+    u.ps_out = codes_cg_bytes(A->rows, ct);
+  } else {
+    st = make_epilogue(upd_ep, out, ld_out, A->rows, W->cols, QGTC_RIGHT, false, &p.up);
+    if (st != QGTC_OK) return st;
+  }
+  EpiParams& e = p.a.ep;
+  e.relu = agg_ep->relu ? 1 : 0;
+  e.self_term = agg_ep->self_term ? 1 : 0;
+  e.rq_nbits = agg_ep->rq_nbits;
+  e.rq_lo = agg_ep->rq_lo;
+  e.rq_inv_scale = agg_ep->rq_inv_scale;
+  return layer_run(&p, layer_split(A->rows, x.cols, W->cols), X == nullptr, W, upd_ep, stream);
+}
+
+}  // namespace qgtc
+
+using namespace qgtc;
+
+extern "C" size_t qgtc_stack_buffer_bytes(int32_t rows, int32_t cols) {
+  if (rows < 0 || cols < 0) return 0;
+  const int ct = agg_col_tiles(cols);
+  return (size_t)cdiv(cols, 16 * ct) * (size_t)codes_cg_bytes(rows, ct);
+}
+
+extern "C" qgtc_status qgtc_stack_input(const float* src, int32_t rows, int32_t cols, int64_t ld_src, const qgtc_quant* q,
+                                        void* buffer, size_t buffer_bytes, void* stream) {
+  if (!src || !q || !buffer) return QGTC_ERR_NULL;
+  if (rows < 0 || cols < 0 || ld_src < cols || !(q->hi > q->lo)) return QGTC_ERR_SHAPE;
+  if (q->nbits < 1 || q->nbits > 8) return QGTC_ERR_BITWIDTH;
+  if (((uintptr_t)buffer & 15u) != 0) return QGTC_ERR_ALIGN;
+  if (buffer_bytes < qgtc_stack_buffer_bytes(rows, cols)) return QGTC_ERR_WORKSPACE;
+  if (rows == 0 || cols == 0) return QGTC_OK;
+  return pack_codes(src, ld_src, rows, cols, q, reinterpret_cast<uint8_t*>(buffer), reinterpret_cast<hipStream_t>(stream));
+}
+
+extern "C" qgtc_status qgtc_stack_forward(const qgtc_stack* st, const float* src, int64_t ld_src, const qgtc_quant* q,
+                                          const qgtc_bits* X, void* out, int64_t ld_out, void* stream) {
+  if (!st || !st->A || !st->layers || !st->buffer[0] || !st->buffer[1]) return QGTC_ERR_NULL;
+  if (st->n_layers < 1) return QGTC_ERR_SHAPE;
+  // everything is checked before anything is launched
+  qgtc_status rc = check_adjacency(st->A);
+  if (rc != QGTC_OK) return rc;
+  const int rows = st->A->rows;
+  if (st->A->block_rows == 0 && st->A->cols != rows) return QGTC_ERR_SHAPE;
+  for (int l = 0; l < st->n_layers; ++l) {
+    const qgtc_stack_layer& y = st->layers[l];
+    const bool last = l == st->n_layers - 1;
+    rc = check_bits(&y.W, QGTC_RIGHT_BYTES);
+    if (rc != QGTC_OK) return rc;
+    if (l > 0 && y.W.rows != st->layers[l - 1].W.cols) return QGTC_ERR_SHAPE;
+    if (!plan_fused_applies(y.W.rows, y.W.cols, st->s, y.W.nbits)) return QGTC_ERR_UNSUPPORTED;
+    if (y.first.mode != QGTC_OUT_BITS || (last ? y.second.mode == QGTC_OUT_BITS : y.second.mode != QGTC_OUT_BITS))
+      return QGTC_ERR_UNSUPPORTED;
+    if (y.first.rq_nbits < 1 || y.first.rq_nbits > 8 || (!last && y.second.rq_nbits != st->s)) return QGTC_ERR_BITWIDTH;
+    if (!(y.first.rq_inv_scale > 0.0f) || (!last && !(y.second.rq_inv_scale > 0.0f))) return QGTC_ERR_SHAPE;
+    rc = check_tuning(y.second.tuning);
+    if (rc != QGTC_OK) return rc;
+    if (st->buffer_bytes < qgtc_stack_buffer_bytes(rows, y.W.rows)) return QGTC_ERR_WORKSPACE;
+  }
+  if (!out && rows > 0) return QGTC_ERR_NULL;
+  const int d0 = st->layers[0].W.rows;
+  if (X) {
+    rc = check_bits(X, QGTC_RIGHT);
+    if (rc != QGTC_OK) return rc;
+    if (X->rows != rows || X->cols != d0) return QGTC_ERR_SHAPE;
+    if (X->nbits != st->s) return QGTC_ERR_BITWIDTH;
+  }
+  if (src) {
+    if (q && q->nbits != st->s) return QGTC_ERR_BITWIDTH;
+    rc = qgtc_stack_input(src, rows, d0, ld_src, q, st->buffer[0], st->buffer_bytes, stream);
+    if (rc != QGTC_OK) return rc;
+  }
+  if (rows == 0) return QGTC_OK;
+  hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+  for (int l = 0; l < st->n_layers; ++l) {
+    const qgtc_stack_layer& y = st->layers[l];
+    const bool last = l == st->n_layers - 1;
+    rc = layer_codes(st->A, st->map, l == 0 ? X : nullptr, reinterpret_cast<const uint8_t*>(st->buffer[l & 1]), y.W.rows,
+                     st->s, &y.W, &y.first, &y.second, last ? nullptr : reinterpret_cast<uint8_t*>(st->buffer[(l + 1) & 1]),
+                     out, ld_out, s);
+    if (rc != QGTC_OK) return rc;
+  }
+  return QGTC_OK;
+}

@@ -122,9 +122,19 @@ class QuantGNN:
         dmax = max(d for d, _ in self.dims)
         ws_bytes = max(B.lib().qgtc_layer_workspace_bytes(n, d, h, s) for d, h in self.dims)
         self.workspace = torch.empty(ws_bytes // 4 + 1, dtype=torch.int32, device=self.A.words.device)
-        # ping-pong buffers for the low-bit activations between layers
         hmax = max(h for _, h in self.dims)
-        self.x_bufs = [B.alloc_bits(n, max(dmax, hmax), s, B.RIGHT) for _ in range(2)]
+        # Layers of at most 8 bits run as one native call on codes in operand order
+        # (qgtc_stack_forward): two activation buffers.  Everything else goes layer by layer on
+        # bit planes: ping-pong buffers of planes, made when they are first needed.
+        self._fused = not update_first and all(lay == B.RIGHT_BYTES for lay in self.w_layout) and \
+            (self.tuning is None or self.tuning.layer_path == B.LAYER_FUSED)
+        self._wmax = max(dmax, hmax)
+        self._x_bufs = None
+        self._x_form = None            # what the last packing of the input left: "codes" or "planes"
+        self._stacks = {}
+        if self._fused:
+            nbytes = max(B.lib().qgtc_stack_buffer_bytes(n, d) for d, _ in self.dims)
+            self._codes = [torch.empty(max(nbytes // 4, 4), dtype=torch.int32, device=self.A.words.device) for _ in range(2)]
         if update_first:                 # activations between layers as left operands of the update
             self.xl_bufs = [B.alloc_bits(n, max(dmax, hmax), s, B.LEFT) for _ in range(2)]
         self.pack_static()
@@ -149,7 +159,11 @@ class QuantGNN:
             # only the last layer dequantizes, so only its column sums are needed
             self.w_colsum = [None] * (len(self.W) - 1) + [B.qgtc_col_sums(self.W[-1], out=self._w_colsum_buf)]
             if X is not None and not self.update_first:
-                self.pack_input(X, x_range)
+                if self._fused and X.dtype == torch.float32:
+                    B.qgtc_stack_input(X, self.s, x_range, self._codes[0])
+                    self._x_form = "codes"
+                else:
+                    self.pack_input(X, x_range)
         if self.A_src is not None:
             B.qgtc_pack_bits(self.A_src, 1, B.LEFT, out=self.A)
         if self.use_map:
@@ -160,6 +174,12 @@ class QuantGNN:
         cur.wait_stream(self._w_stream)
 
     # -- helpers -----------------------------------------------------------------
+    @property
+    def x_bufs(self):
+        if self._x_bufs is None:
+            self._x_bufs = [B.alloc_bits(self.A.rows, self._wmax, self.s, B.RIGHT) for _ in range(2)]
+        return self._x_bufs
+
     def _x_view(self, which: int, cols: int) -> B.Bits:
         """A [N, cols] RIGHT-packed view on one of the activation buffers.  Every view has
         the strides of the widest layer, so that a range of rows is the same range of
@@ -222,6 +242,7 @@ class QuantGNN:
         return B.Bits(full.words, d)
 
     def pack_input(self, X: torch.Tensor, x_range) -> B.Bits:
+        self._x_form = "planes"
         return B.qgtc_pack_bits(X, self.s, B.RIGHT, quant=x_range,
                                 out=self._x_view(0, X.shape[1]))
 
@@ -366,6 +387,17 @@ class QuantGNN:
                               device=self.A.words.device)
         if self.update_first:
             return self._forward_update_first(X, x_range, ranges, out, want_int)
+        if self._fused and (x_bits is not None or x_packed or X.dtype == torch.float32):
+            # one run whatever `streams` says: the launches of a stack fill the device by themselves
+            stack = self._stack(x_range, ranges, want_int)
+            if x_bits is not None:
+                B.qgtc_stack_forward(stack, out, X=x_bits)
+            elif x_packed:
+                B.qgtc_stack_forward(stack, out, X=self._x_view(0, self.dims[0][0]) if self._x_form == "planes" else None)
+            else:
+                self._x_form = "codes"
+                B.qgtc_stack_forward(stack, out, src=X, quant=x_range)
+            return out
         if x_bits is not None:
             assert isinstance(streams, int) and streams <= 1
             xb = x_bits
@@ -480,32 +512,53 @@ class QuantGNN:
                         layer_ksplit=plan["ksplit"], zero_words=base.zero_words,
                         even_progress=base.even_progress or (plan["even_progress"] if same_form else 1))
 
-    def _run_layers(self, r0, r1, A, tmap, deg, xb, x_range, ranges, out, want_int, workspace):
-        """All layers on rows [r0, r1) (whole subgraphs), on the current stream."""
-        n_layers = len(self.W)
-        whole = r0 == 0 and r1 == self.A.rows
-        # the first layer's codes stand for x_lo + x_scale * code; behind a hidden layer the
-        # codes are read as pure scales (x_lo = 0)
+    def _stack(self, x_range, ranges, want_int) -> "B.Stack":
+        """The prepared native call for these ranges (a caller's handful of them is kept)."""
+        key = (float(x_range[0]), float(x_range[1]), bool(want_int), id(self.tuning),
+               self.map.c.row_cnt if self.map is not None else None, self.deg.data_ptr(),
+               *[(r.agg_hi, r.out_hi) for r in ranges])
+        stack = self._stacks.get(key)
+        if stack is None:
+            layers = [(W, first, second) for W, (first, second) in zip(self.W, self._epilogues(x_range, ranges, want_int))]
+            stack = B.Stack(self.A, self.map, layers, self.s, self._codes)
+            if len(self._stacks) >= 8:
+                self._stacks.pop(next(iter(self._stacks)))
+            self._stacks[key] = stack
+        return stack
+
+    def _epilogues(self, x_range, ranges, want_int):
+        """(first, second) epilogue of every layer.  The first layer's codes stand for x_lo +
+        x_scale * code; behind a hidden layer they are read as pure scales (x_lo = 0)."""
         x_lo = float(x_range[0])
         x_scale = (float(x_range[1]) - float(x_range[0])) / float(2 ** self.s)
-        for l, W in enumerate(self.W):
-            r = ranges[l]
-            last = l == n_layers - 1
-            agg_ep, ep, z_scale, x_next = self._layer_eps(l, x_lo, x_scale, r.agg_hi, r.out_hi, last)
-            tuning = self._run_tuning(l, whole)
-            ep.tuning = tuning
+        out = []
+        for l, r in enumerate(ranges):
+            last = l == len(self.W) - 1
+            first, second, z_scale, x_next = self._layer_eps(l, x_lo, x_scale, r.agg_hi, r.out_hi, last)
             if not last:
                 if self.batchnorm[l] is not None:
-                    ep.col_scale, ep.col_shift = self._bn_fold(l, z_scale)
-                xb = B.qgtc_layer(A, tmap, xb, W, agg_ep, ep, workspace,
-                                  out=self._x_rows((l + 1) & 1, self.dims[l][1], r0, r1))
+                    second.col_scale, second.col_shift = self._bn_fold(l, z_scale)
                 x_lo, x_scale = 0.0, x_next
             elif want_int:
-                B.qgtc_layer(A, tmap, xb, W, agg_ep, B.Epilogue(mode=B.OUT_I32, tuning=tuning), workspace,
-                             out=out)
+                second = B.Epilogue(mode=B.OUT_I32)
             else:
                 # row_i = None: the layer takes the row sums of its own requantized Y
-                ep.row_l, ep.col_i = deg, self.w_colsum[l]
+                second.row_l, second.col_i = self.deg, self.w_colsum[l]
                 if self.batchnorm[l] is not None:      # acts on the real output value
-                    ep.col_scale, ep.col_shift = self._bn_fold(l, 1.0)
-                B.qgtc_layer(A, tmap, xb, W, agg_ep, ep, workspace, out=out)
+                    second.col_scale, second.col_shift = self._bn_fold(l, 1.0)
+            second.tuning = self.tuning
+            out.append((first, second))
+        return out
+
+    def _run_layers(self, r0, r1, A, tmap, deg, xb, x_range, ranges, out, want_int, workspace):
+        """All layers on rows [r0, r1) (whole subgraphs), on the current stream."""
+        whole = r0 == 0 and r1 == self.A.rows
+        for l, (W, (first, second)) in enumerate(zip(self.W, self._epilogues(x_range, ranges, want_int))):
+            second.tuning = self._run_tuning(l, whole)
+            if l < len(self.W) - 1:
+                xb = B.qgtc_layer(A, tmap, xb, W, first, second, workspace,
+                                  out=self._x_rows((l + 1) & 1, self.dims[l][1], r0, r1))
+            else:
+                if second.row_l is not None:
+                    second.row_l = deg
+                B.qgtc_layer(A, tmap, xb, W, first, second, workspace, out=out)
