@@ -369,14 +369,17 @@ __device__ __forceinline__ void agg_list(const AggParams& p, AggWave* w, uint8_t
 // Wave-wide loads of 16 bytes per lane straight to LDS address `to` (+ 16 lane).  Written as
 // assembly because the compiler, which sees such a load as a store to LDS, would make every
 // later read of LDS wait for it: nothing would overlap.  wait_loads() and a barrier complete them.
+// The scalar offset is held to the buffer's size: the unit compares the lane's offset with size -
+// scalar offset, which must not wrap (a unit without rows has size 0, stages past the last chunk
+// lie behind the end).
 __device__ __forceinline__ void load_lds(const v4u& rsrc, uint32_t voff, uint32_t soff, uint32_t to) {
   asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
-               :: "v"(voff), "s"(rsrc), "s"(soff), "s"(to) : "memory", "m0");
+               :: "v"(voff), "s"(rsrc), "s"(min(soff, rsrc.z)), "s"(to) : "memory", "m0");
 }
 __device__ __forceinline__ void load_lds_2k(const v4u& rsrc, uint32_t voff, uint32_t soff, uint32_t to) {
   asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds\n\t"
                "buffer_load_dwordx4 %0, %1, %2 offen offset:1024 lds"
-               :: "v"(voff), "s"(rsrc), "s"(soff), "s"(to) : "memory", "m0");
+               :: "v"(voff), "s"(rsrc), "s"(min(soff, rsrc.z)), "s"(to) : "memory", "m0");
 }
 // At most about n of the wave's loads are still on their way.
 __device__ __forceinline__ void wait_loads(int n) {

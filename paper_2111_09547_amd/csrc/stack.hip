@@ -31,8 +31,13 @@ __device__ __forceinline__ uint32_t quantize_small(float x, float lo, float inv,
 template <bool VEC>
 __global__ __launch_bounds__(256) void pack_codes_kernel(const CodesParams p) {
   const unsigned idx = blockIdx.x * 256u + threadIdx.x;
-  const unsigned rest = p.quad_magic ? __umulhi(idx, p.quad_magic) : idx;
-  const int quad = (int)(idx - rest * (unsigned)p.n_quads);
+  // (the product with the rounded-up reciprocal is at most one too large, for any idx)
+  unsigned rest = p.quad_magic ? __umulhi(idx, p.quad_magic) : idx;
+  int quad = (int)(idx - rest * (unsigned)p.n_quads);
+  if (quad < 0) {
+    quad += p.n_quads;
+    --rest;
+  }
   const int h = (int)(rest & 1u);
   const int kw = (int)(rest >> 1);
   const int r0 = kw * 32 + 4 * h;
@@ -194,6 +199,19 @@ extern "C" qgtc_status qgtc_stack_forward(const qgtc_stack* st, const float* src
   }
   if (!out && rows > 0) return QGTC_ERR_NULL;
   const int d0 = st->layers[0].W.rows;
+  if (rows > 0) {
+    const qgtc_stack_layer& y = st->layers[st->n_layers - 1];
+    EpiParams e{};
+    rc = make_epilogue(&y.second, out, ld_out, rows, y.W.cols, QGTC_RIGHT, false, &e);
+    if (rc != QGTC_OK) return rc;
+    if (codes_cg_bytes(rows, 4) >= (int64_t)1 << 32) return QGTC_ERR_UNSUPPORTED;
+    AggParams a{};
+    qgtc_bits x{};                                   // the shape only
+    qgtc_describe(&x, rows, d0, st->s, QGTC_RIGHT, 0);
+    x.data = reinterpret_cast<uint32_t*>(st->buffer[0]);
+    rc = agg_fill_params(st->A, st->map, X ? X : &x, &a);
+    if (rc != QGTC_OK) return rc;
+  }
   if (X) {
     rc = check_bits(X, QGTC_RIGHT);
     if (rc != QGTC_OK) return rc;
