@@ -420,7 +420,8 @@ class Stack:
 
     def __init__(self, A: Bits, tmap: TileMap | None, layers, s: int, buffers):
         self.keep = (A, tmap, layers, buffers)
-        self.rows, self.in_cols = A.rows, layers[0][0].rows
+        self.rows, self.in_cols, self.out_cols = A.rows, layers[0][0].rows, layers[-1][0].cols
+        self.last = layers[-1][2]
         self._layers = (_StackLayerC * len(layers))()
         for dst, (W, first, second) in zip(self._layers, layers):
             dst.W, dst.first, dst.second = W.c, first.to_c(), second.to_c()
@@ -445,14 +446,13 @@ def qgtc_stack_forward(stack: Stack, out: torch.Tensor, src: torch.Tensor | None
     q = ptr = None
     ld = 0
     if src is not None:
-        assert src.dtype == torch.float32 and src.is_cuda and src.stride(1) == 1
+        assert src.dim() == 2 and src.dtype == torch.float32 and src.is_cuda and src.stride(1) == 1
         assert tuple(src.shape) == (stack.rows, stack.in_cols)
         q = C.byref(_QuantC(float(quant[0]), float(quant[1]), stack.c.s))
         ptr, ld = src.data_ptr(), src.stride(0) if src.shape[0] > 1 else max(src.shape[1], 1)
-    assert out.stride(1) == 1
-    _check(lib().qgtc_stack_forward(C.byref(stack.c), ptr, ld, q, C.byref(X.c) if X is not None else None, out.data_ptr(),
-                                    out.stride(0) if out.shape[0] > 1 else max(out.shape[1], 1), _stream()),
-           "qgtc_stack_forward")
+    _, out_ptr, ld_out = _out_arg(stack.last, stack.rows, stack.out_cols, out, RIGHT, out.device)
+    _check(lib().qgtc_stack_forward(C.byref(stack.c), ptr, ld, q, C.byref(X.c) if X is not None else None, out_ptr, ld_out,
+                                    _stream()), "qgtc_stack_forward")
 
 
 LAYER_FUSED, LAYER_TWO_KERNELS = 0, 1

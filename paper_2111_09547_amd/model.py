@@ -126,7 +126,8 @@ class QuantGNN:
         # Layers of at most 8 bits run as one native call on codes in operand order
         # (qgtc_stack_forward): two activation buffers.  Everything else goes layer by layer on
         # bit planes: ping-pong buffers of planes, made when they are first needed.
-        self._fused = not update_first and all(lay == B.RIGHT_BYTES for lay in self.w_layout) and \
+        # (A buffer's column group, 64 bytes a row, is addressed with 32 bits.)
+        self._fused = not update_first and n < 1 << 26 and all(lay == B.RIGHT_BYTES for lay in self.w_layout) and \
             (self.tuning is None or self.tuning.layer_path == B.LAYER_FUSED)
         self._wmax = max(dmax, hmax)
         self._x_bufs = None
@@ -160,6 +161,7 @@ class QuantGNN:
             self.w_colsum = [None] * (len(self.W) - 1) + [B.qgtc_col_sums(self.W[-1], out=self._w_colsum_buf)]
             if X is not None and not self.update_first:
                 if self._fused and X.dtype == torch.float32:
+                    assert tuple(X.shape) == (self.A.rows, self.dims[0][0])
                     B.qgtc_stack_input(X, self.s, x_range, self._codes[0])
                     self._x_form = "codes"
                 else:
@@ -389,6 +391,9 @@ class QuantGNN:
             return self._forward_update_first(X, x_range, ranges, out, want_int)
         if self._fused and (x_bits is not None or x_packed or X.dtype == torch.float32):
             # one run whatever `streams` says: the launches of a stack fill the device by themselves
+            if not isinstance(streams, int) and self.A.c.block_rows > 0:
+                assert sum(streams) >= -(-n // self.A.c.block_rows)
+            assert x_bits is None or (isinstance(streams, int) and streams <= 1)
             stack = self._stack(x_range, ranges, want_int)
             if x_bits is not None:
                 B.qgtc_stack_forward(stack, out, X=x_bits)
@@ -514,7 +519,7 @@ class QuantGNN:
 
     def _stack(self, x_range, ranges, want_int) -> "B.Stack":
         """The prepared native call for these ranges (a caller's handful of them is kept)."""
-        key = (float(x_range[0]), float(x_range[1]), bool(want_int), id(self.tuning),
+        key = (float(x_range[0]), float(x_range[1]), bool(want_int), tuple(vars(self.tuning).values()) if self.tuning else None, *self.w_ranges,
                self.map.c.row_cnt if self.map is not None else None, self.deg.data_ptr(),
                *[(r.agg_hi, r.out_hi) for r in ranges])
         stack = self._stacks.get(key)
@@ -522,7 +527,7 @@ class QuantGNN:
             layers = [(W, first, second) for W, (first, second) in zip(self.W, self._epilogues(x_range, ranges, want_int))]
             stack = B.Stack(self.A, self.map, layers, self.s, self._codes)
             if len(self._stacks) >= 8:
-                self._stacks.pop(next(iter(self._stacks)))
+                self._stacks.pop(next(iter(self._stacks)), None)
             self._stacks[key] = stack
         return stack
 
