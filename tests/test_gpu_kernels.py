@@ -471,6 +471,35 @@ def test_update_from_bytes(st, shape):
     assert_fp32_close(got, ref, '')
 
 
+@pytest.mark.parametrize("src", ["f32", "i32", "u8"])
+@pytest.mark.parametrize("n,d,pad,skip", [
+    (1, 4, 0, 0), (3, 12, 0, 0), (257, 20, 4, 0), (70, 516, 0, 0), (1025, 1040, 8, 0), (4099, 8, 0, 0),   # 16-byte loads
+    (257, 20, 3, 0), (70, 21, 0, 0), (33, 64, 0, 1), (1, 3, 0, 0),                       # element by element
+])
+def test_left_bytes_in_quads_and_element_by_element(src, n, d, pad, skip):
+    """Codes as bytes from rows of every alignment: `pad` elements behind each row, `skip` in
+    front of the first; padding bytes are zeros."""
+    rng = np.random.default_rng([31, n, d, pad, skip])
+    flat = rng.standard_normal(skip + n * (d + pad)).astype(np.float32)
+    if src == "f32":
+        flat[skip] = np.nan
+        flat[skip + 1:skip + 3] = [np.inf, -np.inf]
+    else:
+        flat = rng.integers(0, 256, flat.shape).astype(np.int32 if src == "i32" else np.uint8)
+    x = flat[skip:].reshape(n, d + pad)[:, :d]
+    t = dev(flat)[skip:].view(n, d + pad)[:, :d]
+    if src == "f32":
+        ref = qgnn.quantize(np.nan_to_num(x, nan=-9.0, posinf=9.0, neginf=-9.0), -1.5, 2.0, 5)   # NaN: code 0
+    else:
+        ref = x.astype(np.uint32) & 31
+    Yb = q.alloc_bits(n, d, 5, q.LEFT_BYTES)
+    Yb.words.fill_(-1)
+    q.qgtc_pack_bits(t, 5, q.LEFT_BYTES, quant=(-1.5, 2.0) if src == "f32" else None, out=Yb)
+    ld = Yb.c.ld_words * 4
+    raw = Yb.words.cpu().numpy().view(np.uint8)[:n * ld].reshape(n, ld)
+    assert (raw[:, :d] == ref).all() and (raw[:, d:] == 0).all()
+
+
 # ------------------------------------------------------------------- fused layer
 def _compact_rows(A, block):
     """Block-diagonal storage: row r keeps the columns of its own diagonal block."""
