@@ -266,41 +266,17 @@ enum { QGTC_OUT_I32 = 0, QGTC_OUT_F32 = 1, QGTC_OUT_BITS = 2 };
  *                 8 x 8 bit planes, so the update can re-assemble the planes into bytes in
  *                 registers and run there.  0 = automatic, 1 = popcount kernel,
  *                 2 = matrix cores whenever the operands fit.
- *   agg_xcd_run   how qgtc_aggregate deals its workgroups to the 8 XCDs (each with an L2
- *                 of its own): runs of that many consecutive tile rows go to one XCD, the
- *                 next run to the next XCD.  0 = the run length the tile-map build chose
- *                 (8 tile rows without a map), > 0 = that many tile rows (at most 4096),
- *                 < 0 = one contiguous range per XCD.
+ *   agg_xcd_run   how the aggregation and the fused layer deal their workgroups to the 8 XCDs
+ *                 (each with an L2 of its own): runs of about that many consecutive 16-row tile
+ *                 rows go to one XCD, the next run to the next XCD.  0 = the library's choice,
+ *                 > 0 = that many tile rows (at most 4096), < 0 = one contiguous range per XCD.
  *   layer_path    0 = qgtc_layer uses its fused kernel whenever it applies, 1 = always
  *                 aggregate and update as two kernels.
- *   layer_ksplit  waves of a workgroup of the fused kernel that split one tile list:
- *                 0 = automatic (more when the grid is small), 1, 2 or 4.
- *   zero_words    zero-word jumping inside the tiles the map keeps: the aggregation's unit
- *                 of work is one row of a tile times one 32-bit word, and the word of a row
- *                 is wave-uniform, so rows whose word is zero can be jumped over (the
- *                 paper's zero-tile jumping, Section 4.3, at the granularity of the vector
- *                 ALUs instead of the Tensor-Core tile).  Results are the same either way.
- *                 0 = automatic: on when a tile map is passed (a sparse adjacency) and X
- *                 has at least 3 planes; 1 = visit every word of a kept tile (faster when
- *                 most words hold a bit: a row that is present costs one scalar branch
- *                 more in the jumping form); 2 = jump whenever X has at least 3 planes.
- *                 qgtc_plan_layer says which from the statistics of the adjacency.
- *                 From 5 planes on, and while a row of A (of a diagonal block, for block
- *                 storage), rounded up to whole tiles, has at most 2047 words of 32 bits, the
- *                 jumping form keeps two rows of a tile per accumulator register, 16 bits
- *                 each (no count can reach 65536), which lets a fourth wave per SIMD run;
- *                 wider adjacencies take the same form with full-width accumulators.  The
- *                 caller sees no difference but the speed.
- *   even_progress issue priority inside the fused kernel's tile loop by the share of the
- *                 tile list that is left, so that the waves of a SIMD move through their
- *                 lists side by side instead of the oldest finishing long before the
- *                 youngest (which then runs alone).  It pays when every wave of the launch
- *                 is resident from the start - at most one wave per wave slot of the device -
- *                 and costs when there are more, because then the oldest waves should
- *                 finish first and hand their slots on.  0 = automatic: on when this
- *                 launch alone has at most one wave per slot; 1 = off; 2 = on.  A caller
- *                 that runs several launches side by side (runs of a batch on several
- *                 streams) passes what qgtc_plan_layer says for the whole batch.
+ *   layer_ksplit, zero_words, even_progress
+ *                 0, 1, 2 or 4; 0, 1 or 2; 0, 1 or 2.  Hints that say how the waves of an AND +
+ *                 popcount aggregation share and walk a tile list.  The products run on the int8
+ *                 matrix cores, whose kernels choose their split from the sizes alone: the fields
+ *                 are checked, carried by qgtc_plan_layer and change neither results nor launches.
  * Values outside these ranges: QGTC_ERR_UNSUPPORTED. */
 typedef struct qgtc_tuning {
   int32_t update_path;
