@@ -241,7 +241,8 @@ __global__ __launch_bounds__(256) void pack_left_bytes_kernel(const PackParams p
 // of 4, aligned): bound by HBM.  A thread takes kByteWords words that lie 256 apart, so that
 // every load of a wave is 1 KiB in one piece and all of them are in flight together; the
 // (row, word) pairs follow from one 32-bit division and additions (rows x ld below 2^31).
-// Four columns make a whole word, or padding, which is not read.  262144 x 512 fp32 (671 MB in
+// Four columns make a whole word, or padding, which is not read.  The source is not kept in the
+// caches, so that the codes still are when the product reads them.  262144 x 512 fp32 (671 MB in
 // and out): 119 us = 5.7 TB/s; with 4-byte loads and a 64-bit division per word, as above, the
 // pass around it (two layers, update first) took 240 instead of 222 us.
 constexpr int kByteWords = 4;
@@ -252,14 +253,14 @@ __global__ __launch_bounds__(256) void pack_left_bytes_wide_kernel(const PackPar
   const unsigned idx = blockIdx.x * (256u * kByteWords) + threadIdx.x;
   const int r0 = (int)(idx / (unsigned)ld), w0 = (int)(idx % (unsigned)ld);
   using T = typename src_type<SRC>::type;
-  struct alignas(16) Quad { T v[4]; };
+  typedef T Quad __attribute__((ext_vector_type(4)));
   Quad raw[kByteWords];
   int r = r0, w = w0;
 #pragma unroll
   for (int k = 0; k < kByteWords; ++k) {
     // clamped to a quad that exists: no branch around the load
     const int64_t at = (int64_t)min(r, p.rows - 1) * p.ld_src + min(4 * w, p.cols - 4);
-    raw[k] = *reinterpret_cast<const Quad*>(reinterpret_cast<const T*>(p.src) + at);
+    raw[k] = __builtin_nontemporal_load(reinterpret_cast<const Quad*>(reinterpret_cast<const T*>(p.src) + at));
     r += step_r;
     w += step_w;
     if (w >= ld) { w -= ld; ++r; }
@@ -270,7 +271,7 @@ __global__ __launch_bounds__(256) void pack_left_bytes_wide_kernel(const PackPar
   for (int k = 0; k < kByteWords; ++k) {
     uint32_t v = 0u;
 #pragma unroll
-    for (int b = 0; b < 4; ++b) v |= to_code<SRC>(p, raw[k].v[b]) << (8 * b);
+    for (int b = 0; b < 4; ++b) v |= to_code<SRC>(p, raw[k][b]) << (8 * b);
     if (r < p.rows) p.dst[(int64_t)r * ld + w] = 4 * w < p.cols ? v : 0u;
     r += step_r;
     w += step_w;
