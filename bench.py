@@ -469,10 +469,9 @@ def main():
                    "nonzero_tile_ratio": nnz / float(net.map.c.n_tile_rows * net.map.c.n_tile_cols),
                    "nonzero_tile_ratio_8x128": ratio_8x128(net),
                    "step": "pack A + tile map + pack W + pack X + all layers"},
-        "value_counts": "aggregation: AND + popcount bit-ops of the tiles the zero-tile map keeps (where the kernels "
-                        "also jump over the zero words inside kept tiles, value_popcount_executed counts only "
-                        "the words they visit); update: nominal 2 N D H s t (it executes as int8 "
-                        "multiply-accumulates on the matrix cores)",
+        "value_counts": "aggregation: AND + popcount bit-ops of the tiles the zero-tile map keeps "
+                        "(value_popcount_executed: of their non-zero words only); update: nominal 2 N D H s t; "
+                        "both execute as int8 multiply-accumulates on the matrix cores",
         "value_popcount_kept_tiles": sum(agg_ops) / (ms_step * 1e-3) / 1e12,
         "value_popcount_executed": sum(visited) / (ms_step * 1e-3) / 1e12,
         "zero_word_jumping": visited != agg_ops,
@@ -495,9 +494,10 @@ def main():
                      "achieved": agg_rate / 1e12, "peak": PEAK_BITOPS / 1e12,
                      "unit": "Tbit-op/s", "frac": agg_rate / PEAK_BITOPS,
                      "avg_launch_ms": dom_avg_ms, "launches": dom_n,
-                     "counted": "executed (visited) AND+popcount bit-ops of the aggregation only; the update "
-                                "inside the same kernel runs on the matrix cores and is not counted; launch "
-                                "durations are taken with the launches one after the other on one stream",
+                     "counted": "AND + popcount bit-ops of the non-zero words of the aggregation, the method's work, "
+                                "against the vector-ALU ceiling of that form; the kernel itself takes all planes at "
+                                "once on the int8 matrix cores, so this is a rate and no utilisation (it can pass 1); "
+                                "launch durations are taken with the launches one after the other on one stream",
                      "frac_in_step": sum(visited) / (ms_layers * 1e-3) / PEAK_BITOPS,
                      # the work of the kept tiles (what a kernel without zero-word jumping executes, and
                      # what `frac` counted before that existed) over the same launch time: above 1 when
