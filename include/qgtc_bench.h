@@ -43,6 +43,14 @@ qgtc_status qgtc_prof_read(int32_t kind, double* total_ms, int64_t* launches);
 qgtc_status qgtc_probe_popcount(int32_t workgroups, int32_t waves_per_workgroup,
                                 int32_t iters, uint32_t* sink, void* stream);
 
+/* Host only: the rows that an aggregation of x_cols columns over A takes where (out_cols > 0:
+ * as the first half of the fused layer with out_cols output columns), as the kernels find
+ * them.  Returns the number of workgroups (-1: bad arguments) and fills, for the workgroups
+ * first .. first + count - 1 that exist and for four units of each, the workgroup's place along
+ * the columns, the unit's first row and its number of rows (0: none). */
+int64_t qgtc_probe_units(const qgtc_bits* A, int32_t x_cols, int32_t out_cols, int64_t first,
+                         int64_t count, int32_t* column, int32_t* row0, int32_t* rows);
+
 #ifdef __cplusplus
 }
 #endif

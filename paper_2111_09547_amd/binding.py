@@ -150,6 +150,7 @@ def lib():
                                          C.c_double, C.c_double, i32, P(C.c_float), P(C.c_float)]),
         "qgtc_device_info": (C.c_int, [P(_DeviceC)]),
         "qgtc_probe_popcount": (C.c_int, [i32, i32, i32, C.c_void_p, C.c_void_p]),
+        "qgtc_probe_units": (i64, [P(_BitsC), i32, i32, i64, i64, vp, vp, vp]),
         "qgtc_prof_enable": (C.c_int, [i32]),
         "qgtc_prof_reset": (C.c_int, []),
         "qgtc_prof_read": (C.c_int, [i32, P(C.c_double), P(i64)]),

@@ -143,11 +143,18 @@ inline qgtc_status agg_fill_params(const qgtc_bits* A, const qgtc_tile_map* map,
   return QGTC_OK;
 }
 
-// n / d as the upper half of n * div_magic(d): exact while n * d < 2^32, which numbers of
-// 32-row units and of workgroups are far below.  (A runtime division costs ~30 instructions,
-// and the code in front of the first load is fetched cold by every launch.)
+// n / d by the upper half of n * div_magic(d), for any n below 2^31: the rounded-up reciprocal is
+// too large by less than 1 / 2^32, so the product by less than one, and the quotient is at most
+// one too large.  (A runtime division costs ~30 instructions, and the code in front of the first
+// load is fetched cold by every launch.)
 inline uint32_t div_magic(int d) { return d <= 1 ? 0u : (uint32_t)((((uint64_t)1 << 32) + (uint64_t)d - 1) / (uint64_t)d); }
-__device__ __forceinline__ unsigned div_by(unsigned n, uint32_t magic) { return magic ? __umulhi(n, magic) : n; }
+__host__ __device__ __forceinline__ unsigned div_by(unsigned n, unsigned d, uint32_t magic) {
+  const unsigned q = magic ? (unsigned)(((uint64_t)n * magic) >> 32) : n;
+  return magic && q * d > n ? q - 1u : q;
+}
+
+// The split of a stand-alone aggregation of `cols` columns.
+AggSplit aggregate_split(int rows, int cols, int a_words);
 
 // Launch shape for a split; n_col_wg: workgroups along the columns.
 // Returns the dynamic LDS that the aggregation needs.
@@ -262,19 +269,12 @@ struct AggWave {
   int n_list;            // chunks to take
 };
 
-// False: no work for this workgroup (it leaves as a whole).
-template <int WAYS, int KS>
-__device__ __forceinline__ bool agg_place(const AggParams& p, AggWave* w) {
-  unsigned b = xcd_deal(blockIdx.x, p.run_shift);
-  if (b >= p.nblocks) return false;
-  w->wave = (int)uniform(threadIdx.x >> 6);
-  w->u = w->wave / (WAYS * KS);
-  w->way = w->wave % WAYS;
-  w->kp = w->wave / WAYS % KS;
-  unsigned q = div_by(b, p.rb_magic);
+// Rows of unit w->u of workgroup b (host and device).
+__host__ __device__ __forceinline__ void agg_locate(const AggParams& p, unsigned b, AggWave* w) {
+  unsigned q = div_by(b, (unsigned)p.rb_per_sub, p.rb_magic);
   const int j = (int)(b - q * (unsigned)p.rb_per_sub);
   b = q;
-  q = div_by(b, p.col_magic);
+  q = div_by(b, (unsigned)p.n_col_wg, p.col_magic);
   w->cw = (int)(b - q * (unsigned)p.n_col_wg);
   const int bw = p.block_rows >> 5;
   int sub = (int)q * p.sub_per_wg, lrow = (j * p.nu + w->u) * kUnitRows;
@@ -288,7 +288,21 @@ __device__ __forceinline__ bool agg_place(const AggParams& p, AggWave* w) {
   }
   w->row0 = sub * p.block_rows + lrow;
   w->own_kw = lrow >> 5;
-  w->rows_here = min(min(p.eff_rows - lrow, p.rows - w->row0), kUnitRows);
+  const int in_block = p.eff_rows - lrow, in_all = p.rows - w->row0;
+  const int here = in_block < in_all ? in_block : in_all;
+  w->rows_here = here < kUnitRows ? here : kUnitRows;
+}
+
+// False: no work for this workgroup (it leaves as a whole).
+template <int WAYS, int KS>
+__device__ __forceinline__ bool agg_place(const AggParams& p, AggWave* w) {
+  const unsigned b = xcd_deal(blockIdx.x, p.run_shift);
+  if (b >= p.nblocks) return false;
+  w->wave = (int)uniform(threadIdx.x >> 6);
+  w->u = w->wave / (WAYS * KS);
+  w->way = w->wave % WAYS;
+  w->kp = w->wave / WAYS % KS;
+  agg_locate(p, b, w);
   w->n_list = p.n_chunks;
   return true;
 }

@@ -203,6 +203,19 @@ qgtc_status launch(const AggParams& p, size_t lds, hipStream_t stream) {
 }
 
 }  // namespace
+
+// Narrower column groups where wide ones would leave compute units without a workgroup of two
+// units: the rows of A are then expanded once per group, which costs less than idle units.
+// Where that leaves two or fewer waves per compute unit, four of them share a unit's stages
+// (8192 x 8192 x 64: two waves of 16 columns 33 us, eight of them 18 us).
+AggSplit aggregate_split(int rows, int cols, int a_words) {
+  const int64_t units = cdiv(rows, kUnitRows), enough = 2 * (int64_t)device_compute_units();
+  AggSplit sp{2, 2, 2, 1};
+  if (cols <= 32 || units * cdiv(cols, 64) < enough) sp = AggSplit{1, 2, 1, 1};
+  if (cols <= 16 || units * cdiv(cols, 32) < enough) sp = AggSplit{1, 1, 1, units * cdiv(cols, 16) <= enough && a_words > 32 ? 4 : 1};
+  return sp;
+}
+
 }  // namespace qgtc
 
 using namespace qgtc;
@@ -221,14 +234,7 @@ extern "C" qgtc_status qgtc_aggregate(const qgtc_bits* A, const qgtc_tile_map* m
   if (st != QGTC_OK) return st;
   if (A->rows == 0 || X->cols == 0) return QGTC_OK;
 
-  // Narrower column groups where wide ones would leave compute units without a workgroup of two
-  // units: the rows of A are then expanded once per group, which costs less than idle units.
-  // Where that leaves two or fewer waves per compute unit, four of them share a unit's stages
-  // (8192 x 8192 x 64: two waves of 16 columns 33 us, eight of them 18 us).
-  const int64_t units = cdiv(A->rows, kUnitRows), enough = 2 * (int64_t)device_compute_units();
-  AggSplit sp{2, 2, 2, 1};
-  if (X->cols <= 32 || units * cdiv(X->cols, 64) < enough) sp = AggSplit{1, 2, 1, 1};
-  if (X->cols <= 16 || units * cdiv(X->cols, 32) < enough) sp = AggSplit{1, 1, 1, units * cdiv(X->cols, 16) <= enough && p.a_words > 32 ? 4 : 1};
+  const AggSplit sp = aggregate_split(A->rows, X->cols, p.a_words);
   const size_t lds = agg_set_shape(&p, sp, cdiv(X->cols, sp.group()), ep->tuning ? ep->tuning->agg_xcd_run : 0);
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   ProfScope prof(QGTC_KERNEL_AGGREGATE, s);

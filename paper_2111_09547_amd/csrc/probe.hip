@@ -3,7 +3,8 @@
 // 16 rows x 8 planes) in a loop without any memory traffic.  It gives the
 // measured ceiling that the aggregation is priced against beside the nominal one
 // (256 CUs x 64 lanes per clock x 2.4 GHz).
-#include "qgtc_internal.h"
+// Beside it, on the host: which rows each unit of an aggregation launch takes.
+#include "layer.h"
 
 namespace qgtc {
 namespace {
@@ -46,4 +47,31 @@ extern "C" qgtc_status qgtc_probe_popcount(int32_t workgroups, int32_t waves_per
   hipLaunchKernelGGL(popcount_probe_kernel, dim3((unsigned)workgroups), dim3(64 * waves_per_workgroup), 0,
                      reinterpret_cast<hipStream_t>(stream), iters, sink);
   return launch_status();
+}
+
+extern "C" int64_t qgtc_probe_units(const qgtc_bits* A, int32_t x_cols, int32_t out_cols, int64_t first, int64_t count,
+                                    int32_t* column, int32_t* row0, int32_t* rows) {
+  if (!A || !column || !row0 || !rows || x_cols < 1 || first < 0 || count < 0) return -1;
+  qgtc_bits x{};                                     // the shape only
+  qgtc_describe(&x, A->block_rows > 0 ? A->rows : A->cols, x_cols, 1, QGTC_RIGHT, 0);
+  x.data = A->data;
+  AggParams p{};
+  if (agg_fill_params(A, nullptr, &x, &p) != QGTC_OK) return -1;
+  if (out_cols > 0) {
+    (void)agg_set_shape(&p, layer_split(A->rows, x_cols, out_cols), 1, 0);
+  } else {
+    const AggSplit sp = aggregate_split(A->rows, x_cols, p.a_words);
+    (void)agg_set_shape(&p, sp, cdiv(x_cols, sp.group()), 0);
+  }
+  for (int64_t b = first; b < first + count && b < (int64_t)p.nblocks; ++b)
+    for (int u = 0; u < kMaxUnits; ++u) {
+      AggWave w{};
+      w.u = u;
+      if (u < p.nu) agg_locate(p, (unsigned)b, &w);
+      const int64_t at = (b - first) * kMaxUnits + u;
+      column[at] = w.cw;
+      row0[at] = w.row0;
+      rows[at] = u < p.nu && w.rows_here > 0 ? w.rows_here : 0;
+    }
+  return p.nblocks;
 }
