@@ -522,6 +522,11 @@ __device__ __forceinline__ void agg_run(const AggParams& p, const AggWave& w, ui
 #pragma unroll
         for (int r = 0; r < 8; ++r) raw[k][r] ^= 0x80808080u;
       }
+      // Every wave has its planes here, also one without a piece to store: they were requested
+      // after the stage's words of A, and loads complete in order, so that these have arrived
+      // as well before the wave goes to the next barrier.
+#pragma unroll
+      for (int r = 0; r < 8; ++r) asm volatile("" : "+v"(raw[k][r]));
       if (kl < 4 * TSC) {
         *reinterpret_cast<v4u*>(to + kl * KB) = (v4u){raw[k][0], raw[k][1], raw[k][2], raw[k][3]};
         *reinterpret_cast<v4u*>(to + kl * KB + LT * 256) = (v4u){raw[k][4], raw[k][5], raw[k][6], raw[k][7]};
@@ -691,7 +696,8 @@ __device__ __forceinline__ void agg_run(const AggParams& p, const AggWave& w, ui
   } else {
     // A two stages ahead; X one stage ahead in LDS - its planes are put together behind the
     // products of the stage before, while other waves are still at theirs - and two in registers.
-    // (the planes of a stage are requested after its words of A: with them, those have arrived)
+    // (the planes of a stage are requested after its words of A: with them, those have arrived -
+    // store_x_planes() sees to it that every wave waits for its planes)
     before();
     int x_pass = 0, x_st = 0;
     auto planes_next = [&]() {
@@ -707,7 +713,6 @@ __device__ __forceinline__ void agg_run(const AggParams& p, const AggWave& w, ui
     beside();
     store_x_planes(lds);
     if (total > 1) planes_next();
-    wait_loads(total > 1 ? 8 * NPT : 0);
     for (int it = 0; it < total; ++it) {
       __syncthreads();
       if (it + 2 < total) load_next();

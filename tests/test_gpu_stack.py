@@ -107,3 +107,27 @@ def test_aggregate_splits(s, rows, k, cols, density):
     for tmap in (None, q.qgtc_build_tile_map(A, 16, 128), q.qgtc_build_tile_map(A, 16, 32)):
         y = q.qgtc_aggregate(A, tmap, X, q.Epilogue(mode=q.OUT_I32))
         assert (as_u32(y) == ref).all()
+
+
+@pytest.mark.parametrize("cols", [16, 32])
+@pytest.mark.parametrize("s", [3, 8])
+def test_four_units_side_by_side_on_planes(cols, s):
+    """Rows for four units per workgroup, narrow column groups: half of the waves have no piece
+    of a staged X to store, and multiply with words of A that were requested two stages before."""
+    rows, k, h = 66000, 1300, 20
+    rng = np.random.default_rng(cols + s)
+    a = sp.random(rows, k, density=0.03, format="csr", random_state=rng, dtype=np.float32)
+    a.data[:] = 1
+    some = np.ones(rows, np.float32)
+    some[rows // 2:rows // 2 + 130] = 0              # a unit without a bit
+    a = sp.csr_matrix(sp.diags(some) @ a)
+    a.eliminate_zeros()
+    x = rng.integers(0, 1 << s, (k, cols)).astype(np.int32)
+    w = rng.integers(0, 1 << s, (cols, h)).astype(np.int32)
+    y, _, z, (lo, inv) = qgnn.layer(a.astype(np.int64), x.astype(np.uint32), w.astype(np.uint32), s)
+    A = q.qgtc_pack_bits(dev(a.astype(np.uint8).toarray()), 1, q.LEFT)
+    X, W = q.qgtc_pack_bits(dev(x), s, q.RIGHT), q.qgtc_pack_bits(dev(w), s, q.RIGHT)
+    first = q.Epilogue(mode=q.OUT_BITS, rq_nbits=s, rq_lo=lo, rq_inv_scale=float(inv))
+    for tmap in (None, q.qgtc_build_tile_map(A, 16, 64)):
+        assert (as_u32(q.qgtc_aggregate(A, tmap, X, q.Epilogue(mode=q.OUT_I32))) == y).all()
+        assert (as_u32(q.qgtc_layer(A, tmap, X, W, first, q.Epilogue(mode=q.OUT_I32))) == z).all()
