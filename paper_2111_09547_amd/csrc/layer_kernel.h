@@ -106,18 +106,18 @@ typedef const __attribute__((address_space(4))) LayerParams* LateParams;
 struct Warm {
   uint32_t v[8];
 };
-// (the loads are issued in front of the compiler's own first ones and finished behind them)
+// Ordinary loads, one word of each line, through a pointer of their own: the compiler tracks them
+// and waits in front of warm_done(), where the words are used.
 __device__ __forceinline__ void warm_params(LateParams kp, Warm& w) {
   static_assert(sizeof(LayerParams) > 0x1c0 && sizeof(LayerParams) <= 0x280, "lines of 64 bytes below");
-  asm volatile(
-      "s_load_dword %0, %8, 0x40\n\ts_load_dword %1, %8, 0x80\n\ts_load_dword %2, %8, 0xc0\n\t"
-      "s_load_dword %3, %8, 0x100\n\ts_load_dword %4, %8, 0x140\n\ts_load_dword %5, %8, 0x180\n\t"
-      "s_load_dword %6, %8, 0x1c0\n\ts_load_dword %7, %8, %9"
-      : "=&s"(w.v[0]), "=&s"(w.v[1]), "=&s"(w.v[2]), "=&s"(w.v[3]), "=&s"(w.v[4]), "=&s"(w.v[5]), "=&s"(w.v[6]), "=&s"(w.v[7])
-      : "s"(kp), "n"((sizeof(LayerParams) - 4) & ~63u));
+  QGTC_LATE(kp);
+  const auto* words = reinterpret_cast<const __attribute__((address_space(4))) uint32_t*>(kp);
+#pragma unroll
+  for (int i = 0; i < 7; ++i) w.v[i] = words[16 * (i + 1)];
+  w.v[7] = words[((sizeof(LayerParams) - 4) & ~63u) / 4];
 }
-__device__ __forceinline__ void warm_done(Warm& w) {
-  asm volatile("s_waitcnt lgkmcnt(0)" : "+s"(w.v[0]), "+s"(w.v[1]), "+s"(w.v[2]), "+s"(w.v[3]), "+s"(w.v[4]), "+s"(w.v[5]), "+s"(w.v[6]), "+s"(w.v[7]));
+__device__ __forceinline__ void warm_done(const Warm& w) {
+  asm volatile("" :: "s"(w.v[0]), "s"(w.v[1]), "s"(w.v[2]), "s"(w.v[3]), "s"(w.v[4]), "s"(w.v[5]), "s"(w.v[6]), "s"(w.v[7]));
 }
 
 // A block of RIGHT_BYTES (16 output columns, 64 K positions) as the operand of a step of 16 PT K
