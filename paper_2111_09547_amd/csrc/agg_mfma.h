@@ -150,7 +150,7 @@ inline qgtc_status agg_fill_params(const qgtc_bits* A, const qgtc_tile_map* map,
 inline uint32_t div_magic(int d) { return d <= 1 ? 0u : (uint32_t)((((uint64_t)1 << 32) + (uint64_t)d - 1) / (uint64_t)d); }
 __host__ __device__ __forceinline__ unsigned div_by(unsigned n, unsigned d, uint32_t magic) {
   const unsigned q = magic ? (unsigned)(((uint64_t)n * magic) >> 32) : n;
-  return magic && q * d > n ? q - 1u : q;
+  return q - (unsigned)(q * d > n);
 }
 
 // The split of a stand-alone aggregation of `cols` columns.
