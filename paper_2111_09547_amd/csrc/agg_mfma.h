@@ -95,6 +95,33 @@ struct AggParams {
   EpiParams ep;
 };
 
+// Checks the adjacency of an aggregation and its map, and fills their part of the kernel parameters.
+inline qgtc_status agg_fill_adjacency(const qgtc_bits* A, const qgtc_tile_map* map, AggParams* p) {
+  qgtc_status st = check_adjacency(A);
+  if (st != QGTC_OK) return st;
+  if (A->ld_words * 128 >= (int64_t)1 << 31) return QGTC_ERR_UNSUPPORTED;
+  p->A = A->data;
+  p->lda = A->ld_words;
+  p->a_words = 4 * cdiv(A->cols, 128);
+  p->rows = A->rows;
+  p->block_rows = A->block_rows;
+  p->eff_rows = A->block_rows > 0 ? A->block_rows : A->rows;
+  if (map) {
+    if (!map->row_cnt || !map->col_idx) return QGTC_ERR_NULL;
+    if (map->tile_rows != 16 ||
+        (map->tile_kbits != 32 && map->tile_kbits != 64 && map->tile_kbits != 128))
+      return QGTC_ERR_UNSUPPORTED;
+    if (map->n_tile_rows != cdiv(A->rows, 16) || map->n_tile_cols != cdiv(A->cols, map->tile_kbits))
+      return QGTC_ERR_SHAPE;
+    p->row_cnt = map->row_cnt;
+    p->col_idx = map->col_idx;
+    p->n_tile_rows = map->n_tile_rows;
+    p->n_tile_cols = map->n_tile_cols;
+    p->tile_shift = map->tile_kbits == 128 ? 0 : (map->tile_kbits == 64 ? 1 : 2);
+  }
+  return QGTC_OK;
+}
+
 // Checks the operands of an aggregation and fills the operand part of the kernel
 // parameters (everything but the epilogue and the launch shape).
 inline qgtc_status agg_fill_params(const qgtc_bits* A, const qgtc_tile_map* map, const qgtc_bits* X,
@@ -111,15 +138,8 @@ inline qgtc_status agg_fill_params(const qgtc_bits* A, const qgtc_tile_map* map,
   }
   const int64_t x_words = span_words(X);
   if (x_words * 4 >= (int64_t)1 << 32 || X->ld_words * 4 >= (int64_t)1 << 31 ||
-      X->plane_stride_words * 4 >= (int64_t)1 << 31 || A->ld_words * 128 >= (int64_t)1 << 31)
+      X->plane_stride_words * 4 >= (int64_t)1 << 31)
     return QGTC_ERR_UNSUPPORTED;
-
-  p->A = A->data;
-  p->lda = A->ld_words;
-  p->a_words = 4 * cdiv(A->cols, 128);
-  p->rows = A->rows;
-  p->block_rows = A->block_rows;
-  p->eff_rows = A->block_rows > 0 ? A->block_rows : A->rows;
   p->X = X->data;
   p->ldx4 = (uint32_t)(X->ld_words * 4);
   p->psx4 = (uint32_t)(X->plane_stride_words * 4);
@@ -127,20 +147,7 @@ inline qgtc_status agg_fill_params(const qgtc_bits* A, const qgtc_tile_map* map,
   p->x_kwords = cdiv(X->rows, 32);
   p->s = X->nbits;
   p->cols = X->cols;
-  if (map) {
-    if (!map->row_cnt || !map->col_idx) return QGTC_ERR_NULL;
-    if (map->tile_rows != 16 ||
-        (map->tile_kbits != 32 && map->tile_kbits != 64 && map->tile_kbits != 128))
-      return QGTC_ERR_UNSUPPORTED;
-    if (map->n_tile_rows != cdiv(A->rows, 16) || map->n_tile_cols != cdiv(A->cols, map->tile_kbits))
-      return QGTC_ERR_SHAPE;
-    p->row_cnt = map->row_cnt;
-    p->col_idx = map->col_idx;
-    p->n_tile_rows = map->n_tile_rows;
-    p->n_tile_cols = map->n_tile_cols;
-    p->tile_shift = map->tile_kbits == 128 ? 0 : (map->tile_kbits == 64 ? 1 : 2);
-  }
-  return QGTC_OK;
+  return agg_fill_adjacency(A, map, p);
 }
 
 // n / d by the upper half of n * div_magic(d), for any n below 2^31: the rounded-up reciprocal is

@@ -3,6 +3,8 @@
 // is a plain copy and no bit plane is formed or put back together between the layers.
 #include "layer.h"
 
+#include <cmath>
+
 namespace qgtc {
 namespace {
 
@@ -112,25 +114,23 @@ qgtc_status pack_codes(const float* src, int64_t ld_src, int rows, int cols, con
 
 }  // namespace
 
-qgtc_status layer_codes(const qgtc_bits* A, const qgtc_tile_map* map, const qgtc_bits* X, const uint8_t* x_codes,
+// One layer of a stack whose operands qgtc_stack_forward has checked: X, or x_codes with x_cols
+// columns, in; out_codes, or out, out.
+static qgtc_status layer_codes(const qgtc_bits* A, const qgtc_tile_map* map, const qgtc_bits* X, const uint8_t* x_codes,
                         int x_cols, int s, const qgtc_bits* W, const qgtc_epilogue* agg_ep, const qgtc_epilogue* upd_ep,
                         uint8_t* out_codes, void* out, int64_t ld_out, hipStream_t stream) {
   LayerParams p{};
-  qgtc_bits x{};                                     // codes: the shape only
+  qgtc_status st;
   if (X) {
-    x = *X;
+    st = agg_fill_params(A, map, X, &p.a);
   } else {
-    qgtc_describe(&x, A->block_rows > 0 ? A->rows : A->cols, x_cols, s, QGTC_RIGHT, 0);
-    x.data = reinterpret_cast<uint32_t*>(const_cast<uint8_t*>(x_codes));
+    st = agg_fill_adjacency(A, map, &p.a);
+    p.a.X = reinterpret_cast<const uint32_t*>(x_codes);
+    p.a.x_bytes = (uint32_t)codes_cg_bytes(A->rows, agg_col_tiles(x_cols));
+    p.a.s = s;
+    p.a.cols = x_cols;
   }
-  qgtc_status st = agg_fill_params(A, map, &x, &p.a);
   if (st != QGTC_OK) return st;
-  if (W->rows != x.cols || !plan_fused_applies(x.cols, W->cols, s, W->nbits)) return QGTC_ERR_SHAPE;
-  if (!X) {
-    const int64_t bytes = codes_cg_bytes(x.rows, agg_col_tiles(x.cols));
-    if (bytes >= (int64_t)1 << 32) return QGTC_ERR_UNSUPPORTED;
-    p.a.x_bytes = (uint32_t)bytes;
-  }
   if (out_codes) {
     EpiParams& u = p.up;
     u.mode = kOutCodes;
@@ -154,7 +154,7 @@ qgtc_status layer_codes(const qgtc_bits* A, const qgtc_tile_map* map, const qgtc
   e.rq_nbits = agg_ep->rq_nbits;
   e.rq_lo = agg_ep->rq_lo;
   e.rq_inv_scale = agg_ep->rq_inv_scale;
-  return layer_run(&p, layer_split(A->rows, x.cols, W->cols), X == nullptr, W, upd_ep, stream);
+  return layer_run(&p, layer_split(A->rows, x_cols, W->cols), X == nullptr, W, upd_ep, stream);
 }
 
 }  // namespace qgtc
@@ -182,11 +182,15 @@ extern "C" qgtc_status qgtc_stack_forward(const qgtc_stack* st, const float* src
                                           const qgtc_bits* X, void* out, int64_t ld_out, void* stream) {
   if (!st || !st->A || !st->layers || !st->buffer[0] || !st->buffer[1]) return QGTC_ERR_NULL;
   if (st->n_layers < 1) return QGTC_ERR_SHAPE;
-  // everything is checked before anything is launched
-  qgtc_status rc = check_adjacency(st->A);
+  if (src) X = nullptr;                              // the features come first
+  // Everything is checked before anything is launched, every layer as qgtc_layer checks it.
+  AggParams a{};
+  qgtc_status rc = agg_fill_adjacency(st->A, st->map, &a);
   if (rc != QGTC_OK) return rc;
   const int rows = st->A->rows;
   if (st->A->block_rows == 0 && st->A->cols != rows) return QGTC_ERR_SHAPE;
+  if ((((uintptr_t)st->buffer[0] | (uintptr_t)st->buffer[1]) & 15u) != 0) return QGTC_ERR_ALIGN;
+  auto scale_ok = [](float v) { return v > 0.0f && v < INFINITY; };
   for (int l = 0; l < st->n_layers; ++l) {
     const qgtc_stack_layer& y = st->layers[l];
     const bool last = l == st->n_layers - 1;
@@ -196,10 +200,15 @@ extern "C" qgtc_status qgtc_stack_forward(const qgtc_stack* st, const float* src
     if (!plan_fused_applies(y.W.rows, y.W.cols, st->s, y.W.nbits)) return QGTC_ERR_UNSUPPORTED;
     if (y.first.mode != QGTC_OUT_BITS || (last ? y.second.mode == QGTC_OUT_BITS : y.second.mode != QGTC_OUT_BITS))
       return QGTC_ERR_UNSUPPORTED;
+    if (y.first.col_scale || y.first.col_shift) return QGTC_ERR_UNSUPPORTED;   // the affine map belongs to second
+    if (y.second.col_shift && !y.second.col_scale) return QGTC_ERR_NULL;
+    if (y.second.self_term) return QGTC_ERR_SHAPE;
     if (y.first.rq_nbits < 1 || y.first.rq_nbits > 8 || (!last && y.second.rq_nbits != st->s)) return QGTC_ERR_BITWIDTH;
-    if (!(y.first.rq_inv_scale > 0.0f) || (!last && !(y.second.rq_inv_scale > 0.0f))) return QGTC_ERR_SHAPE;
+    if (!scale_ok(y.first.rq_inv_scale) || (!last && !scale_ok(y.second.rq_inv_scale))) return QGTC_ERR_SHAPE;
     rc = check_tuning(y.second.tuning);
     if (rc != QGTC_OK) return rc;
+    // (codes: a column group is addressed with 32 bits)
+    if (codes_cg_bytes(rows, agg_col_tiles(y.W.rows)) >= (int64_t)1 << 32) return QGTC_ERR_UNSUPPORTED;
     if (st->buffer_bytes < qgtc_stack_buffer_bytes(rows, y.W.rows)) return QGTC_ERR_WORKSPACE;
   }
   if (!out && rows > 0) return QGTC_ERR_NULL;
@@ -209,19 +218,14 @@ extern "C" qgtc_status qgtc_stack_forward(const qgtc_stack* st, const float* src
     EpiParams e{};
     rc = make_epilogue(&y.second, out, ld_out, rows, y.W.cols, QGTC_RIGHT, false, &e);
     if (rc != QGTC_OK) return rc;
-    if (codes_cg_bytes(rows, 4) >= (int64_t)1 << 32) return QGTC_ERR_UNSUPPORTED;
-    AggParams a{};
-    qgtc_bits x{};                                   // the shape only
-    qgtc_describe(&x, rows, d0, st->s, QGTC_RIGHT, 0);
-    x.data = reinterpret_cast<uint32_t*>(st->buffer[0]);
-    rc = agg_fill_params(st->A, st->map, X ? X : &x, &a);
-    if (rc != QGTC_OK) return rc;
   }
   if (X) {
     rc = check_bits(X, QGTC_RIGHT);
     if (rc != QGTC_OK) return rc;
     if (X->rows != rows || X->cols != d0) return QGTC_ERR_SHAPE;
     if (X->nbits != st->s) return QGTC_ERR_BITWIDTH;
+    rc = agg_fill_params(st->A, st->map, X, &a);
+    if (rc != QGTC_OK) return rc;
   }
   if (src) {
     if (q && q->nbits != st->s) return QGTC_ERR_BITWIDTH;

@@ -151,6 +151,82 @@ def test_argument_validation_happens_before_any_launch():
     assert l.qgtc_aggregate(C.byref(A), C.byref(m), C.byref(X), C.byref(ep), out, 16, None) == 7
 
 
+def test_stack_arguments_are_checked_before_any_launch():
+    """qgtc_stack_forward refuses what qgtc_layer refuses, for every layer and before the first
+    launch; hidden activations are codes, to which the limits of bit planes do not apply."""
+    import paper_2111_09547_amd.binding as b
+    l = b.lib()
+    n, dims, s = 128, (20, 24, 9), 4
+    A = _fake_bits(b, n, 64, 1, b.LEFT, block_rows=64)
+    buf, out = 0x100000, C.c_void_p(0x200000)
+    Q = b._QuantC(-1.0, 1.0, s)
+
+    def run(change=None, rows=n, dims=dims, buffer_bytes=1 << 40, ld_out=None, out=out, src=buf, X=None, q=Q, ld_src=None):
+        A.rows = rows
+        layers = (b._StackLayerC * (len(dims) - 1))()
+        for i, y in enumerate(layers):
+            last = i == len(dims) - 2
+            y.W = _fake_bits(b, dims[i], dims[i + 1], s, b.RIGHT_BYTES)
+            y.first = b.Epilogue(mode=b.OUT_BITS, rq_nbits=s, rq_inv_scale=0.5).to_c()
+            y.second = b.Epilogue(mode=b.OUT_F32 if last else b.OUT_BITS, rq_nbits=0 if last else s,
+                                  rq_inv_scale=0.0 if last else 0.5, cc=1.0).to_c()
+        st = b._StackC(C.pointer(A), None, layers, len(layers), s, (C.c_void_p * 2)(buf, buf), buffer_bytes)
+        if change:
+            change(st, layers)
+        return l.qgtc_stack_forward(C.byref(st), src, ld_src or dims[0], C.byref(q) if q is not None else None,
+                                    C.byref(X) if X is not None else None, out, ld_out or dims[-1], None)
+
+    def with_(field, value, layer=0, ep="second"):
+        def change(st, layers):
+            setattr(getattr(layers[layer], ep), field, value)
+        return run(change)
+
+    NULL, SHAPE, BITS, ALIGN, LAYOUT, WORKSPACE, UNSUPPORTED = 1, 2, 3, 4, 5, 6, 7
+    # epilogues
+    assert with_("col_scale", 0x60000, ep="first") == UNSUPPORTED
+    assert with_("col_shift", 0x60000, ep="first") == UNSUPPORTED
+    assert with_("self_term", 1) == SHAPE and with_("self_term", 1, 1) == SHAPE
+    assert with_("col_shift", 0x60000) == NULL and with_("col_shift", 0x60000, 1) == NULL
+    for bad in (float("inf"), float("nan"), 0.0, -1.0):
+        assert with_("rq_inv_scale", bad, ep="first") == SHAPE and with_("rq_inv_scale", bad, 1, "first") == SHAPE
+        assert with_("rq_inv_scale", bad) == SHAPE
+    assert with_("rq_nbits", 9, ep="first") == BITS and with_("rq_nbits", 3) == BITS
+    assert with_("mode", b.OUT_F32) == UNSUPPORTED and with_("mode", b.OUT_BITS, 1) == UNSUPPORTED
+    assert with_("mode", 5, 1) == UNSUPPORTED and with_("mode", b.OUT_I32, ep="first") == UNSUPPORTED
+    # sizes, buffers, operands
+    assert run(ld_out=8) == SHAPE and run(out=None) == NULL and run(q=None) == NULL and run(ld_src=19) == SHAPE
+    assert run(q=b._QuantC(1.0, -1.0, s)) == SHAPE and run(q=b._QuantC(-1.0, 1.0, 5)) == BITS
+    assert run(buffer_bytes=16) == WORKSPACE
+    assert run(dims=(20, 300, 9)) == UNSUPPORTED and run(dims=(1025, 24, 9)) == UNSUPPORTED
+    assert run(src=None, X=_fake_bits(b, n, 19, s, b.RIGHT)) == SHAPE
+    assert run(src=None, X=_fake_bits(b, n, 20, 3, b.RIGHT)) == BITS
+    assert run(src=None, X=_fake_bits(b, n, 20, s, b.LEFT)) == LAYOUT
+    def odd_buffer(st, layers): st.buffer[1] = buf + 4
+    assert run(odd_buffer) == ALIGN
+    def other_width(st, layers): layers[1].W = _fake_bits(b, 25, 9, s, b.RIGHT_BYTES)
+    assert run(other_width) == SHAPE
+    def no_layers(st, layers): st.n_layers = 0
+    assert run(no_layers) == SHAPE
+    # a column group of codes past 4 GiB is refused, also behind a narrow first layer; a narrow one
+    # of as many rows is not
+    assert run(rows=1 << 26, dims=(16, 64, 9)) == UNSUPPORTED
+    import torch
+    if not torch.cuda.is_available():                # accepted: the launch finds no device
+        assert run() == 8
+        assert run(X=_fake_bits(b, n, 19, s, b.RIGHT)) == 8      # features given: planes are not looked at
+        assert run(rows=1 << 26, dims=(16, 16, 9)) == 8
+        assert run(rows=1 << 25, dims=(16, 256, 9)) == 8
+    # the quantizer by itself
+    def quantize(rows=n, cols=20, ld=20, q=Q, buf=buf, nbytes=1 << 30, src=0x80000):
+        return l.qgtc_stack_input(src, rows, cols, ld, C.byref(q) if q is not None else None, buf, nbytes, None)
+    assert quantize(src=None) == NULL and quantize(q=None) == NULL and quantize(buf=None) == NULL
+    assert quantize(ld=19) == SHAPE and quantize(rows=-1) == SHAPE and quantize(q=b._QuantC(1.0, 1.0, s)) == SHAPE
+    assert quantize(q=b._QuantC(-1.0, 1.0, 9)) == BITS and quantize(buf=buf + 8) == ALIGN
+    assert quantize(nbytes=l.qgtc_stack_buffer_bytes(n, 20) - 1) == WORKSPACE
+    assert quantize(rows=0) == 0 and quantize(cols=0) == 0
+    assert l.qgtc_stack_buffer_bytes(-1, 4) == 0 and l.qgtc_stack_buffer_bytes(33, 65) == 2 * 2 * 32 * 64
+
+
 def test_probe_arguments_are_checked():
     import paper_2111_09547_amd.binding as b
     l = b.lib()
