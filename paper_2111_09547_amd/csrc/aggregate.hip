@@ -181,12 +181,8 @@ __global__ __launch_bounds__(512) void aggregate_kernel(const AggParams p) {
 
 template <int CT, int WAYS, int KS, int NPT, bool MULTI>
 qgtc_status launch_one(const AggParams& p, size_t lds, hipStream_t stream) {
-  if (lds > 64 * 1024) {
-    static const bool ok =
-        hipFuncSetAttribute(reinterpret_cast<const void*>(&aggregate_kernel<CT, WAYS, KS, NPT, MULTI>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) == hipSuccess;
-    if (!ok) (void)hipGetLastError();
-  }
+  static OncePerDevice once;
+  if (!allow_lds(once, reinterpret_cast<const void*>(&aggregate_kernel<CT, WAYS, KS, NPT, MULTI>), lds)) return QGTC_ERR_HIP;
   hipLaunchKernelGGL((aggregate_kernel<CT, WAYS, KS, NPT, MULTI>), dim3(xcd_deal_grid(p.nblocks, p.run_shift)),
                      dim3((unsigned)(64 * p.n_waves)), lds, stream, p);
   return launch_status();

@@ -559,11 +559,8 @@ __global__ __launch_bounds__(512) void layer_kernel(const LayerParams p) {
 
 template <int CT, int WAYS, int NT, int SRC, int NPT, bool ROWS>
 qgtc_status launch_one(const LayerParams& p, size_t lds, hipStream_t stream) {
-  if (lds > 64 * 1024) {
-    static const bool ok = hipFuncSetAttribute(reinterpret_cast<const void*>(&layer_kernel<CT, WAYS, NT, SRC, NPT, ROWS>),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) == hipSuccess;
-    if (!ok) (void)hipGetLastError();
-  }
+  static OncePerDevice once;
+  if (!allow_lds(once, reinterpret_cast<const void*>(&layer_kernel<CT, WAYS, NT, SRC, NPT, ROWS>), lds)) return QGTC_ERR_HIP;
   hipLaunchKernelGGL((layer_kernel<CT, WAYS, NT, SRC, NPT, ROWS>), dim3(xcd_deal_grid(p.a.nblocks, p.a.run_shift)),
                      dim3((unsigned)(64 * p.a.n_waves)), lds, stream, p);
   return launch_status();

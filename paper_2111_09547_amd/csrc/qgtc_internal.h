@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "per_device.h"
 #include "qgtc.h"
 #include "qgtc_bench.h"
 
@@ -28,6 +29,18 @@ int device_compute_units();
 // Status of the launch that was just issued.
 inline qgtc_status launch_status() {
   return hipGetLastError() == hipSuccess ? QGTC_OK : QGTC_ERR_HIP;
+}
+
+// More than 64 KiB of LDS for a kernel, which the runtime asks to be told once per kernel and device.
+inline bool allow_lds(OncePerDevice& once, const void* kernel, size_t lds) {
+  if (lds <= 64 * 1024) return true;
+  int dev = -1;
+  if (hipGetDevice(&dev) != hipSuccess) dev = -1;
+  const bool ok = once(dev, [&] {
+    return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) == hipSuccess;
+  });
+  if (!ok) (void)hipGetLastError();
+  return ok;
 }
 
 // Brackets the launches of one entry point with HIP events while profiling is on.
