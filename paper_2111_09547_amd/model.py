@@ -125,12 +125,14 @@ class QuantGNN:
         hmax = max(h for _, h in self.dims)
         # Layers of at most 8 bits run as one native call on codes in operand order
         # (qgtc_stack_forward): two activation buffers.  Everything else goes layer by layer on
-        # bit planes: ping-pong buffers of planes, made when they are first needed.
+        # bit planes: ping-pong buffers of planes.  Such a network needs those only for features
+        # that are not fp32; they are then made on the caller's stream (_ready_planes), never on
+        # one of the network's own, whose memory would be given back without regard to the caller's.
         # (A buffer's column group, 64 bytes a row, is addressed with 32 bits.)
         self._fused = not update_first and n < 1 << 26 and all(lay == B.RIGHT_BYTES for lay in self.w_layout) and \
             (self.tuning is None or self.tuning.layer_path == B.LAYER_FUSED)
         self._wmax = max(dmax, hmax)
-        self._x_bufs = None
+        self._x_bufs = None if self._fused else self._alloc_planes()
         self._x_form = None            # what the last packing of the input left: "codes" or "planes"
         self._stacks = {}
         if self._fused:
@@ -146,6 +148,8 @@ class QuantGNN:
         across layers and subgraphs, end of Section 3.2).  With X: the input features
         of the coming forward pass are quantized and packed as well, after the weights
         on their stream (forward(..., x_packed=True) then skips that step)."""
+        if X is not None:
+            self._ready_planes(X)
         # The weights are a handful of small launches that do not depend on the adjacency:
         # they go to a second stream (forked from and joined to the current one, also
         # inside a HIP graph) and run beside the HBM-bound packing of A and its map.
@@ -176,17 +180,25 @@ class QuantGNN:
         cur.wait_stream(self._w_stream)
 
     # -- helpers -----------------------------------------------------------------
+    def _alloc_planes(self):
+        return [B.alloc_bits(self.A.rows, self._wmax, self.s, B.RIGHT) for _ in range(2)]
+
     @property
     def x_bufs(self):
         if self._x_bufs is None:
-            self._x_bufs = [B.alloc_bits(self.A.rows, self._wmax, self.s, B.RIGHT) for _ in range(2)]
+            self._x_bufs = self._alloc_planes()
         return self._x_bufs
 
-    def _x_view(self, which: int, cols: int) -> B.Bits:
+    def _ready_planes(self, X):
+        """In front of work on another stream than the caller's: the buffers that packing X needs."""
+        if not (self._fused and X.dtype == torch.float32):
+            self.x_bufs
+
+    def _x_view(self, which: int, cols: int, bufs=None) -> B.Bits:
         """A [N, cols] RIGHT-packed view on one of the activation buffers.  Every view has
         the strides of the widest layer, so that a range of rows is the same range of
         words whatever the layer (independent runs of rows work on the buffers at once)."""
-        buf = self.x_bufs[which]
+        buf = (bufs or self.x_bufs)[which]
         d, _ = B.describe(self.A.rows, cols, self.s, B.RIGHT)
         d.ld_words = buf.c.ld_words
         d.plane_stride_words = buf.c.plane_stride_words
@@ -337,7 +349,15 @@ class QuantGNN:
         if self.update_first:
             return self._forward_update_first(X, x_range, None, None, False)
         ranges = []
-        xb = self.pack_input(X, x_range)
+        if self._fused and X.dtype == torch.float32:
+            # planes for this call only; the network keeps the features as codes
+            bufs = self._alloc_planes()
+            B.qgtc_stack_input(X, self.s, x_range, self._codes[0])
+            self._x_form = "codes"
+            xb = B.qgtc_pack_bits(X, self.s, B.RIGHT, quant=x_range, out=self._x_view(0, X.shape[1], bufs))
+        else:
+            bufs = self.x_bufs
+            xb = self.pack_input(X, x_range)
         if self._W_planes is None:          # qgtc_update reads bit planes
             self._W_planes = [B.qgtc_pack_bits(W, self.t, B.RIGHT, quant=r)
                               for W, r in zip(self.Ws, self.w_ranges)]
@@ -364,7 +384,7 @@ class QuantGNN:
             ranges.append(LayerRanges(agg_hi, out_hi))
             _, ep, _, x_scale = self._layer_eps(l, 0.0, x_scale, agg_hi, out_hi, last=False)
             ep.col_scale, ep.col_shift = ca, cb
-            xb = B.qgtc_update(yb, W, ep, out=self._x_view((l + 1) & 1, self.dims[l][1]))
+            xb = B.qgtc_update(yb, W, ep, out=self._x_view((l + 1) & 1, self.dims[l][1], bufs))
         return ranges
 
     # -- forward ---------------------------------------------------------------------
@@ -448,6 +468,9 @@ class QuantGNN:
             self.forward(X, x_range, ranges, out=out, want_int=want_int, streams=streams,
                          x_packed=with_static and not self.update_first)
 
+        self._ready_planes(X)
+        if not self.update_first:
+            self._epilogues(x_range, ranges, want_int)       # folded batch normalizations, on the caller's stream
         cur = torch.cuda.current_stream()
         side = torch.cuda.Stream()
         side.wait_stream(cur)

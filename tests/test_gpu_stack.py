@@ -11,7 +11,8 @@ from oracle import qgnn
 pytestmark = pytest.mark.gpu
 
 q = pytest.importorskip("paper_2111_09547_amd")
-from paper_2111_09547_amd.model import QuantGNN  # noqa: E402
+import paper_2111_09547_amd.binding as B  # noqa: E402
+from paper_2111_09547_amd.model import BatchNorm, LayerRanges, QuantGNN  # noqa: E402
 from gpu_util import dev, as_u32, assert_fp32_close  # noqa: E402
 
 
@@ -131,3 +132,41 @@ def test_four_units_side_by_side_on_planes(cols, s):
     for tmap in (None, q.qgtc_build_tile_map(A, 16, 64)):
         assert (as_u32(q.qgtc_aggregate(A, tmap, X, q.Epilogue(mode=q.OUT_I32))) == y).all()
         assert (as_u32(q.qgtc_layer(A, tmap, X, W, first, q.Epilogue(mode=q.OUT_I32))) == z).all()
+
+
+def small_net(rng, blocks=3, block=96, dims=(20, 24, 9), s=4, bn=False):
+    a, _ = block_graph(rng, blocks, block, 0, 6.0)
+    Ws = [dev(rng.uniform(-1, 1, dh).astype(np.float32)) for dh in zip(dims[:-1], dims[1:])]
+    norms = [BatchNorm(*(rng.uniform(0.5, 1.5, h).tolist() for _ in range(4))) for h in dims[1:-1]] + [None]
+    net = QuantGNN(dev(a), Ws, s, s, False, block_rows=block, batchnorm=norms if bn else None)
+    return net, dev(rng.standard_normal((blocks * block, dims[0])).astype(np.float32))
+
+
+@pytest.mark.parametrize("ints", [False, True])
+def test_buffers_are_made_on_the_callers_stream(monkeypatch, ints):
+    """Memory that a network keeps belongs to the caller's stream: what is made on one of the
+    network's own streams is given back in the order of that one alone."""
+    net, x = small_net(np.random.default_rng(5), bn=True)
+    xr = (-3.0, 3.0)
+    if ints:
+        x = torch.randint(0, 16, x.shape, dtype=torch.int32, device="cuda")
+    ranges = [LayerRanges(300, 2.0), LayerRanges(400, None)]
+    caller, made = torch.cuda.current_stream(), []
+    real_alloc, real_fold = B.alloc_bits, B.qgtc_fold_batchnorm
+    monkeypatch.setattr(B, "alloc_bits", lambda *a, **k: made.append(torch.cuda.current_stream()) or real_alloc(*a, **k))
+    monkeypatch.setattr(B, "qgtc_fold_batchnorm", lambda *a: made.append(torch.cuda.current_stream()) or real_fold(*a))
+    net.pack_static(x, xr)
+    graph = net.capture(x, xr, ranges, torch.empty((x.shape[0], 9), device="cuda"), with_static=True)
+    assert made and all(m == caller for m in made)
+    assert (net._x_bufs is not None) == ints         # planes only where the features need them
+    del graph
+
+
+def test_calibration_leaves_the_features_packed():
+    net, x = small_net(np.random.default_rng(6))
+    xr = (-3.0, 3.0)
+    ranges = net.calibrate(x, xr)
+    out = net.forward(x, xr, ranges)
+    net.calibrate(x, xr)
+    assert torch.equal(net.forward(x, xr, ranges, x_packed=True), out)
+    assert net._x_bufs is None
