@@ -541,9 +541,10 @@ class QuantGNN:
                         even_progress=base.even_progress or (plan["even_progress"] if same_form else 1))
 
     def _stack(self, x_range, ranges, want_int) -> "B.Stack":
-        """The prepared native call for these ranges (a caller's handful of them is kept)."""
+        """The prepared native call for these ranges (a caller's handful of them is kept).  An entry
+        holds on to the operands that its key names, so that none of them can be another one by now."""
         key = (float(x_range[0]), float(x_range[1]), bool(want_int), tuple(vars(self.tuning).values()) if self.tuning else None, *self.w_ranges,
-               self.map.c.row_cnt if self.map is not None else None, self.deg.data_ptr(),
+               self.self_term, id(self.A), id(self.map), self.deg.data_ptr(), *map(id, self.W),
                *[(r.agg_hi, r.out_hi) for r in ranges])
         stack = self._stacks.get(key)
         if stack is None:

@@ -170,3 +170,21 @@ def test_calibration_leaves_the_features_packed():
     net.calibrate(x, xr)
     assert torch.equal(net.forward(x, xr, ranges, x_packed=True), out)
     assert net._x_bufs is None
+
+
+def test_prepared_pass_follows_the_operands():
+    """Adjacency, weights and self term replaced between passes with the same ranges."""
+    rng = np.random.default_rng(7)
+    net, x = small_net(rng)
+    other, _ = small_net(rng)
+    xr, ranges = (-3.0, 3.0), [LayerRanges(300, 900.0), LayerRanges(400, None)]
+    net.w_ranges = other.w_ranges                    # (the same key but for the operands)
+    first = net.forward(x, xr, ranges).clone()
+    want = other.forward(x, xr, ranges)
+    assert not torch.equal(first, want)
+    net.A, net.A_src, net.Ws = other.A, other.A_src, other.Ws
+    net.pack_static()                                # into the same map and weights
+    assert torch.equal(net.forward(x, xr, ranges), want)
+    net.self_term = other.self_term = True
+    with_self = net.forward(x, xr, ranges)
+    assert not torch.equal(with_self, want) and torch.equal(with_self, other.forward(x, xr, ranges))
