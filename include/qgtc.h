@@ -313,6 +313,10 @@ qgtc_status qgtc_aggregate(const qgtc_bits* A, const qgtc_tile_map* map,
                            const qgtc_bits* X, const qgtc_epilogue* ep,
                            void* out, int64_t ld_out, void* stream);
 
+/* 1 if qgtc_aggregate of this A with x_cols columns would look at a tile map, 0 if not (rows too
+ * short for the list of their tiles to save anything: a map need not be built for the call). */
+int32_t qgtc_aggregate_reads_map(const qgtc_bits* A, int32_t x_cols);
+
 /* Node update C = Y.W (second half of Algorithm 1).
  * Y: LEFT, s bits, rows x K, or LEFT_BYTES (then s, t <= 8: the product runs on the
  * int8 matrix cores).  W: RIGHT, t bits, K x cols. */

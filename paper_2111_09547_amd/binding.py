@@ -138,6 +138,7 @@ def lib():
                                  P(_EpilogueC), vp, sz, vp, i64, vp]),
         "qgtc_layer_static": (C.c_int, [P(_BitsC), P(_TileMapC), P(_BitsC), P(_BitsC), P(_EpilogueC),
                                         P(_EpilogueC), vp, i64, vp]),
+        "qgtc_aggregate_reads_map": (i32, [P(_BitsC), i32]),
         "qgtc_stack_buffer_bytes": (sz, [i32, i32]),
         "qgtc_stack_input": (C.c_int, [vp, i32, i32, i64, P(_QuantC), vp, sz, vp]),
         "qgtc_stack_forward": (C.c_int, [P(_StackC), vp, i64, P(_QuantC), P(_BitsC), vp, i64, vp]),
@@ -375,6 +376,11 @@ def qgtc_aggregate(A: Bits, tmap: TileMap | None, X: Bits, ep: Epilogue, out=Non
     _check(lib().qgtc_aggregate(C.byref(A.c), m, C.byref(X.c), C.byref(epc), ptr, ld, _stream()),
            "qgtc_aggregate")
     return res
+
+
+def qgtc_aggregate_reads_map(A: Bits, x_cols: int) -> bool:
+    """Whether a product with x_cols columns would look at a tile map of A."""
+    return bool(lib().qgtc_aggregate_reads_map(C.byref(A.c), x_cols))
 
 
 def qgtc_update(Y: Bits, W: Bits, ep: Epilogue, out=None):

@@ -90,7 +90,8 @@ def _product(A: BitTensor, Bm: BitTensor, ep: B.Epilogue, tile_map):
         raise ValueError("the left operand must be packed with side='left', the right one with side='right'")
     if A.is_adjacency():
         # a binary left operand in adjacency form: the aggregation kernel, with zero-tile jumping
-        if tile_map is None:
+        # where it looks at a map
+        if tile_map is None and B.qgtc_aggregate_reads_map(A.bits, Bm.bits.cols):
             tile_map = B.qgtc_build_tile_map(A.bits, 16, 128)
         return B.qgtc_aggregate(A.bits, tile_map, Bm.bits, ep)
     # any other left operand (several bits, or a 1-bit result without the row padding)

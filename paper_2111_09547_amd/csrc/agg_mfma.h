@@ -163,6 +163,13 @@ __host__ __device__ __forceinline__ unsigned div_by(unsigned n, unsigned d, uint
 // The split of a stand-alone aggregation of `cols` columns.
 AggSplit aggregate_split(int rows, int cols, int a_words);
 
+// A tile map is worth its loads (two dependent ones in front of the first stage) where the list of
+// chunks can save stages: for rows of more than 1024 columns with diagonal blocks, of more than one
+// stage without.
+inline bool agg_reads_map(const AggParams& p, const AggSplit& sp) {
+  return p.sub_per_wg == 1 && p.n_chunks <= 8192 && p.n_chunks > (p.block_rows > 0 ? 8 : sp.chunks());
+}
+
 // Launch shape for a split; n_col_wg: workgroups along the columns.
 // Returns the dynamic LDS that the aggregation needs.
 //   Units side by side: as many (at most four, and eight waves) as leave every compute unit a
@@ -212,10 +219,8 @@ inline size_t agg_set_shape(AggParams* p, const AggSplit& sp, int n_col_wg, int 
   p->run_shift = sh;
   p->slot_bytes = sp.slot_bytes(nu);
   size_t lds = (size_t)p->slot_bytes * kSlots;
-  // The list of chunks pays for its loads (two dependent ones) where it can save stages: for
-  // rows of more than 1024 columns, and for storage with off-diagonal blocks.
   p->list_off = 0;
-  if (p->row_cnt && p->sub_per_wg == 1 && p->n_chunks <= 8192 && p->n_chunks > (p->block_rows > 0 ? 8 : sp.chunks())) {
+  if (p->row_cnt && agg_reads_map(*p, sp)) {
     p->list_off = (int)lds;
     lds += (size_t)((2 * p->n_chunks + 3) / 4 + cdiv(p->n_chunks, 32) + 1) * 4;
     lds = (lds + 15) & ~(size_t)15;

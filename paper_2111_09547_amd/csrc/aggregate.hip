@@ -216,6 +216,15 @@ AggSplit aggregate_split(int rows, int cols, int a_words) {
 
 using namespace qgtc;
 
+extern "C" int32_t qgtc_aggregate_reads_map(const qgtc_bits* A, int32_t x_cols) {
+  AggParams p{};
+  if (!A || x_cols < 1 || agg_fill_adjacency(A, nullptr, &p) != QGTC_OK || A->rows == 0) return 0;
+  p.cols = x_cols;
+  const AggSplit sp = aggregate_split(A->rows, x_cols, p.a_words);
+  (void)agg_set_shape(&p, sp, cdiv(x_cols, sp.group()), 0);
+  return agg_reads_map(p, sp) ? 1 : 0;
+}
+
 extern "C" qgtc_status qgtc_aggregate(const qgtc_bits* A, const qgtc_tile_map* map, const qgtc_bits* X,
                                       const qgtc_epilogue* ep, void* out, int64_t ld_out, void* stream) {
   if (!A || !X || !ep) return QGTC_ERR_NULL;

@@ -91,3 +91,21 @@ def test_one_bit_layer_chained_through_the_products(d):
     padded = BitTensor(dst)
     assert padded.is_adjacency()
     assert (as_u32(bitMM2Int(padded, Wb)) == Z).all()
+
+
+def test_product_builds_no_map_that_nobody_reads(monkeypatch):
+    """Operands whose rows are one stage of the aggregation: two launches and an allocation less;
+    longer rows still get a map, and the integers are the product's either way."""
+    import paper_2111_09547_amd.bit_tensor as bt
+    built = []
+    real = bt.B.qgtc_build_tile_map
+    monkeypatch.setattr(bt.B, "qgtc_build_tile_map", lambda *a, **k: built.append(a) or real(*a, **k))
+    rng = np.random.default_rng(11)
+    for n, d, want in ((256, 16, False), (100, 3, False), (257, 16, True), (3000, 16, True), (2100, 300, True)):
+        a = (rng.random((n, n)) < 0.03).astype(np.uint8)
+        x = rng.integers(0, 4, (n, d)).astype(np.int32)
+        A, X = to_bit(dev(a), 1, side="left"), to_bit(dev(x), 2)
+        built.clear()
+        y = bitMM2Int(A, X)
+        assert bool(built) == want == bt.B.qgtc_aggregate_reads_map(A.bits, d), (n, d)
+        assert (as_u32(y) == qgnn.aggregate(a, x.astype(np.uint32))).all()
