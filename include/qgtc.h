@@ -307,7 +307,8 @@ typedef struct qgtc_epilogue {
  * and non-zero tile reuse, Sections 4.3 and 4.4).
  * A: LEFT, 1 bit, rows x K (or block-diagonal, see block_rows).
  * map: tile map of A, or NULL to visit every tile.
- * X: RIGHT, s bits, K x cols.  X must span less than 4 GiB.
+ * X: RIGHT, s bits, K x cols.  X must span less than 4 GiB, the rows of A lie less than 2^25
+ * words apart.
  * out / ld_out: per epilogue mode (ld_out in elements; ignored for BITS). */
 qgtc_status qgtc_aggregate(const qgtc_bits* A, const qgtc_tile_map* map,
                            const qgtc_bits* X, const qgtc_epilogue* ep,
@@ -386,7 +387,9 @@ qgtc_status qgtc_layer_static(const qgtc_bits* A, const qgtc_tile_map* map,
  *   buffer[2]       device, 16-byte aligned, buffer_bytes each: at least
  *                   qgtc_stack_buffer_bytes(rows, columns) of every layer's input
  * Limits: s and t at most 8 bits, at most 1024 input and 256 output columns per layer, A
- * square or block-diagonal (else QGTC_ERR_UNSUPPORTED / _SHAPE).
+ * square or block-diagonal with rows less than 2^24 words apart, less than 2^26 rows (fewer than
+ * 2^27 or 2^28 where every layer has at most 32 or 16 input columns), else QGTC_ERR_UNSUPPORTED /
+ * _SHAPE.
  *
  * qgtc_stack_input    Eq. (2) of fp32 features into `buffer` (buffer[0] of the pass to come)
  * qgtc_stack_forward  the pass.  Features: src != NULL - fp32, quantized first with q; else

@@ -99,7 +99,7 @@ struct AggParams {
 inline qgtc_status agg_fill_adjacency(const qgtc_bits* A, const qgtc_tile_map* map, AggParams* p) {
   qgtc_status st = check_adjacency(A);
   if (st != QGTC_OK) return st;
-  if (A->ld_words * 128 >= (int64_t)1 << 31) return QGTC_ERR_UNSUPPORTED;
+  if (A->ld_words * 64 >= (int64_t)1 << 31) return QGTC_ERR_UNSUPPORTED;
   p->A = A->data;
   p->lda = A->ld_words;
   p->a_words = 4 * cdiv(A->cols, 128);
@@ -160,8 +160,12 @@ __host__ __device__ __forceinline__ unsigned div_by(unsigned n, unsigned d, uint
   return q - (unsigned)(q * d > n);
 }
 
+// A wave addresses its rows of A with 32 bits: 64 rows where one wave has a unit, 32 or fewer where
+// several share it, which rows of 64 MiB and more need.
+inline bool agg_long_rows(int64_t lda) { return lda >= (int64_t)1 << 24; }
+
 // The split of a stand-alone aggregation of `cols` columns.
-AggSplit aggregate_split(int rows, int cols, int a_words);
+AggSplit aggregate_split(int rows, int cols, int a_words, int64_t lda);
 
 // A tile map is worth its loads (two dependent ones in front of the first stage) where the list of
 // chunks can save stages: for rows of more than 1024 columns with diagonal blocks, of more than one
@@ -456,10 +460,11 @@ __device__ __forceinline__ void agg_run(const AggParams& p, const AggWave& w, ui
 
   // ---- loads of a stage ----
   const uint32_t lda4 = (uint32_t)p.lda * 4u;
-  const v4u ra = uniform_words(p.A + (uint64_t)(uint32_t)w.row0 * (uint64_t)p.lda,
-                               w.rows_here > 0 ? (uint32_t)(w.rows_here - 1) * lda4 + (uint32_t)p.a_words * 4u : 0u);
+  const int a_rows = min(w.rows_here - w.way * RPW, RPW);   // the wave's
+  const v4u ra = uniform_words(p.A + (uint64_t)(uint32_t)(w.row0 + w.way * RPW) * (uint64_t)p.lda,
+                               a_rows > 0 ? (uint32_t)(a_rows - 1) * lda4 + (uint32_t)p.a_words * 4u : 0u);
   // (the stage is a scalar offset where all chunks are taken)
-  const uint32_t arow = (uint32_t)(w.way * RPW + lane % RPW) * lda4, a_chunk = (uint32_t)(lane / RPW);
+  const uint32_t arow = (uint32_t)(lane % RPW) * lda4, a_chunk = (uint32_t)(lane / RPW);
   const uint32_t a_to = (uint32_t)(X_BYTES + w.u * TSC * 1024 + w.kp * SWC * 1024 + w.way * A_WAVE);
   auto load_a = [&](int st, uint32_t slot) {
 #pragma unroll

@@ -204,10 +204,11 @@ qgtc_status launch(const AggParams& p, size_t lds, hipStream_t stream) {
 // units: the rows of A are then expanded once per group, which costs less than idle units.
 // Where that leaves two or fewer waves per compute unit, four of them share a unit's stages
 // (8192 x 8192 x 64: two waves of 16 columns 33 us, eight of them 18 us).
-AggSplit aggregate_split(int rows, int cols, int a_words) {
+AggSplit aggregate_split(int rows, int cols, int a_words, int64_t lda) {
   const int64_t units = cdiv(rows, kUnitRows), enough = 2 * (int64_t)device_compute_units();
   AggSplit sp{2, 2, 2, 1};
   if (cols <= 32 || units * cdiv(cols, 64) < enough) sp = AggSplit{1, 2, 1, 1};
+  if (agg_long_rows(lda)) return sp;
   if (cols <= 16 || units * cdiv(cols, 32) < enough) sp = AggSplit{1, 1, 1, units * cdiv(cols, 16) <= enough && a_words > 32 ? 4 : 1};
   return sp;
 }
@@ -220,7 +221,7 @@ extern "C" int32_t qgtc_aggregate_reads_map(const qgtc_bits* A, int32_t x_cols) 
   AggParams p{};
   if (!A || x_cols < 1 || agg_fill_adjacency(A, nullptr, &p) != QGTC_OK || A->rows == 0) return 0;
   p.cols = x_cols;
-  const AggSplit sp = aggregate_split(A->rows, x_cols, p.a_words);
+  const AggSplit sp = aggregate_split(A->rows, x_cols, p.a_words, A->ld_words);
   (void)agg_set_shape(&p, sp, cdiv(x_cols, sp.group()), 0);
   return agg_reads_map(p, sp) ? 1 : 0;
 }
@@ -239,7 +240,7 @@ extern "C" qgtc_status qgtc_aggregate(const qgtc_bits* A, const qgtc_tile_map* m
   if (st != QGTC_OK) return st;
   if (A->rows == 0 || X->cols == 0) return QGTC_OK;
 
-  const AggSplit sp = aggregate_split(A->rows, X->cols, p.a_words);
+  const AggSplit sp = aggregate_split(A->rows, X->cols, p.a_words, A->ld_words);
   const size_t lds = agg_set_shape(&p, sp, cdiv(X->cols, sp.group()), ep->tuning ? ep->tuning->agg_xcd_run : 0);
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   ProfScope prof(QGTC_KERNEL_AGGREGATE, s);

@@ -25,7 +25,7 @@ template <int NT>
 qgtc_status layer_launch(const LayerParams& p, const AggSplit& sp, bool codes, size_t lds_bytes, hipStream_t stream);
 
 // The split of a fused layer of `cols` input and `h` output columns over `rows` nodes.
-AggSplit layer_split(int rows, int cols, int h);
+AggSplit layer_split(int rows, int cols, int h, int64_t lda);
 
 // Launch of a layer whose operands (p->a) and epilogues (p->a.ep, p->up) are filled in; W: RIGHT_BYTES.
 qgtc_status layer_run(LayerParams* p, const AggSplit& sp, bool codes, const qgtc_bits* W, const qgtc_epilogue* upd_ep, hipStream_t stream);

@@ -83,7 +83,7 @@ qgtc_status layer_fused(const qgtc_bits* A, const qgtc_tile_map* map, const qgtc
   ea.rq_lo = agg_ep->rq_lo;
   ea.rq_inv_scale = agg_ep->rq_inv_scale;
 
-  const AggSplit sp = layer_split(A->rows, X->cols, W->cols);
+  const AggSplit sp = layer_split(A->rows, X->cols, W->cols, A->ld_words);
   if (w_bytes) {
     *done = true;
     return layer_run(&p, sp, false, W, upd_ep, stream);
@@ -110,9 +110,9 @@ qgtc_status layer_fused(const qgtc_bits* A, const qgtc_tile_map* map, const qgtc
 // Two waves per unit where 256 rows per workgroup still give every compute unit one, four below
 // (and for more than 64 output columns behind several passes, whose accumulators do not fit
 // otherwise); the columns are split as evenly as 16-column tiles allow.
-AggSplit layer_split(int rows, int cols, int h) {
+AggSplit layer_split(int rows, int cols, int h, int64_t lda) {
   const bool many = (int64_t)cdiv(rows, kUnitRows) >= (int64_t)kMaxUnits * device_compute_units();
-  if (cols <= 16) return AggSplit{1, 1, 1, 1};
+  if (cols <= 16 && !agg_long_rows(lda)) return AggSplit{1, 1, 1, 1};
   if (cols <= 32) return AggSplit{1, 2, 2, 1};
   if (cols <= 64) return many ? AggSplit{2, 2, 4, 1} : AggSplit{1, 4, 4, 1};
   return many && (cols <= 128 || h <= 64) ? AggSplit{4, 2, 4, 1} : AggSplit{2, 4, 4, 1};

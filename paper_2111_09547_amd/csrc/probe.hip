@@ -58,9 +58,9 @@ extern "C" int64_t qgtc_probe_units(const qgtc_bits* A, int32_t x_cols, int32_t 
   AggParams p{};
   if (agg_fill_params(A, nullptr, &x, &p) != QGTC_OK) return -1;
   if (out_cols > 0) {
-    (void)agg_set_shape(&p, layer_split(A->rows, x_cols, out_cols), 1, 0);
+    (void)agg_set_shape(&p, layer_split(A->rows, x_cols, out_cols, A->ld_words), 1, 0);
   } else {
-    const AggSplit sp = aggregate_split(A->rows, x_cols, p.a_words);
+    const AggSplit sp = aggregate_split(A->rows, x_cols, p.a_words, A->ld_words);
     (void)agg_set_shape(&p, sp, cdiv(x_cols, sp.group()), 0);
   }
   for (int64_t b = first; b < first + count && b < (int64_t)p.nblocks; ++b)

@@ -154,7 +154,7 @@ static qgtc_status layer_codes(const qgtc_bits* A, const qgtc_tile_map* map, con
   e.rq_nbits = agg_ep->rq_nbits;
   e.rq_lo = agg_ep->rq_lo;
   e.rq_inv_scale = agg_ep->rq_inv_scale;
-  return layer_run(&p, layer_split(A->rows, x_cols, W->cols), X == nullptr, W, upd_ep, stream);
+  return layer_run(&p, layer_split(A->rows, x_cols, W->cols, A->ld_words), X == nullptr, W, upd_ep, stream);
 }
 
 }  // namespace qgtc
@@ -189,6 +189,7 @@ extern "C" qgtc_status qgtc_stack_forward(const qgtc_stack* st, const float* src
   if (rc != QGTC_OK) return rc;
   const int rows = st->A->rows;
   if (st->A->block_rows == 0 && st->A->cols != rows) return QGTC_ERR_SHAPE;
+  if (agg_long_rows(st->A->ld_words)) return QGTC_ERR_UNSUPPORTED;   // (their split has another order of codes)
   if ((((uintptr_t)st->buffer[0] | (uintptr_t)st->buffer[1]) & 15u) != 0) return QGTC_ERR_ALIGN;
   auto scale_ok = [](float v) { return v > 0.0f && v < INFINITY; };
   for (int l = 0; l < st->n_layers; ++l) {

@@ -128,8 +128,8 @@ class QuantGNN:
         # bit planes: ping-pong buffers of planes.  Such a network needs those only for features
         # that are not fp32; they are then made on the caller's stream (_ready_planes), never on
         # one of the network's own, whose memory would be given back without regard to the caller's.
-        # (A buffer's column group, 64 bytes a row, is addressed with 32 bits.)
-        self._fused = not update_first and n < 1 << 26 and all(lay == B.RIGHT_BYTES for lay in self.w_layout) and \
+        # (A buffer's column group, 64 bytes a row, is addressed with 32 bits, and so are a wave's rows of A.)
+        self._fused = not update_first and n < 1 << 26 and self.A.c.ld_words < 1 << 24 and all(lay == B.RIGHT_BYTES for lay in self.w_layout) and \
             (self.tuning is None or self.tuning.layer_path == B.LAYER_FUSED)
         self._wmax = max(dmax, hmax)
         self._x_bufs = None if self._fused else self._alloc_planes()

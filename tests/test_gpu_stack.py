@@ -188,3 +188,27 @@ def test_prepared_pass_follows_the_operands():
     net.self_term = other.self_term = True
     with_self = net.forward(x, xr, ranges)
     assert not torch.equal(with_self, want) and torch.equal(with_self, other.forward(x, xr, ranges))
+
+
+def test_adjacency_rows_of_64_MiB_and_more():
+    """Rows that lie so far apart that only 32 of them are within 4 GiB: the same integers as
+    from the same rows side by side, narrow and wide, alone and in a layer."""
+    rng = np.random.default_rng(12)
+    rows, k, pitch, s = 70, 300, 1 << 24, 3
+    a = (rng.random((rows, k)) < 0.1).astype(np.uint8)
+    near = q.qgtc_pack_bits(dev(a), 1, q.LEFT)
+    c = B._BitsC.from_buffer_copy(near.c)
+    words = torch.zeros(rows * pitch, dtype=torch.int32, device="cuda")
+    c.ld_words, c.plane_stride_words, c.data = pitch, rows * pitch, words.data_ptr()
+    words.view(rows, pitch)[:, :near.c.ld_words] = near.words.view(rows, near.c.ld_words)
+    far = q.Bits(words, c)
+    for cols in (5, 40, 200):
+        x = rng.integers(0, 1 << s, (k, cols)).astype(np.int32)
+        w = rng.integers(0, 1 << s, (cols, 7)).astype(np.int32)
+        X, W = q.qgtc_pack_bits(dev(x), s, q.RIGHT), q.qgtc_pack_bits(dev(w), s, q.RIGHT_BYTES)
+        y, _, z, (lo, inv) = qgnn.layer(a, x.astype(np.uint32), w.astype(np.uint32), s)
+        first = q.Epilogue(mode=q.OUT_BITS, rq_nbits=s, rq_lo=lo, rq_inv_scale=float(inv))
+        for A in (near, far):
+            for tmap in (None, q.qgtc_build_tile_map(A, 16, 32)):
+                assert (as_u32(q.qgtc_aggregate(A, tmap, X, q.Epilogue(mode=q.OUT_I32))) == y).all()
+                assert (as_u32(q.qgtc_layer(A, tmap, X, W, first, q.Epilogue(mode=q.OUT_I32))) == z).all()

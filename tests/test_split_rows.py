@@ -42,3 +42,16 @@ def test_every_row_is_taken_once(rows, cols, block_rows, x_cols, out_cols):
     assert (np.bincount(col[on]) == len(starts)).all()           # the same rows along every column workgroup
     assert (first.reshape(-1, n_col) == first.reshape(-1, n_col)[:, :1]).all()
     assert starts[0] == 0 and (starts[1:] == starts[:-1] + lens[:-1]).all() and starts[-1] + lens[-1] == rows
+
+
+@pytest.mark.parametrize("x_cols,out_cols", [(5, 0), (40, 0), (5, 7), (200, 7)])
+def test_rows_of_up_to_128_MiB(x_cols, out_cols):
+    """Rows far apart are taken like those side by side; at 2^25 words they are refused."""
+    for ld, taken in (((1 << 24) - 4, True), (1 << 24, True), ((1 << 25) - 4, True), (1 << 25, False)):
+        d, _ = b.describe(70, 300, 1, b.LEFT)
+        d.data, d.ld_words = 0x10000, ld
+        out = [np.zeros((4, 4), np.int32) for _ in range(3)]
+        n = b.lib().qgtc_probe_units(C.byref(d), x_cols, out_cols, 0, 4, *[o.ctypes.data for o in out])
+        assert (n > 0) == taken, ld
+        if taken:
+            assert sorted(set(out[1][out[2] > 0].tolist())) == [0, 64] and out[2].max() == 64
