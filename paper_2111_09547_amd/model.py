@@ -333,14 +333,15 @@ class QuantGNN:
 
     def _bn_fold(self, l: int, value_scale: float):
         """(col_scale, col_shift) of layer l's batch normalization acting on value_scale * C
-        (qgtc_fold_batchnorm).  Cached per scale so that a recorded pass allocates nothing."""
-        key = (l, float(value_scale))
+        (qgtc_fold_batchnorm).  Cached per scale so that a recorded pass allocates nothing; an entry
+        holds on to its BatchNorm, so that the key stands for no other one."""
+        bn = self.batchnorm[l]
+        key = (l, float(value_scale), id(bn))
         if key not in self._bn_cache:
-            bn = self.batchnorm[l]
             a, b = B.qgtc_fold_batchnorm(bn.gamma, bn.beta, bn.mean, bn.var, bn.eps, value_scale)
             dv = self.A.words.device
-            self._bn_cache[key] = (a.to(dv), b.to(dv))
-        return self._bn_cache[key]
+            self._bn_cache[key] = (a.to(dv), b.to(dv), bn)
+        return self._bn_cache[key][:2]
 
     # -- calibration: integer maxima per layer, from int32 outputs ---------------------
     def calibrate(self, X: torch.Tensor, x_range):
@@ -544,7 +545,7 @@ class QuantGNN:
         """The prepared native call for these ranges (a caller's handful of them is kept).  An entry
         holds on to the operands that its key names, so that none of them can be another one by now."""
         key = (float(x_range[0]), float(x_range[1]), bool(want_int), tuple(vars(self.tuning).values()) if self.tuning else None, *self.w_ranges,
-               self.self_term, id(self.A), id(self.map), self.deg.data_ptr(), *map(id, self.W),
+               self.self_term, id(self.A), id(self.map), self.deg.data_ptr(), *map(id, self.W), *map(id, self.batchnorm),
                *[(r.agg_hi, r.out_hi) for r in ranges])
         stack = self._stacks.get(key)
         if stack is None:

@@ -190,6 +190,24 @@ def test_prepared_pass_follows_the_operands():
     assert not torch.equal(with_self, want) and torch.equal(with_self, other.forward(x, xr, ranges))
 
 
+def test_prepared_pass_follows_the_batch_normalization():
+    """A hidden layer's batch normalization replaced, and taken away, between passes with the same ranges."""
+    net, x = small_net(np.random.default_rng(8), bn=True)
+    xr, ranges = (-3.0, 3.0), [LayerRanges(300, 2.0), LayerRanges(400, None)]
+
+    def fresh(bn):
+        other = QuantGNN(net.A, net.Ws, net.s, net.t, False, block_rows=96, batchnorm=bn)
+        return other.forward(x, xr, ranges)
+
+    bn = net.batchnorm[0]
+    outs = [net.forward(x, xr, ranges)]
+    for new in (BatchNorm([0.5 * v for v in bn.gamma], bn.beta, bn.mean, bn.var), None, bn):
+        net.batchnorm[0] = new
+        outs.append(net.forward(x, xr, ranges))
+        assert torch.equal(outs[-1], fresh(list(net.batchnorm)))
+    assert torch.equal(outs[0], outs[3]) and not torch.equal(outs[0], outs[1]) and not torch.equal(outs[0], outs[2])
+
+
 def test_adjacency_rows_of_64_MiB_and_more():
     """Rows that lie so far apart that only 32 of them are within 4 GiB: the same integers as
     from the same rows side by side, narrow and wide, alone and in a layer."""
