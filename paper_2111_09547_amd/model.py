@@ -410,7 +410,8 @@ class QuantGNN:
                               device=self.A.words.device)
         if self.update_first:
             return self._forward_update_first(X, x_range, ranges, out, want_int)
-        if self._fused and (x_bits is not None or x_packed or X.dtype == torch.float32):
+        # (planes of another width than the network's go layer by layer: their first layer is another one)
+        if self._fused and (x_bits.nbits == self.s if x_bits is not None else x_packed or X.dtype == torch.float32):
             # one run whatever `streams` says: the launches of a stack fill the device by themselves
             if not isinstance(streams, int) and self.A.c.block_rows > 0:
                 assert sum(streams) >= -(-n // self.A.c.block_rows)

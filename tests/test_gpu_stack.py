@@ -208,6 +208,19 @@ def test_prepared_pass_follows_the_batch_normalization():
     assert torch.equal(outs[0], outs[3]) and not torch.equal(outs[0], outs[1]) and not torch.equal(outs[0], outs[2])
 
 
+@pytest.mark.parametrize("width", [2, 8])
+def test_planes_of_another_width_than_the_networks(width):
+    """forward(x_bits=...) takes planes of any width up to 8 bits, as qgtc_layer does."""
+    net, _ = small_net(np.random.default_rng(9), dims=(20, 24, 9))
+    n, ranges = net.A.rows, [LayerRanges(300 << (width - 2), 90000.0), LayerRanges(400, None)]
+    X = q.qgtc_pack_bits(torch.randint(0, 1 << width, (n, 20), dtype=torch.int32, device="cuda"), width, q.RIGHT)
+    got = net.forward(None, (0.0, 1.0), ranges, x_bits=X, want_int=True)
+    (f0, s0), (f1, s1) = net._epilogues((0.0, 1.0), ranges, True)
+    hidden = q.qgtc_layer(net.A, net.map, X, net.W[0], f0, s0)
+    assert torch.equal(got, q.qgtc_layer(net.A, net.map, hidden, net.W[1], f1, s1))
+    assert int(got.abs().sum()) > 0
+
+
 def test_adjacency_rows_of_64_MiB_and_more():
     """Rows that lie so far apart that only 32 of them are within 4 GiB: the same integers as
     from the same rows side by side, narrow and wide, alone and in a layer."""
