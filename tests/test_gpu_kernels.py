@@ -571,10 +571,9 @@ def test_fused_layer_all_outputs(shape, st):
         storages.append((q.qgtc_pack_bits(dev(compact), 1, q.LEFT, block_rows=block), 32))
     for Ab, kb in storages:
         m = q.qgtc_build_tile_map(Ab, 16, kb) if kb else None
-        for path, ksplit in ((q.LAYER_FUSED, 0), (q.LAYER_FUSED, 1), (q.LAYER_FUSED, 2),
-                             (q.LAYER_FUSED, 4), (q.LAYER_TWO_KERNELS, 0)):
-            tn = q.Tuning(layer_path=path, layer_ksplit=ksplit)
-            tag = (kb, path, ksplit)
+        for path in (q.LAYER_FUSED, q.LAYER_TWO_KERNELS):
+            tn = q.Tuning(layer_path=path)
+            tag = (kb, path)
             q.qgtc_prof_enable(True)
             q.qgtc_prof_reset()
             got = q.qgtc_layer(Ab, m, Xb, Wb, agg_ep, q.Epilogue(mode=q.OUT_I32, tuning=tn))
@@ -717,9 +716,10 @@ def test_update_matrix_core_path_equals_popcount_and_oracle(st, shape):
 @pytest.mark.parametrize("shape,p_edge", [((300, 64), 0.01), ((300, 64), 0.6), ((130, 20), 0.03), ((257, 130), 0.002),
                                           ((64, 16), 1.0), ((515, 300), 0.0)])
 def test_zero_word_jumping_gives_the_same_integers(s, shape, p_edge):
-    """The aggregation with every word of a kept tile visited and with the zero words
-    jumped over (qgtc_tuning.zero_words), with and without a map, at the three tile widths,
-    stand-alone and inside the fused layer: the same integers as the oracle."""
+    """Rows and columns of tiles without a bit, every chunk of K taken (no map) and those of the
+    list alone (a map of each tile width), stand-alone and inside the fused layer, where stages of
+    zeros are left out: the same integers as the oracle.  The hints of qgtc_tuning that describe
+    the walk of a tile list change nothing."""
     n, d = shape
     rng = np.random.default_rng([83, s, n, d, int(p_edge * 1000)])
     A = rand_graph(rng, n, n, p_edge)
@@ -738,34 +738,27 @@ def test_zero_word_jumping_gives_the_same_integers(s, shape, p_edge):
     Z = qgnn.update(qgnn.requantize(Y, 0, inv, rq_bits), Wq)
     for kb in (None, 32, 64, 128):
         m = q.qgtc_build_tile_map(Ab, 16, kb) if kb else None
-        for zw in (q.ZERO_WORDS_AUTO, q.ZERO_WORDS_VISIT, q.ZERO_WORDS_SKIP):
-            tn = q.Tuning(zero_words=zw)
+        for tn in (None, q.Tuning(zero_words=q.ZERO_WORDS_SKIP, even_progress=2, layer_ksplit=4)):
             got = q.qgtc_aggregate(Ab, m, Xb, q.Epilogue(mode=q.OUT_I32, self_term=True, tuning=tn))
-            assert (as_u32(got) == Y).all(), (kb, zw)
+            assert (as_u32(got) == Y).all(), (kb, tn)
             agg_ep = q.Epilogue(mode=q.OUT_BITS, rq_nbits=rq_bits, rq_inv_scale=float(inv), self_term=True)
             got = q.qgtc_layer(Ab, m, Xb, Wb, agg_ep, q.Epilogue(mode=q.OUT_I32, tuning=tn))
-            assert (as_u32(got) == Z).all(), (kb, zw)
-            # the issue priority inside the tile loop (qgtc_tuning.even_progress) is scheduling only
-            for evp in (1, 2):
-                tn2 = q.Tuning(zero_words=zw, even_progress=evp)
-                got = q.qgtc_layer(Ab, m, Xb, Wb, agg_ep, q.Epilogue(mode=q.OUT_I32, tuning=tn2))
-                assert (as_u32(got) == Z).all(), (kb, zw, evp)
+            assert (as_u32(got) == Z).all(), (kb, tn)
 
 
 @pytest.mark.parametrize("s", [5, 6, 8])
 @pytest.mark.parametrize("k_words", [2047, 2048, 2049])
-def test_jumping_with_counts_at_the_16_bit_limit(s, k_words):
-    """From five planes on the jumping form keeps two rows of a tile in one register, 16 bits
-    each, while a row of A has at most 2047 words (a count is at most 65504); one word more
-    and a count could be 65536, which takes the form with full-width accumulators.  Rows of
-    ones against columns of ones reach the largest count on both sides of that limit, in a
-    lower and an upper row of a tile, next to sparse rows."""
+def test_largest_sums_of_long_rows(s, k_words):
+    """Rows of ones against columns of the largest code, beside sparse rows, over 65504 to 65568
+    positions of K: the sums of codes less 128 (8 bits) and 128 x the bits of the row that is added
+    back are at their largest, with the last chunk whole and in part, and with all chunks taken
+    and those of the list."""
     k = 32 * k_words
     n, d, h, t = 40, 20, 24, 4
     rng = np.random.default_rng([97, s, k_words])
     A = (rng.random((n, k)) < 0.002).astype(np.uint8)
-    A[3, :] = 1                                             # lower half of a tile (rows 0 - 7)
-    A[12, :] = 1                                            # upper half (rows 8 - 15): the shifted counts
+    A[3, :] = 1
+    A[12, :] = 1
     A[27, :] = 1
     A[21, : k // 2] = 1
     A[16:20, :] = 0
@@ -780,15 +773,13 @@ def test_jumping_with_counts_at_the_16_bit_limit(s, k_words):
     Ab = pack_adjacency(A)
     Xb = q.qgtc_pack_bits(dev(Xq.view(np.int32)), s, q.RIGHT)
     Wb = q.qgtc_pack_bits(dev(Wq.view(np.int32)), t, q.RIGHT)
-    for kb in (32, 64, 128):
-        m = q.qgtc_build_tile_map(Ab, 16, kb)
-        for zw in (q.ZERO_WORDS_SKIP, q.ZERO_WORDS_VISIT):
-            tn = q.Tuning(zero_words=zw)
-            got = q.qgtc_aggregate(Ab, m, Xb, q.Epilogue(mode=q.OUT_I32, tuning=tn))
-            assert (as_u32(got) == Y).all(), (kb, zw)
-            agg_ep = q.Epilogue(mode=q.OUT_BITS, rq_nbits=s, rq_inv_scale=float(inv))
-            got = q.qgtc_layer(Ab, m, Xb, Wb, agg_ep, q.Epilogue(mode=q.OUT_I32, tuning=tn))
-            assert (as_u32(got) == Z).all(), (kb, zw)
+    for kb in (None, 32, 64, 128):
+        m = q.qgtc_build_tile_map(Ab, 16, kb) if kb else None
+        got = q.qgtc_aggregate(Ab, m, Xb, q.Epilogue(mode=q.OUT_I32))
+        assert (as_u32(got) == Y).all(), kb
+        agg_ep = q.Epilogue(mode=q.OUT_BITS, rq_nbits=s, rq_inv_scale=float(inv))
+        got = q.qgtc_layer(Ab, m, Xb, Wb, agg_ep, q.Epilogue(mode=q.OUT_I32))
+        assert (as_u32(got) == Z).all(), kb
 
 
 # ------------------------------------------------------------ seeded random shapes

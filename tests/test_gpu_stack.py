@@ -212,13 +212,95 @@ def test_prepared_pass_follows_the_batch_normalization():
 def test_planes_of_another_width_than_the_networks(width):
     """forward(x_bits=...) takes planes of any width up to 8 bits, as qgtc_layer does."""
     net, _ = small_net(np.random.default_rng(9), dims=(20, 24, 9))
-    n, ranges = net.A.rows, [LayerRanges(300 << (width - 2), 90000.0), LayerRanges(400, None)]
+    n, ranges = net.A.rows, [LayerRanges(6 << width, 2000.0), LayerRanges(100, None)]
     X = q.qgtc_pack_bits(torch.randint(0, 1 << width, (n, 20), dtype=torch.int32, device="cuda"), width, q.RIGHT)
     got = net.forward(None, (0.0, 1.0), ranges, x_bits=X, want_int=True)
     (f0, s0), (f1, s1) = net._epilogues((0.0, 1.0), ranges, True)
     hidden = q.qgtc_layer(net.A, net.map, X, net.W[0], f0, s0)
     assert torch.equal(got, q.qgtc_layer(net.A, net.map, hidden, net.W[1], f1, s1))
     assert int(got.abs().sum()) > 0
+
+
+@pytest.mark.parametrize("cols", [20, 21, 3])        # 16-byte loads, element by element, narrower than four columns
+@pytest.mark.parametrize("s", [1, 5, 8])
+def test_features_that_are_no_ordinary_numbers(cols, s):
+    """NaN, infinities, zeros of both signs and the largest values through the quantizer of a
+    stack: the codes of Eq. (2) with its clamp, a NaN as code 0."""
+    rng = np.random.default_rng(cols + s)
+    net, _ = small_net(rng, dims=(cols, 9), s=s)
+    n, xr, ranges = net.A.rows, (-1.5, 2.0), [LayerRanges(8 << s, None)]
+    x = rng.standard_normal((n, cols)).astype(np.float32)
+    some = np.array([np.nan, np.inf, -np.inf, 3.4e38, -3.4e38, 0.0, -0.0, 1e-40, -1.5, 2.0], np.float32)
+    x.flat[rng.permutation(x.size)[:x.size // 2]] = np.resize(some, x.size // 2)
+    with np.errstate(over="ignore", invalid="ignore"):
+        codes = qgnn.quantize(np.where(np.isnan(x), np.float32(xr[0]), x), *xr, s)
+    X = q.qgtc_pack_bits(dev(codes.astype(np.int32)), s, q.RIGHT)
+    want = net.forward(None, xr, ranges, x_bits=X, want_int=True)
+    assert torch.equal(net.forward(dev(x), xr, ranges, want_int=True), want)
+    assert (as_u32(q.qgtc_unpack_bits(q.qgtc_pack_bits(dev(x), s, q.RIGHT, quant=xr))) == codes).all()
+
+
+@pytest.mark.parametrize("dims", ["200-40-9", "300-150-200-7"])
+@pytest.mark.parametrize("s,t", [(8, 8), (4, 7)])
+def test_batchnorm_behind_several_passes(dims, s, t):
+    """Column maps of hidden layers whose output tiles are kept over several passes (up to 4 and up to 16)."""
+    rng = np.random.default_rng(s)
+    d = [int(v) for v in dims.split("-")]
+    a, csr = block_graph(rng, 3, 160, 33, 6.0)
+    X = rng.standard_normal((a.shape[0], d[0])).astype(np.float32)
+    Ws = [rng.uniform(-0.5, 0.5, dh).astype(np.float32) for dh in zip(d[:-1], d[1:])]
+    params = [dict(gamma=rng.uniform(0.5, 1.5, h), beta=rng.uniform(-0.3, 0.6, h), mean=rng.uniform(-0.2, 0.4, h),
+                   var=rng.uniform(0.5, 2.0, h), eps=1e-5) for h in d[1:-1]] + [None]
+    net = QuantGNN(dev(a), [dev(W) for W in Ws], s, t, False, block_rows=160,
+                   batchnorm=[p and BatchNorm(**p) for p in params])
+    assert net._fused
+    xr, x = (float(X.min()), float(X.max())), dev(X)
+    ranges = net.calibrate(x, xr)
+    rqs = [((0, qgnn.inv_scale(0.0, float(r.agg_hi), s)),
+            None if r.out_hi is None else (0, qgnn.inv_scale(0.0, float(r.out_hi), s))) for r in ranges]
+    wr = [(float(W.min()), float(W.max())) for W in Ws]
+    ref, trace, _ = qgnn.forward_dequantized(csr, X, xr, Ws, wr, s, t, False, rqs=rqs, batchnorms=params)
+    assert (as_u32(net.forward(x, xr, ranges, want_int=True)) == trace[-1]["Z"]).all()
+    assert_fp32_close(net.forward(x, xr, ranges).cpu().numpy(), ref, f"{dims} s={s}")
+
+
+@pytest.mark.parametrize("kind", ["11 bits", "two kernels", "integer features", "batch normalization"])
+def test_independent_runs_of_subgraphs(monkeypatch, kind):
+    """What is not one native call - more than 8 bits, the two-kernel path, features that are not
+    fp32 - runs layer by layer, and as several runs of whole subgraphs on streams of their own
+    where asked to: the same bytes as one run, eager and recorded."""
+    rng = np.random.default_rng(13)
+    s = 11 if kind in ("11 bits", "batch normalization") else 8
+    a, _ = block_graph(rng, 5, 96, 31, 6.0)
+    Ws = [dev(rng.uniform(-1, 1, dh).astype(np.float32)) for dh in ((20, 24), (24, 9))]
+    norm = BatchNorm(*(rng.uniform(0.5, 1.5, 24).tolist() for _ in range(4)))
+    net = QuantGNN(dev(a), Ws, s, s, False, block_rows=96,
+                   batchnorm=[norm, None] if kind == "batch normalization" else None,
+                   tuning=q.Tuning(layer_path=q.LAYER_TWO_KERNELS) if kind == "two kernels" else None)
+    assert net._fused == (kind == "integer features")
+    x, xr = dev(rng.standard_normal((a.shape[0], 20)).astype(np.float32)), (-3.0, 3.0)
+    if kind == "integer features":
+        x = torch.randint(0, 1 << s, x.shape, dtype=torch.int32, device="cuda")
+    ranges = net.calibrate(x, xr)
+    firsts, real = [], net._run_layers
+    monkeypatch.setattr(net, "_run_layers", lambda r0, *args: firsts.append(r0) or real(r0, *args))
+    want, want_z = net.forward(x, xr, ranges).clone(), net.forward(x, xr, ranges, want_int=True).clone()
+    assert firsts == [0, 0] and int(want_z.abs().sum()) > 0
+    for streams, rows in ((2, [0, 288]), (3, [0, 192, 384]), ([4, 1], [0, 384]), ([1, 4], [0, 96])):
+        for want_int, ref in ((False, want), (True, want_z)):
+            firsts.clear()
+            got = net.forward(x, xr, ranges, want_int=want_int, streams=streams)
+            torch.cuda.synchronize()
+            assert firsts == rows and torch.equal(got, ref), streams
+    out = torch.empty_like(want)
+    graph = net.capture(x, xr, ranges, out, streams=[1, 4], with_static=True)
+    for _ in range(3):
+        out.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
+        assert torch.equal(net.forward(x, xr, ranges), want)
+    del graph
 
 
 def test_adjacency_rows_of_64_MiB_and_more():
