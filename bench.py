@@ -64,9 +64,9 @@ def make_net(cfg, bits, tile_kbits, w=None):
 def workload_bitops(net, n_nodes):
     """Bit-operations of one forward pass, per layer: the aggregation over the tiles the
     zero-tile map keeps, the update (nominal), the number of kept tiles, and the
-    aggregation over the words the kernels really visit - the same as the first list unless
-    they jump over the zero words inside kept tiles (then: 32 bits per (row, word) pair of A
-    that holds a bit)."""
+    aggregation over the non-zero words of the kept tiles alone where the selector says that
+    jumping over the others would pay (32 bits per (row, word) pair of A that holds a bit), else
+    the first list again."""
     import paper_2111_09547_amd as q
     nnz = int(net.map.nnz_tiles.cpu()[0])
     kb = net.map.c.tile_kbits
@@ -351,7 +351,8 @@ def main():
 
     # The step as one HIP graph: the same launches, recorded once, so that the host's
     # per-launch cost (Python + ctypes, ~25 us each) does not limit a step of ~20 launches.
-    n_runs = net.auto_runs() if args.runs < 0 else args.runs
+    # (a network that runs as one native call is one run whatever is asked for)
+    n_runs = 1 if net._fused else net.auto_runs() if args.runs < 0 else args.runs
     graph_step = net.capture(X, xr, ranges, out, with_static=True, streams=n_runs)
     graph_layers = net.capture(X, xr, ranges, out, streams=n_runs)
     for _ in range(args.warmup):
@@ -427,23 +428,6 @@ def main():
     agg_ops, upd_ops, nnz, visited = workload_bitops(net, g.n_nodes)
     total_ops = sum(agg_ops) + sum(upd_ops)
     dom_name, agg_rate, dom_avg_ms, dom_n = dominant_kernel(net, w, prof, args.steps, visited)
-    # the same launches with every word of the kept tiles visited (the form whose work is the
-    # tile-level count: bound by the vector ALUs)
-    visit_all = None
-    if visited != agg_ops:
-        keep = net.tuning
-        net.tuning = q.Tuning(update_path=keep.update_path, agg_xcd_run=keep.agg_xcd_run, layer_path=keep.layer_path,
-                              layer_ksplit=keep.layer_ksplit, zero_words=q.ZERO_WORDS_VISIT,
-                              even_progress=keep.even_progress)
-        for _ in range(3):
-            step()
-        prof_v = kernel_events(step, args.steps)
-        g_v = net.capture(X, xr, ranges, out, streams=n_runs)
-        ms_layers_v = timed(g_v.replay, args.steps)
-        del g_v
-        net.tuning = keep
-        _, rate_v, avg_v, _ = dominant_kernel(net, w, prof_v, args.steps, agg_ops)
-        visit_all = {"frac": rate_v / PEAK_BITOPS, "avg_launch_ms": avg_v, "ms_layers_only": ms_layers_v}
     n_layers = len(net.dims)
     dense_macs = sum(2.0 * g.n_nodes * g.block * d + 2.0 * g.n_nodes * d * h for d, h in net.dims)
     # every entry of the (block-diagonal) products counted, zero tiles included, times the bit widths
@@ -499,11 +483,9 @@ def main():
                                 "once on the int8 matrix cores, so this is a rate and no utilisation (it can pass 1); "
                                 "launch durations are taken with the launches one after the other on one stream",
                      "frac_in_step": sum(visited) / (ms_layers * 1e-3) / PEAK_BITOPS,
-                     # the work of the kept tiles (what a kernel without zero-word jumping executes, and
-                     # what `frac` counted before that existed) over the same launch time: above 1 when
-                     # the jumping form skips more than the vector ALUs could have done
+                     # the bit-ops of the kept tiles over the same launch time: a rate as well, above 1
+                     # where a vector-ALU kernel that visits them all could not keep up
                      "frac_kept_tile_work": agg_rate / PEAK_BITOPS * (sum(agg_ops) / sum(visited)),
-                     "visit_all_form": visit_all,
                      "measured_peak": measured_peak / 1e12,
                      "frac_of_measured_peak": agg_rate / measured_peak,
                      "traffic": traffic, "traffic_source": traffic_note},

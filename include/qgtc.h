@@ -176,13 +176,13 @@ qgtc_status qgtc_col_sums(const qgtc_bits* m, int32_t* out, void* stream);
  *   row_cnt[tr]                      number of non-zero tiles in tile row tr
  *   col_idx[tr*n_tile_cols + i]      their tile-column indices, i < row_cnt[tr]
  *   nnz_tiles[0]                     total number of non-zero tiles
- *   nnz_tiles[1]                     log2 of the run of consecutive tile rows the
- *                                    product kernels keep on one XCD, 3..6: the
- *                                    longest run of 8..64 tile rows for which the
+ *   nnz_tiles[1]                     log2 of a run of consecutive tile rows, 3..6:
+ *                                    the longest run of 8..64 tile rows for which the
  *                                    busiest of the 8 XCDs (runs dealt round-robin,
  *                                    a tile row weighing its tiles + 1) carries at
- *                                    most 2 % more than the mean.  A hint that only
- *                                    affects speed; nnz_tiles[2..3] are reserved.
+ *                                    most 2 % more than the mean.  A statistic of the
+ *                                    adjacency, e.g. for qgtc_tuning.agg_xcd_run; no
+ *                                    kernel reads it.  nnz_tiles[2..3] are reserved.
  *   deg[r]                           popcount of row r of A (node degree)
  * Any tile shape with tile_rows in {8, 16, 32, 64} and tile_kbits in {32, 64,
  * 128, 256, 512} can be built (8 x 128 reproduces the statistic of the paper's
@@ -438,8 +438,11 @@ qgtc_status qgtc_tile_stats(const qgtc_bits* A, int32_t* counts, void* stream);
  * The selector: which tile width, which kernels and which launch shape the library
  * takes for one layer (the paper leaves such a heuristic as future work, end of its
  * Section 6.3).  A pure host function over the shape, the bit widths and the tile
- * statistics; qgtc_update and qgtc_layer make their automatic choices through it, so
- * the rules exist once.  Every rule is a measured crossover on MI355X.
+ * statistics; qgtc_update and qgtc_layer take its rules for the update's kernel and for one
+ * kernel or two, so those exist once.  tile_kbits, ksplit, runs, zero_words, even_progress and the
+ * estimates follow from crossovers measured on the AND + popcount form of the aggregation.  On the
+ * int8 matrix cores results and launches do not depend on ksplit, zero_words and even_progress,
+ * and the tile width decides only which chunks of 128 positions a list names.
  *   in:  rows (nodes), in_cols (D), out_cols (H), s, t,
  *        nnz_tiles[3] from qgtc_tile_stats (all zero: unknown, 128-bit tiles assumed,
  *        every tile of a row counted), n_tile_rows, a_cols (columns of A as stored),

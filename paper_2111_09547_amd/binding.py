@@ -219,9 +219,10 @@ class Tuning:
     update_path: int = 0      # UPDATE_AUTO / UPDATE_POPCOUNT / UPDATE_MATRIX_CORES
     agg_xcd_run: int = 0
     layer_path: int = 0       # LAYER_FUSED / LAYER_TWO_KERNELS
+    # carried and checked; the int8 matrix-core kernels do not read them
     layer_ksplit: int = 0
     zero_words: int = 0       # ZERO_WORDS_AUTO / ZERO_WORDS_VISIT / ZERO_WORDS_SKIP
-    even_progress: int = 0    # 0 automatic, 1 off, 2 on (issue priority by remaining work in the fused kernel's tile loop)
+    even_progress: int = 0    # 0 automatic, 1 off, 2 on
 
 
 @dataclass

@@ -33,7 +33,7 @@
 //   lane group g = lane / 16 takes words SWC g .. SWC g + SWC - 1 of the stage's 4 SWC words.
 //
 // Pipeline.  X in operand order and the words of A go to LDS without passing through registers
-// (8 to 16 KiB of X and SWC KiB of A per unit and stage), two stages ahead, through three slots with
+// (4 to 16 KiB of X and SWC KiB of A per unit and stage), two stages ahead, through three slots with
 // one barrier per stage; the matrix cores' time per stage is 256 to 512 cycles per wave.
 #pragma once
 #include <type_traits>
@@ -230,28 +230,6 @@ inline size_t agg_set_shape(AggParams* p, const AggSplit& sp, int n_col_wg, int 
     lds = (lds + 15) & ~(size_t)15;
   }
   return lds;
-}
-
-// a[p] = 32 K positions of plane p  ->  a[r] = the codes of K positions r, 8 + r, 16 + r,
-// 24 + r in its bytes 0..3 (bit p of a code = its bit in plane p): three rounds of masked
-// swaps between the plane registers transpose the four 8 x 8 blocks at once.
-template <int SH, uint32_t M>
-__device__ __forceinline__ void swap_bits(uint32_t& x, uint32_t& y) {
-  const uint32_t nx = (x & ~(M << SH)) | ((y & M) << SH);
-  const uint32_t ny = (y & ~M) | ((x >> SH) & M);
-  x = nx;
-  y = ny;
-}
-__device__ __forceinline__ void planes_word_to_codes(uint32_t (&a)[8]) {
-#pragma unroll
-  for (int p = 0; p < 4; ++p) swap_bits<4, 0x0f0f0f0fu>(a[p], a[p + 4]);
-#pragma unroll
-  for (int p = 0; p < 8; p += 4) {
-    swap_bits<2, 0x33333333u>(a[p], a[p + 2]);
-    swap_bits<2, 0x33333333u>(a[p + 1], a[p + 3]);
-  }
-#pragma unroll
-  for (int p = 0; p < 8; p += 2) swap_bits<1, 0x55555555u>(a[p], a[p + 1]);
 }
 
 // Place of column c of a group in the staged order (see the top): tile, position m.
@@ -596,11 +574,8 @@ __device__ __forceinline__ void agg_run(const AggParams& p, const AggWave& w, ui
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
       const uint8_t* from = slot + a_at + (t & 1) * 64 + (t >> 1) * (RPW == 64 ? 512 : SWC * 512);
-      if constexpr (SWC == 4) {
-        const v4u v = *reinterpret_cast<const v4u*>(from);
-#pragma unroll
-        for (int i = 0; i < SWC; ++i) aw[t][i] = v[i];
-      } else if constexpr (SWC == 2) {
+      static_assert(SWC == 1 || SWC == 2, "words of A a lane reads at once");
+      if constexpr (SWC == 2) {
         const v2u v = *reinterpret_cast<const v2u*>(from);
         aw[t][0] = v.x;
         aw[t][SWC - 1] = v.y;

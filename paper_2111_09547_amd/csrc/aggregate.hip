@@ -116,7 +116,7 @@ __global__ __launch_bounds__(512) void aggregate_kernel(const AggParams p) {
     return;
   }
 
-  // Packed planes along the columns: the lane's codes are 4, 8 or 16 consecutive bits of a
+  // Packed planes along the columns: the lane's codes are 4 or 8 consecutive bits of a
   // word; it stores bytes or 16-bit halves where that is a whole number of bytes.
   const int qbits = e.rq_nbits;
   const uint32_t qmax = qbits >= 32 ? 0xffffffffu : ((1u << qbits) - 1u);
@@ -155,10 +155,7 @@ __global__ __launch_bounds__(512) void aggregate_kernel(const AggParams p) {
         for (int b = 0; b < (LC + 7) / 8; ++b) v[b] = ((i < 4 ? lo[b] : hi[b]) >> sh) & 0xffu;
         uint32_t* dst = drow + (int64_t)(p0 + i) * e.ps_out;
         const bool plane_ok = p0 + i < qbits;
-        if constexpr (CT == 4) {
-          if (plane_ok && row_ok && (col0 >> 5) < data_words)
-            reinterpret_cast<uint16_t*>(dst)[col0 >> 4] = (uint16_t)(v[0] | (v[1] << 8));
-        } else if constexpr (CT == 2) {
+        if constexpr (CT == 2) {
           if (plane_ok && row_ok) reinterpret_cast<uint8_t*>(dst)[4 * cg + g] = (uint8_t)v[0];
         } else {
           uint32_t word = v[0] << (4 * g);

@@ -155,24 +155,7 @@ __device__ __forceinline__ uint32_t requantize_code(uint32_t c_u32, int relu, in
   return (uint32_t)t;
 }
 
-// requantize_code for codes of at most 24 bits: relu_floor is 0 with ReLU, INT32_MIN
-// without; 2^bits - 1 is exact in fp32, so the clamp can be taken on the float (t is never
-// negative or NaN: the difference is >= 0, the scale finite and > 0), and the conversion to
-// an integer truncates, which is the floor of a non-negative value.
-__device__ __forceinline__ uint32_t requantize_code_small(uint32_t c_u32, int32_t relu_floor, int32_t rq_lo,
-                                                          float rq_inv_scale, float qmaxf) {
-  const int32_t c = max((int32_t)c_u32, relu_floor);
-  const uint32_t du = (uint32_t)max(c, rq_lo) - (uint32_t)rq_lo;
-  return (uint32_t)fminf((float)du * rq_inv_scale, qmaxf);
-}
-
-// The same for a range that starts at 0, [0, hi): max(c, 0) is the whole integer part,
-// with or without ReLU.
-__device__ __forceinline__ uint32_t requantize_code_relu0(uint32_t c_u32, float rq_inv_scale, float qmaxf) {
-  return (uint32_t)fminf((float)(uint32_t)max((int32_t)c_u32, 0) * rq_inv_scale, qmaxf);
-}
-
-// The same behind a per-column affine map (a folded batch normalization); see
+// requantize_code behind a per-column affine map (a folded batch normalization); see
 // col_scale in qgtc.h.  Two separately rounded fp32 operations, then Eq. (2).
 __device__ __forceinline__ uint32_t requantize_affine(uint32_t c_u32, float a, float b, int relu,
                                                       int32_t rq_lo, float rq_inv_scale,
@@ -228,6 +211,31 @@ __device__ __forceinline__ void planes_to_bytes(const uint32_t (&f)[8], int npla
       if (pl < nplanes) v |= spread4((f[pl] >> (4 * q)) & 0xfu) << pl;   // wave-uniform test
     d[q] = v;
   }
+}
+
+// One masked swap between two plane registers: the bits of x at positions p + SH and the
+// bits of y at positions p trade places, for every p in mask M.
+template <int SH, uint32_t M>
+__device__ __forceinline__ void swap_bits(uint32_t& x, uint32_t& y) {
+  const uint32_t nx = (x & ~(M << SH)) | ((y & M) << SH);
+  const uint32_t ny = (y & ~M) | ((x >> SH) & M);
+  x = nx;
+  y = ny;
+}
+
+// a[p] = 32 K positions of plane p  ->  a[r] = the codes of K positions r, 8 + r, 16 + r,
+// 24 + r in its bytes 0..3 (bit p of a code = its bit in plane p): three rounds of masked
+// swaps between the plane registers transpose the four 8 x 8 blocks at once.
+__device__ __forceinline__ void planes_word_to_codes(uint32_t (&a)[8]) {
+#pragma unroll
+  for (int p = 0; p < 4; ++p) swap_bits<4, 0x0f0f0f0fu>(a[p], a[p + 4]);
+#pragma unroll
+  for (int p = 0; p < 8; p += 4) {
+    swap_bits<2, 0x33333333u>(a[p], a[p + 2]);
+    swap_bits<2, 0x33333333u>(a[p + 1], a[p + 3]);
+  }
+#pragma unroll
+  for (int p = 0; p < 8; p += 2) swap_bits<1, 0x55555555u>(a[p], a[p + 1]);
 }
 
 // Transpose of an 8 x 8 bit matrix held as 8 bytes (byte r of hi:lo = row r, bit c

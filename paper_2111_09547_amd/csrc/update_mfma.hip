@@ -53,30 +53,6 @@ constexpr int kRowsPerGroup = 32;
 constexpr int kPad = 16;   // bytes of padding per LDS row of W
 constexpr uint32_t kOutOfRange = 0x80000000u;   // buffer offset past any operand: the load returns 0
 
-// One masked swap between two plane registers: the bits of x at positions p + SH and the
-// bits of y at positions p trade places, for every p in mask M.
-template <int SH, uint32_t M>
-__device__ __forceinline__ void swap_bits(uint32_t& x, uint32_t& y) {
-  const uint32_t nx = (x & ~(M << SH)) | ((y & M) << SH);
-  const uint32_t ny = (y & ~M) | ((x >> SH) & M);
-  x = nx;
-  y = ny;
-}
-
-// a[p] = 32 K positions of plane p  ->  a[r] = the codes of K positions r, 8 + r, 16 + r,
-// 24 + r in its bytes 0..3 (bit p of a code = its bit in plane p).
-__device__ __forceinline__ void planes_word_to_codes(uint32_t (&a)[8]) {
-#pragma unroll
-  for (int p = 0; p < 4; ++p) swap_bits<4, 0x0f0f0f0fu>(a[p], a[p + 4]);
-#pragma unroll
-  for (int p = 0; p < 8; p += 4) {
-    swap_bits<2, 0x33333333u>(a[p], a[p + 2]);
-    swap_bits<2, 0x33333333u>(a[p + 1], a[p + 3]);
-  }
-#pragma unroll
-  for (int p = 0; p < 8; p += 2) swap_bits<1, 0x55555555u>(a[p], a[p + 1]);
-}
-
 // SPLIT_Y / SPLIT_W: the operand has 8 planes and is taken as code - 128 (see the top);
 // NTC: 16-column tiles per workgroup (1 or 4); LW: see above (1, 2 or 8).
 template <bool SPLIT_Y, bool SPLIT_W, int NTC, int LW>

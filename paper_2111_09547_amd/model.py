@@ -97,8 +97,8 @@ class QuantGNN:
             self.A_src = A_src
             self.A = B.alloc_bits(A_src.shape[0], A_src.shape[1], 1, B.LEFT, block_rows)
         self.map = None
-        # The selector's choices that depend on the adjacency (tile width when "auto", zero-word
-        # jumping unless the caller's tuning says which): pack A now, read its statistics once.
+        # The selector's choices that depend on the adjacency (tile width when "auto", the hints for
+        # walking a tile list, auto_runs()): pack A now, read its statistics once.
         self.plan = None
         if tile_kbits == "auto" or tuning is None or tuning.zero_words == 0:
             if self.A_src is not None:
@@ -394,11 +394,13 @@ class QuantGNN:
                 x_bits: B.Bits | None = None):
         """fp32 [N, H_last] (or the last int32 accumulators when want_int).
 
-        streams > 1 (block-diagonal storage): the subgraphs are cut into that many
-        independent runs, each issued on a stream of its own, so that the start and the
-        drain of one run's kernels overlap with the other runs' work.  A list gives the
+        streams > 1 (block-diagonal storage): a network that runs layer by layer - more than
+        8 bits, the two-kernel path, features that are not fp32 - has its subgraphs cut into
+        that many independent runs, each issued on a stream of its own, so that the start and
+        the drain of one run's kernels overlap with the other runs' work.  A list gives the
         number of subgraphs of each run instead ([48, 16]: the first 48, then 16); "auto"
         takes auto_runs() (resolve it before recording a graph: it reads the tile map back).
+        Everything else is one run, whose launches fill the device by themselves.
         x_packed: the features are already packed (pack_static(X, x_range)).
         x_bits: the features as packed planes that live elsewhere (a SubgraphPacket's,
         packed on the host with the same x_range); X is then not read (single run only)."""
@@ -412,7 +414,7 @@ class QuantGNN:
             return self._forward_update_first(X, x_range, ranges, out, want_int)
         # (planes of another width than the network's go layer by layer: their first layer is another one)
         if self._fused and (x_bits.nbits == self.s if x_bits is not None else x_packed or X.dtype == torch.float32):
-            # one run whatever `streams` says: the launches of a stack fill the device by themselves
+            # one run whatever `streams` says
             if not isinstance(streams, int) and self.A.c.block_rows > 0:
                 assert sum(streams) >= -(-n // self.A.c.block_rows)
             assert x_bits is None or (isinstance(streams, int) and streams <= 1)
@@ -525,23 +527,6 @@ class QuantGNN:
         return B.qgtc_plan_layer(self.A.rows, d, h, self.s, self.t, n_tile_rows=-(-self.A.rows // 16),
                                  a_cols=self.A.cols, nnz_tiles=tiles, nnz_row_words=row_words, subgraphs=subgraphs)
 
-    def _run_tuning(self, l: int, whole_batch: bool):
-        """Tuning of layer l.  A run that covers part of the batch shares the device with the
-        other runs: it takes the K split and the issue-priority choice the whole batch would
-        get from the selector, not the ones its own (smaller) number of tile rows suggests -
-        those would split the tile lists to fill a device the other runs are already filling,
-        and treat a launch as alone on the device that is not."""
-        if whole_batch or (self.tuning is not None and self.tuning.layer_ksplit):
-            return self.tuning
-        plan = self._batch_plan(l)
-        base = self.tuning or B.Tuning()
-        # (the selector's wave-slot count assumes its own choice of kernel form: where the
-        # caller fixed another one, the priority scheme stays off)
-        same_form = plan["zero_words"] == 0 or base.zero_words in (0, plan["zero_words"])
-        return B.Tuning(update_path=base.update_path, agg_xcd_run=base.agg_xcd_run, layer_path=base.layer_path,
-                        layer_ksplit=plan["ksplit"], zero_words=base.zero_words,
-                        even_progress=base.even_progress or (plan["even_progress"] if same_form else 1))
-
     def _stack(self, x_range, ranges, want_int) -> "B.Stack":
         """The prepared native call for these ranges (a caller's handful of them is kept).  An entry
         holds on to the operands that its key names, so that none of them can be another one by now."""
@@ -583,9 +568,7 @@ class QuantGNN:
 
     def _run_layers(self, r0, r1, A, tmap, deg, xb, x_range, ranges, out, want_int, workspace):
         """All layers on rows [r0, r1) (whole subgraphs), on the current stream."""
-        whole = r0 == 0 and r1 == self.A.rows
         for l, (W, (first, second)) in enumerate(zip(self.W, self._epilogues(x_range, ranges, want_int))):
-            second.tuning = self._run_tuning(l, whole)
             if l < len(self.W) - 1:
                 xb = B.qgtc_layer(A, tmap, xb, W, first, second, workspace,
                                   out=self._x_rows((l + 1) & 1, self.dims[l][1], r0, r1))
