@@ -200,13 +200,16 @@ qgtc_status launch(const AggParams& p, size_t lds, hipStream_t stream) {
 // Narrower column groups where wide ones would leave compute units without a workgroup of two
 // units: the rows of A are then expanded once per group, which costs less than idle units.
 // Where that leaves two or fewer waves per compute unit, four of them share a unit's stages
-// (8192 x 8192 x 64: two waves of 16 columns 33 us, eight of them 18 us).
+// (8192 x 8192 x 64: two waves of 16 columns 33 us, eight of them 18 us), unless all of K is one
+// stage of two chunks anyway (1024 x 1024 x 64: four stages 8.6 us, one for all waves 4.7 us).  With
+// up to four waves per compute unit it depends on the adjacency: every tile occupied 8192 x 8192 x
+// 128 36.5 and 33.4 us, diagonal blocks of 256 in 4096 x 4096 x 200 7.3 and 11.5 us.
 AggSplit aggregate_split(int rows, int cols, int a_words, int64_t lda) {
   const int64_t units = cdiv(rows, kUnitRows), enough = 2 * (int64_t)device_compute_units();
   AggSplit sp{2, 2, 2, 1};
   if (cols <= 32 || units * cdiv(cols, 64) < enough) sp = AggSplit{1, 2, 1, 1};
   if (agg_long_rows(lda)) return sp;
-  if (cols <= 16 || units * cdiv(cols, 32) < enough) sp = AggSplit{1, 1, 1, units * cdiv(cols, 16) <= enough && a_words > 32 ? 4 : 1};
+  if (cols <= 16 || units * cdiv(cols, 32) < enough) sp = AggSplit{1, 1, 1, units * cdiv(cols, 16) <= enough && a_words > 8 ? 4 : 1};
   return sp;
 }
 

@@ -230,7 +230,7 @@ def test_stack_arguments_are_checked_before_any_launch():
 def test_which_products_look_at_a_tile_map():
     import paper_2111_09547_amd.binding as b
     reads = b.lib().qgtc_aggregate_reads_map
-    for n, d, block, want in ((256, 16, 0, 0), (257, 16, 0, 1), (3000, 16, 0, 1), (2100, 300, 0, 1), (100, 3, 0, 0),
+    for n, d, block, want in ((256, 16, 0, 0), (257, 16, 0, 0), (1024, 64, 0, 0), (1025, 64, 0, 1), (3000, 16, 0, 1), (2100, 300, 0, 1), (100, 3, 0, 0),
                               (65536, 64, 1024, 0), (65536, 64, 1056, 1), (8192, 64, 64, 0)):
         A = _fake_bits(b, n, block or n, 1, b.LEFT, block_rows=block)
         assert reads(C.byref(A), d) == want, (n, d, block)

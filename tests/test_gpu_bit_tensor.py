@@ -101,7 +101,7 @@ def test_product_builds_no_map_that_nobody_reads(monkeypatch):
     real = bt.B.qgtc_build_tile_map
     monkeypatch.setattr(bt.B, "qgtc_build_tile_map", lambda *a, **k: built.append(a) or real(*a, **k))
     rng = np.random.default_rng(11)
-    for n, d, want in ((256, 16, False), (100, 3, False), (257, 16, True), (3000, 16, True), (2100, 300, True)):
+    for n, d, want in ((256, 16, False), (100, 3, False), (257, 16, False), (1024, 16, False), (1025, 16, True), (3000, 16, True), (2100, 300, True)):
         a = (rng.random((n, n)) < 0.03).astype(np.uint8)
         x = rng.integers(0, 4, (n, d)).astype(np.int32)
         A, X = to_bit(dev(a), 1, side="left"), to_bit(dev(x), 2)

@@ -93,6 +93,7 @@ def test_stack_refuses_what_the_layers_refuse():
 @pytest.mark.parametrize("s", [1, 8, 11])
 @pytest.mark.parametrize("rows,k,cols,density", [
     (70, 2500, 20, 0.3), (200, 1100, 16, 0.002),     # four waves share the stages of a unit
+    (130, 257, 20, 0.2), (500, 640, 16, 0.01), (70, 1024, 65, 0.3),   # ... all of K one stage, in part and whole
     (33000, 130, 32, 0.2), (33000, 260, 17, 0.01),   # two waves of 16 columns
     (6700, 200, 300, 0.2), (6700, 1300, 290, 0.001),  # two waves of 32 columns, several workgroups along the columns
 ])
