@@ -473,8 +473,8 @@ class QuantGNN:
                          x_packed=with_static and not self.update_first)
 
         self._ready_planes(X)
-        if not self.update_first:
-            self._epilogues(x_range, ranges, want_int)       # folded batch normalizations, on the caller's stream
+        if any(bn is not None for bn in self.batchnorm):
+            self._epilogues(x_range, ranges, want_int)       # folds them, on the caller's stream
         cur = torch.cuda.current_stream()
         side = torch.cuda.Stream()
         side.wait_stream(cur)
