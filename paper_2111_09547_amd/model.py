@@ -194,11 +194,11 @@ class QuantGNN:
         if not (self._fused and X.dtype == torch.float32):
             self.x_bufs
 
-    def _x_view(self, which: int, cols: int, bufs=None) -> B.Bits:
+    def _x_view(self, which: int, cols: int) -> B.Bits:
         """A [N, cols] RIGHT-packed view on one of the activation buffers.  Every view has
         the strides of the widest layer, so that a range of rows is the same range of
         words whatever the layer (independent runs of rows work on the buffers at once)."""
-        buf = (bufs or self.x_bufs)[which]
+        buf = self.x_bufs[which]
         d, _ = B.describe(self.A.rows, cols, self.s, B.RIGHT)
         d.ld_words = buf.c.ld_words
         d.plane_stride_words = buf.c.plane_stride_words
@@ -351,13 +351,17 @@ class QuantGNN:
             return self._forward_update_first(X, x_range, None, None, False)
         ranges = []
         if self._fused and X.dtype == torch.float32:
-            # planes for this call only; the network keeps the features as codes
-            bufs = self._alloc_planes()
-            B.qgtc_stack_input(X, self.s, x_range, self._codes[0])
-            self._x_form = "codes"
-            xb = B.qgtc_pack_bits(X, self.s, B.RIGHT, quant=x_range, out=self._x_view(0, X.shape[1], bufs))
+            # the planes of this call in the buffers of the codes, which hold a byte per entry: no others are made
+            assert tuple(X.shape) == (self.A.rows, self.dims[0][0])
+
+            def planes(which, cols):
+                d, _ = B.describe(self.A.rows, cols, self.s, B.RIGHT)
+                d.data = self._codes[which].data_ptr()
+                return B.Bits(self._codes[which], d)
+
+            xb = B.qgtc_pack_bits(X, self.s, B.RIGHT, quant=x_range, out=planes(0, X.shape[1]))
         else:
-            bufs = self.x_bufs
+            planes = self._x_view
             xb = self.pack_input(X, x_range)
         if self._W_planes is None:          # qgtc_update reads bit planes
             self._W_planes = [B.qgtc_pack_bits(W, self.t, B.RIGHT, quant=r)
@@ -385,7 +389,10 @@ class QuantGNN:
             ranges.append(LayerRanges(agg_hi, out_hi))
             _, ep, _, x_scale = self._layer_eps(l, 0.0, x_scale, agg_hi, out_hi, last=False)
             ep.col_scale, ep.col_shift = ca, cb
-            xb = B.qgtc_update(yb, W, ep, out=self._x_view((l + 1) & 1, self.dims[l][1], bufs))
+            xb = B.qgtc_update(yb, W, ep, out=planes((l + 1) & 1, self.dims[l][1]))
+        if planes != self._x_view:               # the features are left packed, as codes
+            B.qgtc_stack_input(X, self.s, x_range, self._codes[0])
+            self._x_form = "codes"
         return ranges
 
     # -- forward ---------------------------------------------------------------------

@@ -173,6 +173,23 @@ def test_calibration_leaves_the_features_packed():
     assert net._x_bufs is None
 
 
+@pytest.mark.parametrize("s", [1, 8])
+def test_calibration_makes_no_buffers_of_planes(monkeypatch, s):
+    """... and stays inside those of the codes, also with a hidden layer wider than the others."""
+    net, x = small_net(np.random.default_rng(16), blocks=3, block=32, dims=(3, 50, 17, 9), s=s)
+    for i, c in enumerate(net._codes):               # the same buffers with a margin behind them
+        wide = torch.full((c.numel() + 64,), 0x5a5a5a5a, dtype=torch.int32, device="cuda")
+        net._codes[i] = wide[:c.numel()]
+        net._codes[i].margin = wide
+    packed = net._W_planes = [q.qgtc_pack_bits(W, net.t, q.RIGHT, quant=r) for W, r in zip(net.Ws, net.w_ranges)]
+    made, real = [], B.alloc_bits
+    monkeypatch.setattr(B, "alloc_bits", lambda *a, **k: made.append(a[3]) or real(*a, **k))
+    net.calibrate(x, (-3.0, 3.0))
+    assert B.RIGHT not in made and net._W_planes is packed
+    for c in net._codes:
+        assert (c.margin[c.numel():] == 0x5a5a5a5a).all()
+
+
 def test_prepared_pass_follows_the_operands():
     """Adjacency, weights and self term replaced between passes with the same ranges."""
     rng = np.random.default_rng(7)
