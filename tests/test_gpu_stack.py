@@ -111,6 +111,21 @@ def test_aggregate_splits(s, rows, k, cols, density):
         assert (as_u32(y) == ref).all()
 
 
+@pytest.mark.parametrize("s", [3, 8, 11])
+@pytest.mark.parametrize("blocks,block,short,cols", [(5, 288, 31, 16), (3, 512, 0, 40), (2, 1024, 77, 130), (3, 1056, 1, 20)])
+def test_aggregate_blocks_as_one_stage(s, blocks, block, short, cols):
+    """Diagonal blocks whose K is one stage of the four waves of a unit (up to 1024 columns; 1056
+    are more), with the rows themselves added."""
+    rng = np.random.default_rng(block + s)
+    a, csr = block_graph(rng, blocks, block, short, 9.0)
+    x = rng.integers(0, 1 << s, (a.shape[0], cols)).astype(np.int32)
+    ref = qgnn.aggregate(csr, x.astype(np.uint32), True)
+    A, X = q.qgtc_pack_bits(dev(a), 1, q.LEFT, block_rows=block), q.qgtc_pack_bits(dev(x), s, q.RIGHT)
+    for tmap in (None, q.qgtc_build_tile_map(A, 16, 64)):
+        y = q.qgtc_aggregate(A, tmap, X, q.Epilogue(mode=q.OUT_I32, self_term=True))
+        assert (as_u32(y) == ref).all()
+
+
 @pytest.mark.parametrize("cols", [16, 32])
 @pytest.mark.parametrize("s", [3, 8])
 def test_four_units_side_by_side_on_planes(cols, s):
