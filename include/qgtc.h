@@ -211,6 +211,9 @@ qgtc_status qgtc_tile_map_carve(qgtc_tile_map* map, void* buffer, int32_t rows,
 /* Scans the packed adjacency A (LEFT, 1 bit) and fills the map. */
 qgtc_status qgtc_build_tile_map(const qgtc_bits* A, const qgtc_tile_map* map,
                                 void* stream);
+/* nnz_tiles of a map whose row_cnt is filled in (qgtc_build_tile_map does this as well). */
+qgtc_status qgtc_tile_map_total(const qgtc_tile_map* map, void* stream);
+
 
 /* ---------------------------------------------------------------------------
  * Epilogue fused into the product kernels (inter-layer kernel fusion,
@@ -373,6 +376,35 @@ qgtc_status qgtc_layer_static(const qgtc_bits* A, const qgtc_tile_map* map,
                               void* out, int64_t ld_out, void* stream);
 
 /* ---------------------------------------------------------------------------
+ * Neighbour lists of a sparse adjacency: zero-tile jumping (Section 4.3) down to the single
+ * entry, for graphs of a few neighbours per node.  Built once per adjacency, like the tile map;
+ * a list holds up to 256 columns (16-bit), rows of more bits are marked by their degree and
+ * taken from A itself.  For A square or block-diagonal with fewer than 65535 columns.
+ *   qgtc_neighbours_bytes   bytes of the buffer for A (0: A is not covered)
+ *   qgtc_neighbours_carve   points n's fields into `buffer` (device, 16-byte aligned)
+ *   qgtc_build_neighbours   fills deg (bits per row) and the lists; with a map (16 x 32, 64 or 128)
+ *                           its row_cnt, col_idx and deg as qgtc_build_tile_map does, in the same
+ *                           pass over A, but not its nnz_tiles (qgtc_tile_map_total)
+ */
+typedef struct qgtc_neighbours {
+  int32_t rows, cols, block_rows;     /* of A */
+  int32_t rest_cap;                   /* entries per row in `rest` */
+  int32_t* deg;                       /* [rows] */
+  uint64_t* heavy;                    /* per 64 rows: those of more than 64 bits, and how many */
+  uint8_t* heavy_cnt;
+  uint16_t* first;                    /* the first 16 entries of every row, and the others, */
+  uint16_t* rest;                     /* in an order of the library's */
+} qgtc_neighbours;
+
+size_t qgtc_neighbours_bytes(const qgtc_bits* A);
+qgtc_status qgtc_neighbours_carve(qgtc_neighbours* n, void* buffer, const qgtc_bits* A);
+qgtc_status qgtc_build_neighbours(const qgtc_bits* A, const qgtc_neighbours* n,
+                                  const qgtc_tile_map* map, void* stream);
+/* Whether a stack of n_layers (widths[0] -> ... -> widths[n_layers]) is faster over lists of A, which has
+ * `bits` bits, than over its tiles: 1 or 0.  A host function of sizes alone. */
+int32_t qgtc_neighbours_pay(const qgtc_bits* A, int64_t bits, const int32_t* widths, int32_t n_layers);
+
+/* ---------------------------------------------------------------------------
  * A stack of layers on one adjacency in one call (the driver loop of Section 4.5: every
  * hidden layer hands low-bit codes to the next one, the last emits fp32 or int32).  The
  * same integers as qgtc_pack_bits followed by qgtc_layer per layer; the activations between
@@ -386,12 +418,18 @@ qgtc_status qgtc_layer_static(const qgtc_bits* A, const qgtc_tile_map* map,
  *   W               RIGHT_BYTES
  *   buffer[2]       device, 16-byte aligned, buffer_bytes each: at least
  *                   qgtc_stack_buffer_bytes(rows, columns) of every layer's input
+ *   lists           neighbour lists of A (qgtc_build_neighbours): the aggregation adds up a row's
+ *                   neighbours instead of multiplying whole tiles of A.  The same results; the
+ *                   activations are then row-major bytes, and features that are quantized ahead go
+ *                   through qgtc_stack_input_rows.  A of few bits per row; any A gives the right
+ *                   result, rows of more than 256 bits are slow
  * Limits: s and t at most 8 bits, at most 1024 input and 256 output columns per layer, A
  * square or block-diagonal with rows less than 2^24 words apart, less than 2^26 rows (fewer than
  * 2^27 or 2^28 where every layer has at most 32 or 16 input columns), else QGTC_ERR_UNSUPPORTED /
  * _SHAPE.
  *
- * qgtc_stack_input    Eq. (2) of fp32 features into `buffer` (buffer[0] of the pass to come)
+ * qgtc_stack_input    Eq. (2) of fp32 features into `buffer` (buffer[0] of the pass to come);
+ *                     qgtc_stack_input_rows: for a stack with lists
  * qgtc_stack_forward  the pass.  Features: src != NULL - fp32, quantized first with q; else
  *                     X != NULL - packed planes (RIGHT, s bits); else what
  *                     qgtc_stack_input left in buffer[0]. */
@@ -409,11 +447,14 @@ typedef struct qgtc_stack {
   int32_t s;
   void* buffer[2];
   size_t buffer_bytes;
+  const qgtc_neighbours* lists;       /* or NULL: whole tiles of A on the matrix cores */
 } qgtc_stack;
 
 size_t qgtc_stack_buffer_bytes(int32_t rows, int32_t cols);
 qgtc_status qgtc_stack_input(const float* src, int32_t rows, int32_t cols, int64_t ld_src,
                              const qgtc_quant* q, void* buffer, size_t buffer_bytes, void* stream);
+qgtc_status qgtc_stack_input_rows(const float* src, int32_t rows, int32_t cols, int64_t ld_src,
+                                  const qgtc_quant* q, void* buffer, size_t buffer_bytes, void* stream);
 qgtc_status qgtc_stack_forward(const qgtc_stack* stack, const float* src, int64_t ld_src,
                                const qgtc_quant* q, const qgtc_bits* X, void* out, int64_t ld_out,
                                void* stream);

@@ -67,9 +67,16 @@ class _StackLayerC(C.Structure):
     _fields_ = [("W", _BitsC), ("first", _EpilogueC), ("second", _EpilogueC)]
 
 
+class _NeighboursC(C.Structure):
+    _fields_ = [("rows", C.c_int32), ("cols", C.c_int32), ("block_rows", C.c_int32), ("rest_cap", C.c_int32),
+                ("deg", C.c_void_p), ("heavy", C.c_void_p), ("heavy_cnt", C.c_void_p),
+                ("first", C.c_void_p), ("rest", C.c_void_p)]
+
+
 class _StackC(C.Structure):
     _fields_ = [("A", C.POINTER(_BitsC)), ("map", C.POINTER(_TileMapC)), ("layers", C.POINTER(_StackLayerC)),
-                ("n_layers", C.c_int32), ("s", C.c_int32), ("buffer", C.c_void_p * 2), ("buffer_bytes", C.c_size_t)]
+                ("n_layers", C.c_int32), ("s", C.c_int32), ("buffer", C.c_void_p * 2), ("buffer_bytes", C.c_size_t),
+                ("lists", C.POINTER(_NeighboursC))]
 
 
 class _PlanInC(C.Structure):
@@ -131,6 +138,11 @@ def lib():
         "qgtc_tile_map_bytes": (sz, [i32, i32, i32, i32]),
         "qgtc_tile_map_carve": (C.c_int, [P(_TileMapC), vp, i32, i32, i32, i32]),
         "qgtc_build_tile_map": (C.c_int, [P(_BitsC), P(_TileMapC), vp]),
+        "qgtc_tile_map_total": (C.c_int, [P(_TileMapC), vp]),
+        "qgtc_neighbours_bytes": (sz, [P(_BitsC)]),
+        "qgtc_neighbours_carve": (C.c_int, [P(_NeighboursC), vp, P(_BitsC)]),
+        "qgtc_neighbours_pay": (i32, [P(_BitsC), i64, P(i32), i32]),
+        "qgtc_build_neighbours": (C.c_int, [P(_BitsC), P(_NeighboursC), P(_TileMapC), vp]),
         "qgtc_aggregate": (C.c_int, [P(_BitsC), P(_TileMapC), P(_BitsC), P(_EpilogueC), vp, i64, vp]),
         "qgtc_update": (C.c_int, [P(_BitsC), P(_BitsC), P(_EpilogueC), vp, i64, vp]),
         "qgtc_layer_workspace_bytes": (sz, [i32, i32, i32, i32]),
@@ -141,6 +153,7 @@ def lib():
         "qgtc_aggregate_reads_map": (i32, [P(_BitsC), i32]),
         "qgtc_stack_buffer_bytes": (sz, [i32, i32]),
         "qgtc_stack_input": (C.c_int, [vp, i32, i32, i64, P(_QuantC), vp, sz, vp]),
+        "qgtc_stack_input_rows": (C.c_int, [vp, i32, i32, i64, P(_QuantC), vp, sz, vp]),
         "qgtc_stack_forward": (C.c_int, [P(_StackC), vp, i64, P(_QuantC), P(_BitsC), vp, i64, vp]),
         "qgtc_tile_stats": (C.c_int, [P(_BitsC), vp, vp]),
         "qgtc_plan_layer": (C.c_int, [P(_PlanInC), P(_PlanOutC)]),
@@ -196,6 +209,7 @@ class TileMap:
     buffer: torch.Tensor
     c: _TileMapC
     rows: int
+    totals: bool = True       # nnz_tiles is filled in by whoever fills the rest
 
     def _view(self, ptr, n):
         off = (ptr - self.buffer.data_ptr()) // 4
@@ -208,9 +222,22 @@ class TileMap:
         return self._view(self.c.col_idx, self.c.n_tile_rows * self.c.n_tile_cols) \
             .view(self.c.n_tile_rows, self.c.n_tile_cols)
     @property
-    def nnz_tiles(self): return self._view(self.c.nnz_tiles, 2)
+    def nnz_tiles(self):
+        if not self.totals:
+            _check(lib().qgtc_tile_map_total(C.byref(self.c), _stream()), "qgtc_tile_map_total")
+        return self._view(self.c.nnz_tiles, 2)
     @property
     def deg(self): return self._view(self.c.deg, self.rows)
+
+
+@dataclass
+class Neighbours:
+    """Neighbour lists of an adjacency (qgtc_neighbours)."""
+    buffer: torch.Tensor
+    c: _NeighboursC
+
+    @property
+    def deg(self): return self.buffer[:self.c.rows]
 
 
 @dataclass
@@ -340,19 +367,52 @@ def qgtc_col_sums(bits: Bits, out: torch.Tensor | None = None) -> torch.Tensor:
     return out
 
 
+def _alloc_tile_map(A: Bits, tile_rows: int, tile_kbits: int) -> TileMap:
+    nbytes = lib().qgtc_tile_map_bytes(A.rows, A.cols, tile_rows, tile_kbits)
+    if nbytes == 0:
+        raise QgtcError(7, "qgtc_tile_map_bytes")
+    buf = torch.empty(nbytes // 4, dtype=torch.int32, device=A.words.device)
+    m = _TileMapC()
+    _check(lib().qgtc_tile_map_carve(C.byref(m), C.c_void_p(buf.data_ptr()), A.rows, A.cols,
+                                     tile_rows, tile_kbits), "qgtc_tile_map_carve")
+    return TileMap(buf, m, A.rows)
+
+
 def qgtc_build_tile_map(A: Bits, tile_rows: int = 16, tile_kbits: int = 128,
                         out: TileMap | None = None) -> TileMap:
     if out is None:
-        nbytes = lib().qgtc_tile_map_bytes(A.rows, A.cols, tile_rows, tile_kbits)
-        if nbytes == 0:
-            raise QgtcError(7, "qgtc_tile_map_bytes")
-        buf = torch.empty(nbytes // 4, dtype=torch.int32, device=A.words.device)
-        m = _TileMapC()
-        _check(lib().qgtc_tile_map_carve(C.byref(m), C.c_void_p(buf.data_ptr()), A.rows, A.cols,
-                                         tile_rows, tile_kbits), "qgtc_tile_map_carve")
-        out = TileMap(buf, m, A.rows)
+        out = _alloc_tile_map(A, tile_rows, tile_kbits)
+    out.totals = True
     _check(lib().qgtc_build_tile_map(C.byref(A.c), C.byref(out.c), _stream()),
            "qgtc_build_tile_map")
+    return out
+
+
+def neighbours_bytes(A: Bits) -> int:
+    """Bytes of the neighbour lists of A; 0 where they do not cover it."""
+    return int(lib().qgtc_neighbours_bytes(C.byref(A.c)))
+
+
+def qgtc_neighbours_pay(A: Bits, bits: int, dims) -> bool:
+    """Whether layers of these (inputs, outputs) are faster over neighbour lists of A, which has `bits` bits."""
+    widths = [d for d, _ in dims] + [dims[-1][1]]
+    return bool(lib().qgtc_neighbours_pay(C.byref(A.c), bits, (C.c_int32 * len(widths))(*widths), len(dims)))
+
+
+def qgtc_build_neighbours(A: Bits, out: Neighbours | None = None, tmap: TileMap | None = None) -> Neighbours:
+    """Neighbour lists and degrees of A; with tmap, its lists of tiles in the same pass."""
+    if out is None:
+        nbytes = neighbours_bytes(A)
+        if nbytes == 0:
+            raise QgtcError(7, "qgtc_neighbours_bytes")
+        buf = torch.empty(-(-nbytes // 4), dtype=torch.int32, device=A.words.device)
+        n = _NeighboursC()
+        _check(lib().qgtc_neighbours_carve(C.byref(n), C.c_void_p(buf.data_ptr()), C.byref(A.c)), "qgtc_neighbours_carve")
+        out = Neighbours(buf, n)
+    if tmap is not None:
+        tmap.totals = False
+    _check(lib().qgtc_build_neighbours(C.byref(A.c), C.byref(out.c), C.byref(tmap.c) if tmap is not None else None,
+                                       _stream()), "qgtc_build_neighbours")
     return out
 
 
@@ -426,8 +486,8 @@ class Stack:
     second epilogue) per layer, and the two activation buffers.  Holds on to every tensor it
     points at."""
 
-    def __init__(self, A: Bits, tmap: TileMap | None, layers, s: int, buffers):
-        self.keep = (A, tmap, layers, buffers)
+    def __init__(self, A: Bits, tmap: TileMap | None, layers, s: int, buffers, lists: Neighbours | None = None):
+        self.keep = (A, tmap, layers, buffers, lists)
         self.rows, self.in_cols, self.out_cols = A.rows, layers[0][0].rows, layers[-1][0].cols
         self.last = layers[-1][2]
         self._layers = (_StackLayerC * len(layers))()
@@ -435,16 +495,19 @@ class Stack:
             dst.W, dst.first, dst.second = W.c, first.to_c(), second.to_c()
         nbytes = buffers[0].numel() * buffers[0].element_size()
         self.c = _StackC(C.pointer(A.c), C.pointer(tmap.c) if tmap is not None else None, self._layers, len(layers), s,
-                         (C.c_void_p * 2)(*[b.data_ptr() for b in buffers]), nbytes)
+                         (C.c_void_p * 2)(*[b.data_ptr() for b in buffers]), nbytes,
+                         C.pointer(lists.c) if lists is not None else None)
 
 
-def qgtc_stack_input(src: torch.Tensor, nbits: int, quant, buffer: torch.Tensor):
-    """Eq. (2) of fp32 features into an activation buffer."""
+def qgtc_stack_input(src: torch.Tensor, nbits: int, quant, buffer: torch.Tensor, rows_form: bool = False):
+    """Eq. (2) of fp32 features into an activation buffer; rows_form: of a stack with neighbour lists
+    (qgtc_stack_input_rows)."""
     assert src.dim() == 2 and src.dtype == torch.float32 and src.is_cuda and src.stride(1) == 1
     rows, cols = src.shape
     q = _QuantC(float(quant[0]), float(quant[1]), nbits)
-    _check(lib().qgtc_stack_input(src.data_ptr(), rows, cols, src.stride(0) if rows > 1 else max(cols, 1), C.byref(q),
-                                  buffer.data_ptr(), buffer.numel() * buffer.element_size(), _stream()), "qgtc_stack_input")
+    fn = lib().qgtc_stack_input_rows if rows_form else lib().qgtc_stack_input
+    _check(fn(src.data_ptr(), rows, cols, src.stride(0) if rows > 1 else max(cols, 1), C.byref(q),
+              buffer.data_ptr(), buffer.numel() * buffer.element_size(), _stream()), "qgtc_stack_input")
 
 
 def qgtc_stack_forward(stack: Stack, out: torch.Tensor, src: torch.Tensor | None = None, quant=None,

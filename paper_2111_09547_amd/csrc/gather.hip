@@ -1,0 +1,115 @@
+// Host side of the fused layer over neighbour lists (gather_kernel.h), and features in its form
+// from packed planes.
+#include "gather.h"
+
+namespace qgtc {
+namespace {
+
+struct PlanesParams {
+  const uint32_t* X;
+  int64_t ld, ps;
+  int32_t rows, cols, s;
+  uint8_t* dst;
+  int32_t ld_dst;            // bytes
+  uint32_t flip;
+};
+
+// Planes to bytes: a thread has 32 rows of four columns, whose plane words it transposes as 8 x 8 bit
+// matrices; eight rows at a time its bytes are put in row order and stored as words.
+__global__ __launch_bounds__(256) void planes_to_rows_kernel(const PlanesParams p) {
+  const int quads = p.ld_dst / 4;
+  const unsigned idx = blockIdx.x * 256u + threadIdx.x;
+  const int kw = (int)(idx / (unsigned)quads), c0 = 4 * (int)(idx % (unsigned)quads);
+  if (kw * 32 >= p.rows) return;
+  uint32_t code[4][8];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int c = min(c0 + k, p.cols - 1);
+#pragma unroll
+    for (int pl = 0; pl < 8; ++pl) {
+      code[k][pl] = 0u;
+      if (pl < p.s) code[k][pl] = p.X[(int64_t)pl * p.ps + (int64_t)kw * p.ld + c];
+    }
+    planes_word_to_codes(code[k]);
+    if (c0 + k >= p.cols) {
+#pragma unroll
+      for (int r = 0; r < 8; ++r) code[k][r] = 0u;
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < 8; ++r) {
+    // byte b of the four words: row 8 b + r
+    const uint32_t lo01 = __builtin_amdgcn_perm(code[1][r], code[0][r], 0x05010400u), hi01 = __builtin_amdgcn_perm(code[1][r], code[0][r], 0x07030602u);
+    const uint32_t lo23 = __builtin_amdgcn_perm(code[3][r], code[2][r], 0x05010400u), hi23 = __builtin_amdgcn_perm(code[3][r], code[2][r], 0x07030602u);
+    const uint32_t v[4] = {__builtin_amdgcn_perm(lo23, lo01, 0x05040100u), __builtin_amdgcn_perm(lo23, lo01, 0x07060302u),
+                           __builtin_amdgcn_perm(hi23, hi01, 0x05040100u), __builtin_amdgcn_perm(hi23, hi01, 0x07060302u)};
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      const int row = 32 * kw + 8 * b + r;
+      if (row < p.rows) *reinterpret_cast<uint32_t*>(p.dst + (int64_t)row * p.ld_dst + c0) = v[b] ^ p.flip;
+    }
+  }
+}
+
+}  // namespace
+
+qgtc_status planes_to_rows(const qgtc_bits* X, uint8_t* dst, hipStream_t stream) {
+  PlanesParams p{X->data, X->ld_words, X->plane_stride_words, X->rows, X->cols, X->nbits, dst, (int32_t)row_codes_ld(X->cols),
+                 row_codes_flip(X->nbits)};
+  ProfScope prof(QGTC_KERNEL_PACK, stream);
+  hipLaunchKernelGGL(planes_to_rows_kernel, dim3((unsigned)cdiv((int64_t)cdiv(p.rows, 32) * (p.ld_dst / 4), 256)), dim3(256), 0, stream, p);
+  return launch_status();
+}
+
+qgtc_status gather_layer(GatherParams* gp, int mode, const qgtc_bits* W, hipStream_t stream) {
+  GatherParams& p = *gp;
+  p.wb = reinterpret_cast<const uint8_t*>(W->data);
+  p.wb_part = W->plane_stride_words * 4;
+  p.h = W->cols;
+  p.n_nt = cdiv(W->cols, 16);
+  p.n_ks = cdiv(W->rows, 64);
+  p.split_y = p.agg_nbits == 8;
+  p.split_w = W->nbits == 8;
+  if (p.up.l0b == 0.0) p.up.row_l = nullptr;
+  p.want_rowsum = p.up.mode == QGTC_OUT_F32 && p.up.row_i == nullptr && p.up.rs != 0.0;
+  // A tile per wave where that gives every compute unit eight waves (65536 rows, 64 -> 64: 8.8 us, with four waves
+  // per tile 11.3; 8192 rows have half a wave per SIMD that way).
+  const int cus = device_compute_units();
+  const bool share = p.ldx > 32 && p.n_tiles < 8 * cus;
+  const int tiles = share ? 1 : 4;
+  const int n_ntp = share || p.n_nt == 1 ? p.n_nt : (p.n_nt + 3) / 4 * 4;
+  int pieces = 1;
+  while (16 * pieces < p.ldx) pieces <<= 1;
+  // The codes of a tile: of 256 columns at a time where one group of output tiles is all.  Heavy rows,
+  // one at a time, need those of all columns, their counts, the row that is taken and its sums.
+  const bool parts = pieces > 16 && !share && p.n_nt <= (p.n_nt == 1 ? 1 : 4);
+  size_t lds = (size_t)tiles * (parts ? 4 : p.n_ks) * 1024;
+  const size_t one = (size_t)p.n_ks * 1024, heavy = one + 2048 + 64 + (size_t)pieces * 64;
+  p.heavy_off = (int)one;
+  if (lds < heavy) lds = heavy;
+  lds = (lds + 63) & ~(size_t)63;
+  p.cols_off = (int)lds;
+  lds += (size_t)n_ntp * (64 + 128);
+  p.w_off = -1;
+  if (p.n_ks * n_ntp <= 48) {
+    p.w_off = (int)lds;
+    lds += (size_t)p.n_ks * n_ntp * 1024;
+  }
+  p.nblocks = (uint32_t)cdiv(p.n_tiles, tiles);
+  // workgroups that read the same rows of X stay on one XCD, as far as every XCD still gets a run
+  int64_t run = cdiv(cdiv(p.block, 16), tiles);
+  if (run > (int64_t)p.nblocks / 8) run = p.nblocks / 8;
+  p.run_shift = 0;
+  while (((int64_t)2 << p.run_shift) <= run && p.run_shift < 24) ++p.run_shift;
+  // 1543 of them in 262144 rows, 16 -> 16: 256 workgroups 29.9, 512 19.2, 1024 15.4 us; without any, 64 -> 64 on 65536
+  // rows, 8.8, 8.8 and 9.6.
+  p.n_heavy_wg = p.block > kListLight ? (p.n_groups < 2 * cus ? (p.n_groups + 7) / 8 * 8 : 2 * cus / 8 * 8) : 0;
+  ProfScope prof(QGTC_KERNEL_LAYER, stream);
+  switch (mode) {
+    case kGatherCodes: return gather_launch<kGatherCodes>(p, share, lds, stream);
+    case kGatherAffine: return gather_launch<kGatherAffine>(p, share, lds, stream);
+    default: return gather_launch<kGatherRows>(p, share, lds, stream);
+  }
+}
+
+}  // namespace qgtc

@@ -1,0 +1,608 @@
+// One quantized GNN layer over neighbour lists (lists.h): the fused layer of layer_kernel.h for
+// graphs of a few neighbours per node, where the products of whole tiles of A are mostly with zeros.
+//
+// X is kept as bytes, row-major, so that a neighbour is one piece of memory of up to 1 KiB:
+//   1. Aggregation.  A load brings 16 columns (a piece) of four neighbours of each of 16 slots, a slot
+//      being a row of A and one of its P = 2^LP pieces: lane (n, g) has neighbour 4 k + g of slot n.
+//      The matrix cores add them up: with the operand A[m][16 g + b] = (b == m),
+//      v_mfma_i32_16x16x64_i8 adds byte m of the four lanes of a slot to sum m of it, so that a load of
+//      64 x 16 bytes costs one instruction instead of some 50 of the vector ALUs (which halves a
+//      layer's instructions), and sums are exact in 32 bits.  Lists end in kListNone, which lies past
+//      the end of X: such a load gives zeros and costs no traffic.
+//      Heavy rows are left out, and taken one by one by workgroups of their own: from their list, or
+//      from the words of A where that does not hold all neighbours.
+//   2. Requantization: lane (n, g) has columns 4 g .. 4 g + 3 of slot n.  The codes of a tile of 16
+//      rows go to LDS, [64 columns][row][64 bytes].
+//   3. Update and epilogue as in layer_kernel.h, weights along M.  Codes are stored 16 bytes per lane:
+//      the weights of 64 columns are dealt to four tiles so that a lane has 16 columns side by side.
+// WPT = 1: a wave has a tile, and waits for nobody but the weights.  WPT = 4: four waves share a tile, where
+// there are few.  LT: 16-column output tiles at a time.
+// What bounds it: narrow rows the vector ALUs (some 500 instructions per tile and wave) and the latency of
+// four dependent loads behind a launch of 2.4 us; wide rows HBM and latency.  Whole tiles and lists, us:
+// 65536 rows in blocks of 1024, 9 neighbours, 64 -> 64 13.2 and 9.0, 128 -> 128 19.5 and 15.0; 8192 rows,
+// 64 -> 64 8.6 and 4.1; 262144 rows of a power-law graph, 512 -> 16 159 and 85 (134 MB of codes: 27 at the
+// rate of a copy), 1024 -> 64 on 65536 rows 168 and 95; without heavy rows 512 -> 16 320 and 64.
+// Adding bytes up on the vector ALUs instead: 64 -> 64 11.0 us.  Heavy rows in the tiles' own waves: 512 -> 16
+// on the power-law graph 232 us.
+#pragma once
+#include "gather.h"
+#include "layer_parts.h"
+
+namespace qgtc {
+namespace {
+
+typedef v4u v4u_a4 __attribute__((aligned(4)));      // 16 bytes at a multiple of four
+
+// At the end of a loop that is left right behind its last product: the compiler (ROCm 7.2) copies the
+// sums at the loop's head two wait states after it, where the instruction needs seven, and the copy is
+// then of the old values.
+__device__ __forceinline__ void settle(v4i& sum) { asm volatile("s_nop 7" : "+v"(sum)); }
+
+// The dimensions of an instance.
+template <int LP, int WPT>
+struct GatherShape {
+  static constexpr int P = 1 << LP;
+  static constexpr int PS = P < 16 ? P : 16;         // pieces of a unit: 16 slots
+  static constexpr int RC = 16 / PS, HV = P / PS;    // rows of a unit; P > 16: parts of 256 columns
+  static constexpr int UNITS = 16 / WPT / RC;        // units of a wave per part
+  static constexpr int W = UNITS < 4 ? UNITS : 4;    // at a time
+};
+
+__device__ __forceinline__ v4i mfma_i8(const v4i& a, const v4i& x, const v4i& c) { return __builtin_amdgcn_mfma_i32_16x16x64_i8(a, x, c, 0, 0, 0); }
+// A[m][16 g + b] = (b == m), which adds up the bytes of the four lanes of a slot.
+__device__ __forceinline__ v4i adder(int ln) {
+  const uint32_t mark = 1u << (8 * (ln & 3));
+  return (v4i){(int)((ln >> 2) == 0 ? mark : 0u), (int)((ln >> 2) == 1 ? mark : 0u),
+               (int)((ln >> 2) == 2 ? mark : 0u), (int)((ln >> 2) == 3 ? mark : 0u)};
+}
+__device__ __forceinline__ uint32_t list_entry(const v2u& idx, int k) { return k & 1 ? idx[k >> 1] >> 16 : idx[k >> 1] & 0xffffu; }
+
+// Rows of X that a row of A can have as neighbours: its diagonal block's.
+struct Neighbours {
+  __amdgpu_buffer_rsrc_t rx;
+  uint32_t ldx;
+  __device__ __forceinline__ Neighbours(const GatherParams& p, int row0) {
+    const int first_row = (int)div_by((unsigned)row0, (unsigned)p.block, p.block_magic) * p.block;
+    ldx = (uint32_t)p.ldx;
+    rx = uniform_rsrc(p.X + (int64_t)first_row * p.ldx, (uint32_t)(min(p.rows - first_row, p.block) * p.ldx));
+  }
+  __device__ __forceinline__ v4i load(uint32_t idx, uint32_t pofs) const {
+    return (v4i)__builtin_amdgcn_raw_buffer_load_b128(rx, __umul24(idx, ldx) + pofs, 0, 0);
+  }
+  // past the end where a row has no such piece
+  __device__ __forceinline__ uint32_t piece_offset(int piece) const { return 16u * (uint32_t)piece < ldx ? 16u * (uint32_t)piece : 0x80000000u; }
+};
+
+// Codes of four columns from col on as they are multiplied: code 0 past the last column, minus 128 for eight bits.
+__device__ __forceinline__ uint32_t kept_codes(const GatherParams& p, uint32_t word, int col) {
+  return (word & (uint32_t)((1ull << (8 * min(max(p.cols - col, 0), 4))) - 1ull)) ^ (p.split_y ? 0x80808080u : 0u);
+}
+
+// Weights as operands (codes, minus 128 for eight bits) into LDS, their sums and the column terms.
+template <int LT, int MODE>
+__device__ __forceinline__ void stage_weights(const GatherParams& p, uint8_t* lds, int wave, int lane) {
+  constexpr bool PERM = LT == 4 && MODE != kGatherRows;
+  const int ln = lane & 15, g = lane >> 4;
+  const int n_ks = p.n_ks, n_nt = p.n_nt, n_ntp = LT == 4 ? (n_nt + 3) & ~3 : n_nt;
+  const bool w8 = p.split_w != 0;
+  uint32_t* const wsum = reinterpret_cast<uint32_t*>(lds + p.cols_off);
+  double* const colterm = reinterpret_cast<double*>(lds + p.cols_off + n_ntp * 64);
+  for (int nt = wave; nt < n_ntp; nt += 4) {
+    uint32_t sum = 0u;
+    // column c of a group of 64 is position 4 (c / 16) + c % 4 of tile (c / 4) % 4
+    const int to = PERM ? ((nt & ~3) + (ln >> 2)) * 1024 + (4 * (nt & 3) + (ln & 3) + 16 * g) * 16 : nt * 1024 + lane * 16;
+    for (int ks = 0; ks < n_ks; ++ks) {
+      v4u v = {0u, 0u, 0u, 0u};
+      if (LT == 1 || nt < n_nt) {
+        const uint8_t* blk = p.wb + (int64_t)(nt * n_ks + ks) * 1024;
+        v = load_w<4>(blk, lane);
+        if (w8) v |= load_w<4>(blk + p.wb_part, lane) << 7;
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) sum = __builtin_amdgcn_sad_u8(v[i], 0u, sum);
+      if (w8) v ^= 0x80808080u;
+      if (p.w_off >= 0) *reinterpret_cast<v4u*>(lds + p.w_off + ks * n_ntp * 1024 + to) = v;
+    }
+    sum += (uint32_t)__shfl_xor((int)sum, 16, 64);
+    sum += (uint32_t)__shfl_xor((int)sum, 32, 64);
+    const int h = nt * 16 + ln;
+    if (g == 0) wsum[h] = sum << 7;
+    if (MODE == kGatherRows && p.up.mode == QGTC_OUT_F32) {
+      const double t = p.up.ck + p.up.cs * (p.up.col_i ? (double)p.up.col_i[min(h, p.h - 1)] : 0.0);
+      if (g == 0) colterm[h] = t;
+    }
+  }
+}
+
+// Products of the codes at yb (of the steps ks0 .. ks1 - 1, the first one's in front) with the weights of
+// output tiles nt0 .. nt0 + LT - 1 onto z, and their sums onto rs.
+template <int LT, int MODE>
+__device__ __forceinline__ void add_products(const GatherParams& p, const uint8_t* lds, const uint8_t* yb, int ks0, int ks1, int nt0, bool row_sums,
+                                             v4i (&z)[LT], v4i& rs, int lane) {
+  constexpr bool PERM = LT == 4 && MODE != kGatherRows;
+  const int ln = lane & 15, g = lane >> 4;
+  const int n_ntp = LT == 4 ? (p.n_nt + 3) & ~3 : p.n_nt;
+  const uint8_t* ya = yb + ln * 64 + g * 16;
+  const v4i ones = {0x01010101, 0x01010101, 0x01010101, 0x01010101};
+  if (p.w_off >= 0) {
+    const uint8_t* w = lds + p.w_off + (ks0 * n_ntp + nt0) * 1024 + lane * 16;
+    for (int ks = ks0; ks < ks1; ++ks) {
+      const v4i y = *reinterpret_cast<const v4i*>(ya);
+      if (row_sums) rs = mfma_i8(ones, y, rs);
+#pragma unroll
+      for (int j = 0; j < LT; ++j) z[j] = mfma_i8(*reinterpret_cast<const v4i*>(w + j * 1024), y, z[j]);
+      ya += 1024;
+      w += n_ntp * 1024;
+    }
+  } else {                                           // too many for LDS
+    for (int ks = ks0; ks < ks1; ++ks) {
+      const v4i y = *reinterpret_cast<const v4i*>(ya);
+      if (row_sums) rs = mfma_i8(ones, y, rs);
+#pragma unroll
+      for (int j = 0; j < LT; ++j) {
+        const int nt = PERM ? nt0 + (ln >> 2) : nt0 + j, l = PERM ? 4 * j + (ln & 3) + 16 * g : lane;
+        const uint8_t* blk = p.wb + (int64_t)(min(nt, p.n_nt - 1) * p.n_ks + ks) * 1024;   // (past the last tile: not used)
+        v4i wv = *reinterpret_cast<const v4i*>(blk + l * 16);
+        if (p.split_w) wv = (wv | *reinterpret_cast<const v4i*>(blk + p.wb_part + l * 16) << 7) ^ (int)0x80808080;
+        z[j] = mfma_i8(wv, y, z[j]);
+      }
+      ya += 1024;
+    }
+  }
+}
+
+// Epilogue of output tiles nt0 .. nt0 + LT - 1 of the 16 rows from row0 on; lane (node n, group g), which
+// writes if out_ok.
+template <int LT, int MODE>
+__device__ __forceinline__ void emit_tile(const GatherParams& p, const uint8_t* lds, int row0, bool out_ok, int nt0, v4i (&z)[LT], const v4i& rs,
+                                          int32_t rl, int lane) {
+  constexpr bool PERM = LT == 4 && MODE != kGatherRows;
+  const int ln = lane & 15, g = lane >> 4;
+  const int n_nt = p.n_nt, n_ntp = LT == 4 ? (n_nt + 3) & ~3 : n_nt;
+  const int out_row = row0 + ln;
+  const uint32_t* const wsum = reinterpret_cast<const uint32_t*>(lds + p.cols_off);
+  const double* const colterm = reinterpret_cast<const double*>(lds + p.cols_off + n_ntp * 64);
+  const EpiParams& u = p.up;
+  const Rq oq = make_rq(u.rq_lo, u.relu, u.rq_inv_scale, u.rq_nbits);
+  double t1 = 0.0, l0 = 0.0;
+  if (MODE == kGatherRows && u.mode == QGTC_OUT_F32) {
+    double ri = 0.0;
+    if (p.want_rowsum) ri = (double)((uint32_t)rs[0] + (p.split_y ? (uint32_t)(p.n_ks * 64) << 7 : 0u));
+    else if (u.row_i && out_ok) ri = (double)u.row_i[out_row];
+    t1 = u.rs * ri;
+    l0 = u.l0a + u.l0b * (double)rl;
+  }
+  if (p.split_w) {
+#pragma unroll
+    for (int j = 0; j < LT; ++j) z[j] += rs << 7;
+  }
+  const int h0 = nt0 * 16 + (PERM ? 16 * g : 4 * g);   // first column of the lane, tile 0; the next tile's is HJ further
+  constexpr int HJ = PERM ? 4 : 16;
+  if (p.split_y) {
+#pragma unroll
+    for (int j = 0; j < LT; ++j) z[j] += *reinterpret_cast<const v4i*>(wsum + h0 + HJ * j);
+  }
+  if constexpr (MODE != kGatherRows) {
+    uint32_t d[LT];
+    if constexpr (MODE == kGatherAffine) {
+      const uint32_t qmax = (uint32_t)oq.qmaxf;
+#pragma unroll
+      for (int j = 0; j < LT; ++j) {
+        d[j] = 0u;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int hc = min(h0 + HJ * j + r, p.h - 1);
+          const float ca = u.col_a[hc], cb = u.col_b ? u.col_b[hc] : 0.0f;
+          d[j] |= requantize_affine((uint32_t)z[j][r], ca, cb, u.relu, oq.lo, oq.inv, qmax, oq.qmaxf) << (8 * r);
+        }
+      }
+    } else {
+      uint32_t c[LT][4];
+#pragma unroll
+      for (int j = 0; j < LT; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) c[j][r] = (uint32_t)z[j][r];
+      pack_codes_words(c, oq, d);
+    }
+    if (out_ok && h0 < (int)u.ld_out) {
+      uint8_t* const dst = reinterpret_cast<uint8_t*>(u.out) + (int64_t)out_row * u.ld_out + h0;
+      const uint32_t f = (uint32_t)p.out_flip;
+      if constexpr (LT == 4) *reinterpret_cast<v4u*>(dst) = (v4u){d[0] ^ f, d[1] ^ f, d[2] ^ f, d[3] ^ f};
+      else *reinterpret_cast<uint32_t*>(dst) = d[0] ^ f;
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < LT; ++j) {
+      if (nt0 + j >= n_nt) continue;             // wave-uniform
+      const int h = h0 + HJ * j;
+      uint32_t res[4];
+      if (u.mode == QGTC_OUT_I32) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) res[r] = (uint32_t)(u.relu ? max(z[j][r], 0) : z[j][r]);
+      } else {
+        // the arithmetic of dequantize_f64, with the row and column terms formed once
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          double v = (u.cc * (double)z[j][r] + t1) + l0 * colterm[h + r];
+          if (u.col_a) {
+            const int hc = min(h + r, p.h - 1);
+            v = v * (double)u.col_a[hc] + (u.col_b ? (double)u.col_b[hc] : 0.0);
+          }
+          if (u.relu) v = v < 0.0 ? 0.0 : v;
+          res[r] = __float_as_uint((float)v);
+        }
+      }
+      if (out_ok) {
+        uint32_t* const dst = reinterpret_cast<uint32_t*>(u.out) + (int64_t)out_row * u.ld_out + h;
+        if (h + 4 <= p.h) {
+          *reinterpret_cast<v4u_a4*>(dst) = (v4u){res[0], res[1], res[2], res[3]};
+        } else {
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            if (h + r < p.h) dst[r] = res[r];
+        }
+      }
+    }
+  }
+}
+
+// Update and epilogue of all output tiles, from nt_first on and every nt_step.
+template <int LT, int MODE>
+__device__ __forceinline__ void finish_tile(const GatherParams& p, const uint8_t* lds, const uint8_t* yb, int row0, bool out_ok, int nt_first,
+                                            int nt_step, int32_t rl, int lane) {
+  const v4i zero = {0, 0, 0, 0};
+  bool row_sums = p.split_w || (MODE == kGatherRows && p.want_rowsum);
+  v4i rs = zero;
+#pragma unroll 1
+  for (int nt0 = nt_first; nt0 < p.n_nt; nt0 += nt_step) {
+    v4i z[LT];
+#pragma unroll
+    for (int j = 0; j < LT; ++j) z[j] = zero;
+    add_products<LT, MODE>(p, lds, yb, 0, p.n_ks, nt0, row_sums, z, rs, lane);
+    row_sums = false;                                // (once)
+    emit_tile<LT, MODE>(p, lds, row0, out_ok, nt0, z, rs, rl, lane);
+  }
+}
+
+// The heavy rows, one after the other, by all n_heavy_wg workgroups.
+template <int LP, int LT, int MODE>
+__device__ __forceinline__ void heavy_rows(const GatherParams& p, uint8_t* lds, int wave, int lane) {
+  using Sh = GatherShape<LP, 1>;
+  constexpr int P = Sh::P, PS = Sh::PS, RC = Sh::RC, HV = Sh::HV;
+  const int ln = lane & 15, g = lane >> 4;
+  const int self = p.self_term, ldx = p.ldx, n_ks = p.n_ks;
+  // their number in front of each thread's groups
+  uint32_t* const before = reinterpret_cast<uint32_t*>(lds + p.heavy_off);   // [256], then [256] of the thread's own
+  int32_t* const taken = reinterpret_cast<int32_t*>(lds + p.heavy_off + 2048);
+  uint32_t* const sums = reinterpret_cast<uint32_t*>(lds + p.heavy_off + 2048 + 64);
+  const int per = (p.n_groups + 4095) / 4096 * 16;   // groups of a thread
+  uint32_t mine = 0u;
+  for (int i = 0; i < per; i += 16) {
+    const int at = (int)threadIdx.x * per + i;
+    v4u v = {0u, 0u, 0u, 0u};
+    if (at < p.n_groups) v = *reinterpret_cast<const v4u*>(p.heavy_cnt + at);   // (whole pieces)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int left = p.n_groups - at - 4 * c;    // counts that exist
+      const uint32_t m = (uint32_t)((1ull << (8 * min(max(left, 0), 4))) - 1ull);
+      mine = __builtin_amdgcn_sad_u8(v[c] & m, 0u, mine);
+    }
+  }
+  uint32_t incl = mine;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t up = (uint32_t)__shfl_up((int)incl, d, 64);
+    if (lane >= d) incl += up;
+  }
+  if (lane == 63) taken[4 + wave] = (int32_t)incl;
+  __syncthreads();
+  uint32_t base = 0u, all = 0u;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    const uint32_t c = (uint32_t)taken[4 + w];
+    if (w < wave) base += c;
+    all += c;
+  }
+  if (blockIdx.x >= all) return;                   // whole workgroup
+  before[threadIdx.x] = base + incl - mine;
+  before[256 + threadIdx.x] = mine;
+  stage_weights<LT, MODE>(p, lds, wave, lane);
+  uint8_t* const yb = lds;
+  const uint32_t flip = p.split_y ? 0x80808080u : 0u;
+  if (P < 4 && (lane & 3) >= P) *reinterpret_cast<v4u*>(yb + lane * 16) = (v4u){flip, flip, flip, flip};   // columns no lane has
+  const v4i ident = adder(ln), zero = {0, 0, 0, 0};
+  const Rq q = make_rq(p.agg_lo, p.agg_relu, p.agg_inv, p.agg_nbits);
+#pragma unroll 1
+  for (uint32_t tile = blockIdx.x; tile < all; tile += (uint32_t)p.n_heavy_wg) {
+    __syncthreads();                                 // what the last row left has been read
+    const uint32_t k = tile - before[threadIdx.x];
+    if (tile >= before[threadIdx.x] && k < before[256 + threadIdx.x]) {
+      int at = (int)threadIdx.x * per;
+      uint32_t rest = k;
+      while (rest >= p.heavy_cnt[at]) rest -= p.heavy_cnt[at++];
+      uint64_t m = p.heavy[at];
+      for (; rest > 0u; --rest) m &= m - 1u;
+      taken[0] = at * kListGroup + __builtin_ctzll(m);
+    }
+    for (int i = (int)threadIdx.x; i < P * 16; i += 256) sums[i] = 0u;
+    __syncthreads();
+    const int row0 = (int)uniform((uint32_t)taken[0]);
+    const Neighbours nb(p, row0);
+    int32_t rl = 0;
+    if (MODE == kGatherRows && p.up.mode == QGTC_OUT_F32 && p.up.row_l) rl = p.up.row_l[row0];
+    // the waves and the slots of a unit share the row's neighbours; the sums of its columns meet in LDS
+    const int n = (int)uniform((uint32_t)p.deg[row0]);
+    const int rs = ln / PS;
+#pragma unroll 1
+    for (int hv = 0; hv < HV; ++hv) {
+      const int piece = (ln & (PS - 1)) + 16 * hv;
+      const uint32_t pofs = nb.piece_offset(piece);
+      v4i h = zero;
+      if (n <= kListMax) {
+#pragma unroll 1
+        for (int e = (wave * RC + rs) * kListBlock; __builtin_amdgcn_ballot_w64(e < n) != 0ull; e += 4 * RC * kListBlock) {
+          v2u idx = {~0u, ~0u};
+          if (e < n) idx = *reinterpret_cast<const v2u*>((e == 0 ? p.first + (int64_t)row0 * kListBlock : p.rest + (int64_t)row0 * p.rest_cap + (e - kListBlock)) + 4 * g);
+          v4i y[4];
+#pragma unroll
+          for (int k = 0; k < 4; ++k) y[k] = nb.load(list_entry(idx, k), pofs);
+#pragma unroll
+          for (int k = 0; k < 4; ++k) h = mfma_i8(ident, y[k], h);
+          settle(h);
+        }
+      } else {
+        const uint32_t* words = p.A + (int64_t)row0 * p.lda;
+#pragma unroll 1
+        for (int k0 = 0; k0 < p.a_words; k0 += 256) {
+          uint32_t word = 0u;
+          if (k0 + 4 * lane + wave < p.a_words) word = words[k0 + 4 * lane + wave];
+          unsigned long long some = __builtin_amdgcn_ballot_w64(word != 0u);
+#pragma unroll 1
+          while (some) {
+            const int l = __builtin_ctzll(some);
+            some &= some - 1ull;
+            const uint32_t wd = (uint32_t)__builtin_amdgcn_readlane((int)word, l);
+            const uint32_t col = (uint32_t)(k0 + 4 * l + wave) * 32u;
+            constexpr int STEPS = RC < 8 ? 8 / RC : 1, HB = STEPS < 8 ? STEPS : 8;
+            v4i y[HB];
+#pragma unroll
+            for (int s = 0; s < HB; ++s) {
+              const uint32_t bit = (uint32_t)((s * RC + rs) * 4 + g);
+              y[s] = nb.load(bit < 32u && ((wd >> (bit & 31u)) & 1u) ? col + bit : (uint32_t)kListNone, pofs);
+            }
+#pragma unroll
+            for (int s = 0; s < HB; ++s) h = mfma_i8(ident, y[s], h);
+            settle(h);
+          }
+        }
+      }
+      if (wave == 0) {                             // (once: the own row, and 128 for every code that is code - 128)
+        uint32_t own = 0u;
+        if (self && 16 * piece < ldx) own = *reinterpret_cast<const uint32_t*>(p.X + (int64_t)row0 * ldx + 16 * piece + 4 * g);
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (rs == 0) h[r] += p.x_offset * (n + self) + (int)(int8_t)(own >> (8 * r));
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) atomicAdd(&sums[16 * piece + 4 * g + r], (uint32_t)h[r]);
+    }
+    __syncthreads();
+    for (int i = (int)threadIdx.x; i < 4 * P && i < 16 * n_ks; i += 256) {   // four columns each
+      uint32_t c[1][4], d[1];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) c[0][r] = sums[4 * i + r];
+      pack_codes_words(c, q, d);
+      *reinterpret_cast<uint32_t*>(yb + (i >> 4) * 1024 + (i & 15) * 4) = kept_codes(p, d[0], 4 * i);
+    }
+    __syncthreads();
+    finish_tile<LT, MODE>(p, lds, yb, row0, ln == 0, LT * wave, 4 * LT, rl, lane);
+  }
+}
+
+template <int LP, int WPT, int LT, int MODE>
+__global__ __launch_bounds__(256, 4) void gather_layer_kernel(const GatherParams p) {
+  extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+  using Sh = GatherShape<LP, WPT>;
+  constexpr int P = Sh::P, PS = Sh::PS, RC = Sh::RC, HV = Sh::HV, UNITS = Sh::UNITS, W = Sh::W;
+  static_assert(WPT == 1 || (WPT == 4 && P >= 4 && LT == 1), "shapes");
+  const int wave = (int)uniform(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (__builtin_expect((int)blockIdx.x < p.n_heavy_wg, 0)) {
+    heavy_rows<LP, LT, MODE>(p, lds, wave, lane);
+    return;
+  }
+  const unsigned b = xcd_deal(blockIdx.x - (unsigned)p.n_heavy_wg, p.run_shift);
+  if (b >= p.nblocks) return;                        // whole workgroup leaves together
+  const int ln = lane & 15, g = lane >> 4;
+  const int tile = WPT == 1 ? (int)b * 4 + wave : (int)b;
+  const int row0 = tile * 16, n_rows = min(p.rows - row0, 16);   // (none for a wave behind the last tile)
+  const int self = p.self_term, ldx = p.ldx, n_ks = p.n_ks;
+
+  // ---- lists: lane (row n of the tile, g) has the first block's entries g, 4 + g, 8 + g, 12 + g --------
+  // What lies past the last row reads as zeros: sums of column 0, which nobody stores.
+  const uint32_t here = (uint32_t)max(n_rows, 0);
+  const __amdgpu_buffer_rsrc_t r_first = uniform_rsrc(p.first + (int64_t)row0 * kListBlock, here * (kListBlock * 2)),
+                               r_deg = uniform_rsrc(p.deg + row0, here * 4);
+  const v2u t_idx = __builtin_amdgcn_raw_buffer_load_b64(r_first, ln * (kListBlock * 2) + 8 * g, 0, 0);
+  int t_n = (int)__builtin_amdgcn_raw_buffer_load_b32(r_deg, ln * 4, 0, 0);
+  int32_t rl = 0;
+  if (MODE == kGatherRows && p.up.mode == QGTC_OUT_F32 && p.up.row_l && ln < n_rows) rl = p.up.row_l[row0 + ln];
+  stage_weights<LT, MODE>(p, lds, wave, lane);
+  const bool out_ok = ln < n_rows && t_n <= kListLight;
+  if (t_n > kListLight) t_n = 0;                     // (heavy: what comes out is not stored, the row is written by others)
+  const uint32_t flip = p.split_y ? 0x80808080u : 0u;
+  // one group of output tiles: the codes of 256 columns at a time
+  const bool parts = HV > 1 && WPT == 1 && p.n_nt <= LT;
+  uint8_t* const yb = lds + (WPT == 1 ? wave * (parts ? 4 : n_ks) * 1024 : 0);   // the tile's codes
+  if (P < 4 && (lane & 3) >= P) *reinterpret_cast<v4u*>(yb + lane * 16) = (v4u){flip, flip, flip, flip};   // columns no lane has
+  if (WPT == 1) {                                    // waits for the weights here, and for nobody later
+    __syncthreads();
+    if (n_rows <= 0) return;
+  }
+
+  // ---- 1, 2: the tile's codes ---------------------------------------------------------------------
+  const v4i ident = adder(ln);
+  const Rq q = make_rq(p.agg_lo, p.agg_relu, p.agg_inv, p.agg_nbits);
+  const Neighbours nb(p, row0);
+  const __amdgpu_buffer_rsrc_t r_own = uniform_rsrc(p.X + (int64_t)row0 * ldx, here * (uint32_t)ldx);
+  constexpr int LR = LP < 4 ? LP : 4;
+  const uint32_t v_own = (uint32_t)((ln >> LR) * ldx + 16 * (ln & (PS - 1)) + 4 * g);
+  const int first_row = WPT == 1 ? 0 : wave * (16 / WPT);   // of the wave in the tile
+  const bool row_sums = p.split_w || (MODE == kGatherRows && p.want_rowsum);
+  v4i z[LT], rs = {0, 0, 0, 0};
+#pragma unroll
+  for (int j = 0; j < LT; ++j) z[j] = rs;
+#pragma unroll 1
+  for (int hv = 0; hv < HV; ++hv) {
+    const int piece = (ln & (PS - 1)) + 16 * hv;
+    if (HV > 1 && 256 * hv >= p.cols) break;         // (uniform)
+    const uint32_t pofs = nb.piece_offset(piece);
+#pragma unroll 1
+    for (int u0 = 0; u0 < UNITS; u0 += W) {
+      v2u idx[W];
+      int n[W], most = 0;
+      uint32_t own[W];
+#pragma unroll
+      for (int j = 0; j < W; ++j) {
+        const int row = first_row + (u0 + j) * RC + (ln >> LR);
+        if (RC == 16) {
+          idx[j] = t_idx;
+          n[j] = t_n;
+        } else {
+          idx[j].x = (uint32_t)__shfl((int)t_idx.x, row + 16 * g, 64);
+          idx[j].y = (uint32_t)__shfl((int)t_idx.y, row + 16 * g, 64);
+          n[j] = RC == 1 ? __builtin_amdgcn_readlane(t_n, row) : __shfl(t_n, row, 64);
+        }
+        most = max(most, n[j]);
+        own[j] = 0u;
+        if (self) own[j] = __builtin_amdgcn_raw_buffer_load_b32(r_own, v_own, (uint32_t)(first_row + (u0 + j) * RC) * (uint32_t)ldx + hv * 256u, 0);
+      }
+      // The first block in up to three steps, each with all of its loads in flight: wide rows are few
+      // neighbours of many bytes from HBM, narrow ones more neighbours from the caches.
+      constexpr int K1 = P >= 16 ? 1 : 2;            // 4 K1 entries of every row, then up to 8, then all 16
+      v4i acc[W], x[W][2];
+      const bool five = K1 == 1 && __builtin_amdgcn_ballot_w64(most > 4) != 0ull, nine = __builtin_amdgcn_ballot_w64(most > 8) != 0ull;
+#pragma unroll
+      for (int k = 0; k < K1; ++k)
+#pragma unroll
+        for (int j = 0; j < W; ++j) x[j][k] = nb.load(list_entry(idx[j], k), pofs);
+      if (five) {
+#pragma unroll
+        for (int j = 0; j < W; ++j) x[j][1] = nb.load(list_entry(idx[j], 1), pofs);
+      }
+      // (the own row, and 128 for every code that is code - 128)
+#pragma unroll
+      for (int j = 0; j < W; ++j) {
+        const int bias = p.x_offset * (n[j] + self);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[j][r] = bias + (int)(int8_t)(own[j] >> (8 * r));
+      }
+#pragma unroll
+      for (int k = 0; k < K1; ++k)
+#pragma unroll
+        for (int j = 0; j < W; ++j) acc[j] = mfma_i8(ident, x[j][k], acc[j]);
+      if (five) {
+#pragma unroll
+        for (int j = 0; j < W; ++j) acc[j] = mfma_i8(ident, x[j][1], acc[j]);
+      }
+      if (nine) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+#pragma unroll
+          for (int j = 0; j < W; ++j) x[j][k] = nb.load(list_entry(idx[j], 2 + k), pofs);
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+#pragma unroll
+          for (int j = 0; j < W; ++j) acc[j] = mfma_i8(ident, x[j][k], acc[j]);
+      }
+      // further blocks, a block's entries requested beside the products of the one in front
+      if (__builtin_amdgcn_ballot_w64(most > kListBlock) != 0ull) {
+        auto more = [&](int base) {
+#pragma unroll
+          for (int j = 0; j < W; ++j) {
+            idx[j] = (v2u){~0u, ~0u};
+            const int64_t row = row0 + first_row + (u0 + j) * RC + (ln >> LR);
+            if (n[j] > base) idx[j] = *reinterpret_cast<const v2u*>(p.rest + row * p.rest_cap + (base - kListBlock) + 4 * g);
+          }
+        };
+        more(kListBlock);
+#pragma unroll 1
+        for (int base = kListBlock; __builtin_amdgcn_ballot_w64(most > base) != 0ull; base += kListBlock) {
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+#pragma unroll
+              for (int j = 0; j < W; ++j) x[j][k] = nb.load(list_entry(idx[j], 2 * h + k), pofs);
+            if (h == 1) more(base + kListBlock);
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+#pragma unroll
+              for (int j = 0; j < W; ++j) acc[j] = mfma_i8(ident, x[j][k], acc[j]);
+          }
+#pragma unroll
+          for (int j = 0; j < W; ++j) settle(acc[j]);
+        }
+      }
+      uint32_t c[W][4], d[W];
+#pragma unroll
+      for (int j = 0; j < W; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) c[j][r] = (uint32_t)acc[j][r];
+      pack_codes_words(c, q, d);
+      const int at = parts ? piece & 15 : piece;
+      if (P <= 4 || piece < 4 * n_ks) {
+        uint8_t* const to = yb + (at >> 2) * 1024 + (at & 3) * 16 + 4 * g;
+#pragma unroll
+        for (int j = 0; j < W; ++j)
+          *reinterpret_cast<uint32_t*>(to + (first_row + (u0 + j) * RC + (ln >> LR)) * 64) = kept_codes(p, d[j], 16 * piece + 4 * g);
+      }
+    }
+    if (HV > 1 && parts) {
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the lanes read each other's codes
+      add_products<LT, MODE>(p, lds, yb, 4 * hv, min(4 * hv + 4, n_ks), 0, row_sums, z, rs, lane);
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
+  }
+
+  // ---- 3 --------------------------------------------------------------------------------------------
+  if (HV > 1 && parts) {
+    emit_tile<LT, MODE>(p, lds, row0, out_ok, 0, z, rs, rl, lane);
+    return;
+  }
+  if (WPT != 1) __syncthreads();
+  else __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  finish_tile<LT, MODE>(p, lds, yb, row0, out_ok, WPT == 1 ? 0 : wave, WPT == 1 ? LT : 4, rl, lane);
+}
+
+template <int LP, int WPT, int LT, int MODE>
+qgtc_status launch_one(const GatherParams& p, size_t lds, hipStream_t stream) {
+  static OncePerDevice once;
+  if (!allow_lds(once, reinterpret_cast<const void*>(&gather_layer_kernel<LP, WPT, LT, MODE>), lds)) return QGTC_ERR_HIP;
+  hipLaunchKernelGGL((gather_layer_kernel<LP, WPT, LT, MODE>), dim3((unsigned)p.n_heavy_wg + xcd_deal_grid(p.nblocks, p.run_shift)), dim3(256),
+                     lds, stream, p);
+  return launch_status();
+}
+
+template <int LP, int MODE>
+qgtc_status launch_pieces(const GatherParams& p, bool share, size_t lds, hipStream_t stream) {
+  if constexpr (LP >= 2) {
+    if (share) return launch_one<LP, 4, 1, MODE>(p, lds, stream);
+  }
+  return p.n_nt > 1 ? launch_one<LP, 1, 4, MODE>(p, lds, stream) : launch_one<LP, 1, 1, MODE>(p, lds, stream);
+}
+
+}  // namespace
+
+template <int MODE>
+qgtc_status gather_launch(const GatherParams& p, bool share, size_t lds, hipStream_t stream) {
+  const int pieces = p.ldx / 16;
+  if (pieces <= 1) return launch_pieces<0, MODE>(p, share, lds, stream);
+  if (pieces <= 2) return launch_pieces<1, MODE>(p, share, lds, stream);
+  if (pieces <= 4) return launch_pieces<2, MODE>(p, share, lds, stream);
+  if (pieces <= 8) return launch_pieces<3, MODE>(p, share, lds, stream);
+  if (pieces <= 16) return launch_pieces<4, MODE>(p, share, lds, stream);
+  if (pieces <= 32) return launch_pieces<5, MODE>(p, share, lds, stream);
+  return launch_pieces<6, MODE>(p, share, lds, stream);
+}
+
+}  // namespace qgtc

@@ -2,7 +2,7 @@
 // and the value sums of packed operands.  Eq. (2) and the 3D-stacked bit
 // compression of Section 4.2 of the paper, for gfx950.  All of these are
 // streaming kernels bound by HBM bandwidth.
-#include "qgtc_internal.h"
+#include "gather.h"
 
 namespace qgtc {
 namespace {
@@ -17,6 +17,7 @@ struct PackParams {
   float lo, inv;        // Eq. (2), fp32 sources only
   uint32_t qmax;
   float qmaxf;
+  uint32_t flip;        // QGTC_LEFT_BYTES: on every word (0x80808080: codes - 128)
 };
 
 template <int SRC> struct src_type { using type = uint32_t; };
@@ -234,7 +235,7 @@ __global__ __launch_bounds__(256) void pack_left_bytes_kernel(const PackParams p
     const int c = w * 4 + b;
     v |= (c < p.cols ? to_code<SRC>(p, raw[b]) : 0u) << (8 * b);
   }
-  p.dst[idx] = v;
+  p.dst[idx] = v ^ p.flip;
 }
 
 // The same where four columns are one 16-byte load (32-bit sources; cols and ld_src multiples
@@ -272,7 +273,7 @@ __global__ __launch_bounds__(256) void pack_left_bytes_wide_kernel(const PackPar
     uint32_t v = 0u;
 #pragma unroll
     for (int b = 0; b < 4; ++b) v |= to_code<SRC>(p, raw[k][b]) << (8 * b);
-    if (r < p.rows) p.dst[(int64_t)r * ld + w] = 4 * w < p.cols ? v : 0u;
+    if (r < p.rows) p.dst[(int64_t)r * ld + w] = (4 * w < p.cols ? v : 0u) ^ p.flip;
     r += step_r;
     w += step_w;
     if (w >= ld) { w -= ld; ++r; }
@@ -438,6 +439,26 @@ UnpackParams unpack_params(const qgtc_bits* m) {
 }
 
 }  // namespace
+
+qgtc_status pack_row_codes(const float* src, int64_t ld_src, int rows, int cols, const qgtc_quant* q, uint8_t* dst,
+                           hipStream_t stream) {
+  PackParams p{};
+  p.src = src;
+  p.ld_src = ld_src;
+  p.rows = rows;
+  p.cols = cols;
+  p.nbits = q->nbits;
+  p.dst = reinterpret_cast<uint32_t*>(dst);
+  p.ld = row_codes_ld(cols) / 4;
+  p.qmax = (1u << q->nbits) - 1u;
+  p.qmaxf = (float)p.qmax;
+  p.lo = (float)q->lo;
+  p.inv = qgtc_quant_inv_scale(q->lo, q->hi, q->nbits);
+  p.flip = row_codes_flip(q->nbits);
+  ProfScope prof(QGTC_KERNEL_PACK, stream);
+  return launch_pack<QGTC_SRC_F32>(p, QGTC_LEFT_BYTES, stream);
+}
+
 }  // namespace qgtc
 
 using namespace qgtc;

@@ -220,6 +220,29 @@ extern "C" qgtc_status qgtc_layer_epilogues(const qgtc_layer_spec* sp, qgtc_epil
   return QGTC_OK;
 }
 
+// Lists against whole tiles, by the times of a layer (us, rows x D -> H, bits per row of A, columns K of A)
+// on uniform subgraphs.  65536 rows, lists and tiles: 64 -> 64, K 1024, 6 bits 12.6 and 16.0, 24 bits 18.0
+// and 15.8; K 256, 6 bits 12.4 and 11.0; K 2048, 24 bits 18.9 and 23.5; 256 -> 64, K 1024, 12 bits 25.0 and
+// 29.5, 24 bits 32.1 and 29.5; 16 -> 16, K 1024, 24 bits 7.5 and 9.9.  8192 rows, K 1024, 24 bits: 64 -> 64
+// 5.5 and 9.4.  512 -> 16 on 262144 rows of a power-law graph 85 and 159.  The formulas below are fits to
+// these; from a mean of 40 bits on rows of more than 64, which cost a workgroup each, become frequent.
+extern "C" int32_t qgtc_neighbours_pay(const qgtc_bits* A, int64_t bits, const int32_t* widths, int32_t n_layers) {
+  if (!A || !widths || n_layers < 1 || A->rows < 1 || bits < 0 || qgtc_neighbours_bytes(A) == 0) return 0;
+  const double deg = (double)bits / (double)A->rows, share = (double)A->rows / 65536.0;
+  if (deg > 40.0) return 0;
+  // without blocks the tile map leaves out most of a row
+  const double k = A->block_rows > 0 || A->cols < 1024 ? (double)A->cols : 1024.0;
+  double lists = 0.0, tiles = 0.0;
+  for (int32_t l = 0; l < n_layers; ++l) {
+    const double d = (double)widths[l], h = (double)widths[l + 1], root = std::sqrt(d);
+    const double many = 1.0 + 0.75 * root + 0.06 * h + 0.04 * root * deg, few = 3.7;
+    const double tmany = 5.4 + 0.026 * d + 0.03 * h + (0.0035 + 0.0000535 * d) * k, tfew = 5.7 + 0.003 * k;
+    lists += few + share * std::fmax(many - few, 0.0);
+    tiles += tfew + share * std::fmax(tmany - tfew, 0.0);
+  }
+  return lists < tiles ? 1 : 0;
+}
+
 extern "C" qgtc_status qgtc_fold_batchnorm(const double* gamma, const double* beta, const double* mean,
                                            const double* var, double eps, double value_scale, int32_t n,
                                            float* col_scale, float* col_shift) {

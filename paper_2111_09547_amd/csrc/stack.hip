@@ -1,6 +1,7 @@
 // A stack of layers with its activations kept as codes in operand order (layer.h): the
 // quantizer writes the first layer's, every hidden layer the next one's, so that staging X
 // is a plain copy and no bit plane is formed or put back together between the layers.
+#include "gather.h"
 #include "layer.h"
 
 #include <cmath>
@@ -157,6 +158,52 @@ static qgtc_status layer_codes(const qgtc_bits* A, const qgtc_tile_map* map, con
   return layer_run(&p, layer_split(A->rows, x_cols, W->cols, A->ld_words), X == nullptr, W, upd_ep, stream);
 }
 
+// The same over neighbour lists: row-major codes in; out_codes, or out, out.
+static qgtc_status layer_lists(const qgtc_bits* A, const qgtc_neighbours* nb, const uint8_t* x_codes, int s, const qgtc_stack_layer& y,
+                               uint8_t* out_codes, void* out, int64_t ld_out, hipStream_t stream) {
+  GatherParams p{};
+  p.X = x_codes;
+  p.first = nb->first;
+  p.rest = nb->rest;
+  p.deg = nb->deg;
+  p.heavy = nb->heavy;
+  p.heavy_cnt = nb->heavy_cnt;
+  p.n_groups = cdiv(A->rows, kListGroup);
+  p.A = A->data;
+  p.lda = A->ld_words;
+  p.a_words = 4 * cdiv(A->cols, 128);
+  p.rest_cap = nb->rest_cap;
+  p.rows = A->rows;
+  p.block = A->block_rows > 0 ? A->block_rows : A->rows;
+  p.block_magic = div_magic(p.block);
+  p.n_tiles = cdiv(p.rows, 16);
+  p.cols = y.W.rows;
+  p.ldx = (int32_t)row_codes_ld(p.cols);
+  p.self_term = y.first.self_term ? 1 : 0;
+  p.agg_lo = y.first.rq_lo;
+  p.agg_relu = y.first.relu ? 1 : 0;
+  p.agg_nbits = y.first.rq_nbits;
+  p.agg_inv = y.first.rq_inv_scale;
+  if (out_codes) {
+    EpiParams& u = p.up;
+    u.mode = QGTC_OUT_BITS;
+    u.relu = y.second.relu ? 1 : 0;
+    u.rq_nbits = y.second.rq_nbits;
+    u.rq_lo = y.second.rq_lo;
+    u.rq_inv_scale = y.second.rq_inv_scale;
+    u.col_a = y.second.col_scale;
+    u.col_b = y.second.col_shift;
+    u.out = out_codes;
+    u.ld_out = row_codes_ld(y.W.cols);
+    p.out_flip = (int32_t)row_codes_flip(u.rq_nbits);
+  } else {
+    const qgtc_status st = make_epilogue(&y.second, out, ld_out, A->rows, y.W.cols, QGTC_RIGHT, false, &p.up);
+    if (st != QGTC_OK) return st;
+  }
+  p.x_offset = s == 8 ? 128 : 0;
+  return gather_layer(&p, !out_codes ? kGatherRows : (p.up.col_a ? kGatherAffine : kGatherCodes), &y.W, stream);
+}
+
 }  // namespace qgtc
 
 using namespace qgtc;
@@ -167,15 +214,28 @@ extern "C" size_t qgtc_stack_buffer_bytes(int32_t rows, int32_t cols) {
   return (size_t)cdiv(cols, 16 * ct) * (size_t)codes_cg_bytes(rows, ct);
 }
 
-extern "C" qgtc_status qgtc_stack_input(const float* src, int32_t rows, int32_t cols, int64_t ld_src, const qgtc_quant* q,
-                                        void* buffer, size_t buffer_bytes, void* stream) {
+static qgtc_status check_input(const float* src, int32_t rows, int32_t cols, int64_t ld_src, const qgtc_quant* q, const void* buffer,
+                               size_t buffer_bytes) {
   if (!src || !q || !buffer) return QGTC_ERR_NULL;
   if (rows < 0 || cols < 0 || ld_src < cols || !(q->hi > q->lo)) return QGTC_ERR_SHAPE;
   if (q->nbits < 1 || q->nbits > 8) return QGTC_ERR_BITWIDTH;
   if (((uintptr_t)buffer & 15u) != 0) return QGTC_ERR_ALIGN;
   if (buffer_bytes < qgtc_stack_buffer_bytes(rows, cols)) return QGTC_ERR_WORKSPACE;
-  if (rows == 0 || cols == 0) return QGTC_OK;
+  return QGTC_OK;
+}
+
+extern "C" qgtc_status qgtc_stack_input(const float* src, int32_t rows, int32_t cols, int64_t ld_src, const qgtc_quant* q,
+                                        void* buffer, size_t buffer_bytes, void* stream) {
+  const qgtc_status st = check_input(src, rows, cols, ld_src, q, buffer, buffer_bytes);
+  if (st != QGTC_OK || rows == 0 || cols == 0) return st;
   return pack_codes(src, ld_src, rows, cols, q, reinterpret_cast<uint8_t*>(buffer), reinterpret_cast<hipStream_t>(stream));
+}
+
+extern "C" qgtc_status qgtc_stack_input_rows(const float* src, int32_t rows, int32_t cols, int64_t ld_src, const qgtc_quant* q,
+                                             void* buffer, size_t buffer_bytes, void* stream) {
+  const qgtc_status st = check_input(src, rows, cols, ld_src, q, buffer, buffer_bytes);
+  if (st != QGTC_OK || rows == 0 || cols == 0) return st;
+  return pack_row_codes(src, ld_src, rows, cols, q, reinterpret_cast<uint8_t*>(buffer), reinterpret_cast<hipStream_t>(stream));
 }
 
 extern "C" qgtc_status qgtc_stack_forward(const qgtc_stack* st, const float* src, int64_t ld_src, const qgtc_quant* q,
@@ -228,13 +288,29 @@ extern "C" qgtc_status qgtc_stack_forward(const qgtc_stack* st, const float* src
     rc = agg_fill_params(st->A, st->map, X, &a);
     if (rc != QGTC_OK) return rc;
   }
+  if (st->lists && rows > 0) {
+    rc = check_neighbours(st->lists, st->A);
+    if (rc != QGTC_OK) return rc;
+  }
   if (src) {
     if (q && q->nbits != st->s) return QGTC_ERR_BITWIDTH;
-    rc = qgtc_stack_input(src, rows, d0, ld_src, q, st->buffer[0], st->buffer_bytes, stream);
+    rc = (st->lists ? qgtc_stack_input_rows : qgtc_stack_input)(src, rows, d0, ld_src, q, st->buffer[0], st->buffer_bytes, stream);
     if (rc != QGTC_OK) return rc;
   }
   if (rows == 0) return QGTC_OK;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+  if (st->lists) {
+    uint8_t* const codes[2] = {reinterpret_cast<uint8_t*>(st->buffer[0]), reinterpret_cast<uint8_t*>(st->buffer[1])};
+    if (X) {
+      rc = planes_to_rows(X, codes[0], s);
+      if (rc != QGTC_OK) return rc;
+    }
+    for (int l = 0; l < st->n_layers; ++l) {
+      rc = layer_lists(st->A, st->lists, codes[l & 1], st->s, st->layers[l], l == st->n_layers - 1 ? nullptr : codes[(l + 1) & 1], out, ld_out, s);
+      if (rc != QGTC_OK) return rc;
+    }
+    return QGTC_OK;
+  }
   for (int l = 0; l < st->n_layers; ++l) {
     const qgtc_stack_layer& y = st->layers[l];
     const bool last = l == st->n_layers - 1;

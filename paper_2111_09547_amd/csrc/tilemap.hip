@@ -344,6 +344,19 @@ extern "C" qgtc_status qgtc_build_tile_map(const qgtc_bits* A, const qgtc_tile_m
   return QGTC_OK;
 }
 
+extern "C" qgtc_status qgtc_tile_map_total(const qgtc_tile_map* map, void* stream) {
+  if (!map || !map->row_cnt || !map->nnz_tiles) return QGTC_ERR_NULL;
+  if (map->n_tile_rows < 0) return QGTC_ERR_SHAPE;
+  MapParams p{};
+  p.n_tile_rows = map->n_tile_rows;
+  p.row_cnt = map->row_cnt;
+  p.nnz = map->nnz_tiles;
+  hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+  ProfScope prof(QGTC_KERNEL_TILE_MAP, s);
+  hipLaunchKernelGGL(tile_total_kernel, dim3(1), dim3(256), 0, s, p);
+  return launch_status();
+}
+
 extern "C" qgtc_status qgtc_tile_stats(const qgtc_bits* A, int32_t* counts, void* stream) {
   if (!A || !counts) return QGTC_ERR_NULL;
   qgtc_status st = check_adjacency(A);

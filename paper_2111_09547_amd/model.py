@@ -71,7 +71,7 @@ class QuantGNN:
     def __init__(self, A_src, Ws, s: int, t: int, self_term: bool,
                  tile_kbits: int | str = 128, use_map: bool = True, block_rows: int = 0,
                  weights_as_bytes: bool = True, update_first: bool = False, batchnorm=None,
-                 tuning: "B.Tuning | None" = None):
+                 tuning: "B.Tuning | None" = None, lists: bool | None = None):
         self.s, self.t = s, t
         self.tuning = tuning           # per-call speed choices handed to qgtc_layer (None: the library's)
         # batchnorm: per layer None or a BatchNorm; it is folded into the layer's output
@@ -138,6 +138,15 @@ class QuantGNN:
         if self._fused:
             nbytes = max(B.lib().qgtc_stack_buffer_bytes(n, d) for d, _ in self.dims)
             self._codes = [torch.empty(max(nbytes // 4, 4), dtype=torch.int32, device=self.A.words.device) for _ in range(2)]
+        # Neighbour lists in place of products with whole tiles of A where they pay (lists=None; the bits of A
+        # are counted once), or as the caller says.  The results are the same.
+        self.lists = None
+        if self._fused and lists is not False and (lists or self.plan is not None) and B.neighbours_bytes(self.A) > 0:
+            if self.plan is None and self.A_src is not None:
+                B.qgtc_pack_bits(self.A_src, 1, B.LEFT, out=self.A)
+            built = B.qgtc_build_neighbours(self.A)
+            if lists or B.qgtc_neighbours_pay(self.A, int(built.deg.sum(dtype=torch.int64)), self.dims):
+                self.lists, self._lists_of = built, self.A
         if update_first:                 # activations between layers as left operands of the update
             self.xl_bufs = [B.alloc_bits(n, max(dmax, hmax), s, B.LEFT) for _ in range(2)]
         self.pack_static()
@@ -166,13 +175,18 @@ class QuantGNN:
             if X is not None and not self.update_first:
                 if self._fused and X.dtype == torch.float32:
                     assert tuple(X.shape) == (self.A.rows, self.dims[0][0])
-                    B.qgtc_stack_input(X, self.s, x_range, self._codes[0])
-                    self._x_form = "codes"
+                    self._pack_codes(X, x_range)
                 else:
                     self.pack_input(X, x_range)
         if self.A_src is not None:
             B.qgtc_pack_bits(self.A_src, 1, B.LEFT, out=self.A)
-        if self.use_map:
+        if self.lists is not None:
+            if self.use_map and self.map is None:
+                self.map = B._alloc_tile_map(self.A, 16, self.tile_kbits)
+            B.qgtc_build_neighbours(self.A, self.lists, self.map)
+            self._lists_of = self.A
+            self.deg = self.map.deg if self.use_map else self.lists.deg
+        elif self.use_map:
             self.map = B.qgtc_build_tile_map(self.A, 16, self.tile_kbits, out=self.map)
             self.deg = self.map.deg
         else:
@@ -180,6 +194,10 @@ class QuantGNN:
         cur.wait_stream(self._w_stream)
 
     # -- helpers -----------------------------------------------------------------
+    def _pack_codes(self, X, x_range):
+        B.qgtc_stack_input(X, self.s, x_range, self._codes[0], rows_form=self.lists is not None)
+        self._x_form = "codes"
+
     def _alloc_planes(self):
         return [B.alloc_bits(self.A.rows, self._wmax, self.s, B.RIGHT) for _ in range(2)]
 
@@ -391,8 +409,7 @@ class QuantGNN:
             ep.col_scale, ep.col_shift = ca, cb
             xb = B.qgtc_update(yb, W, ep, out=planes((l + 1) & 1, self.dims[l][1]))
         if planes != self._x_view:               # the features are left packed, as codes
-            B.qgtc_stack_input(X, self.s, x_range, self._codes[0])
-            self._x_form = "codes"
+            self._pack_codes(X, x_range)
         return ranges
 
     # -- forward ---------------------------------------------------------------------
@@ -538,12 +555,15 @@ class QuantGNN:
         """The prepared native call for these ranges (a caller's handful of them is kept).  An entry
         holds on to the operands that its key names, so that none of them can be another one by now."""
         key = (float(x_range[0]), float(x_range[1]), bool(want_int), tuple(vars(self.tuning).values()) if self.tuning else None, *self.w_ranges,
-               self.self_term, id(self.A), id(self.map), self.deg.data_ptr(), *map(id, self.W), *map(id, self.batchnorm),
+               self.self_term, id(self.A), id(self.map), id(self.lists), self.deg.data_ptr(), *map(id, self.W), *map(id, self.batchnorm),
                *[(r.agg_hi, r.out_hi) for r in ranges])
+        if self.lists is not None and self._lists_of is not self.A:      # (replaced, and not packed since)
+            B.qgtc_build_neighbours(self.A, self.lists)
+            self._lists_of = self.A
         stack = self._stacks.get(key)
         if stack is None:
             layers = [(W, first, second) for W, (first, second) in zip(self.W, self._epilogues(x_range, ranges, want_int))]
-            stack = B.Stack(self.A, self.map, layers, self.s, self._codes)
+            stack = B.Stack(self.A, self.map, layers, self.s, self._codes, self.lists)
             if len(self._stacks) >= 8:
                 self._stacks.pop(next(iter(self._stacks)), None)
             self._stacks[key] = stack

@@ -371,3 +371,29 @@ def test_missing_library_fails_loudly(monkeypatch, tmp_path):
     monkeypatch.setattr(b, "lib_path", lambda: str(tmp_path / "nope.so"))
     with pytest.raises(ImportError):
         b.lib()
+
+
+def test_neighbour_lists_on_the_host():
+    import paper_2111_09547_amd.binding as b
+    l = b.lib()
+    size = lambda n, block=0: l.qgtc_neighbours_bytes(C.byref(_fake_bits(b, n, block or n, 1, b.LEFT, block_rows=block)))
+    assert size(100) == 400 + 16 + 16 + 100 * (16 + 96) * 2
+    assert size(4096, 32) == 4096 * 4 + 64 * 8 + 64 + 4096 * 32 * 2 and size(65534) > 0 and size(65535) == 0 and size(1 << 20, 65536) == 0
+    assert l.qgtc_neighbours_bytes(C.byref(_fake_bits(b, 64, 100, 1, b.LEFT))) == 0      # neither square nor in blocks
+    A, n = _fake_bits(b, 4096, 64, 1, b.LEFT, block_rows=64), b._NeighboursC()
+    carve, build = l.qgtc_neighbours_carve, l.qgtc_build_neighbours
+    assert carve(None, 0x10000, C.byref(A)) == 1 and carve(C.byref(n), None, C.byref(A)) == 1 and carve(C.byref(n), 0x10008, C.byref(A)) == 4
+    assert carve(C.byref(n), 0x10000, C.byref(A)) == 0 and n.rest - n.first == 4096 * 32
+    assert build(None, C.byref(n), None, None) == 1 and build(C.byref(A), None, None, None) == 1
+    other = _fake_bits(b, 4096, 96, 1, b.LEFT, block_rows=96)
+    assert build(C.byref(other), C.byref(n), None, None) == 2
+    m = b._TileMapC()
+    assert build(C.byref(A), C.byref(n), C.byref(m), None) == 1
+    assert l.qgtc_tile_map_carve(C.byref(m), 0x40000, 4096, 64, 8, 128) == 0 and build(C.byref(A), C.byref(n), C.byref(m), None) == 7
+    assert l.qgtc_tile_map_carve(C.byref(m), 0x40000, 4090, 64, 16, 128) == 0 and m.n_tile_rows == 256
+    assert l.qgtc_tile_map_carve(C.byref(m), 0x40000, 4000, 64, 16, 128) == 0 and build(C.byref(A), C.byref(n), C.byref(m), None) == 2
+    # sparse graphs take them, dense ones do not
+    pay = lambda rows, block, deg, *widths: b.qgtc_neighbours_pay(
+        type("A", (), {"c": _fake_bits(b, rows, block or rows, 1, b.LEFT, block_rows=block)}), int(rows * deg), list(zip(widths[:-1], widths[1:])))
+    assert pay(65536, 1024, 8, 128, 64, 64) and pay(262144, 2048, 3.3, 512, 16, 16) and pay(8192, 0, 10, 64, 64)
+    assert not pay(65536, 256, 24, 64, 64) and not pay(65536, 1024, 100, 64, 64) and not pay(70000, 0, 3, 64, 64)

@@ -1,0 +1,140 @@
+"""Neighbour lists: what they hold, and layers over them against the oracle and against whole tiles."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import qgnn
+from test_gpu_stack import block_graph
+
+pytestmark = pytest.mark.gpu
+
+q = pytest.importorskip("paper_2111_09547_amd")
+import paper_2111_09547_amd.binding as B  # noqa: E402
+from paper_2111_09547_amd.model import QuantGNN  # noqa: E402
+from gpu_util import dev, as_u32  # noqa: E402
+
+
+def with_degrees(rng, n, k, degrees):
+    """uint8 [n, k]: row i has degrees[i % len] bits."""
+    a = np.zeros((n, k), np.uint8)
+    for i in range(n):
+        d = min(degrees[i % len(degrees)], k)
+        a[i, rng.choice(k, d, replace=False)] = 1
+    return a
+
+
+@pytest.mark.parametrize("n,k,block", [(100, 100, 0), (700, 700, 0), (3 * 96 - 5, 96, 96), (2 * 1056 - 500, 1056, 1056)])
+@pytest.mark.parametrize("kbits", [32, 64, 128])
+def test_lists_and_the_map_of_one_pass(n, k, block, kbits):
+    rng = np.random.default_rng(n)
+    a = with_degrees(rng, n, k, [0, 1, 16, 17, 32, 64, 65, 255, 256, 257, 5, 700])
+    if block:
+        a[n // block * block:, n % block:] = 0
+    A = q.qgtc_pack_bits(dev(a), 1, q.LEFT, block_rows=block)
+    tmap = B._alloc_tile_map(A, 16, kbits)
+    nb = B.qgtc_build_neighbours(A, tmap=tmap)
+    ref = q.qgtc_build_tile_map(A, 16, kbits)
+    deg = a.sum(1).astype(np.int64)
+    assert (nb.deg.cpu().numpy() == deg).all() and torch.equal(tmap.deg, ref.deg) and torch.equal(tmap.row_cnt, ref.row_cnt)
+    assert torch.equal(tmap.nnz_tiles, ref.nnz_tiles)
+    kept = torch.arange(ref.c.n_tile_cols, device="cuda")[None] < ref.row_cnt[:, None]
+    assert torch.equal(torch.where(kept, tmap.col_idx, 0), torch.where(kept, ref.col_idx, 0))
+    host = nb.buffer.cpu().numpy().view(np.uint16)
+    at = lambda ptr: (ptr - nb.buffer.data_ptr()) // 2
+    first, rest, cap = at(nb.c.first), at(nb.c.rest), nb.c.rest_cap
+    for i in range(n):
+        got = np.concatenate([host[first + 16 * i:first + 16 * i + 16], host[rest + cap * i:rest + cap * (i + 1)]])
+        have = min(deg[i], 256)
+        got = got[:max(-(-have // 16), 1) * 16]      # whole blocks
+        entries = np.sort(got[got != 0xffff])
+        assert len(entries) == have and (np.isin(entries, np.nonzero(a[i])[0])).all() and len(np.unique(entries)) == have
+        e = np.arange(len(got))                      # entry e at 4 (e % 4) + e / 4 of its block
+        order = got[e // 16 * 16 + 4 * (e % 4) + e // 4 % 4]
+        assert (order[:have] != 0xffff).all() and (order[have:] == 0xffff).all()
+
+
+@pytest.mark.parametrize("blocks,block,short,dims,s,t,gin", [
+    (3, 64, 5, "1-2", 1, 1, True),                   # a piece of one column
+    (5, 96, 31, "17-33-16", 5, 3, False),            # two pieces, of which one column
+    (3, 160, 33, "64-65-47", 8, 8, True),            # whole groups of columns and one more
+    (2, 1024, 1, "130-129-7", 8, 4, False),          # sixteen pieces, seven of them empty
+    (2, 512, 0, "256-200-64", 7, 8, True),
+    (2, 300 // 32 * 32, 3, "300-101-5", 8, 8, False),  # two parts of 256 columns
+    (1, 640, 40, "1024-256-16", 8, 8, True),         # four parts, more weights than LDS keeps
+    (130, 256, 77, "64-64-12", 8, 8, True),          # a tile per wave: one, four and more output tiles
+    (130, 256, 0, "300-16-100", 8, 8, False),
+    (33, 1024, 9, "513-64", 6, 6, True),
+    (40, 1024, 0, "16-16-32", 8, 8, True),
+])
+@pytest.mark.parametrize("degree", [2.0, 20.0])
+def test_layers_over_lists_equal_the_oracle(blocks, block, short, dims, s, t, gin, degree):
+    rng = np.random.default_rng(blocks + block + s)
+    d = [int(v) for v in dims.split("-")]
+    a, csr = block_graph(rng, blocks, block, short, degree)
+    n = a.shape[0]
+    hubs = [0, n // 2, n - 1]                        # more neighbours than a tile's waves take, and than a list holds
+    csr = csr.tolil()
+    for r, want in zip(hubs, (65, 256, 700)):
+        r0 = r // block * block
+        cols = rng.choice(min(block, n - r0), min(want, block, n - r0), replace=False)
+        a[r, cols] = 1
+        csr[r, r0 + cols] = 1
+    csr = csr.tocsr()
+    X = rng.standard_normal((n, d[0])).astype(np.float32)
+    Ws = [rng.uniform(-0.5, 0.5, dh).astype(np.float32) for dh in zip(d[:-1], d[1:])]
+    make = lambda lists: QuantGNN(dev(a), [dev(W) for W in Ws], s, t, gin, block_rows=block, lists=lists)
+    net, tiles = make(True), make(False)
+    assert net.lists is not None and tiles.lists is None
+    xr, x = (float(X.min()), float(X.max())), dev(X)
+    ranges = tiles.calibrate(x, xr)
+    assert net.calibrate(x, xr) == ranges
+    rqs = [((0, qgnn.inv_scale(0.0, float(r.agg_hi), s)),
+            None if r.out_hi is None else (0, qgnn.inv_scale(0.0, float(r.out_hi), s))) for r in ranges]
+    wr = [(float(W.min()), float(W.max())) for W in Ws]
+    _, trace, _ = qgnn.forward_dequantized(csr, X, xr, Ws, wr, s, t, gin, rqs=rqs)
+    assert (as_u32(net.forward(x, xr, ranges, want_int=True)) == trace[-1]["Z"]).all()
+    out = tiles.forward(x, xr, ranges)
+    assert torch.equal(net.forward(x, xr, ranges), out)
+    planes = q.qgtc_pack_bits(x, s, q.RIGHT, quant=xr)
+    assert torch.equal(net.forward(None, xr, ranges, x_bits=planes), out)
+    net.pack_static(x, xr)
+    assert torch.equal(net.forward(x, xr, ranges, x_packed=True), out)
+
+
+def test_rows_that_are_all_hubs():
+    """Every row has more neighbours than a list holds, without blocks, and negative requantization bounds."""
+    rng = np.random.default_rng(3)
+    n, dims = 900, [40, 48, 9]
+    a = (rng.random((n, n), dtype=np.float32) < 0.4).astype(np.uint8)
+    x = dev(rng.standard_normal((n, dims[0])).astype(np.float32))
+    Ws = [dev(rng.uniform(-0.5, 0.5, dh).astype(np.float32)) for dh in zip(dims[:-1], dims[1:])]
+    nets = [QuantGNN(dev(a), Ws, 8, 8, True, lists=lists) for lists in (True, False)]
+    ranges = nets[1].calibrate(x, (-3.0, 3.0))
+    outs = [net.forward(x, (-3.0, 3.0), ranges) for net in nets]
+    assert torch.equal(outs[0], outs[1])
+    graph = nets[0].capture(x, (-3.0, 3.0), ranges, outs[0], with_static=True)
+    for _ in range(3):
+        outs[0].zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(outs[0], outs[1])
+
+
+def test_lists_follow_the_adjacency():
+    """pack_static() of another adjacency, and one that was replaced without it."""
+    rng = np.random.default_rng(5)
+    graphs = [block_graph(rng, 3, 96, 0, deg)[0] for deg in (4.0, 30.0)]
+    W = dev(rng.uniform(-1, 1, (20, 9)).astype(np.float32))
+    x = dev(rng.standard_normal((288, 20)).astype(np.float32))
+    net, other = (QuantGNN(dev(g), [W], 4, 4, False, block_rows=96, lists=True) for g in graphs)
+    ranges = other.calibrate(x, (-3.0, 3.0))
+    want = QuantGNN(dev(graphs[1]), [W], 4, 4, False, block_rows=96, lists=False).forward(x, (-3.0, 3.0), ranges, want_int=True)
+    net.forward(x, (-3.0, 3.0), ranges, want_int=True)
+    first = net.A
+    net.A_src.copy_(dev(graphs[1]))
+    net.pack_static()
+    assert torch.equal(net.forward(x, (-3.0, 3.0), ranges, want_int=True), want)
+    net.A_src.copy_(dev(graphs[0]))
+    net.pack_static()
+    net.A = other.A
+    assert net.A is not first and torch.equal(net.forward(x, (-3.0, 3.0), ranges, want_int=True), want)
