@@ -458,6 +458,12 @@ qgtc_status qgtc_stack_input_rows(const float* src, int32_t rows, int32_t cols, 
 qgtc_status qgtc_stack_forward(const qgtc_stack* stack, const float* src, int64_t ld_src,
                                const qgtc_quant* q, const qgtc_bits* X, void* out, int64_t ld_out,
                                void* stream);
+/* The same in the other order, A.(X.W) per layer (Section 6.1), over neighbour lists: first is the epilogue
+ * of X.W (QGTC_OUT_BITS, s bits), second that of the aggregation (which has the self term); features are
+ * fp32 rows, quantized beside the first product.  buffer[2]: qgtc_stack_buffer_bytes(rows, columns) of
+ * every layer's output.  The same integers as qgtc_pack_bits, qgtc_update and qgtc_aggregate per layer. */
+qgtc_status qgtc_stack_forward_update_first(const qgtc_stack* stack, const float* src, int64_t ld_src,
+                                            const qgtc_quant* q, void* out, int64_t ld_out, void* stream);
 
 /* ---------------------------------------------------------------------------
  * Non-zero tiles of A at the three tile widths qgtc_aggregate takes, in one pass over

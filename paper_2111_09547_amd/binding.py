@@ -155,6 +155,7 @@ def lib():
         "qgtc_stack_input": (C.c_int, [vp, i32, i32, i64, P(_QuantC), vp, sz, vp]),
         "qgtc_stack_input_rows": (C.c_int, [vp, i32, i32, i64, P(_QuantC), vp, sz, vp]),
         "qgtc_stack_forward": (C.c_int, [P(_StackC), vp, i64, P(_QuantC), P(_BitsC), vp, i64, vp]),
+        "qgtc_stack_forward_update_first": (C.c_int, [P(_StackC), vp, i64, P(_QuantC), vp, i64, vp]),
         "qgtc_tile_stats": (C.c_int, [P(_BitsC), vp, vp]),
         "qgtc_plan_layer": (C.c_int, [P(_PlanInC), P(_PlanOutC)]),
         "qgtc_quant_inv_scale": (C.c_float, [C.c_double, C.c_double, i32]),
@@ -524,6 +525,16 @@ def qgtc_stack_forward(stack: Stack, out: torch.Tensor, src: torch.Tensor | None
     _, out_ptr, ld_out = _out_arg(stack.last, stack.rows, stack.out_cols, out, RIGHT, out.device)
     _check(lib().qgtc_stack_forward(C.byref(stack.c), ptr, ld, q, C.byref(X.c) if X is not None else None, out_ptr, ld_out,
                                     _stream()), "qgtc_stack_forward")
+
+
+def qgtc_stack_forward_update_first(stack: Stack, out: torch.Tensor, src: torch.Tensor, quant):
+    """One pass of fp32 features in the order A.(X.W)."""
+    assert src.dim() == 2 and src.dtype == torch.float32 and src.is_cuda and src.stride(1) == 1
+    assert tuple(src.shape) == (stack.rows, stack.in_cols)
+    q = _QuantC(float(quant[0]), float(quant[1]), stack.c.s)
+    _, out_ptr, ld_out = _out_arg(stack.last, stack.rows, stack.out_cols, out, RIGHT, out.device)
+    _check(lib().qgtc_stack_forward_update_first(C.byref(stack.c), src.data_ptr(), src.stride(0) if src.shape[0] > 1 else max(src.shape[1], 1),
+                                                 C.byref(q), out_ptr, ld_out, _stream()), "qgtc_stack_forward_update_first")
 
 
 LAYER_FUSED, LAYER_TWO_KERNELS = 0, 1

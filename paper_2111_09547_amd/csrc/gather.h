@@ -42,15 +42,30 @@ struct GatherParams {
 };
 
 // What a layer emits.
-enum { kGatherCodes = 0, kGatherAffine = 1, kGatherRows = 2 };   // codes; behind an affine map; fp32 or int32
+enum { kGatherCodes = 0, kGatherAffine = 1, kGatherRows = 2,     // codes; behind an affine map; fp32 or int32;
+       kGatherSums = 3 };                                        // the sums themselves as fp32 or int32, no second product
 
 // The instances for one kind of output; share: four waves share a tile, else each has one.
 template <int MODE>
 qgtc_status gather_launch(const GatherParams& p, bool share, size_t lds, hipStream_t stream);
 
+// The product of fp32 features, quantized on the way, with weights: first_product.hip.
+struct FirstParams {
+  GatherParams g;            // rows, cols, weights, epilogue (codes)
+  const float* src;
+  int64_t ld_src;
+  float lo, inv, qmaxf;
+};
+qgtc_status first_product(FirstParams* p, const qgtc_bits* W, hipStream_t stream);
+
+// What GatherParams says about the weights.
+void gather_weights(GatherParams* p, const qgtc_bits* W);
+
 // One layer: p has its operands and epilogues (up.out, up.ld_out: the codes' rows in bytes where
 // codes are emitted); W: RIGHT_BYTES.
 qgtc_status gather_layer(GatherParams* p, int mode, const qgtc_bits* W, hipStream_t stream);
+// The aggregation by itself, fp32 or int32 out.
+qgtc_status gather_sums(GatherParams* p, hipStream_t stream);
 
 // Rows of codes between the layers of a stack over lists: whole pieces of 16 bytes, code - 128 for
 // eight bits (what is past the last column is not used).

@@ -61,40 +61,32 @@ qgtc_status planes_to_rows(const qgtc_bits* X, uint8_t* dst, hipStream_t stream)
   return launch_status();
 }
 
-qgtc_status gather_layer(GatherParams* gp, int mode, const qgtc_bits* W, hipStream_t stream) {
-  GatherParams& p = *gp;
-  p.wb = reinterpret_cast<const uint8_t*>(W->data);
-  p.wb_part = W->plane_stride_words * 4;
-  p.h = W->cols;
-  p.n_nt = cdiv(W->cols, 16);
-  p.n_ks = cdiv(W->rows, 64);
-  p.split_y = p.agg_nbits == 8;
-  p.split_w = W->nbits == 8;
-  if (p.up.l0b == 0.0) p.up.row_l = nullptr;
-  p.want_rowsum = p.up.mode == QGTC_OUT_F32 && p.up.row_i == nullptr && p.up.rs != 0.0;
-  // A tile per wave where that gives every compute unit eight waves (65536 rows, 64 -> 64: 8.8 us, with four waves
-  // per tile 11.3; 8192 rows have half a wave per SIMD that way).
-  const int cus = device_compute_units();
-  const bool share = p.ldx > 32 && p.n_tiles < 8 * cus;
-  const int tiles = share ? 1 : 4;
-  const int n_ntp = share || p.n_nt == 1 ? p.n_nt : (p.n_nt + 3) / 4 * 4;
+void gather_weights(GatherParams* p, const qgtc_bits* W) {
+  p->wb = reinterpret_cast<const uint8_t*>(W->data);
+  p->wb_part = W->plane_stride_words * 4;
+  p->h = W->cols;
+  p->n_nt = cdiv(W->cols, 16);
+  p->n_ks = cdiv(W->rows, 64);
+  p->split_y = p->agg_nbits == 8;
+  p->split_w = W->nbits == 8;
+}
+
+namespace {
+
+// A tile per wave where that gives every compute unit eight waves (65536 rows, 64 -> 64: 8.8 us, with four waves
+// per tile 11.3; 8192 rows have half a wave per SIMD that way).
+bool four_waves_share(const GatherParams& p) { return p.ldx > 32 && p.n_tiles < 8 * device_compute_units(); }
+
+int pieces_of(const GatherParams& p) {
   int pieces = 1;
   while (16 * pieces < p.ldx) pieces <<= 1;
-  // The codes of a tile: of 256 columns at a time where one group of output tiles is all.  Heavy rows,
-  // one at a time, need those of all columns, their counts, the row that is taken and its sums.
-  const bool parts = pieces > 16 && !share && p.n_nt <= (p.n_nt == 1 ? 1 : 4);
-  size_t lds = (size_t)tiles * (parts ? 4 : p.n_ks) * 1024;
-  const size_t one = (size_t)p.n_ks * 1024, heavy = one + 2048 + 64 + (size_t)pieces * 64;
-  p.heavy_off = (int)one;
-  if (lds < heavy) lds = heavy;
-  lds = (lds + 63) & ~(size_t)63;
-  p.cols_off = (int)lds;
-  lds += (size_t)n_ntp * (64 + 128);
-  p.w_off = -1;
-  if (p.n_ks * n_ntp <= 48) {
-    p.w_off = (int)lds;
-    lds += (size_t)p.n_ks * n_ntp * 1024;
-  }
+  return pieces;
+}
+size_t heavy_bytes(const GatherParams& p) { return 2048 + 64 + (size_t)pieces_of(p) * 64; }   // counts, the row that is taken, its sums
+
+void set_grid(GatherParams* gp, int tiles) {
+  GatherParams& p = *gp;
+  const int cus = device_compute_units();
   p.nblocks = (uint32_t)cdiv(p.n_tiles, tiles);
   // workgroups that read the same rows of X stay on one XCD, as far as every XCD still gets a run
   int64_t run = cdiv(cdiv(p.block, 16), tiles);
@@ -104,12 +96,47 @@ qgtc_status gather_layer(GatherParams* gp, int mode, const qgtc_bits* W, hipStre
   // 1543 of them in 262144 rows, 16 -> 16: 256 workgroups 29.9, 512 19.2, 1024 15.4 us; without any, 64 -> 64 on 65536
   // rows, 8.8, 8.8 and 9.6.
   p.n_heavy_wg = p.block > kListLight ? (p.n_groups < 2 * cus ? (p.n_groups + 7) / 8 * 8 : 2 * cus / 8 * 8) : 0;
+}
+
+}  // namespace
+
+qgtc_status gather_layer(GatherParams* gp, int mode, const qgtc_bits* W, hipStream_t stream) {
+  GatherParams& p = *gp;
+  gather_weights(gp, W);
+  if (p.up.l0b == 0.0) p.up.row_l = nullptr;
+  p.want_rowsum = p.up.mode == QGTC_OUT_F32 && p.up.row_i == nullptr && p.up.rs != 0.0;
+  const bool share = four_waves_share(p);
+  const int tiles = share ? 1 : 4;
+  const int n_ntp = share || p.n_nt == 1 ? p.n_nt : (p.n_nt + 3) / 4 * 4;
+  // The codes of a tile: of 256 columns at a time where one group of output tiles is all.  Heavy rows,
+  // one at a time, need those of all columns.
+  const bool parts = pieces_of(p) > 16 && !share && p.n_nt <= (p.n_nt == 1 ? 1 : 4);
+  size_t lds = (size_t)tiles * (parts ? 4 : p.n_ks) * 1024;
+  const size_t one = (size_t)p.n_ks * 1024;
+  p.heavy_off = (int)one;
+  if (lds < one + heavy_bytes(p)) lds = one + heavy_bytes(p);
+  lds = (lds + 63) & ~(size_t)63;
+  p.cols_off = (int)lds;
+  lds += (size_t)n_ntp * (64 + 128);
+  p.w_off = -1;
+  if (p.n_ks * n_ntp <= 48) {
+    p.w_off = (int)lds;
+    lds += (size_t)p.n_ks * n_ntp * 1024;
+  }
+  set_grid(gp, tiles);
   ProfScope prof(QGTC_KERNEL_LAYER, stream);
   switch (mode) {
     case kGatherCodes: return gather_launch<kGatherCodes>(p, share, lds, stream);
     case kGatherAffine: return gather_launch<kGatherAffine>(p, share, lds, stream);
     default: return gather_launch<kGatherRows>(p, share, lds, stream);
   }
+}
+
+qgtc_status gather_sums(GatherParams* gp, hipStream_t stream) {
+  const bool share = four_waves_share(*gp);
+  set_grid(gp, share ? 1 : 4);
+  ProfScope prof(QGTC_KERNEL_AGGREGATE, stream);
+  return gather_launch<kGatherSums>(*gp, share, heavy_bytes(*gp), stream);
 }
 
 }  // namespace qgtc

@@ -158,9 +158,8 @@ static qgtc_status layer_codes(const qgtc_bits* A, const qgtc_tile_map* map, con
   return layer_run(&p, layer_split(A->rows, x_cols, W->cols, A->ld_words), X == nullptr, W, upd_ep, stream);
 }
 
-// The same over neighbour lists: row-major codes in; out_codes, or out, out.
-static qgtc_status layer_lists(const qgtc_bits* A, const qgtc_neighbours* nb, const uint8_t* x_codes, int s, const qgtc_stack_layer& y,
-                               uint8_t* out_codes, void* out, int64_t ld_out, hipStream_t stream) {
+// The operands of an aggregation over neighbour lists: row-major codes of x_cols columns, s bits.
+static GatherParams list_operands(const qgtc_bits* A, const qgtc_neighbours* nb, const uint8_t* x_codes, int x_cols, int s) {
   GatherParams p{};
   p.X = x_codes;
   p.first = nb->first;
@@ -177,31 +176,45 @@ static qgtc_status layer_lists(const qgtc_bits* A, const qgtc_neighbours* nb, co
   p.block = A->block_rows > 0 ? A->block_rows : A->rows;
   p.block_magic = div_magic(p.block);
   p.n_tiles = cdiv(p.rows, 16);
-  p.cols = y.W.rows;
-  p.ldx = (int32_t)row_codes_ld(p.cols);
-  p.self_term = y.first.self_term ? 1 : 0;
-  p.agg_lo = y.first.rq_lo;
-  p.agg_relu = y.first.relu ? 1 : 0;
-  p.agg_nbits = y.first.rq_nbits;
-  p.agg_inv = y.first.rq_inv_scale;
+  p.cols = x_cols;
+  p.ldx = (int32_t)row_codes_ld(x_cols);
+  p.x_offset = s == 8 ? 128 : 0;
+  return p;
+}
+
+// Row-major codes as the output of a product of `cols` columns.
+static void codes_out(GatherParams* p, const qgtc_epilogue& ep, int cols, uint8_t* out) {
+  EpiParams& u = p->up;
+  u.mode = QGTC_OUT_BITS;
+  u.relu = ep.relu ? 1 : 0;
+  u.rq_nbits = ep.rq_nbits;
+  u.rq_lo = ep.rq_lo;
+  u.rq_inv_scale = ep.rq_inv_scale;
+  u.col_a = ep.col_scale;
+  u.col_b = ep.col_shift;
+  u.out = out;
+  u.ld_out = row_codes_ld(cols);
+  p->out_flip = (int32_t)row_codes_flip(ep.rq_nbits);
+}
+
+// A layer over neighbour lists: row-major codes in; agg: epilogue of the aggregation, upd: of the product
+// with W; out_codes, or out, out.
+static qgtc_status layer_lists(const qgtc_bits* A, const qgtc_neighbours* nb, const uint8_t* x_codes, int s, const qgtc_epilogue& agg,
+                               const qgtc_bits* W, const qgtc_epilogue& upd, uint8_t* out_codes, void* out, int64_t ld_out,
+                               hipStream_t stream) {
+  GatherParams p = list_operands(A, nb, x_codes, W->rows, s);
+  p.self_term = agg.self_term ? 1 : 0;
+  p.agg_lo = agg.rq_lo;
+  p.agg_relu = agg.relu ? 1 : 0;
+  p.agg_nbits = agg.rq_nbits;
+  p.agg_inv = agg.rq_inv_scale;
   if (out_codes) {
-    EpiParams& u = p.up;
-    u.mode = QGTC_OUT_BITS;
-    u.relu = y.second.relu ? 1 : 0;
-    u.rq_nbits = y.second.rq_nbits;
-    u.rq_lo = y.second.rq_lo;
-    u.rq_inv_scale = y.second.rq_inv_scale;
-    u.col_a = y.second.col_scale;
-    u.col_b = y.second.col_shift;
-    u.out = out_codes;
-    u.ld_out = row_codes_ld(y.W.cols);
-    p.out_flip = (int32_t)row_codes_flip(u.rq_nbits);
+    codes_out(&p, upd, W->cols, out_codes);
   } else {
-    const qgtc_status st = make_epilogue(&y.second, out, ld_out, A->rows, y.W.cols, QGTC_RIGHT, false, &p.up);
+    const qgtc_status st = make_epilogue(&upd, out, ld_out, A->rows, W->cols, QGTC_RIGHT, false, &p.up);
     if (st != QGTC_OK) return st;
   }
-  p.x_offset = s == 8 ? 128 : 0;
-  return gather_layer(&p, !out_codes ? kGatherRows : (p.up.col_a ? kGatherAffine : kGatherCodes), &y.W, stream);
+  return gather_layer(&p, !out_codes ? kGatherRows : (p.up.col_a ? kGatherAffine : kGatherCodes), W, stream);
 }
 
 }  // namespace qgtc
@@ -306,7 +319,9 @@ extern "C" qgtc_status qgtc_stack_forward(const qgtc_stack* st, const float* src
       if (rc != QGTC_OK) return rc;
     }
     for (int l = 0; l < st->n_layers; ++l) {
-      rc = layer_lists(st->A, st->lists, codes[l & 1], st->s, st->layers[l], l == st->n_layers - 1 ? nullptr : codes[(l + 1) & 1], out, ld_out, s);
+      const qgtc_stack_layer& y = st->layers[l];
+      rc = layer_lists(st->A, st->lists, codes[l & 1], st->s, y.first, &y.W, y.second, l == st->n_layers - 1 ? nullptr : codes[(l + 1) & 1],
+                       out, ld_out, s);
       if (rc != QGTC_OK) return rc;
     }
     return QGTC_OK;
@@ -320,4 +335,63 @@ extern "C" qgtc_status qgtc_stack_forward(const qgtc_stack* st, const float* src
     if (rc != QGTC_OK) return rc;
   }
   return QGTC_OK;
+}
+
+extern "C" qgtc_status qgtc_stack_forward_update_first(const qgtc_stack* st, const float* src, int64_t ld_src, const qgtc_quant* q,
+                                                       void* out, int64_t ld_out, void* stream) {
+  if (!st || !st->A || !st->layers || !st->lists || !st->buffer[0] || !st->buffer[1] || !src || !q) return QGTC_ERR_NULL;
+  if (st->n_layers < 1) return QGTC_ERR_SHAPE;
+  qgtc_status rc = check_adjacency(st->A);
+  if (rc != QGTC_OK) return rc;
+  const int rows = st->A->rows, d0 = st->layers[0].W.rows;
+  if (st->A->block_rows == 0 && st->A->cols != rows) return QGTC_ERR_SHAPE;
+  if ((((uintptr_t)st->buffer[0] | (uintptr_t)st->buffer[1]) & 15u) != 0) return QGTC_ERR_ALIGN;
+  if (q->nbits != st->s) return QGTC_ERR_BITWIDTH;
+  if (ld_src < d0 || !(q->hi > q->lo)) return QGTC_ERR_SHAPE;
+  auto scale_ok = [](float v) { return v > 0.0f && v < INFINITY; };
+  for (int l = 0; l < st->n_layers; ++l) {
+    const qgtc_stack_layer& y = st->layers[l];
+    const bool last = l == st->n_layers - 1;
+    rc = check_bits(&y.W, QGTC_RIGHT_BYTES);
+    if (rc != QGTC_OK) return rc;
+    if (l > 0 && y.W.rows != st->layers[l - 1].W.cols) return QGTC_ERR_SHAPE;
+    if (!plan_fused_applies(y.W.rows, y.W.cols, st->s, y.W.nbits)) return QGTC_ERR_UNSUPPORTED;
+    if (y.first.mode != QGTC_OUT_BITS || (last ? y.second.mode == QGTC_OUT_BITS : y.second.mode != QGTC_OUT_BITS))
+      return QGTC_ERR_UNSUPPORTED;
+    if (y.first.self_term) return QGTC_ERR_SHAPE;
+    if (y.first.col_scale || y.first.col_shift || (!last && (y.second.col_scale || y.second.col_shift))) return QGTC_ERR_UNSUPPORTED;
+    if (y.first.rq_nbits != st->s || (!last && y.second.rq_nbits != st->s)) return QGTC_ERR_BITWIDTH;
+    if (!scale_ok(y.first.rq_inv_scale) || (!last && !scale_ok(y.second.rq_inv_scale))) return QGTC_ERR_SHAPE;
+    rc = check_tuning(y.second.tuning);
+    if (rc != QGTC_OK) return rc;
+    if (st->buffer_bytes < qgtc_stack_buffer_bytes(rows, y.W.cols)) return QGTC_ERR_WORKSPACE;
+  }
+  if (rows == 0) return QGTC_OK;
+  if (!out) return QGTC_ERR_NULL;
+  rc = check_neighbours(st->lists, st->A);
+  if (rc != QGTC_OK) return rc;
+  const qgtc_stack_layer& end = st->layers[st->n_layers - 1];
+  uint8_t* const codes[2] = {reinterpret_cast<uint8_t*>(st->buffer[0]), reinterpret_cast<uint8_t*>(st->buffer[1])};
+  hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+  GatherParams sums = list_operands(st->A, st->lists, codes[(st->n_layers - 1) & 1], end.W.cols, st->s);
+  sums.self_term = end.second.self_term ? 1 : 0;
+  rc = make_epilogue(&end.second, out, ld_out, rows, end.W.cols, QGTC_LEFT, true, &sums.up);
+  if (rc != QGTC_OK) return rc;
+
+  FirstParams fp{};
+  fp.src = src;
+  fp.ld_src = ld_src;
+  fp.lo = (float)q->lo;
+  fp.inv = qgtc_quant_inv_scale(q->lo, q->hi, q->nbits);
+  fp.qmaxf = (float)((1u << q->nbits) - 1u);
+  fp.g.rows = rows;
+  fp.g.n_tiles = cdiv(rows, 16);
+  fp.g.cols = d0;
+  fp.g.agg_nbits = st->s;
+  codes_out(&fp.g, st->layers[0].first, st->layers[0].W.cols, codes[0]);
+  rc = first_product(&fp, &st->layers[0].W, s);
+  for (int l = 0; rc == QGTC_OK && l + 1 < st->n_layers; ++l)
+    rc = layer_lists(st->A, st->lists, codes[l & 1], st->s, st->layers[l].second, &st->layers[l + 1].W, st->layers[l + 1].first,
+                     codes[(l + 1) & 1], nullptr, 0, s);
+  return rc == QGTC_OK ? gather_sums(&sums, s) : rc;
 }

@@ -141,12 +141,20 @@ class QuantGNN:
         # Neighbour lists in place of products with whole tiles of A where they pay (lists=None; the bits of A
         # are counted once), or as the caller says.  The results are the same.
         self.lists = None
-        if self._fused and lists is not False and (lists or self.plan is not None) and B.neighbours_bytes(self.A) > 0:
+        whole = self._fused or (update_first and all(fused_layer_applies(d, h, s, t) for d, h in self.dims) and
+                                (self.tuning is None or self.tuning.layer_path == B.LAYER_FUSED))
+        if whole and lists is not False and (lists or self.plan is not None) and B.neighbours_bytes(self.A) > 0:
             if self.plan is None and self.A_src is not None:
                 B.qgtc_pack_bits(self.A_src, 1, B.LEFT, out=self.A)
             built = B.qgtc_build_neighbours(self.A)
-            if lists or B.qgtc_neighbours_pay(self.A, int(built.deg.sum(dtype=torch.int64)), self.dims):
+            # (update first aggregates the outputs of each layer, and the last one has no further product)
+            dims = [(h, h) for _, h in self.dims] if update_first else self.dims
+            if lists or B.qgtc_neighbours_pay(self.A, int(built.deg.sum(dtype=torch.int64)), dims):
                 self.lists, self._lists_of = built, self.A
+        if update_first and self.lists is not None:
+            nbytes = max(B.lib().qgtc_stack_buffer_bytes(n, h) for _, h in self.dims)
+            self._codes = [torch.empty(max(nbytes // 4, 4), dtype=torch.int32, device=self.A.words.device) for _ in range(2)]
+            self._W_bytes = [B.alloc_bits(d, h, t, B.RIGHT_BYTES) for d, h in self.dims]
         if update_first:                 # activations between layers as left operands of the update
             self.xl_bufs = [B.alloc_bits(n, max(dmax, hmax), s, B.LEFT) for _ in range(2)]
         self.pack_static()
@@ -170,6 +178,9 @@ class QuantGNN:
         with torch.cuda.stream(self._w_stream):
             for W, r, dst, lay in zip(self.Ws, self.w_ranges, self.W, self.w_layout):
                 B.qgtc_pack_bits(W, self.t, lay, quant=r, out=dst)
+            if self.update_first and self.lists is not None:
+                for W, r, dst in zip(self.Ws, self.w_ranges, self._W_bytes):
+                    B.qgtc_pack_bits(W, self.t, B.RIGHT_BYTES, quant=r, out=dst)
             # only the last layer dequantizes, so only its column sums are needed
             self.w_colsum = [None] * (len(self.W) - 1) + [B.qgtc_col_sums(self.W[-1], out=self._w_colsum_buf)]
             if X is not None and not self.update_first:
@@ -435,6 +446,9 @@ class QuantGNN:
             out = torch.empty((n, self.dims[-1][1]), dtype=torch.int32 if want_int else torch.float32,
                               device=self.A.words.device)
         if self.update_first:
+            if self.lists is not None and X.dtype == torch.float32:
+                B.qgtc_stack_forward_update_first(self._stack(x_range, ranges, want_int), out, X, x_range)
+                return out
             return self._forward_update_first(X, x_range, ranges, out, want_int)
         # (planes of another width than the network's go layer by layer: their first layer is another one)
         if self._fused and (x_bits.nbits == self.s if x_bits is not None else x_packed or X.dtype == torch.float32):
@@ -562,7 +576,8 @@ class QuantGNN:
             self._lists_of = self.A
         stack = self._stacks.get(key)
         if stack is None:
-            layers = [(W, first, second) for W, (first, second) in zip(self.W, self._epilogues(x_range, ranges, want_int))]
+            Ws = self._W_bytes if self.update_first else self.W
+            layers = [(W, first, second) for W, (first, second) in zip(Ws, self._epilogues(x_range, ranges, want_int))]
             stack = B.Stack(self.A, self.map, layers, self.s, self._codes, self.lists)
             if len(self._stacks) >= 8:
                 self._stacks.pop(next(iter(self._stacks)), None)
@@ -572,13 +587,17 @@ class QuantGNN:
     def _epilogues(self, x_range, ranges, want_int):
         """(first, second) epilogue of every layer.  The first layer's codes stand for x_lo +
         x_scale * code; behind a hidden layer they are read as pure scales (x_lo = 0)."""
-        x_lo = float(x_range[0])
+        x_lo = 0.0 if self.update_first else float(x_range[0])
         x_scale = (float(x_range[1]) - float(x_range[0])) / float(2 ** self.s)
         out = []
         for l, r in enumerate(ranges):
             last = l == len(self.W) - 1
             first, second, z_scale, x_next = self._layer_eps(l, x_lo, x_scale, r.agg_hi, r.out_hi, last)
-            if not last:
+            if self.update_first:                    # codes read as pure scales throughout
+                x_scale = x_next
+                if last and want_int:
+                    second = B.Epilogue(mode=B.OUT_I32, self_term=self.self_term)
+            elif not last:
                 if self.batchnorm[l] is not None:
                     second.col_scale, second.col_shift = self._bn_fold(l, z_scale)
                 x_lo, x_scale = 0.0, x_next

@@ -59,7 +59,7 @@ def test_lists_and_the_map_of_one_pass(n, k, block, kbits):
     (3, 160, 33, "64-65-47", 8, 8, True),            # whole groups of columns and one more
     (2, 1024, 1, "130-129-7", 8, 4, False),          # sixteen pieces, seven of them empty
     (2, 512, 0, "256-200-64", 7, 8, True),
-    (2, 300 // 32 * 32, 3, "300-101-5", 8, 8, False),  # two parts of 256 columns
+    (2, 288, 3, "300-101-5", 8, 8, False),  # two parts of 256 columns
     (1, 640, 40, "1024-256-16", 8, 8, True),         # four parts, more weights than LDS keeps
     (130, 256, 77, "64-64-12", 8, 8, True),          # a tile per wave: one, four and more output tiles
     (130, 256, 0, "300-16-100", 8, 8, False),
@@ -138,3 +138,36 @@ def test_lists_follow_the_adjacency():
     net.pack_static()
     net.A = other.A
     assert net.A is not first and torch.equal(net.forward(x, (-3.0, 3.0), ranges, want_int=True), want)
+
+
+@pytest.mark.parametrize("blocks,block,short,dims,s,t,gin", [
+    (3, 96, 5, "12-16-5", 8, 8, True),               # a quarter of a wave per row, one output tile
+    (3, 96, 5, "13-40-70", 3, 5, False),             # rows that are no multiple of 16 bytes, several tiles, two groups of them
+    (2, 288, 31, "128-64-16", 8, 4, True),           # half a wave per row
+    (2, 288, 0, "129-16-200", 5, 8, False),
+    (140, 256, 77, "260-16-16", 8, 8, True),         # two parts of 256 columns, a tile per wave in every kernel
+    (1, 672, 0, "1024-200-3", 7, 8, False),   # four parts, more output tiles than one group
+])
+def test_update_first_over_lists(blocks, block, short, dims, s, t, gin):
+    rng = np.random.default_rng(blocks + block + s)
+    d = [int(v) for v in dims.split("-")]
+    a, _ = block_graph(rng, blocks, block, short, 6.0)
+    a[:: max(1, a.shape[0] // 5), : min(block, 70)] = 1   # some heavy rows
+    n = a.shape[0]
+    if short:
+        a[(blocks - 1) * block:, block - short:] = 0
+    Ws = [dev(rng.uniform(-0.5, 0.5, dh).astype(np.float32)) for dh in zip(d[:-1], d[1:])]
+    x = dev(rng.standard_normal((n, d[0])).astype(np.float32))
+    x[0, 0], x[1, 1], x[n - 1, d[0] - 1] = float("nan"), float("inf"), -float("inf")
+    nets = [QuantGNN(dev(a), Ws, s, t, gin, block_rows=block, update_first=True, lists=lists) for lists in (True, False)]
+    assert nets[0].lists is not None and nets[1].lists is None
+    xr = (-3.0, 3.0)
+    ranges = nets[1].calibrate(x, xr)
+    assert nets[0].calibrate(x, xr) == ranges
+    wide = torch.full((n, d[0] + 3), float("nan"), device="cuda")
+    wide[:, 1:1 + d[0]] = x
+    for ints in (True, False):
+        want = nets[1].forward(x, xr, ranges, want_int=ints)
+        assert int((want != 0).sum()) > 0
+        assert torch.equal(nets[0].forward(x, xr, ranges, want_int=ints), want)
+        assert torch.equal(nets[0].forward(wide[:, 1:1 + d[0]], xr, ranges, want_int=ints), want)
