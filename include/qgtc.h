@@ -149,6 +149,16 @@ qgtc_status qgtc_pack_bits(const void* src, int32_t src_dtype, int32_t rows,
 qgtc_status qgtc_pack_bits_host(const void* src, int32_t src_dtype, int32_t rows,
                                 int32_t cols, int64_t ld_src, const qgtc_quant* q,
                                 const qgtc_bits* dst, int32_t threads);
+
+/* Up to two operands (the adjacency and the features of a batch) packed by the same threads. */
+typedef struct qgtc_host_operand {
+  const void* src;
+  int32_t src_dtype, rows, cols, reserved;
+  int64_t ld_src;
+  const qgtc_quant* q;                /* as qgtc_pack_bits_host's */
+  const qgtc_bits* dst;
+} qgtc_host_operand;
+qgtc_status qgtc_pack_batch_host(const qgtc_host_operand* ops, int32_t n, int32_t threads);
 /* Places n objects of bytes[i] bytes one after the other in one buffer, each at a
  * multiple of 256 bytes: writes their offsets and returns the size of the buffer
  * (the "compound memory object" of Section 4.6: allocate it once in pinned host

@@ -101,6 +101,11 @@ class _LayerSpecC(C.Structure):
                 ("out_hi", C.c_double)]
 
 
+class _HostOperandC(C.Structure):
+    _fields_ = [("src", C.c_void_p), ("src_dtype", C.c_int32), ("rows", C.c_int32), ("cols", C.c_int32), ("reserved", C.c_int32),
+                ("ld_src", C.c_int64), ("q", C.POINTER(_QuantC)), ("dst", C.POINTER(_BitsC))]
+
+
 class _DeviceC(C.Structure):
     _fields_ = [("compute_units", C.c_int32), ("xcds", C.c_int32), ("is_gfx950", C.c_int32),
                 ("xcds_assumed", C.c_int32)]
@@ -132,6 +137,7 @@ def lib():
         "qgtc_pack_bits": (C.c_int, [vp, i32, i32, i32, i64, P(_QuantC), P(_BitsC), vp]),
         "qgtc_unpack_bits": (C.c_int, [P(_BitsC), vp, i64, vp]),
         "qgtc_pack_bits_host": (C.c_int, [vp, i32, i32, i32, i64, P(_QuantC), P(_BitsC), i32]),
+        "qgtc_pack_batch_host": (C.c_int, [P(_HostOperandC), i32, i32]),
         "qgtc_compound_layout": (sz, [P(sz), i32, P(sz)]),
         "qgtc_row_sums": (C.c_int, [P(_BitsC), vp, vp]),
         "qgtc_col_sums": (C.c_int, [P(_BitsC), vp, vp]),

@@ -1,7 +1,7 @@
 """Bandwidth-optimized subgraph packing (Section 4.6 of the paper): a batch is packed to
 bit planes on the host - adjacency and node features side by side in one pinned buffer -
 and crosses to the GPU in one copy of low-bit data.  Argument set-up only: the packing is
-qgtc_pack_bits_host in the library, the copy is one asynchronous memcpy on the current
+qgtc_pack_batch_host in the library, the copy is one asynchronous memcpy on the current
 stream."""
 from __future__ import annotations
 
@@ -55,15 +55,13 @@ class SubgraphPacket:
         assert tuple(A.shape) == (self.rows, self.a_cols) and tuple(X.shape) == (self.rows, self.x_cols)
         a_bits, x_bits = self.host_bits()
         dt = {torch.float32: B.SRC_F32, torch.uint8: B.SRC_U8, torch.int32: B.SRC_I32}
-        B._check(B.lib().qgtc_pack_bits_host(C.c_void_p(A.data_ptr()), dt[A.dtype], self.rows, self.a_cols,
-                                             A.stride(0), None, C.byref(a_bits.c), threads),
-                 "qgtc_pack_bits_host")
         q = None
         if x_range is not None:
-            q = C.byref(B._QuantC(float(x_range[0]), float(x_range[1]), self.s))
-        B._check(B.lib().qgtc_pack_bits_host(C.c_void_p(X.data_ptr()), dt[X.dtype], self.rows, self.x_cols,
-                                             X.stride(0), q, C.byref(x_bits.c), threads),
-                 "qgtc_pack_bits_host")
+            q = C.pointer(B._QuantC(float(x_range[0]), float(x_range[1]), self.s))
+        ops = (B._HostOperandC * 2)(
+            B._HostOperandC(A.data_ptr(), dt[A.dtype], self.rows, self.a_cols, 0, A.stride(0), None, C.pointer(a_bits.c)),
+            B._HostOperandC(X.data_ptr(), dt[X.dtype], self.rows, self.x_cols, 0, X.stride(0), q, C.pointer(x_bits.c)))
+        B._check(B.lib().qgtc_pack_batch_host(ops, 2, threads), "qgtc_pack_batch_host")
 
     def upload(self):
         """One copy of the whole buffer on the current stream; (A, X) descriptors into the

@@ -132,3 +132,44 @@ def test_subgraph_packet_on_the_host():
         for kw in range(n // 32):
             o = pk.offsets[1] // 4 + p * xb.c.plane_stride_words + kw * xb.c.ld_words
             assert (host[o:o + dcols] == wx[p, kw]).all()
+
+
+@pytest.mark.parametrize("cols", [15, 16, 33, 64])
+@pytest.mark.parametrize("bits", [1, 3, 8])
+def test_host_quantizer_sixteen_columns_at_a_time(bits, cols):
+    """Whole groups of 16 columns and the rest, rows that end inside a word, a source with a row stride,
+    values that are no ordinary numbers."""
+    b = _b()
+    rng = np.random.default_rng([57, bits, cols])
+    wide = rng.normal(size=(71, cols + 5)).astype(np.float32)
+    x = wide[:, 2:2 + cols]
+    x[0, 0], x[31, cols - 1], x[32, 1], x[70, 7], x[5, 3] = np.nan, np.inf, -np.inf, -0.0, np.float32(3e38)
+    lo, hi = -2.5, 3.0
+    ordinary = np.where(np.isfinite(x), x, np.where(x > 0, 4.0, -4.0)).astype(np.float32)   # (a NaN: code 0)
+    want = qgnn.quantize(ordinary, lo, hi, bits)
+    got, _, _, _ = host_pack(b, x, bits, b.RIGHT, quant=(lo, hi), threads=2)
+    assert (got == bp.pack(want, bits, bp.RIGHT)).all()
+
+
+def test_two_operands_by_the_same_threads():
+    b = _b()
+    rng = np.random.default_rng(58)
+    a = (rng.random((700, 96)) < 0.3).astype(np.uint8)
+    x = rng.normal(size=(700, 40)).astype(np.float32)
+    fn = b.lib().qgtc_pack_batch_host
+    q = b._QuantC(-3.0, 3.0, 8)
+    def operand(src, dtype, nbits, lay, quant=None, block_rows=0):
+        d, words = b.describe(*src.shape, nbits, lay, block_rows)
+        buf = np.zeros(words + 4, np.uint32)
+        d.data = buf.ctypes.data + (-buf.ctypes.data % 16)
+        return b._HostOperandC(src.ctypes.data, dtype, *src.shape, 0, src.shape[1], C.pointer(quant) if quant is not None else None, C.pointer(d)), d, buf
+    oa, da, ba = operand(a, b.SRC_U8, 1, b.LEFT, block_rows=96)
+    ox, dx, bx = operand(x, b.SRC_F32, 8, b.RIGHT, quant=q)
+    assert fn((b._HostOperandC * 2)(oa, ox), 2, 5) == 0
+    off = (da.data - ba.ctypes.data) // 4
+    assert (ba[off:off + 700 * 4].reshape(700, 4)[:, :3] == bp.pack(a.astype(np.uint32), 1, bp.LEFT)[0]).all()
+    off = (dx.data - bx.ctypes.data) // 4
+    assert (bx[off:off + 8 * 22 * 40].reshape(8, 22, 40) == bp.pack(qgnn.quantize(x, -3.0, 3.0, 8), 8, bp.RIGHT)).all()
+    assert fn(None, 2, 1) == 1 and fn((b._HostOperandC * 1)(oa), 0, 1) == 2 and fn((b._HostOperandC * 2)(oa, ox), 2, -1) == 2
+    bad = b._HostOperandC(x.ctypes.data, b.SRC_F32, 700, 40, 0, 39, C.pointer(q), C.pointer(dx))
+    assert fn((b._HostOperandC * 2)(oa, bad), 2, 1) == 2
