@@ -166,6 +166,18 @@ qgtc_status qgtc_pack_batch_host(const qgtc_host_operand* ops, int32_t n, int32_
  * features into it, pack on the host, copy once).  Host-only. */
 size_t qgtc_compound_layout(const size_t* bytes, int32_t n, size_t* offsets);
 
+/* The weights of the layers of a stack in one launch: ws[i].src (fp32, ld_src floats per row) by Eq. (2) into
+ * ws[i].dst (QGTC_RIGHT_BYTES), as qgtc_pack_bits of each; col_sums (device, or NULL with sums_of < 0) gets the
+ * column sums of the codes of ws[sums_of], as qgtc_col_sums. */
+typedef struct qgtc_weight_source {
+  const float* src;
+  int64_t ld_src;
+  qgtc_quant q;
+  const qgtc_bits* dst;
+} qgtc_weight_source;
+qgtc_status qgtc_pack_weights(const qgtc_weight_source* ws, int32_t n, int32_t sums_of, int32_t* col_sums,
+                              void* stream);
+
 /* Decode a packed matrix (any layout) back to one uint32 per entry
  * ("Tensor.to_val", Section 5).  dst: device, row-major rows x cols, leading
  * dimension ld_dst. */

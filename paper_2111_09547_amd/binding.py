@@ -106,6 +106,10 @@ class _HostOperandC(C.Structure):
                 ("ld_src", C.c_int64), ("q", C.POINTER(_QuantC)), ("dst", C.POINTER(_BitsC))]
 
 
+class _WeightSourceC(C.Structure):
+    _fields_ = [("src", C.c_void_p), ("ld_src", C.c_int64), ("q", _QuantC), ("dst", C.POINTER(_BitsC))]
+
+
 class _DeviceC(C.Structure):
     _fields_ = [("compute_units", C.c_int32), ("xcds", C.c_int32), ("is_gfx950", C.c_int32),
                 ("xcds_assumed", C.c_int32)]
@@ -135,6 +139,7 @@ def lib():
         "qgtc_version": (i32, []),
         "qgtc_describe": (sz, [P(_BitsC), i32, i32, i32, i32, i32]),
         "qgtc_pack_bits": (C.c_int, [vp, i32, i32, i32, i64, P(_QuantC), P(_BitsC), vp]),
+        "qgtc_pack_weights": (C.c_int, [P(_WeightSourceC), i32, i32, vp, vp]),
         "qgtc_unpack_bits": (C.c_int, [P(_BitsC), vp, i64, vp]),
         "qgtc_pack_bits_host": (C.c_int, [vp, i32, i32, i32, i64, P(_QuantC), P(_BitsC), i32]),
         "qgtc_pack_batch_host": (C.c_int, [P(_HostOperandC), i32, i32]),
@@ -349,6 +354,24 @@ def qgtc_pack_bits(src: torch.Tensor, nbits: int, layout: int, quant=None,
     _check(lib().qgtc_pack_bits(C.c_void_p(src.data_ptr()), dt, rows, cols, ld_src, q,
                                 C.byref(dst.c), _stream()), "qgtc_pack_bits")
     return dst
+
+
+class WeightSources:
+    """The weights of a stack (contiguous fp32 device tensors, their ranges and RIGHT_BYTES operands) as
+    qgtc_pack_weights takes them."""
+
+    def __init__(self, Ws, ranges, outs):
+        assert all(W.dim() == 2 and W.dtype == torch.float32 and W.is_cuda and W.is_contiguous() for W in Ws)
+        assert all(tuple(W.shape) == (o.rows, o.cols) for W, o in zip(Ws, outs))
+        self.keep = (list(Ws), list(outs))
+        self.c = (_WeightSourceC * len(outs))(*[
+            _WeightSourceC(W.data_ptr(), W.shape[1], _QuantC(float(r[0]), float(r[1]), o.nbits), C.pointer(o.c))
+            for W, r, o in zip(Ws, ranges, outs)])
+
+
+def qgtc_pack_weights(sources: WeightSources, sums_of: int = -1, col_sums: torch.Tensor | None = None):
+    _check(lib().qgtc_pack_weights(sources.c, len(sources.c), sums_of, col_sums.data_ptr() if col_sums is not None else None, _stream()),
+           "qgtc_pack_weights")
 
 
 def qgtc_unpack_bits(bits: Bits) -> torch.Tensor:

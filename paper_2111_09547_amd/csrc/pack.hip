@@ -185,8 +185,7 @@ __global__ __launch_bounds__(256) void pack_left_u8_kernel(const PackParams p) {
 // RIGHT_BYTES: thread (tile nt, step ks, lane l) writes the 16 codes of column
 // 16 nt + l % 16, rows 64 ks + 16 (l / 16) .. + 15, as bytes (see qgtc.h).
 template <int SRC>
-__global__ __launch_bounds__(256) void pack_bytes_kernel(const PackParams p, int n_nt, int n_ks) {
-  const int idx = blockIdx.x * 256 + threadIdx.x;
+__device__ __forceinline__ void pack_bytes_of(const PackParams& p, int n_nt, int n_ks, int idx) {
   const int lane = idx & 63;
   const int ks = (idx >> 6) % n_ks;
   const int nt = (idx >> 6) / n_ks;
@@ -214,6 +213,41 @@ __global__ __launch_bounds__(256) void pack_bytes_kernel(const PackParams p, int
   } else {
     dst[0] = make_uint4(d[0], d[1], d[2], d[3]);
   }
+}
+
+template <int SRC>
+__global__ __launch_bounds__(256) void pack_bytes_kernel(const PackParams p, int n_nt, int n_ks) {
+  pack_bytes_of<SRC>(p, n_nt, n_ks, blockIdx.x * 256 + threadIdx.x);
+}
+
+// The weights of several layers at once (RIGHT_BYTES from fp32), and the column sums of the codes of one of
+// them.  Each is a few KiB: what a launch of its own took was the launch.
+constexpr int kWeightJobs = 16;
+struct WeightsParams {
+  PackParams w[kWeightJobs];
+  int32_t n_nt[kWeightJobs], n_ks[kWeightJobs];
+  int32_t end[kWeightJobs];  // first workgroup behind the job's
+  int32_t n;
+  int32_t sums_of;           // job whose column sums are wanted, by the workgroups behind the last job (-1: none)
+  int32_t* sums;
+};
+__global__ __launch_bounds__(256) void pack_weights_kernel(const WeightsParams jobs) {
+  int j = 0;
+  while (j < jobs.n && (int)blockIdx.x >= jobs.end[j]) ++j;
+  const int lane = threadIdx.x & 63;
+  if (j == jobs.n) {                                 // a wave has 16 columns, a quarter of the rows per lane
+    const PackParams& p = jobs.w[jobs.sums_of];
+    const int c0 = (((int)blockIdx.x - jobs.end[jobs.n - 1]) * 4 + (int)(threadIdx.x >> 6)) * 16, col = c0 + (lane & 15);
+    if (c0 >= p.cols) return;
+    uint32_t sum = 0u;
+#pragma unroll 8
+    for (int r = lane >> 4; r < p.rows; r += 4) sum += fetch<QGTC_SRC_F32>(p, (int64_t)r * p.ld_src + min(col, p.cols - 1));
+    sum += (uint32_t)__shfl_xor((int)sum, 16, 64);
+    sum += (uint32_t)__shfl_xor((int)sum, 32, 64);
+    if (lane < 16 && col < p.cols) jobs.sums[col] = (int32_t)sum;
+    return;
+  }
+  pack_bytes_of<QGTC_SRC_F32>(jobs.w[j], jobs.n_nt[j], jobs.n_ks[j], ((int)blockIdx.x - (j > 0 ? jobs.end[j - 1] : 0)) * 256 + (int)threadIdx.x);
 }
 
 // LEFT_BYTES: one code per byte, row-major; a thread writes 4 consecutive bytes.
@@ -502,6 +536,54 @@ extern "C" qgtc_status qgtc_pack_bits(const void* src, int32_t src_dtype, int32_
     case QGTC_SRC_U8: return launch_pack<QGTC_SRC_U8>(p, dst->layout, s);
     default: return launch_pack<QGTC_SRC_I32>(p, dst->layout, s);
   }
+}
+
+extern "C" qgtc_status qgtc_pack_weights(const qgtc_weight_source* ws, int32_t n, int32_t sums_of, int32_t* col_sums, void* stream) {
+  if (!ws) return QGTC_ERR_NULL;
+  if (n < 1 || sums_of >= n) return QGTC_ERR_SHAPE;
+  if (sums_of >= 0 && !col_sums) return QGTC_ERR_NULL;
+  for (int i = 0; i < n; ++i) {
+    if (!ws[i].src || !ws[i].dst) return QGTC_ERR_NULL;
+    const qgtc_status st = check_bits(ws[i].dst, QGTC_RIGHT_BYTES);
+    if (st != QGTC_OK) return st;
+    if (ws[i].ld_src < ws[i].dst->cols || !(ws[i].q.hi > ws[i].q.lo)) return QGTC_ERR_SHAPE;
+    if (ws[i].q.nbits != ws[i].dst->nbits) return QGTC_ERR_BITWIDTH;
+  }
+  hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+  for (int i0 = 0; i0 < n; i0 += kWeightJobs) {
+    WeightsParams jobs{};
+    jobs.n = n - i0 < kWeightJobs ? n - i0 : kWeightJobs;
+    int groups = 0;
+    for (int i = 0; i < jobs.n; ++i) {
+      const qgtc_weight_source& w = ws[i0 + i];
+      const qgtc_bits* dst = w.dst;
+      PackParams& p = jobs.w[i];
+      p.src = w.src;
+      p.ld_src = w.ld_src;
+      p.rows = dst->rows;
+      p.cols = dst->cols;
+      p.nbits = dst->nbits;
+      p.dst = dst->data;
+      p.ld = dst->ld_words;
+      p.ps = dst->plane_stride_words;
+      p.qmax = (1u << dst->nbits) - 1u;
+      p.qmaxf = (float)p.qmax;
+      p.lo = (float)w.q.lo;
+      p.inv = qgtc_quant_inv_scale(w.q.lo, w.q.hi, w.q.nbits);
+      jobs.n_nt[i] = cdiv(p.cols, 16);
+      jobs.n_ks[i] = cdiv(p.rows, 64);
+      groups += cdiv((int64_t)jobs.n_nt[i] * jobs.n_ks[i] * 64, 256);
+      jobs.end[i] = groups;
+    }
+    jobs.sums_of = sums_of >= i0 && sums_of < i0 + jobs.n ? sums_of - i0 : -1;
+    jobs.sums = col_sums;
+    if (jobs.sums_of >= 0) groups += cdiv(ws[sums_of].dst->cols, 64);
+    if (groups == 0) continue;
+    ProfScope prof(QGTC_KERNEL_PACK, s);
+    hipLaunchKernelGGL(pack_weights_kernel, dim3((unsigned)groups), dim3(256), 0, s, jobs);
+    if (launch_status() != QGTC_OK) return QGTC_ERR_HIP;
+  }
+  return QGTC_OK;
 }
 
 extern "C" qgtc_status qgtc_unpack_bits(const qgtc_bits* src, uint32_t* dst, int64_t ld_dst, void* stream) {

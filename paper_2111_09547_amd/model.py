@@ -167,28 +167,46 @@ class QuantGNN:
         on their stream (forward(..., x_packed=True) then skips that step)."""
         if X is not None:
             self._ready_planes(X)
-        # The weights are a handful of small launches that do not depend on the adjacency:
-        # they go to a second stream (forked from and joined to the current one, also
-        # inside a HIP graph) and run beside the HBM-bound packing of A and its map.
+        # Inside a HIP graph the weights and the features go to a second stream (forked from and joined to the
+        # current one) and run beside the HBM-bound packing of A and its map; launched one by one they
+        # would only wait for the host, and two streams cost it more (batches of 8192 nodes 158 -> 62 us with one launch for all weights).
         cur = torch.cuda.current_stream()
         if getattr(self, "_w_stream", None) is None:
             self._w_stream = torch.cuda.Stream()
             self._w_colsum_buf = torch.empty(self.dims[-1][1], dtype=torch.int32, device=self.A.words.device)
-        self._w_stream.wait_stream(cur)
-        with torch.cuda.stream(self._w_stream):
+        if torch.cuda.is_current_stream_capturing():
+            self._w_stream.wait_stream(cur)
+            with torch.cuda.stream(self._w_stream):
+                self._pack_weights_and(X, x_range)
+            self._pack_adjacency()
+            cur.wait_stream(self._w_stream)
+        else:
+            self._pack_weights_and(X, x_range)
+            self._pack_adjacency()
+
+    def _pack_weights_and(self, X, x_range):
+        if all(lay == B.RIGHT_BYTES for lay in self.w_layout) and all(W.dtype == torch.float32 and W.is_contiguous() for W in self.Ws):
+            key = [(W.data_ptr(), o.c.data, *r) for W, o, r in zip(self.Ws, self.W, self.w_ranges)]
+            if getattr(self, "_w_sources", (None,))[0] != key:
+                self._w_sources = (key, B.WeightSources(self.Ws, self.w_ranges, self.W))
+            # only the last layer dequantizes, so only its column sums are needed
+            B.qgtc_pack_weights(self._w_sources[1], len(self.W) - 1, self._w_colsum_buf)
+            self.w_colsum = [None] * (len(self.W) - 1) + [self._w_colsum_buf]
+        else:
             for W, r, dst, lay in zip(self.Ws, self.w_ranges, self.W, self.w_layout):
                 B.qgtc_pack_bits(W, self.t, lay, quant=r, out=dst)
-            if self.update_first and self.lists is not None:
-                for W, r, dst in zip(self.Ws, self.w_ranges, self._W_bytes):
-                    B.qgtc_pack_bits(W, self.t, B.RIGHT_BYTES, quant=r, out=dst)
-            # only the last layer dequantizes, so only its column sums are needed
             self.w_colsum = [None] * (len(self.W) - 1) + [B.qgtc_col_sums(self.W[-1], out=self._w_colsum_buf)]
-            if X is not None and not self.update_first:
-                if self._fused and X.dtype == torch.float32:
-                    assert tuple(X.shape) == (self.A.rows, self.dims[0][0])
-                    self._pack_codes(X, x_range)
-                else:
-                    self.pack_input(X, x_range)
+        if self.update_first and self.lists is not None:
+            for W, r, dst in zip(self.Ws, self.w_ranges, self._W_bytes):
+                B.qgtc_pack_bits(W, self.t, B.RIGHT_BYTES, quant=r, out=dst)
+        if X is not None and not self.update_first:
+            if self._fused and X.dtype == torch.float32:
+                assert tuple(X.shape) == (self.A.rows, self.dims[0][0])
+                self._pack_codes(X, x_range)
+            else:
+                self.pack_input(X, x_range)
+
+    def _pack_adjacency(self):
         if self.A_src is not None:
             B.qgtc_pack_bits(self.A_src, 1, B.LEFT, out=self.A)
         if self.lists is not None:
@@ -202,7 +220,6 @@ class QuantGNN:
             self.deg = self.map.deg
         else:
             self.deg = B.qgtc_row_sums(self.A)
-        cur.wait_stream(self._w_stream)
 
     # -- helpers -----------------------------------------------------------------
     def _pack_codes(self, X, x_range):

@@ -9,6 +9,7 @@ from oracle import qgnn, bitplane as bp
 pytestmark = pytest.mark.gpu
 
 q = pytest.importorskip("paper_2111_09547_amd")
+import paper_2111_09547_amd.binding as B  # noqa: E402
 from paper_2111_09547_amd.bit_tensor import (BitTensor, to_bit, to_val, bitMM2Int, bitMM2Bit,  # noqa: E402
                                              calibrate_inv_scale, enable_tensor_methods)
 from gpu_util import dev, as_u32, words_np  # noqa: E402
@@ -109,3 +110,24 @@ def test_product_builds_no_map_that_nobody_reads(monkeypatch):
         y = bitMM2Int(A, X)
         assert bool(built) == want == bt.B.qgtc_aggregate_reads_map(A.bits, d), (n, d)
         assert (as_u32(y) == qgnn.aggregate(a, x.astype(np.uint32))).all()
+
+
+@pytest.mark.parametrize("t", [1, 5, 8])
+@pytest.mark.parametrize("shapes", [[(1, 1)], [(64, 16), (65, 17), (300, 101), (512, 16)], [(16 + i, 70 - i) for i in range(19)]])
+def test_weights_of_a_stack_in_one_launch(t, shapes):
+    """As qgtc_pack_bits of each, also more than one launch takes; the column sums of any one of them."""
+    rng = np.random.default_rng(t + len(shapes))
+    Ws = [torch.from_numpy(rng.uniform(-0.5, 0.5, s).astype(np.float32)).cuda() for s in shapes]
+    ranges = [(-0.4, 0.45 + 0.01 * i) for i in range(len(Ws))]
+    want = [q.qgtc_pack_bits(W, t, q.RIGHT_BYTES, quant=r) for W, r in zip(Ws, ranges)]
+    outs = [B.alloc_bits(*s, t, q.RIGHT_BYTES) for s in shapes]
+    sources = B.WeightSources(Ws, ranges, outs)
+    for k in {0, len(Ws) // 2, len(Ws) - 1}:
+        sums = torch.full((shapes[k][1] + 3,), -7, dtype=torch.int32, device="cuda")
+        B.qgtc_pack_weights(sources, k, sums)
+        assert torch.equal(sums[:-3], q.qgtc_col_sums(want[k])) and (sums[-3:] == -7).all()
+    for got, ref in zip(outs, want):
+        assert torch.equal(got.words, ref.words)
+    B.qgtc_pack_weights(sources)
+    with pytest.raises(q.QgtcError):
+        B.qgtc_pack_weights(sources, len(Ws), sums)
