@@ -163,26 +163,28 @@ class QuantGNN:
         """Everything that does not depend on the features: pack A, build its
         zero-tile map, quantize and pack the weights (the paper caches these
         across layers and subgraphs, end of Section 3.2).  With X: the input features
-        of the coming forward pass are quantized and packed as well, after the weights
-        on their stream (forward(..., x_packed=True) then skips that step)."""
+        of the coming forward pass are quantized and packed as well (forward(..., x_packed=True)
+        then skips that step)."""
         if X is not None:
             self._ready_planes(X)
-        # Inside a HIP graph the weights and the features go to a second stream (forked from and joined to the
-        # current one) and run beside the HBM-bound packing of A and its map; launched one by one they
-        # would only wait for the host, and two streams cost it more (batches of 8192 nodes 158 -> 62 us with one launch for all weights).
-        cur = torch.cuda.current_stream()
-        if getattr(self, "_w_stream", None) is None:
-            self._w_stream = torch.cuda.Stream()
+        # (one stream: a second one for the weights and features costs more in gaps than it overlaps, the recorded
+        # step on 65536 nodes 102.2 and 98.3 us, and launched one by one they wait for the host)
+        if getattr(self, "_w_colsum_buf", None) is None:
             self._w_colsum_buf = torch.empty(self.dims[-1][1], dtype=torch.int32, device=self.A.words.device)
-        if torch.cuda.is_current_stream_capturing():
-            self._w_stream.wait_stream(cur)
-            with torch.cuda.stream(self._w_stream):
-                self._pack_weights_and(X, x_range)
-            self._pack_adjacency()
-            cur.wait_stream(self._w_stream)
+        self._pack_weights_and(X, x_range)
+        if self.A_src is not None:
+            B.qgtc_pack_bits(self.A_src, 1, B.LEFT, out=self.A)
+        if self.lists is not None:
+            if self.use_map and self.map is None:
+                self.map = B._alloc_tile_map(self.A, 16, self.tile_kbits)
+            B.qgtc_build_neighbours(self.A, self.lists, self.map)
+            self._lists_of = self.A
+            self.deg = self.map.deg if self.use_map else self.lists.deg
+        elif self.use_map:
+            self.map = B.qgtc_build_tile_map(self.A, 16, self.tile_kbits, out=self.map)
+            self.deg = self.map.deg
         else:
-            self._pack_weights_and(X, x_range)
-            self._pack_adjacency()
+            self.deg = B.qgtc_row_sums(self.A)
 
     def _pack_weights_and(self, X, x_range):
         if all(lay == B.RIGHT_BYTES for lay in self.w_layout) and all(W.dtype == torch.float32 and W.is_contiguous() for W in self.Ws):
@@ -205,21 +207,6 @@ class QuantGNN:
                 self._pack_codes(X, x_range)
             else:
                 self.pack_input(X, x_range)
-
-    def _pack_adjacency(self):
-        if self.A_src is not None:
-            B.qgtc_pack_bits(self.A_src, 1, B.LEFT, out=self.A)
-        if self.lists is not None:
-            if self.use_map and self.map is None:
-                self.map = B._alloc_tile_map(self.A, 16, self.tile_kbits)
-            B.qgtc_build_neighbours(self.A, self.lists, self.map)
-            self._lists_of = self.A
-            self.deg = self.map.deg if self.use_map else self.lists.deg
-        elif self.use_map:
-            self.map = B.qgtc_build_tile_map(self.A, 16, self.tile_kbits, out=self.map)
-            self.deg = self.map.deg
-        else:
-            self.deg = B.qgtc_row_sums(self.A)
 
     # -- helpers -----------------------------------------------------------------
     def _pack_codes(self, X, x_range):
