@@ -167,13 +167,15 @@ qgtc_status qgtc_pack_batch_host(const qgtc_host_operand* ops, int32_t n, int32_
 size_t qgtc_compound_layout(const size_t* bytes, int32_t n, size_t* offsets);
 
 /* The weights of the layers of a stack in one launch: ws[i].src (fp32, ld_src floats per row) by Eq. (2) into
- * ws[i].dst (QGTC_RIGHT_BYTES), as qgtc_pack_bits of each; col_sums (device, or NULL with sums_of < 0) gets the
+ * ws[i].dst (QGTC_RIGHT_BYTES), as qgtc_pack_bits of each; codes of up to 16 bits (q.nbits) go byte by byte, the
+ * bits from ws[i].shift (0 or 8) on into a destination of as many bits as are left, at most 8; col_sums (device, or NULL with sums_of < 0) gets the
  * column sums of the codes of ws[sums_of], as qgtc_col_sums. */
 typedef struct qgtc_weight_source {
   const float* src;
   int64_t ld_src;
   qgtc_quant q;
   const qgtc_bits* dst;
+  int32_t shift, reserved;
 } qgtc_weight_source;
 qgtc_status qgtc_pack_weights(const qgtc_weight_source* ws, int32_t n, int32_t sums_of, int32_t* col_sums,
                               void* stream);
@@ -486,6 +488,33 @@ qgtc_status qgtc_stack_forward(const qgtc_stack* stack, const float* src, int64_
  * every layer's output.  The same integers as qgtc_pack_bits, qgtc_update and qgtc_aggregate per layer. */
 qgtc_status qgtc_stack_forward_update_first(const qgtc_stack* stack, const float* src, int64_t ld_src,
                                             const qgtc_quant* q, void* out, int64_t ld_out, void* stream);
+
+/* A stack of 9 to 16 bits (s) over neighbour lists, weights of at most 16: the same integers as qgtc_layer per
+ * layer.  W[0]: the low 8 (or fewer) bits of the weights' codes, W[1]: the others (data NULL where there are
+ * none), QGTC_RIGHT_BYTES, see qgtc_pack_weights; first and second as in qgtc_stack, of 9 to 16 bits; at most 512
+ * input and 256 output columns per layer; buffer[2]: 2 x 16 ceil(columns / 16) bytes per row of every
+ * layer's input.  The features as in qgtc_stack_forward: src (fp32, quantized by *q), X (planes of s bits) or what
+ * qgtc_wide_input left in buffer[0]. */
+typedef struct qgtc_wide_layer {
+  qgtc_bits W[2];
+  qgtc_epilogue first;
+  qgtc_epilogue second;
+} qgtc_wide_layer;
+
+typedef struct qgtc_wide_stack {
+  const qgtc_bits* A;
+  const qgtc_neighbours* lists;
+  const qgtc_wide_layer* layers;      /* HOST array */
+  int32_t n_layers;
+  int32_t s;
+  void* buffer[2];
+  size_t buffer_bytes;
+} qgtc_wide_stack;
+
+qgtc_status qgtc_wide_input(const float* src, int32_t rows, int32_t cols, int64_t ld_src, const qgtc_quant* q,
+                            void* buffer, size_t buffer_bytes, void* stream);
+qgtc_status qgtc_wide_forward(const qgtc_wide_stack* stack, const float* src, int64_t ld_src,
+                              const qgtc_quant* q, const qgtc_bits* X, void* out, int64_t ld_out, void* stream);
 
 /* ---------------------------------------------------------------------------
  * Non-zero tiles of A at the three tile widths qgtc_aggregate takes, in one pass over

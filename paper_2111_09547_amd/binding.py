@@ -107,7 +107,17 @@ class _HostOperandC(C.Structure):
 
 
 class _WeightSourceC(C.Structure):
-    _fields_ = [("src", C.c_void_p), ("ld_src", C.c_int64), ("q", _QuantC), ("dst", C.POINTER(_BitsC))]
+    _fields_ = [("src", C.c_void_p), ("ld_src", C.c_int64), ("q", _QuantC), ("dst", C.POINTER(_BitsC)),
+                ("shift", C.c_int32), ("reserved", C.c_int32)]
+
+
+class _WideLayerC(C.Structure):
+    _fields_ = [("W", _BitsC * 2), ("first", _EpilogueC), ("second", _EpilogueC)]
+
+
+class _WideStackC(C.Structure):
+    _fields_ = [("A", C.POINTER(_BitsC)), ("lists", C.POINTER(_NeighboursC)), ("layers", C.POINTER(_WideLayerC)),
+                ("n_layers", C.c_int32), ("s", C.c_int32), ("buffer", C.c_void_p * 2), ("buffer_bytes", C.c_size_t)]
 
 
 class _DeviceC(C.Structure):
@@ -167,6 +177,8 @@ def lib():
         "qgtc_stack_input_rows": (C.c_int, [vp, i32, i32, i64, P(_QuantC), vp, sz, vp]),
         "qgtc_stack_forward": (C.c_int, [P(_StackC), vp, i64, P(_QuantC), P(_BitsC), vp, i64, vp]),
         "qgtc_stack_forward_update_first": (C.c_int, [P(_StackC), vp, i64, P(_QuantC), vp, i64, vp]),
+        "qgtc_wide_input": (C.c_int, [vp, i32, i32, i64, P(_QuantC), vp, sz, vp]),
+        "qgtc_wide_forward": (C.c_int, [P(_WideStackC), vp, i64, P(_QuantC), P(_BitsC), vp, i64, vp]),
         "qgtc_tile_stats": (C.c_int, [P(_BitsC), vp, vp]),
         "qgtc_plan_layer": (C.c_int, [P(_PlanInC), P(_PlanOutC)]),
         "qgtc_quant_inv_scale": (C.c_float, [C.c_double, C.c_double, i32]),
@@ -358,15 +370,16 @@ def qgtc_pack_bits(src: torch.Tensor, nbits: int, layout: int, quant=None,
 
 class WeightSources:
     """The weights of a stack (contiguous fp32 device tensors, their ranges and RIGHT_BYTES operands) as
-    qgtc_pack_weights takes them."""
+    qgtc_pack_weights takes them.  nbits, shifts: codes of nbits bits, of which each operand has those
+    from its shift on."""
 
-    def __init__(self, Ws, ranges, outs):
+    def __init__(self, Ws, ranges, outs, nbits=None, shifts=None):
         assert all(W.dim() == 2 and W.dtype == torch.float32 and W.is_cuda and W.is_contiguous() for W in Ws)
         assert all(tuple(W.shape) == (o.rows, o.cols) for W, o in zip(Ws, outs))
         self.keep = (list(Ws), list(outs))
         self.c = (_WeightSourceC * len(outs))(*[
-            _WeightSourceC(W.data_ptr(), W.shape[1], _QuantC(float(r[0]), float(r[1]), o.nbits), C.pointer(o.c))
-            for W, r, o in zip(Ws, ranges, outs)])
+            _WeightSourceC(W.data_ptr(), W.shape[1], _QuantC(float(r[0]), float(r[1]), nbits or o.nbits), C.pointer(o.c), k, 0)
+            for W, r, o, k in zip(Ws, ranges, outs, shifts or [0] * len(outs))])
 
 
 def qgtc_pack_weights(sources: WeightSources, sums_of: int = -1, col_sums: torch.Tensor | None = None):
@@ -564,6 +577,49 @@ def qgtc_stack_forward_update_first(stack: Stack, out: torch.Tensor, src: torch.
     _, out_ptr, ld_out = _out_arg(stack.last, stack.rows, stack.out_cols, out, RIGHT, out.device)
     _check(lib().qgtc_stack_forward_update_first(C.byref(stack.c), src.data_ptr(), src.stride(0) if src.shape[0] > 1 else max(src.shape[1], 1),
                                                  C.byref(q), out_ptr, ld_out, _stream()), "qgtc_stack_forward_update_first")
+
+
+class WideStack:
+    """A stack of 9 to 16 bits over neighbour lists (qgtc_wide_stack): one ((low, high or None), first epilogue,
+    second epilogue) per layer.  Holds on to every tensor it points at."""
+
+    def __init__(self, A: Bits, layers, s: int, buffers, lists: Neighbours):
+        self.keep = (A, layers, buffers, lists)
+        self.rows, self.in_cols, self.out_cols = A.rows, layers[0][0][0].rows, layers[-1][0][0].cols
+        self.last = layers[-1][2]
+        self._layers = (_WideLayerC * len(layers))()
+        for dst, ((low, high), first, second) in zip(self._layers, layers):
+            dst.W[0], dst.first, dst.second = low.c, first.to_c(), second.to_c()
+            if high is not None:
+                dst.W[1] = high.c
+        nbytes = buffers[0].numel() * buffers[0].element_size()
+        self.c = _WideStackC(C.pointer(A.c), C.pointer(lists.c), self._layers, len(layers), s,
+                             (C.c_void_p * 2)(*[b.data_ptr() for b in buffers]), nbytes)
+
+
+def qgtc_wide_input(src: torch.Tensor, nbits: int, quant, buffer: torch.Tensor):
+    """Eq. (2) of fp32 features into an activation buffer of a WideStack."""
+    assert src.dim() == 2 and src.dtype == torch.float32 and src.is_cuda and src.stride(1) == 1
+    rows, cols = src.shape
+    q = _QuantC(float(quant[0]), float(quant[1]), nbits)
+    _check(lib().qgtc_wide_input(src.data_ptr(), rows, cols, src.stride(0) if rows > 1 else max(cols, 1), C.byref(q),
+                                 buffer.data_ptr(), buffer.numel() * buffer.element_size(), _stream()), "qgtc_wide_input")
+
+
+def qgtc_wide_forward(stack: WideStack, out: torch.Tensor, src: torch.Tensor | None = None, quant=None,
+                      X: Bits | None = None):
+    """One pass: from fp32 features (src, quant), packed planes (X) or, with neither, what qgtc_wide_input
+    left in the stack's first buffer."""
+    q = ptr = None
+    ld = 0
+    if src is not None:
+        assert src.dim() == 2 and src.dtype == torch.float32 and src.is_cuda and src.stride(1) == 1
+        assert tuple(src.shape) == (stack.rows, stack.in_cols)
+        q = C.byref(_QuantC(float(quant[0]), float(quant[1]), stack.c.s))
+        ptr, ld = src.data_ptr(), src.stride(0) if src.shape[0] > 1 else max(src.shape[1], 1)
+    _, out_ptr, ld_out = _out_arg(stack.last, stack.rows, stack.out_cols, out, RIGHT, out.device)
+    _check(lib().qgtc_wide_forward(C.byref(stack.c), ptr, ld, q, C.byref(X.c) if X is not None else None, out_ptr, ld_out,
+                                   _stream()), "qgtc_wide_forward")
 
 
 LAYER_FUSED, LAYER_TWO_KERNELS = 0, 1

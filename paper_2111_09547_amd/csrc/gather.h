@@ -39,6 +39,9 @@ struct GatherParams {
   int64_t lda;
   int32_t a_words;
   int32_t out_flip;          // 0x80808080 where the output is code - 128
+  // codes of 9 to 16 bits: the weights' high bytes, bytes they have, parts of the column sums
+  const uint8_t* wb_high;
+  int32_t w_parts, split_w_high, sum_parts;
 };
 
 // What a layer emits.
@@ -46,7 +49,8 @@ enum { kGatherCodes = 0, kGatherAffine = 1, kGatherRows = 2,     // codes; behin
        kGatherSums = 3 };                                        // the sums themselves as fp32 or int32, no second product
 
 // The instances for one kind of output; share: four waves share a tile, else each has one.
-template <int MODE>
+// PARTS = 2: codes of 9 to 16 bits.
+template <int MODE, int PARTS>
 qgtc_status gather_launch(const GatherParams& p, bool share, size_t lds, hipStream_t stream);
 
 // The product of fp32 features, quantized on the way, with weights: first_product.hip.
@@ -64,6 +68,10 @@ void gather_weights(GatherParams* p, const qgtc_bits* W);
 // One layer: p has its operands and epilogues (up.out, up.ld_out: the codes' rows in bytes where
 // codes are emitted); W: RIGHT_BYTES.
 qgtc_status gather_layer(GatherParams* p, int mode, const qgtc_bits* W, hipStream_t stream);
+// The same for codes of 9 to 16 bits, rows of low bytes and behind them high bytes, all minus 128 (ldx is
+// twice row_codes_ld()); high: the weights' bits from 8 on, or NULL.
+qgtc_status gather_wide_layer(GatherParams* p, int mode, const qgtc_bits* low, const qgtc_bits* high, hipStream_t stream);
+qgtc_status pack_wide_rows(const float* src, int64_t ld_src, int rows, int cols, const qgtc_quant* q, uint8_t* dst, hipStream_t stream);
 // The aggregation by itself, fp32 or int32 out.
 qgtc_status gather_sums(GatherParams* p, hipStream_t stream);
 

@@ -12,12 +12,13 @@ struct PlanesParams {
   uint8_t* dst;
   int32_t ld_dst;            // bytes
   uint32_t flip;
+  int32_t parts;             // 2: planes from 8 on behind the others, in the second half of a row
 };
 
 // Planes to bytes: a thread has 32 rows of four columns, whose plane words it transposes as 8 x 8 bit
 // matrices; eight rows at a time its bytes are put in row order and stored as words.
 __global__ __launch_bounds__(256) void planes_to_rows_kernel(const PlanesParams p) {
-  const int quads = p.ld_dst / 4;
+  const int part = (int)blockIdx.y, quads = p.ld_dst / p.parts / 4;
   const unsigned idx = blockIdx.x * 256u + threadIdx.x;
   const int kw = (int)(idx / (unsigned)quads), c0 = 4 * (int)(idx % (unsigned)quads);
   if (kw * 32 >= p.rows) return;
@@ -28,7 +29,7 @@ __global__ __launch_bounds__(256) void planes_to_rows_kernel(const PlanesParams 
 #pragma unroll
     for (int pl = 0; pl < 8; ++pl) {
       code[k][pl] = 0u;
-      if (pl < p.s) code[k][pl] = p.X[(int64_t)pl * p.ps + (int64_t)kw * p.ld + c];
+      if (8 * part + pl < p.s) code[k][pl] = p.X[(int64_t)(8 * part + pl) * p.ps + (int64_t)kw * p.ld + c];
     }
     planes_word_to_codes(code[k]);
     if (c0 + k >= p.cols) {
@@ -46,7 +47,7 @@ __global__ __launch_bounds__(256) void planes_to_rows_kernel(const PlanesParams 
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
       const int row = 32 * kw + 8 * b + r;
-      if (row < p.rows) *reinterpret_cast<uint32_t*>(p.dst + (int64_t)row * p.ld_dst + c0) = v[b] ^ p.flip;
+      if (row < p.rows) *reinterpret_cast<uint32_t*>(p.dst + (int64_t)row * p.ld_dst + 4 * quads * part + c0) = v[b] ^ p.flip;
     }
   }
 }
@@ -54,10 +55,12 @@ __global__ __launch_bounds__(256) void planes_to_rows_kernel(const PlanesParams 
 }  // namespace
 
 qgtc_status planes_to_rows(const qgtc_bits* X, uint8_t* dst, hipStream_t stream) {
-  PlanesParams p{X->data, X->ld_words, X->plane_stride_words, X->rows, X->cols, X->nbits, dst, (int32_t)row_codes_ld(X->cols),
-                 row_codes_flip(X->nbits)};
+  const int parts = X->nbits > 8 ? 2 : 1, ld = (int)row_codes_ld(X->cols);
+  PlanesParams p{X->data, X->ld_words, X->plane_stride_words, X->rows, X->cols, X->nbits, dst, parts * ld,
+                 parts == 2 ? 0x80808080u : row_codes_flip(X->nbits), parts};
   ProfScope prof(QGTC_KERNEL_PACK, stream);
-  hipLaunchKernelGGL(planes_to_rows_kernel, dim3((unsigned)cdiv((int64_t)cdiv(p.rows, 32) * (p.ld_dst / 4), 256)), dim3(256), 0, stream, p);
+  hipLaunchKernelGGL(planes_to_rows_kernel, dim3((unsigned)cdiv((int64_t)cdiv(p.rows, 32) * (ld / 4), 256), (unsigned)parts), dim3(256), 0,
+                     stream, p);
   return launch_status();
 }
 
@@ -69,6 +72,7 @@ void gather_weights(GatherParams* p, const qgtc_bits* W) {
   p->n_ks = cdiv(W->rows, 64);
   p->split_y = p->agg_nbits == 8;
   p->split_w = W->nbits == 8;
+  p->sum_parts = 1;
 }
 
 namespace {
@@ -77,12 +81,12 @@ namespace {
 // per tile 11.3; 8192 rows have half a wave per SIMD that way).
 bool four_waves_share(const GatherParams& p) { return p.ldx > 32 && p.n_tiles < 8 * device_compute_units(); }
 
-int pieces_of(const GatherParams& p) {
+int pieces_of(const GatherParams& p, int parts = 1) {
   int pieces = 1;
-  while (16 * pieces < p.ldx) pieces <<= 1;
+  while (16 * pieces * parts < p.ldx) pieces <<= 1;
   return pieces;
 }
-size_t heavy_bytes(const GatherParams& p) { return 2048 + 64 + (size_t)pieces_of(p) * 64; }   // counts, the row that is taken, its sums
+size_t heavy_bytes(const GatherParams& p, int parts = 1) { return 2048 + 64 + (size_t)pieces_of(p, parts) * 64 * parts; }   // counts, the row that is taken, its sums
 
 void set_grid(GatherParams* gp, int tiles) {
   GatherParams& p = *gp;
@@ -126,9 +130,42 @@ qgtc_status gather_layer(GatherParams* gp, int mode, const qgtc_bits* W, hipStre
   set_grid(gp, tiles);
   ProfScope prof(QGTC_KERNEL_LAYER, stream);
   switch (mode) {
-    case kGatherCodes: return gather_launch<kGatherCodes>(p, share, lds, stream);
-    case kGatherAffine: return gather_launch<kGatherAffine>(p, share, lds, stream);
-    default: return gather_launch<kGatherRows>(p, share, lds, stream);
+    case kGatherCodes: return gather_launch<kGatherCodes, 1>(p, share, lds, stream);
+    case kGatherAffine: return gather_launch<kGatherAffine, 1>(p, share, lds, stream);
+    default: return gather_launch<kGatherRows, 1>(p, share, lds, stream);
+  }
+}
+
+qgtc_status gather_wide_layer(GatherParams* gp, int mode, const qgtc_bits* low, const qgtc_bits* high, hipStream_t stream) {
+  GatherParams& p = *gp;
+  gather_weights(gp, low);
+  p.split_y = 1;                                     // (kept_codes(): every byte minus 128)
+  p.wb_high = high ? reinterpret_cast<const uint8_t*>(high->data) : nullptr;
+  p.w_parts = high ? 2 : 1;
+  p.split_w_high = high && high->nbits == 8;
+  p.sum_parts = 2;
+  if (p.up.l0b == 0.0) p.up.row_l = nullptr;
+  p.want_rowsum = p.up.mode == QGTC_OUT_F32 && p.up.row_i == nullptr && p.up.rs != 0.0;
+  const bool share = p.ldx > 64 && p.n_tiles < 8 * device_compute_units();
+  const int tiles = share ? 1 : 4;
+  size_t lds = (size_t)tiles * 2 * p.n_ks * 1024;
+  const size_t one = (size_t)2 * p.n_ks * 1024;
+  p.heavy_off = (int)one;
+  if (lds < one + heavy_bytes(p, 2)) lds = one + heavy_bytes(p, 2);
+  lds = (lds + 63) & ~(size_t)63;
+  p.cols_off = (int)lds;
+  lds += (size_t)p.n_nt * (128 + 128);
+  p.w_off = -1;
+  if (p.n_ks * p.n_nt * p.w_parts <= 48) {
+    p.w_off = (int)lds;
+    lds += (size_t)p.n_ks * p.n_nt * p.w_parts * 1024;
+  }
+  set_grid(gp, tiles);
+  ProfScope prof(QGTC_KERNEL_LAYER, stream);
+  switch (mode) {
+    case kGatherCodes: return gather_launch<kGatherCodes, 2>(p, share, lds, stream);
+    case kGatherAffine: return gather_launch<kGatherAffine, 2>(p, share, lds, stream);
+    default: return gather_launch<kGatherRows, 2>(p, share, lds, stream);
   }
 }
 
@@ -136,7 +173,7 @@ qgtc_status gather_sums(GatherParams* gp, hipStream_t stream) {
   const bool share = four_waves_share(*gp);
   set_grid(gp, share ? 1 : 4);
   ProfScope prof(QGTC_KERNEL_AGGREGATE, stream);
-  return gather_launch<kGatherSums>(*gp, share, heavy_bytes(*gp), stream);
+  return gather_launch<kGatherSums, 1>(*gp, share, heavy_bytes(*gp), stream);
 }
 
 }  // namespace qgtc

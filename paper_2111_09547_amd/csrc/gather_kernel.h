@@ -35,14 +35,14 @@ namespace {
 // then of the old values.
 __device__ __forceinline__ void settle(v4i& sum) { asm volatile("s_nop 7" : "+v"(sum)); }
 
-// The dimensions of an instance.
-template <int LP, int WPT>
+// The dimensions of an instance; PARTS = 2: codes of 9 to 16 bits, a low and a high byte each.
+template <int LP, int WPT, int PARTS>
 struct GatherShape {
   static constexpr int P = 1 << LP;
   static constexpr int PS = P < 16 ? P : 16;         // pieces of a unit: 16 slots
   static constexpr int RC = 16 / PS, HV = P / PS;    // rows of a unit; P > 16: parts of 256 columns
   static constexpr int UNITS = 16 / WPT / RC;        // units of a wave per part
-  static constexpr int W = UNITS < 4 ? UNITS : 4;    // at a time
+  static constexpr int W = UNITS * PARTS < 4 ? UNITS * PARTS : 4;   // sums at a time: parts of units
 };
 
 // A[m][16 g + b] = (b == m), which adds up the bytes of the four lanes of a slot.
@@ -56,17 +56,18 @@ __device__ __forceinline__ uint32_t list_entry(const v2u& idx, int k) { return k
 // Rows of X that a row of A can have as neighbours: its diagonal block's.
 struct Neighbours {
   __amdgpu_buffer_rsrc_t rx;
-  uint32_t ldx;
-  __device__ __forceinline__ Neighbours(const GatherParams& p, int row0) {
+  uint32_t ldx, part;                                // bytes of a row, of a part of it
+  __device__ __forceinline__ Neighbours(const GatherParams& p, int row0, int parts) {
     const int first_row = (int)div_by((unsigned)row0, (unsigned)p.block, p.block_magic) * p.block;
     ldx = (uint32_t)p.ldx;
+    part = ldx / (uint32_t)parts;
     rx = uniform_rsrc(p.X + (int64_t)first_row * p.ldx, (uint32_t)(min(p.rows - first_row, p.block) * p.ldx));
   }
   __device__ __forceinline__ v4i load(uint32_t idx, uint32_t pofs) const {
     return (v4i)__builtin_amdgcn_raw_buffer_load_b128(rx, __umul24(idx, ldx) + pofs, 0, 0);
   }
   // past the end where a row has no such piece
-  __device__ __forceinline__ uint32_t piece_offset(int piece) const { return 16u * (uint32_t)piece < ldx ? 16u * (uint32_t)piece : 0x80000000u; }
+  __device__ __forceinline__ uint32_t piece_offset(int piece) const { return 16u * (uint32_t)piece < part ? 16u * (uint32_t)piece : 0x80000000u; }
 };
 
 // Sums of four columns from col on as the output (kGatherSums).
@@ -89,9 +90,9 @@ __device__ __forceinline__ void emit_sums(const GatherParams& p, int row, int co
 }
 
 // The heavy rows, one after the other, by all n_heavy_wg workgroups.
-template <int LP, int LT, int MODE>
+template <int LP, int LT, int MODE, int PARTS>
 __device__ __forceinline__ void heavy_rows(const GatherParams& p, uint8_t* lds, int wave, int lane) {
-  using Sh = GatherShape<LP, 1>;
+  using Sh = GatherShape<LP, 1, PARTS>;
   constexpr int P = Sh::P, PS = Sh::PS, RC = Sh::RC, HV = Sh::HV;
   const int ln = lane & 15, g = lane >> 4;
   const int self = p.self_term, ldx = p.ldx, n_ks = p.n_ks;
@@ -130,11 +131,13 @@ __device__ __forceinline__ void heavy_rows(const GatherParams& p, uint8_t* lds, 
   if (blockIdx.x >= all) return;                   // whole workgroup
   before[threadIdx.x] = base + incl - mine;
   before[256 + threadIdx.x] = mine;
-  if constexpr (MODE != kGatherSums) stage_weights<LT, MODE>(p, lds, wave, lane);
+  if constexpr (PARTS == 2) stage_wide_weights<MODE>(p, lds, wave, lane);
+  else if constexpr (MODE != kGatherSums) stage_weights<LT, MODE>(p, lds, wave, lane);
   uint8_t* const yb = lds;
   const uint32_t flip = p.split_y ? 0x80808080u : 0u;
-  if (MODE != kGatherSums && P < 4 && (lane & 3) >= P)
-    *reinterpret_cast<v4u*>(yb + lane * 16) = (v4u){flip, flip, flip, flip};   // columns no lane has
+  if (MODE != kGatherSums && P < 4 && (lane & 3) >= P) {   // columns no lane has
+    for (int i = 0; i < PARTS; ++i) *reinterpret_cast<v4u*>(yb + i * n_ks * 1024 + lane * 16) = (v4u){flip, flip, flip, flip};
+  }
   const v4i ident = adder(ln), zero = {0, 0, 0, 0};
   const Rq q = make_rq(p.agg_lo, p.agg_relu, p.agg_inv, p.agg_nbits);
 #pragma unroll 1
@@ -149,19 +152,19 @@ __device__ __forceinline__ void heavy_rows(const GatherParams& p, uint8_t* lds, 
       for (; rest > 0u; --rest) m &= m - 1u;
       taken[0] = at * kListGroup + __builtin_ctzll(m);
     }
-    for (int i = (int)threadIdx.x; i < P * 16; i += 256) sums[i] = 0u;
+    for (int i = (int)threadIdx.x; i < P * 16 * PARTS; i += 256) sums[i] = 0u;
     __syncthreads();
     const int row0 = (int)uniform((uint32_t)taken[0]);
-    const Neighbours nb(p, row0);
+    const Neighbours nb(p, row0, PARTS);
     int32_t rl = 0;
     if (MODE == kGatherRows && p.up.mode == QGTC_OUT_F32 && p.up.row_l) rl = p.up.row_l[row0];
     // the waves and the slots of a unit share the row's neighbours; the sums of its columns meet in LDS
     const int n = (int)uniform((uint32_t)p.deg[row0]);
     const int rs = ln / PS;
 #pragma unroll 1
-    for (int hv = 0; hv < HV; ++hv) {
-      const int piece = (ln & (PS - 1)) + 16 * hv;
-      const uint32_t pofs = nb.piece_offset(piece);
+    for (int hv = 0; hv < HV * PARTS; ++hv) {
+      const int piece = (ln & (PS - 1)) + 16 * (hv % HV), part = hv / HV;
+      const uint32_t pofs = nb.piece_offset(piece) + (uint32_t)part * nb.part;
       v4i h = zero;
       if (n <= kListMax) {
 #pragma unroll 1
@@ -203,13 +206,13 @@ __device__ __forceinline__ void heavy_rows(const GatherParams& p, uint8_t* lds, 
       }
       if (wave == 0) {                             // (once: the own row, and 128 for every code that is code - 128)
         uint32_t own = 0u;
-        if (self && 16 * piece < ldx) own = *reinterpret_cast<const uint32_t*>(p.X + (int64_t)row0 * ldx + 16 * piece + 4 * g);
+        if (self && 16u * (uint32_t)piece < nb.part) own = *reinterpret_cast<const uint32_t*>(p.X + (int64_t)row0 * ldx + pofs + 4 * g);
 #pragma unroll
         for (int r = 0; r < 4; ++r)
           if (rs == 0) h[r] += p.x_offset * (n + self) + (int)(int8_t)(own >> (8 * r));
       }
 #pragma unroll
-      for (int r = 0; r < 4; ++r) atomicAdd(&sums[16 * piece + 4 * g + r], (uint32_t)h[r]);
+      for (int r = 0; r < 4; ++r) atomicAdd(&sums[16 * P * part + 16 * piece + 4 * g + r], (uint32_t)h[r]);
     }
     __syncthreads();
     if constexpr (MODE == kGatherSums) {
@@ -218,26 +221,36 @@ __device__ __forceinline__ void heavy_rows(const GatherParams& p, uint8_t* lds, 
       continue;
     }
     for (int i = (int)threadIdx.x; i < 4 * P && i < 16 * n_ks; i += 256) {   // four columns each
-      uint32_t c[1][4], d[1];
+      uint8_t* const to = yb + (i >> 4) * 1024 + (i & 15) * 4;
+      uint32_t c[1][4];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) c[0][r] = sums[4 * i + r];
-      pack_codes_words(c, q, d);
-      *reinterpret_cast<uint32_t*>(yb + (i >> 4) * 1024 + (i & 15) * 4) = kept_codes(p, d[0], 4 * i);
+      for (int r = 0; r < 4; ++r) c[0][r] = sums[4 * i + r] + (PARTS == 2 ? sums[16 * P + 4 * i + r] << 8 : 0u);
+      if constexpr (PARTS == 2) {
+        uint32_t lo, hi;
+        wide_codes(p, c[0], lo, hi);
+        *reinterpret_cast<uint32_t*>(to) = kept_codes(p, lo, 4 * i);
+        *reinterpret_cast<uint32_t*>(to + n_ks * 1024) = kept_codes(p, hi, 4 * i);
+      } else {
+        uint32_t d[1];
+        pack_codes_words(c, q, d);
+        *reinterpret_cast<uint32_t*>(to) = kept_codes(p, d[0], 4 * i);
+      }
     }
     __syncthreads();
-    finish_tile<LT, MODE>(p, lds, yb, row0, ln == 0, LT * wave, 4 * LT, rl, lane);
+    if constexpr (PARTS == 2) finish_wide_tile<MODE>(p, lds, yb, row0, ln == 0, wave, 4, rl, lane);
+    else finish_tile<LT, MODE>(p, lds, yb, row0, ln == 0, LT * wave, 4 * LT, rl, lane);
   }
 }
 
-template <int LP, int WPT, int LT, int MODE>
+template <int LP, int WPT, int LT, int MODE, int PARTS>
 __global__ __launch_bounds__(256, 4) void gather_layer_kernel(const GatherParams p) {
   extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
-  using Sh = GatherShape<LP, WPT>;
+  using Sh = GatherShape<LP, WPT, PARTS>;
   constexpr int P = Sh::P, PS = Sh::PS, RC = Sh::RC, HV = Sh::HV, UNITS = Sh::UNITS, W = Sh::W;
   static_assert(WPT == 1 || (WPT == 4 && P >= 4 && LT == 1), "shapes");
   const int wave = (int)uniform(threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (__builtin_expect((int)blockIdx.x < p.n_heavy_wg, 0)) {
-    heavy_rows<LP, LT, MODE>(p, lds, wave, lane);
+    heavy_rows<LP, LT, MODE, PARTS>(p, lds, wave, lane);
     return;
   }
   const unsigned b = xcd_deal(blockIdx.x - (unsigned)p.n_heavy_wg, p.run_shift);
@@ -256,15 +269,17 @@ __global__ __launch_bounds__(256, 4) void gather_layer_kernel(const GatherParams
   int t_n = (int)__builtin_amdgcn_raw_buffer_load_b32(r_deg, ln * 4, 0, 0);
   int32_t rl = 0;
   if (MODE == kGatherRows && p.up.mode == QGTC_OUT_F32 && p.up.row_l && ln < n_rows) rl = p.up.row_l[row0 + ln];
-  if constexpr (MODE != kGatherSums) stage_weights<LT, MODE>(p, lds, wave, lane);
+  if constexpr (PARTS == 2) stage_wide_weights<MODE>(p, lds, wave, lane);
+  else if constexpr (MODE != kGatherSums) stage_weights<LT, MODE>(p, lds, wave, lane);
   const bool out_ok = ln < n_rows && t_n <= kListLight;
   if (t_n > kListLight) t_n = -1;                    // (heavy: what comes out is not stored, the row is written by others)
   const uint32_t flip = p.split_y ? 0x80808080u : 0u;
   // one group of output tiles: the codes of 256 columns at a time
-  const bool parts = HV > 1 && WPT == 1 && p.n_nt <= LT;
-  uint8_t* const yb = lds + (WPT == 1 ? wave * (parts ? 4 : n_ks) * 1024 : 0);   // the tile's codes
-  if (MODE != kGatherSums && P < 4 && (lane & 3) >= P)
-    *reinterpret_cast<v4u*>(yb + lane * 16) = (v4u){flip, flip, flip, flip};   // columns no lane has
+  const bool parts = HV > 1 && WPT == 1 && PARTS == 1 && p.n_nt <= LT;
+  uint8_t* const yb = lds + (WPT == 1 ? wave * (parts ? 4 : PARTS * n_ks) * 1024 : 0);   // the tile's codes
+  if (MODE != kGatherSums && P < 4 && (lane & 3) >= P) {   // columns no lane has
+    for (int i = 0; i < PARTS; ++i) *reinterpret_cast<v4u*>(yb + i * n_ks * 1024 + lane * 16) = (v4u){flip, flip, flip, flip};
+  }
   if (WPT == 1 && MODE != kGatherSums) {             // waits for the weights here, and for nobody later
     __syncthreads();
   }
@@ -273,7 +288,7 @@ __global__ __launch_bounds__(256, 4) void gather_layer_kernel(const GatherParams
   // ---- 1, 2: the tile's codes ---------------------------------------------------------------------
   const v4i ident = adder(ln);
   const Rq q = make_rq(p.agg_lo, p.agg_relu, p.agg_inv, p.agg_nbits);
-  const Neighbours nb(p, row0);
+  const Neighbours nb(p, row0, PARTS);
   const __amdgpu_buffer_rsrc_t r_own = uniform_rsrc(p.X + (int64_t)row0 * ldx, here * (uint32_t)ldx);
   constexpr int LR = LP < 4 ? LP : 4;
   const uint32_t v_own = (uint32_t)((ln >> LR) * ldx + 16 * (ln & (PS - 1)) + 4 * g);
@@ -288,14 +303,17 @@ __global__ __launch_bounds__(256, 4) void gather_layer_kernel(const GatherParams
     if (HV > 1 && 256 * hv >= p.cols) break;         // (uniform)
     const uint32_t pofs = nb.piece_offset(piece);
 #pragma unroll 1
-    for (int u0 = 0; u0 < UNITS; u0 += W) {
+    for (int u0 = 0; u0 < UNITS; u0 += W / PARTS) {   // sum j: part j % PARTS of unit u0 + j / PARTS
       v2u idx[W];
       int n[W], most = 0;
       uint32_t own[W];
 #pragma unroll
       for (int j = 0; j < W; ++j) {
-        const int row = first_row + (u0 + j) * RC + (ln >> LR);
-        if (RC == 16) {
+        const int row = first_row + (u0 + j / PARTS) * RC + (ln >> LR);
+        if (PARTS == 2 && j % 2 == 1) {
+          idx[j] = idx[j - 1];
+          n[j] = n[j - 1];
+        } else if (RC == 16) {
           idx[j] = t_idx;
           n[j] = t_n;
         } else {
@@ -305,7 +323,8 @@ __global__ __launch_bounds__(256, 4) void gather_layer_kernel(const GatherParams
         }
         most = max(most, n[j]);
         own[j] = 0u;
-        if (self) own[j] = __builtin_amdgcn_raw_buffer_load_b32(r_own, v_own, (uint32_t)(first_row + (u0 + j) * RC) * (uint32_t)ldx + hv * 256u, 0);
+        if (self)
+          own[j] = __builtin_amdgcn_raw_buffer_load_b32(r_own, v_own, (uint32_t)(first_row + (u0 + j / PARTS) * RC) * (uint32_t)ldx + hv * 256u + j % PARTS * nb.part, 0);
       }
       // The first block in up to three steps, each with all of its loads in flight: wide rows are few
       // neighbours of many bytes from HBM, narrow ones more neighbours from the caches.
@@ -315,10 +334,10 @@ __global__ __launch_bounds__(256, 4) void gather_layer_kernel(const GatherParams
 #pragma unroll
       for (int k = 0; k < K1; ++k)
 #pragma unroll
-        for (int j = 0; j < W; ++j) x[j][k] = nb.load(list_entry(idx[j], k), pofs);
+        for (int j = 0; j < W; ++j) x[j][k] = nb.load(list_entry(idx[j], k), pofs + j % PARTS * nb.part);
       if (five) {
 #pragma unroll
-        for (int j = 0; j < W; ++j) x[j][1] = nb.load(list_entry(idx[j], 1), pofs);
+        for (int j = 0; j < W; ++j) x[j][1] = nb.load(list_entry(idx[j], 1), pofs + j % PARTS * nb.part);
       }
       // (the own row, and 128 for every code that is code - 128)
 #pragma unroll
@@ -339,7 +358,7 @@ __global__ __launch_bounds__(256, 4) void gather_layer_kernel(const GatherParams
 #pragma unroll
         for (int k = 0; k < 2; ++k)
 #pragma unroll
-          for (int j = 0; j < W; ++j) x[j][k] = nb.load(list_entry(idx[j], 2 + k), pofs);
+          for (int j = 0; j < W; ++j) x[j][k] = nb.load(list_entry(idx[j], 2 + k), pofs + j % PARTS * nb.part);
 #pragma unroll
         for (int k = 0; k < 2; ++k)
 #pragma unroll
@@ -351,7 +370,7 @@ __global__ __launch_bounds__(256, 4) void gather_layer_kernel(const GatherParams
 #pragma unroll
           for (int j = 0; j < W; ++j) {
             idx[j] = (v2u){~0u, ~0u};
-            const int64_t row = row0 + first_row + (u0 + j) * RC + (ln >> LR);
+            const int64_t row = row0 + first_row + (u0 + j / PARTS) * RC + (ln >> LR);
             if (n[j] > base) idx[j] = *reinterpret_cast<const v2u*>(p.rest + row * p.rest_cap + (base - kListBlock) + 4 * g);
           }
         };
@@ -363,7 +382,7 @@ __global__ __launch_bounds__(256, 4) void gather_layer_kernel(const GatherParams
 #pragma unroll
             for (int k = 0; k < 2; ++k)
 #pragma unroll
-              for (int j = 0; j < W; ++j) x[j][k] = nb.load(list_entry(idx[j], 2 * h + k), pofs);
+              for (int j = 0; j < W; ++j) x[j][k] = nb.load(list_entry(idx[j], 2 * h + k), pofs + j % PARTS * nb.part);
             if (h == 1) more(base + kListBlock);
 #pragma unroll
             for (int k = 0; k < 2; ++k)
@@ -382,18 +401,33 @@ __global__ __launch_bounds__(256, 4) void gather_layer_kernel(const GatherParams
         }
         continue;
       }
-      uint32_t c[W][4], d[W];
-#pragma unroll
-      for (int j = 0; j < W; ++j)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) c[j][r] = (uint32_t)acc[j][r];
-      pack_codes_words(c, q, d);
       const int at = parts ? piece & 15 : piece;
-      if (P <= 4 || piece < 4 * n_ks) {
-        uint8_t* const to = yb + (at >> 2) * 1024 + (at & 3) * 16 + 4 * g;
+      uint8_t* const to = yb + (at >> 2) * 1024 + (at & 3) * 16 + 4 * g;
+      if constexpr (PARTS == 2) {
+#pragma unroll
+        for (int j = 0; j < W; j += 2) {
+          uint32_t c[4], lo, hi;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) c[r] = (uint32_t)acc[j][r] + ((uint32_t)acc[j + 1][r] << 8);
+          wide_codes(p, c, lo, hi);
+          if (P <= 4 || piece < 4 * n_ks) {
+            uint32_t* const word = reinterpret_cast<uint32_t*>(to + (first_row + (u0 + j / 2) * RC + (ln >> LR)) * 64);
+            word[0] = kept_codes(p, lo, 16 * piece + 4 * g);
+            word[n_ks * 256] = kept_codes(p, hi, 16 * piece + 4 * g);
+          }
+        }
+      } else {
+        uint32_t c[W][4], d[W];
 #pragma unroll
         for (int j = 0; j < W; ++j)
-          *reinterpret_cast<uint32_t*>(to + (first_row + (u0 + j) * RC + (ln >> LR)) * 64) = kept_codes(p, d[j], 16 * piece + 4 * g);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) c[j][r] = (uint32_t)acc[j][r];
+        pack_codes_words(c, q, d);
+        if (P <= 4 || piece < 4 * n_ks) {
+#pragma unroll
+          for (int j = 0; j < W; ++j)
+            *reinterpret_cast<uint32_t*>(to + (first_row + (u0 + j) * RC + (ln >> LR)) * 64) = kept_codes(p, d[j], 16 * piece + 4 * g);
+        }
       }
     }
     if (HV > 1 && parts) {
@@ -411,39 +445,40 @@ __global__ __launch_bounds__(256, 4) void gather_layer_kernel(const GatherParams
   }
   if (WPT != 1) __syncthreads();
   else __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  finish_tile<LT, MODE>(p, lds, yb, row0, out_ok, WPT == 1 ? 0 : wave, WPT == 1 ? LT : 4, rl, lane);
+  if constexpr (PARTS == 2) finish_wide_tile<MODE>(p, lds, yb, row0, out_ok, WPT == 1 ? 0 : wave, WPT == 1 ? 1 : 4, rl, lane);
+  else finish_tile<LT, MODE>(p, lds, yb, row0, out_ok, WPT == 1 ? 0 : wave, WPT == 1 ? LT : 4, rl, lane);
 }
 
-template <int LP, int WPT, int LT, int MODE>
+template <int LP, int WPT, int LT, int MODE, int PARTS>
 qgtc_status launch_one(const GatherParams& p, size_t lds, hipStream_t stream) {
   static OncePerDevice once;
-  if (!allow_lds(once, reinterpret_cast<const void*>(&gather_layer_kernel<LP, WPT, LT, MODE>), lds)) return QGTC_ERR_HIP;
-  hipLaunchKernelGGL((gather_layer_kernel<LP, WPT, LT, MODE>), dim3((unsigned)p.n_heavy_wg + xcd_deal_grid(p.nblocks, p.run_shift)), dim3(256),
+  if (!allow_lds(once, reinterpret_cast<const void*>(&gather_layer_kernel<LP, WPT, LT, MODE, PARTS>), lds)) return QGTC_ERR_HIP;
+  hipLaunchKernelGGL((gather_layer_kernel<LP, WPT, LT, MODE, PARTS>), dim3((unsigned)p.n_heavy_wg + xcd_deal_grid(p.nblocks, p.run_shift)), dim3(256),
                      lds, stream, p);
   return launch_status();
 }
 
-template <int LP, int MODE>
+template <int LP, int MODE, int PARTS>
 qgtc_status launch_pieces(const GatherParams& p, bool share, size_t lds, hipStream_t stream) {
   if constexpr (LP >= 2) {
-    if (share) return launch_one<LP, 4, 1, MODE>(p, lds, stream);
+    if (share) return launch_one<LP, 4, 1, MODE, PARTS>(p, lds, stream);
   }
-  if constexpr (MODE == kGatherSums) return launch_one<LP, 1, 1, MODE>(p, lds, stream);
-  else return p.n_nt > 1 ? launch_one<LP, 1, 4, MODE>(p, lds, stream) : launch_one<LP, 1, 1, MODE>(p, lds, stream);
+  if constexpr (MODE == kGatherSums || PARTS == 2) return launch_one<LP, 1, 1, MODE, PARTS>(p, lds, stream);
+  else return p.n_nt > 1 ? launch_one<LP, 1, 4, MODE, 1>(p, lds, stream) : launch_one<LP, 1, 1, MODE, 1>(p, lds, stream);
 }
 
 }  // namespace
 
-template <int MODE>
+template <int MODE, int PARTS>
 qgtc_status gather_launch(const GatherParams& p, bool share, size_t lds, hipStream_t stream) {
-  const int pieces = p.ldx / 16;
-  if (pieces <= 1) return launch_pieces<0, MODE>(p, share, lds, stream);
-  if (pieces <= 2) return launch_pieces<1, MODE>(p, share, lds, stream);
-  if (pieces <= 4) return launch_pieces<2, MODE>(p, share, lds, stream);
-  if (pieces <= 8) return launch_pieces<3, MODE>(p, share, lds, stream);
-  if (pieces <= 16) return launch_pieces<4, MODE>(p, share, lds, stream);
-  if (pieces <= 32) return launch_pieces<5, MODE>(p, share, lds, stream);
-  return launch_pieces<6, MODE>(p, share, lds, stream);
+  const int pieces = p.ldx / (16 * PARTS);
+  if (pieces <= 1) return launch_pieces<0, MODE, PARTS>(p, share, lds, stream);
+  if (pieces <= 2) return launch_pieces<1, MODE, PARTS>(p, share, lds, stream);
+  if (pieces <= 4) return launch_pieces<2, MODE, PARTS>(p, share, lds, stream);
+  if (pieces <= 8) return launch_pieces<3, MODE, PARTS>(p, share, lds, stream);
+  if (pieces <= 16) return launch_pieces<4, MODE, PARTS>(p, share, lds, stream);
+  if constexpr (PARTS == 2) return launch_pieces<5, MODE, PARTS>(p, share, lds, stream);
+  else return pieces <= 32 ? launch_pieces<5, MODE, PARTS>(p, share, lds, stream) : launch_pieces<6, MODE, PARTS>(p, share, lds, stream);
 }
 
 }  // namespace qgtc

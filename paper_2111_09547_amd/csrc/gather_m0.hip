@@ -2,5 +2,5 @@
 #include "gather_kernel.h"
 
 namespace qgtc {
-template qgtc_status gather_launch<0>(const GatherParams&, bool, size_t, hipStream_t);
+template qgtc_status gather_launch<0, 1>(const GatherParams&, bool, size_t, hipStream_t);
 }  // namespace qgtc

@@ -18,6 +18,7 @@ struct PackParams {
   uint32_t qmax;
   float qmaxf;
   uint32_t flip;        // QGTC_LEFT_BYTES: on every word (0x80808080: codes - 128)
+  int32_t shift;        // RIGHT_BYTES of wider codes: their bits from here on
 };
 
 template <int SRC> struct src_type { using type = uint32_t; };
@@ -202,7 +203,7 @@ __device__ __forceinline__ void pack_bytes_of(const PackParams& p, int n_nt, int
 #pragma unroll
   for (int b = 0; b < 16; ++b) {
     const bool ok = col < p.cols && k0 + b < p.rows;
-    const uint32_t code = ok ? to_code<SRC>(p, raw[b]) : 0u;
+    const uint32_t code = ok ? (to_code<SRC>(p, raw[b]) >> p.shift) & 0xffu : 0u;
     d[b >> 2] |= code << (8 * (b & 3));
   }
   uint4* dst = reinterpret_cast<uint4*>(reinterpret_cast<uint8_t*>(p.dst) + (int64_t)idx * 16);
@@ -472,6 +473,27 @@ UnpackParams unpack_params(const qgtc_bits* m) {
   return p;
 }
 
+// Codes of 9 to 16 bits as rows of low bytes and behind them of high bytes, all minus 128: a thread has
+// four columns.
+__global__ __launch_bounds__(256) void pack_wide_rows_kernel(const PackParams p, int quads) {
+  const unsigned idx = blockIdx.x * 256u + threadIdx.x;
+  const int r = (int)(idx / (unsigned)quads), c0 = 4 * (int)(idx % (unsigned)quads);
+  if (r >= p.rows) return;
+  float v[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) v[k] = fetch_raw<QGTC_SRC_F32>(p, (int64_t)r * p.ld_src + min(c0 + k, p.cols - 1));
+  uint32_t lo = 0u, hi = 0u;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const uint32_t c = to_code<QGTC_SRC_F32>(p, v[k]);
+    lo |= (c & 0xffu) << (8 * k);
+    hi |= (c >> 8) << (8 * k);
+  }
+  uint32_t* const dst = p.dst + (int64_t)r * p.ld + (c0 >> 2);
+  dst[0] = lo ^ 0x80808080u;
+  dst[p.ld >> 1] = hi ^ 0x80808080u;
+}
+
 }  // namespace
 
 qgtc_status pack_row_codes(const float* src, int64_t ld_src, int rows, int cols, const qgtc_quant* q, uint8_t* dst,
@@ -491,6 +513,25 @@ qgtc_status pack_row_codes(const float* src, int64_t ld_src, int rows, int cols,
   p.flip = row_codes_flip(q->nbits);
   ProfScope prof(QGTC_KERNEL_PACK, stream);
   return launch_pack<QGTC_SRC_F32>(p, QGTC_LEFT_BYTES, stream);
+}
+
+qgtc_status pack_wide_rows(const float* src, int64_t ld_src, int rows, int cols, const qgtc_quant* q, uint8_t* dst, hipStream_t stream) {
+  PackParams p{};
+  p.src = src;
+  p.ld_src = ld_src;
+  p.rows = rows;
+  p.cols = cols;
+  p.nbits = q->nbits;
+  p.dst = reinterpret_cast<uint32_t*>(dst);
+  p.ld = row_codes_ld(cols) / 2;                     // words of both bytes
+  p.qmax = (1u << q->nbits) - 1u;
+  p.qmaxf = (float)p.qmax;
+  p.lo = (float)q->lo;
+  p.inv = qgtc_quant_inv_scale(q->lo, q->hi, q->nbits);
+  const int quads = (int)(p.ld / 2);
+  ProfScope prof(QGTC_KERNEL_PACK, stream);
+  hipLaunchKernelGGL(pack_wide_rows_kernel, dim3((unsigned)cdiv((int64_t)rows * quads, 256)), dim3(256), 0, stream, p, quads);
+  return launch_status();
 }
 
 }  // namespace qgtc
@@ -547,7 +588,9 @@ extern "C" qgtc_status qgtc_pack_weights(const qgtc_weight_source* ws, int32_t n
     const qgtc_status st = check_bits(ws[i].dst, QGTC_RIGHT_BYTES);
     if (st != QGTC_OK) return st;
     if (ws[i].ld_src < ws[i].dst->cols || !(ws[i].q.hi > ws[i].q.lo)) return QGTC_ERR_SHAPE;
-    if (ws[i].q.nbits != ws[i].dst->nbits) return QGTC_ERR_BITWIDTH;
+    // (bytes 0 and 1 of codes of up to 16 bits)
+    const int shift = ws[i].shift, left = ws[i].q.nbits - shift;
+    if ((shift != 0 && shift != 8) || ws[i].q.nbits > 16 || ws[i].dst->nbits != (left < 8 ? left : 8)) return QGTC_ERR_BITWIDTH;
   }
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   for (int i0 = 0; i0 < n; i0 += kWeightJobs) {
@@ -566,7 +609,8 @@ extern "C" qgtc_status qgtc_pack_weights(const qgtc_weight_source* ws, int32_t n
       p.dst = dst->data;
       p.ld = dst->ld_words;
       p.ps = dst->plane_stride_words;
-      p.qmax = (1u << dst->nbits) - 1u;
+      p.shift = w.shift;
+      p.qmax = (1u << w.q.nbits) - 1u;
       p.qmaxf = (float)p.qmax;
       p.lo = (float)w.q.lo;
       p.inv = qgtc_quant_inv_scale(w.q.lo, w.q.hi, w.q.nbits);

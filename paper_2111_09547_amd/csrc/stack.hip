@@ -395,3 +395,100 @@ extern "C" qgtc_status qgtc_stack_forward_update_first(const qgtc_stack* st, con
                      codes[(l + 1) & 1], nullptr, 0, s);
   return rc == QGTC_OK ? gather_sums(&sums, s) : rc;
 }
+
+static size_t wide_bytes_needed(int rows, int cols) { return (size_t)rows * 2 * (size_t)row_codes_ld(cols); }
+
+extern "C" qgtc_status qgtc_wide_input(const float* src, int32_t rows, int32_t cols, int64_t ld_src, const qgtc_quant* q, void* buffer,
+                                       size_t buffer_bytes, void* stream) {
+  if (!src || !q || !buffer) return QGTC_ERR_NULL;
+  if (rows < 0 || cols < 0 || ld_src < cols || !(q->hi > q->lo)) return QGTC_ERR_SHAPE;
+  if (rows >= 1 << 24 || cols > 512) return QGTC_ERR_UNSUPPORTED;
+  if (q->nbits < 9 || q->nbits > 16) return QGTC_ERR_BITWIDTH;
+  if (((uintptr_t)buffer & 15u) != 0) return QGTC_ERR_ALIGN;
+  if (buffer_bytes < wide_bytes_needed(rows, cols)) return QGTC_ERR_WORKSPACE;
+  if (rows == 0 || cols == 0) return QGTC_OK;
+  return pack_wide_rows(src, ld_src, rows, cols, q, reinterpret_cast<uint8_t*>(buffer), reinterpret_cast<hipStream_t>(stream));
+}
+
+extern "C" qgtc_status qgtc_wide_forward(const qgtc_wide_stack* st, const float* src, int64_t ld_src, const qgtc_quant* q,
+                                         const qgtc_bits* X, void* out, int64_t ld_out, void* stream) {
+  if (!st || !st->A || !st->lists || !st->layers || !st->buffer[0] || !st->buffer[1]) return QGTC_ERR_NULL;
+  if (st->n_layers < 1) return QGTC_ERR_SHAPE;
+  qgtc_status rc = check_adjacency(st->A);
+  if (rc != QGTC_OK) return rc;
+  const int rows = st->A->rows;
+  if (st->A->block_rows == 0 && st->A->cols != rows) return QGTC_ERR_SHAPE;
+  if ((((uintptr_t)st->buffer[0] | (uintptr_t)st->buffer[1]) & 15u) != 0) return QGTC_ERR_ALIGN;
+  if (st->s < 9 || st->s > 16) return QGTC_ERR_BITWIDTH;
+  auto scale_ok = [](float v) { return v > 0.0f && v < INFINITY; };
+  for (int l = 0; l < st->n_layers; ++l) {
+    const qgtc_wide_layer& y = st->layers[l];
+    const bool last = l == st->n_layers - 1, high = y.W[1].data != nullptr;
+    for (int i = 0; i < (high ? 2 : 1); ++i) {
+      rc = check_bits(&y.W[i], QGTC_RIGHT_BYTES);
+      if (rc != QGTC_OK) return rc;
+    }
+    if (high && (y.W[1].rows != y.W[0].rows || y.W[1].cols != y.W[0].cols)) return QGTC_ERR_SHAPE;
+    // (one distance between the two parts of a block for both)
+    if (high && y.W[1].nbits == 8 && y.W[1].plane_stride_words != y.W[0].plane_stride_words) return QGTC_ERR_SHAPE;
+    if (high && y.W[0].nbits != 8) return QGTC_ERR_BITWIDTH;
+    if (l > 0 && y.W[0].rows != st->layers[l - 1].W[0].cols) return QGTC_ERR_SHAPE;
+    if (y.W[0].rows < 1 || y.W[0].rows > 512 || y.W[0].cols < 1 || y.W[0].cols > 256) return QGTC_ERR_UNSUPPORTED;
+    if (y.first.mode != QGTC_OUT_BITS || (last ? y.second.mode == QGTC_OUT_BITS : y.second.mode != QGTC_OUT_BITS)) return QGTC_ERR_UNSUPPORTED;
+    if (y.first.col_scale || y.first.col_shift) return QGTC_ERR_UNSUPPORTED;   // the affine map belongs to second
+    if (y.second.col_shift && !y.second.col_scale) return QGTC_ERR_NULL;
+    if (y.second.self_term) return QGTC_ERR_SHAPE;
+    if (y.first.rq_nbits < 9 || y.first.rq_nbits > 16 || (!last && y.second.rq_nbits != st->s)) return QGTC_ERR_BITWIDTH;
+    if (!scale_ok(y.first.rq_inv_scale) || (!last && !scale_ok(y.second.rq_inv_scale))) return QGTC_ERR_SHAPE;
+    rc = check_tuning(y.second.tuning);
+    if (rc != QGTC_OK) return rc;
+    if (st->buffer_bytes < wide_bytes_needed(rows, y.W[0].rows)) return QGTC_ERR_WORKSPACE;
+  }
+  if (rows >= 1 << 24 || st->A->ld_words >= 1 << 24) return QGTC_ERR_UNSUPPORTED;
+  if (src && q && q->nbits != st->s) return QGTC_ERR_BITWIDTH;
+  if (src) X = nullptr;                              // the features come first
+  if (X) {
+    rc = check_bits(X, QGTC_RIGHT);
+    if (rc != QGTC_OK) return rc;
+    if (X->rows != rows || X->cols != st->layers[0].W[0].rows) return QGTC_ERR_SHAPE;
+    if (X->nbits != st->s) return QGTC_ERR_BITWIDTH;
+  }
+  if (rows == 0) return QGTC_OK;
+  if (!out) return QGTC_ERR_NULL;
+  rc = check_neighbours(st->lists, st->A);
+  if (rc != QGTC_OK) return rc;
+  const qgtc_wide_layer& end = st->layers[st->n_layers - 1];
+  EpiParams last_ep{};
+  rc = make_epilogue(&end.second, out, ld_out, rows, end.W[0].cols, QGTC_RIGHT, false, &last_ep);
+  if (rc != QGTC_OK) return rc;
+  if (src) {
+    rc = qgtc_wide_input(src, rows, st->layers[0].W[0].rows, ld_src, q, st->buffer[0], st->buffer_bytes, stream);
+    if (rc != QGTC_OK) return rc;
+  }
+  if (X) {
+    rc = planes_to_rows(X, reinterpret_cast<uint8_t*>(st->buffer[0]), reinterpret_cast<hipStream_t>(stream));
+    if (rc != QGTC_OK) return rc;
+  }
+  uint8_t* const codes[2] = {reinterpret_cast<uint8_t*>(st->buffer[0]), reinterpret_cast<uint8_t*>(st->buffer[1])};
+  for (int l = 0; l < st->n_layers; ++l) {
+    const qgtc_wide_layer& y = st->layers[l];
+    const bool last = l == st->n_layers - 1;
+    GatherParams p = list_operands(st->A, st->lists, codes[l & 1], y.W[0].rows, 8);
+    p.ldx *= 2;
+    p.self_term = y.first.self_term ? 1 : 0;
+    p.agg_lo = y.first.rq_lo;
+    p.agg_relu = y.first.relu ? 1 : 0;
+    p.agg_nbits = y.first.rq_nbits;
+    p.agg_inv = y.first.rq_inv_scale;
+    if (last) {
+      p.up = last_ep;
+    } else {
+      codes_out(&p, y.second, y.W[0].cols, codes[(l + 1) & 1]);
+      p.up.ld_out *= 2;
+    }
+    rc = gather_wide_layer(&p, last ? kGatherRows : (p.up.col_a ? kGatherAffine : kGatherCodes), &y.W[0], y.W[1].data ? &y.W[1] : nullptr,
+                           reinterpret_cast<hipStream_t>(stream));
+    if (rc != QGTC_OK) return rc;
+  }
+  return QGTC_OK;
+}

@@ -116,7 +116,7 @@ class QuantGNN:
         # for the two-kernel path.
         self.w_layout = [B.RIGHT_BYTES if weights_as_bytes and fused_layer_applies(d, h, s, t) else B.RIGHT
                          for d, h in self.dims]
-        self.W = [B.alloc_bits(d, h, t, lay) for (d, h), lay in zip(self.dims, self.w_layout)]
+        self._W_ops = [B.alloc_bits(d, h, t, lay) for (d, h), lay in zip(self.dims, self.w_layout)]
         self._W_planes = None
         n = self.A.rows
         dmax = max(d for d, _ in self.dims)
@@ -141,7 +141,11 @@ class QuantGNN:
         # Neighbour lists in place of products with whole tiles of A where they pay (lists=None; the bits of A
         # are counted once), or as the caller says.  The results are the same.
         self.lists = None
-        whole = self._fused or (update_first and all(fused_layer_applies(d, h, s, t) for d, h in self.dims) and
+        # 9 to 16 bits over lists: codes as two bytes, where lists pay for bytes (planes lose more there: an
+        # aggregation reads s of them, an update multiplies s * t; 64 -> 64 on 8192 rows, 16 bits: 54 us, and 18)
+        wide = not update_first and n < 1 << 24 and self.A.c.ld_words < 1 << 24 and 9 <= s <= 16 and t <= 16 and all(d <= 512 and h <= 256 for d, h in self.dims) and \
+            (self.tuning is None or self.tuning.layer_path == B.LAYER_FUSED) and all(W.dtype == torch.float32 for W in self.Ws)
+        whole = self._fused or wide or (update_first and all(fused_layer_applies(d, h, s, t) for d, h in self.dims) and
                                 (self.tuning is None or self.tuning.layer_path == B.LAYER_FUSED))
         if whole and lists is not False and (lists or self.plan is not None) and B.neighbours_bytes(self.A) > 0:
             if self.plan is None and self.A_src is not None:
@@ -151,6 +155,12 @@ class QuantGNN:
             dims = [(h, h) for _, h in self.dims] if update_first else self.dims
             if lists or B.qgtc_neighbours_pay(self.A, int(built.deg.sum(dtype=torch.int64)), dims):
                 self.lists, self._lists_of = built, self.A
+        self._wide = wide and self.lists is not None
+        if self._wide:
+            nbytes = max(2 * n * 16 * (-(-d // 16)) for d, _ in self.dims)
+            self._codes = [torch.empty(max(nbytes // 4, 4), dtype=torch.int32, device=self.A.words.device) for _ in range(2)]
+            self._W_low = [B.alloc_bits(d, h, min(t, 8), B.RIGHT_BYTES) for d, h in self.dims]
+            self._W_high = [B.alloc_bits(d, h, t - 8, B.RIGHT_BYTES) if t > 8 else None for d, h in self.dims]
         if update_first and self.lists is not None:
             nbytes = max(B.lib().qgtc_stack_buffer_bytes(n, h) for _, h in self.dims)
             self._codes = [torch.empty(max(nbytes // 4, 4), dtype=torch.int32, device=self.A.words.device) for _ in range(2)]
@@ -187,30 +197,51 @@ class QuantGNN:
             self.deg = B.qgtc_row_sums(self.A)
 
     def _pack_weights_and(self, X, x_range):
-        if all(lay == B.RIGHT_BYTES for lay in self.w_layout) and all(W.dtype == torch.float32 and W.is_contiguous() for W in self.Ws):
-            key = [(W.data_ptr(), o.c.data, *r) for W, o, r in zip(self.Ws, self.W, self.w_ranges)]
+        if self._wide:
+            high = [W for W in self._W_high if W is not None]
+            key = [(W.data_ptr(), *r) for W, r in zip(self.Ws, self.w_ranges)]
             if getattr(self, "_w_sources", (None,))[0] != key:
-                self._w_sources = (key, B.WeightSources(self.Ws, self.w_ranges, self.W))
+                twice = 2 if high else 1
+                self._w_sources = (key, B.WeightSources(self.Ws * twice, self.w_ranges * twice, self._W_low + high, self.t,
+                                                        [0] * len(self.Ws) + [8] * len(high)))
+            B.qgtc_pack_weights(self._w_sources[1], len(self.dims) - 1, self._w_colsum_buf)
+            self.w_colsum = [None] * (len(self.dims) - 1) + [self._w_colsum_buf]
+        elif all(lay == B.RIGHT_BYTES for lay in self.w_layout) and all(W.dtype == torch.float32 and W.is_contiguous() for W in self.Ws):
+            key = [(W.data_ptr(), o.c.data, *r) for W, o, r in zip(self.Ws, self._W_ops, self.w_ranges)]
+            if getattr(self, "_w_sources", (None,))[0] != key:
+                self._w_sources = (key, B.WeightSources(self.Ws, self.w_ranges, self._W_ops))
             # only the last layer dequantizes, so only its column sums are needed
-            B.qgtc_pack_weights(self._w_sources[1], len(self.W) - 1, self._w_colsum_buf)
-            self.w_colsum = [None] * (len(self.W) - 1) + [self._w_colsum_buf]
+            B.qgtc_pack_weights(self._w_sources[1], len(self.dims) - 1, self._w_colsum_buf)
+            self.w_colsum = [None] * (len(self.dims) - 1) + [self._w_colsum_buf]
         else:
-            for W, r, dst, lay in zip(self.Ws, self.w_ranges, self.W, self.w_layout):
+            for W, r, dst, lay in zip(self.Ws, self.w_ranges, self._W_ops, self.w_layout):
                 B.qgtc_pack_bits(W, self.t, lay, quant=r, out=dst)
-            self.w_colsum = [None] * (len(self.W) - 1) + [B.qgtc_col_sums(self.W[-1], out=self._w_colsum_buf)]
+            self.w_colsum = [None] * (len(self.dims) - 1) + [B.qgtc_col_sums(self._W_ops[-1], out=self._w_colsum_buf)]
         if self.update_first and self.lists is not None:
             for W, r, dst in zip(self.Ws, self.w_ranges, self._W_bytes):
                 B.qgtc_pack_bits(W, self.t, B.RIGHT_BYTES, quant=r, out=dst)
         if X is not None and not self.update_first:
-            if self._fused and X.dtype == torch.float32:
+            if (self._fused or self._wide) and X.dtype == torch.float32:
                 assert tuple(X.shape) == (self.A.rows, self.dims[0][0])
                 self._pack_codes(X, x_range)
             else:
                 self.pack_input(X, x_range)
 
     # -- helpers -----------------------------------------------------------------
+    @property
+    def W(self):
+        """The packed weights as the layers by themselves take them (pack_static() of a network whose codes are
+        two bytes has not made them)."""
+        if self._wide:
+            for W, r, dst in zip(self.Ws, self.w_ranges, self._W_ops):
+                B.qgtc_pack_bits(W, self.t, B.RIGHT, quant=r, out=dst)
+        return self._W_ops
+
     def _pack_codes(self, X, x_range):
-        B.qgtc_stack_input(X, self.s, x_range, self._codes[0], rows_form=self.lists is not None)
+        if self._wide:
+            B.qgtc_wide_input(X, self.s, x_range, self._codes[0])
+        else:
+            B.qgtc_stack_input(X, self.s, x_range, self._codes[0], rows_form=self.lists is not None)
         self._x_form = "codes"
 
     def _alloc_planes(self):
@@ -327,7 +358,7 @@ class QuantGNN:
             xl = B.qgtc_pack_bits(X, self.s, B.LEFT_BYTES, quant=x_range, out=self._x_bytes)
         else:
             xl = B.qgtc_pack_bits(X, self.s, B.LEFT, quant=x_range, out=self._xl_view(0, X.shape[1]))
-        n_layers = len(self.W)
+        n_layers = len(self.dims)
         x_scale = (float(x_range[1]) - float(x_range[0])) / float(2 ** self.s)
         for l, W in enumerate(self.W):
             d, h = self.dims[l]
@@ -406,7 +437,7 @@ class QuantGNN:
             agg_hi = max(1, int(y32.max()))
             yb = B.qgtc_aggregate(self.A, self.map, xb, self._agg_ep(agg_hi))
             z32 = B.qgtc_update(yb, W, B.Epilogue(mode=B.OUT_I32))
-            last = l == len(self.W) - 1
+            last = l == len(self.dims) - 1
             if last:
                 ranges.append(LayerRanges(agg_hi, None))
                 break
@@ -455,19 +486,20 @@ class QuantGNN:
                 return out
             return self._forward_update_first(X, x_range, ranges, out, want_int)
         # (planes of another width than the network's go layer by layer: their first layer is another one)
-        if self._fused and (x_bits.nbits == self.s if x_bits is not None else x_packed or X.dtype == torch.float32):
+        if (self._fused or self._wide) and (x_bits.nbits == self.s if x_bits is not None else x_packed or X.dtype == torch.float32):
             # one run whatever `streams` says
             if not isinstance(streams, int) and self.A.c.block_rows > 0:
                 assert sum(streams) >= -(-n // self.A.c.block_rows)
             assert x_bits is None or (isinstance(streams, int) and streams <= 1)
             stack = self._stack(x_range, ranges, want_int)
+            run = B.qgtc_wide_forward if self._wide else B.qgtc_stack_forward
             if x_bits is not None:
-                B.qgtc_stack_forward(stack, out, X=x_bits)
+                run(stack, out, X=x_bits)
             elif x_packed:
-                B.qgtc_stack_forward(stack, out, X=self._x_view(0, self.dims[0][0]) if self._x_form == "planes" else None)
+                run(stack, out, X=self._x_view(0, self.dims[0][0]) if self._x_form == "planes" else None)
             else:
                 self._x_form = "codes"
-                B.qgtc_stack_forward(stack, out, src=X, quant=x_range)
+                run(stack, out, src=X, quant=x_range)
             return out
         if x_bits is not None:
             assert isinstance(streams, int) and streams <= 1
@@ -573,16 +605,20 @@ class QuantGNN:
         """The prepared native call for these ranges (a caller's handful of them is kept).  An entry
         holds on to the operands that its key names, so that none of them can be another one by now."""
         key = (float(x_range[0]), float(x_range[1]), bool(want_int), tuple(vars(self.tuning).values()) if self.tuning else None, *self.w_ranges,
-               self.self_term, id(self.A), id(self.map), id(self.lists), self.deg.data_ptr(), *map(id, self.W), *map(id, self.batchnorm),
+               self.self_term, id(self.A), id(self.map), id(self.lists), self.deg.data_ptr(), *map(id, self._W_ops), *map(id, self.batchnorm),
                *[(r.agg_hi, r.out_hi) for r in ranges])
         if self.lists is not None and self._lists_of is not self.A:      # (replaced, and not packed since)
             B.qgtc_build_neighbours(self.A, self.lists)
             self._lists_of = self.A
         stack = self._stacks.get(key)
         if stack is None:
-            Ws = self._W_bytes if self.update_first else self.W
+            Ws = self._W_bytes if self.update_first else self._W_ops
             layers = [(W, first, second) for W, (first, second) in zip(Ws, self._epilogues(x_range, ranges, want_int))]
-            stack = B.Stack(self.A, self.map, layers, self.s, self._codes, self.lists)
+            if self._wide:
+                stack = B.WideStack(self.A, [((lo, hi), f, sec) for lo, hi, (_, f, sec) in zip(self._W_low, self._W_high, layers)],
+                                    self.s, self._codes, self.lists)
+            else:
+                stack = B.Stack(self.A, self.map, layers, self.s, self._codes, self.lists)
             if len(self._stacks) >= 8:
                 self._stacks.pop(next(iter(self._stacks)), None)
             self._stacks[key] = stack
@@ -595,7 +631,7 @@ class QuantGNN:
         x_scale = (float(x_range[1]) - float(x_range[0])) / float(2 ** self.s)
         out = []
         for l, r in enumerate(ranges):
-            last = l == len(self.W) - 1
+            last = l == len(self.dims) - 1
             first, second, z_scale, x_next = self._layer_eps(l, x_lo, x_scale, r.agg_hi, r.out_hi, last)
             if self.update_first:                    # codes read as pure scales throughout
                 x_scale = x_next
@@ -619,7 +655,7 @@ class QuantGNN:
     def _run_layers(self, r0, r1, A, tmap, deg, xb, x_range, ranges, out, want_int, workspace):
         """All layers on rows [r0, r1) (whole subgraphs), on the current stream."""
         for l, (W, (first, second)) in enumerate(zip(self.W, self._epilogues(x_range, ranges, want_int))):
-            if l < len(self.W) - 1:
+            if l < len(self.dims) - 1:
                 xb = B.qgtc_layer(A, tmap, xb, W, first, second, workspace,
                                   out=self._x_rows((l + 1) & 1, self.dims[l][1], r0, r1))
             else:

@@ -1,6 +1,7 @@
 """Neighbour lists: what they hold, and layers over them against the oracle and against whole tiles."""
 import numpy as np
 import pytest
+import scipy.sparse as sp
 import torch
 
 from oracle import qgnn
@@ -10,7 +11,7 @@ pytestmark = pytest.mark.gpu
 
 q = pytest.importorskip("paper_2111_09547_amd")
 import paper_2111_09547_amd.binding as B  # noqa: E402
-from paper_2111_09547_amd.model import QuantGNN  # noqa: E402
+from paper_2111_09547_amd.model import BatchNorm, QuantGNN  # noqa: E402
 from gpu_util import dev, as_u32  # noqa: E402
 
 
@@ -171,3 +172,63 @@ def test_update_first_over_lists(blocks, block, short, dims, s, t, gin):
         assert int((want != 0).sum()) > 0
         assert torch.equal(nets[0].forward(x, xr, ranges, want_int=ints), want)
         assert torch.equal(nets[0].forward(wide[:, 1:1 + d[0]], xr, ranges, want_int=ints), want)
+
+
+@pytest.mark.parametrize("blocks,block,short,dims,s,t,gin", [
+    (3, 64, 5, "1-2-3", 9, 1, True),                 # a piece of one column, one byte of weights
+    (5, 96, 31, "17-33-16", 12, 9, False),           # two pieces, of which one column; a bit of the weights' second byte
+    (3, 160, 33, "64-65-47", 16, 8, True),           # four waves per tile
+    (2, 1024, 1, "130-129-7", 16, 16, False),
+    (2, 288, 3, "300-101-5", 16, 12, False),         # two parts of 256 columns
+    (1, 640, 40, "512-256-16", 16, 16, True),        # more weights than LDS keeps
+    (130, 256, 77, "64-64-12", 16, 16, True),        # a tile per wave
+    (130, 256, 0, "300-16-100", 10, 15, False),
+    (40, 1024, 0, "16-16-32", 16, 16, True),
+])
+def test_codes_of_two_bytes_over_lists(blocks, block, short, dims, s, t, gin):
+    """9 to 16 bits: the oracle's integers (modulo 2^32), and the planes' results, also with batch normalization."""
+    rng = np.random.default_rng(blocks + block + s)
+    d = [int(v) for v in dims.split("-")]
+    a, _ = block_graph(rng, blocks, block, short, 20.0)
+    n = a.shape[0]
+    for r, want in zip([0, n // 2, n - 1], (65, 256, 700)):
+        r0 = r // block * block
+        a[r, rng.choice(min(block, n - r0), min(want, block, n - r0), replace=False)] = 1
+    r, c = np.nonzero(a)
+    csr = sp.csr_matrix((np.ones(len(r), np.int64), (r, c + r // block * block)), shape=(n, n))
+    X = rng.standard_normal((n, d[0])).astype(np.float32)
+    Ws = [rng.uniform(-0.5, 0.5, dh).astype(np.float32) for dh in zip(d[:-1], d[1:])]
+    xr, x = (-3.0, 3.0), dev(X)
+    wr = [(float(W.min()), float(W.max())) for W in Ws]
+    norms = [BatchNorm(*(rng.uniform(0.5, 1.5, h).tolist() for _ in range(4))) for h in d[1:-1]] + [None]
+    for bn in (None, norms):
+        net, tiles = (QuantGNN(dev(a), [dev(W) for W in Ws], s, t, gin, block_rows=block, lists=lists, batchnorm=bn) for lists in (True, False))
+        assert net.lists is not None and tiles.lists is None
+        ranges = tiles.calibrate(x, xr)
+        assert net.calibrate(x, xr) == ranges
+        out, ints = tiles.forward(x, xr, ranges), tiles.forward(x, xr, ranges, want_int=True)
+        assert torch.equal(net.forward(x, xr, ranges, x_packed=True), out)     # as calibrate() left them: planes
+        assert torch.equal(net.forward(x, xr, ranges), out)
+        assert torch.equal(net.forward(x, xr, ranges, want_int=True), ints)
+        if bn is None:
+            rqs = [((0, qgnn.inv_scale(0.0, float(r.agg_hi), s)),
+                    None if r.out_hi is None else (0, qgnn.inv_scale(0.0, float(r.out_hi), s))) for r in ranges]
+            _, trace, _ = qgnn.forward_dequantized(csr, X, xr, Ws, wr, s, t, gin, rqs=rqs)
+            assert (as_u32(ints) == trace[-1]["Z"]).all()
+    planes = q.qgtc_pack_bits(x, s, q.RIGHT, quant=xr)
+    assert torch.equal(net.forward(None, xr, ranges, x_bits=planes), out)
+    codes = dev(np.clip(np.floor((X.astype(np.float64) + 3.0) / 6.0 * 2 ** s), 0, 2 ** s - 1).astype(np.int32))
+    assert torch.equal(net.forward(codes, xr, ranges), tiles.forward(codes, xr, ranges))
+    for old, new in zip(net.Ws, Ws):                 # other weights in place, as a recorded step meets them
+        old.copy_(dev(new[::-1].copy()))
+    net.pack_static(x, xr)
+    for old in tiles.Ws:
+        old.copy_(old.flip(0))
+    tiles.pack_static()
+    want = tiles.forward(x, xr, ranges)
+    graph = net.capture(x, xr, ranges, out, with_static=True)
+    for _ in range(3):
+        out.zero_()
+        graph.replay()
+        assert torch.equal(net.forward(x, xr, ranges), want)
+        assert torch.equal(out, want)
