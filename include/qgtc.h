@@ -341,6 +341,13 @@ qgtc_status qgtc_aggregate(const qgtc_bits* A, const qgtc_tile_map* map,
                            const qgtc_bits* X, const qgtc_epilogue* ep,
                            void* out, int64_t ld_out, void* stream);
 
+/* The same with room for X as codes, which long rows are faster with: qgtc_aggregate_workspace_bytes (0: not used)
+ * of them, 16-byte aligned, written on `stream`.  workspace == NULL: qgtc_aggregate. */
+size_t qgtc_aggregate_workspace_bytes(const qgtc_bits* A, const qgtc_bits* X);
+qgtc_status qgtc_aggregate_ws(const qgtc_bits* A, const qgtc_tile_map* map,
+                              const qgtc_bits* X, const qgtc_epilogue* ep, void* workspace,
+                              size_t workspace_bytes, void* out, int64_t ld_out, void* stream);
+
 /* 1 if qgtc_aggregate of this A with x_cols columns would look at a tile map, 0 if not (rows too
  * short for the list of their tiles to save anything: a map need not be built for the call). */
 int32_t qgtc_aggregate_reads_map(const qgtc_bits* A, int32_t x_cols);

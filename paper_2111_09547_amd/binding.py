@@ -165,6 +165,8 @@ def lib():
         "qgtc_neighbours_pay": (i32, [P(_BitsC), i64, P(i32), i32]),
         "qgtc_build_neighbours": (C.c_int, [P(_BitsC), P(_NeighboursC), P(_TileMapC), vp]),
         "qgtc_aggregate": (C.c_int, [P(_BitsC), P(_TileMapC), P(_BitsC), P(_EpilogueC), vp, i64, vp]),
+        "qgtc_aggregate_workspace_bytes": (sz, [P(_BitsC), P(_BitsC)]),
+        "qgtc_aggregate_ws": (C.c_int, [P(_BitsC), P(_TileMapC), P(_BitsC), P(_EpilogueC), vp, sz, vp, i64, vp]),
         "qgtc_update": (C.c_int, [P(_BitsC), P(_BitsC), P(_EpilogueC), vp, i64, vp]),
         "qgtc_layer_workspace_bytes": (sz, [i32, i32, i32, i32]),
         "qgtc_layer": (C.c_int, [P(_BitsC), P(_TileMapC), P(_BitsC), P(_BitsC), P(_EpilogueC),
@@ -477,8 +479,15 @@ def qgtc_aggregate(A: Bits, tmap: TileMap | None, X: Bits, ep: Epilogue, out=Non
     res, ptr, ld = _out_arg(ep, A.rows, X.cols, out, LEFT, X.words.device)
     epc = ep.to_c()
     m = C.byref(tmap.c) if tmap is not None else None
-    _check(lib().qgtc_aggregate(C.byref(A.c), m, C.byref(X.c), C.byref(epc), ptr, ld, _stream()),
-           "qgtc_aggregate")
+    # (no rows of 2048 columns or less are long; the question costs a microsecond)
+    nbytes = lib().qgtc_aggregate_workspace_bytes(C.byref(A.c), C.byref(X.c)) if A.c.cols > 2048 else 0
+    if nbytes:
+        ws = torch.empty(nbytes, dtype=torch.uint8, device=X.words.device)
+        _check(lib().qgtc_aggregate_ws(C.byref(A.c), m, C.byref(X.c), C.byref(epc), ws.data_ptr(), nbytes, ptr, ld, _stream()),
+               "qgtc_aggregate")
+    else:
+        _check(lib().qgtc_aggregate(C.byref(A.c), m, C.byref(X.c), C.byref(epc), ptr, ld, _stream()),
+               "qgtc_aggregate")
     return res
 
 

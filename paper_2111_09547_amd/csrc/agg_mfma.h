@@ -429,7 +429,8 @@ __device__ __forceinline__ void agg_run(const AggParams& p, const AggWave& w, ui
   const int ln = lane & 15, g = lane >> 4;
   const int np = min(p.s - plane0, 8);
   const bool offset = np == 8;
-  const uint16_t* list = p.list_off ? reinterpret_cast<const uint16_t*>(lds + p.list_off) : nullptr;
+  // (a list of all chunks is the same without it)
+  const uint16_t* list = p.list_off && w.n_list != p.n_chunks ? reinterpret_cast<const uint16_t*>(lds + p.list_off) : nullptr;
   const int n_st = (w.n_list + TSC - 1) / TSC;
   const int x_last = p.sub_per_wg > 1 ? TSC - 1 : w.n_list - 1;
   const int c_wave = w.kp * SWC;                     // the wave's first chunk of a stage

@@ -7,7 +7,40 @@
 namespace qgtc {
 namespace {
 
-template <int CT, int WAYS, int KS, int NPT, bool MULTI>
+// Bytes of a column group of codes.
+int64_t codes_group_bytes(int kwords, int lt) { return (int64_t)kwords * 512 * lt; }
+
+struct CodesParams {
+  const uint32_t* X;
+  int64_t ld, ps;
+  int32_t s, cols, kwords;
+  uint8_t* dst;
+  int64_t cg_bytes;          // of a column group
+  uint32_t flip;
+};
+
+// Planes to codes in the staged order of agg_run(): a thread has 32 rows of a column.  Bound by its launch
+// (16384 x 256 of 4 bits: 2 MB in, 4 MB out).
+template <int LT>
+__global__ __launch_bounds__(256) void planes_to_codes_kernel(const CodesParams p) {
+  constexpr int G = 16 * LT, KB = 512 * LT;
+  const unsigned idx = blockIdx.x * 256u + threadIdx.x, cg = blockIdx.y;
+  const int kw = (int)(idx / G), c = (int)(idx % G);
+  if (kw >= p.kwords) return;
+  const uint32_t* const from = p.X + (int64_t)kw * p.ld + min((int)cg * G + c, p.cols - 1);
+  uint32_t a[8];
+#pragma unroll
+  for (int pl = 0; pl < 8; ++pl) {
+    a[pl] = 0u;
+    if (pl < p.s) a[pl] = from[(int64_t)pl * p.ps];
+  }
+  planes_word_to_codes(a);
+  uint8_t* const to = p.dst + (int64_t)cg * p.cg_bytes + (int64_t)kw * KB + staged_pos<LT>(c) * 16;
+  *reinterpret_cast<v4u*>(to) = (v4u){a[0], a[1], a[2], a[3]} ^ p.flip;
+  *reinterpret_cast<v4u*>(to + LT * 256) = (v4u){a[4], a[5], a[6], a[7]} ^ p.flip;
+}
+
+template <int CT, int WAYS, int KS, int SRC, int NPT, bool MULTI>
 __global__ __launch_bounds__(512) void aggregate_kernel(const AggParams p) {
   extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
   constexpr int LC = 4 * CT;                         // columns of a lane
@@ -23,7 +56,7 @@ __global__ __launch_bounds__(512) void aggregate_kernel(const AggParams p) {
   uint32_t y[4][LC];
   for (int plane0 = 0; plane0 < (MULTI ? p.s : 1); plane0 += 8) {
     if (MULTI && plane0 > 0) __syncthreads();        // every wave is through with the slots
-    agg_run<CT, WAYS, CT, KS, kSrcPlanes, NPT>(p, w, lds, plane0, self_term, [] {}, [] {},
+    agg_run<CT, WAYS, CT, KS, SRC, NPT>(p, w, lds, plane0, self_term, [] {}, [] {},
                                        [&](int, const v4i (&acc)[4][CT], const uint32_t (&deg)[4]) {
 #pragma unroll
       for (int t = 0; t < 4; ++t)
@@ -176,11 +209,11 @@ __global__ __launch_bounds__(512) void aggregate_kernel(const AggParams p) {
   }
 }
 
-template <int CT, int WAYS, int KS, int NPT, bool MULTI>
+template <int CT, int WAYS, int KS, int SRC, int NPT, bool MULTI>
 qgtc_status launch_one(const AggParams& p, size_t lds, hipStream_t stream) {
   static OncePerDevice once;
-  if (!allow_lds(once, reinterpret_cast<const void*>(&aggregate_kernel<CT, WAYS, KS, NPT, MULTI>), lds)) return QGTC_ERR_HIP;
-  hipLaunchKernelGGL((aggregate_kernel<CT, WAYS, KS, NPT, MULTI>), dim3(xcd_deal_grid(p.nblocks, p.run_shift)),
+  if (!allow_lds(once, reinterpret_cast<const void*>(&aggregate_kernel<CT, WAYS, KS, SRC, NPT, MULTI>), lds)) return QGTC_ERR_HIP;
+  hipLaunchKernelGGL((aggregate_kernel<CT, WAYS, KS, SRC, NPT, MULTI>), dim3(xcd_deal_grid(p.nblocks, p.run_shift)),
                      dim3((unsigned)(64 * p.n_waves)), lds, stream, p);
   return launch_status();
 }
@@ -189,10 +222,32 @@ template <int CT, int WAYS, int KS>
 qgtc_status launch(const AggParams& p, size_t lds, hipStream_t stream) {
   const bool multi = p.s > 8;
   switch (agg_items_per_thread(p, AggSplit{CT, WAYS, CT, KS})) {
-    case 1: return multi ? launch_one<CT, WAYS, KS, 1, true>(p, lds, stream) : launch_one<CT, WAYS, KS, 1, false>(p, lds, stream);
-    case 2: return multi ? launch_one<CT, WAYS, KS, 2, true>(p, lds, stream) : launch_one<CT, WAYS, KS, 2, false>(p, lds, stream);
-    default: return multi ? launch_one<CT, WAYS, KS, 4, true>(p, lds, stream) : launch_one<CT, WAYS, KS, 4, false>(p, lds, stream);
+    case 1: return multi ? launch_one<CT, WAYS, KS, kSrcPlanes, 1, true>(p, lds, stream) : launch_one<CT, WAYS, KS, kSrcPlanes, 1, false>(p, lds, stream);
+    case 2: return multi ? launch_one<CT, WAYS, KS, kSrcPlanes, 2, true>(p, lds, stream) : launch_one<CT, WAYS, KS, kSrcPlanes, 2, false>(p, lds, stream);
+    default: return multi ? launch_one<CT, WAYS, KS, kSrcPlanes, 4, true>(p, lds, stream) : launch_one<CT, WAYS, KS, kSrcPlanes, 4, false>(p, lds, stream);
   }
+}
+
+// From codes, which are made first.
+template <int CT, int WAYS, int KS>
+qgtc_status launch_codes(AggParams* p, const qgtc_bits* X, void* workspace, size_t lds, hipStream_t stream) {
+  CodesParams c{};
+  c.X = X->data;
+  c.ld = X->ld_words;
+  c.ps = X->plane_stride_words;
+  c.s = X->nbits;
+  c.cols = X->cols;
+  c.kwords = p->x_kwords;
+  c.dst = reinterpret_cast<uint8_t*>(workspace);
+  c.cg_bytes = codes_group_bytes(p->x_kwords, CT);
+  c.flip = X->nbits == 8 ? 0x80808080u : 0u;
+  hipLaunchKernelGGL(planes_to_codes_kernel<CT>, dim3((unsigned)cdiv((int64_t)c.kwords * 16 * CT, 256), (unsigned)cdiv(c.cols, 16 * CT)), dim3(256),
+                     0, stream, c);
+  const qgtc_status st = launch_status();
+  if (st != QGTC_OK) return st;
+  p->X = reinterpret_cast<const uint32_t*>(workspace);
+  p->x_bytes = (uint32_t)c.cg_bytes;
+  return launch_one<CT, WAYS, KS, kSrcCodes, 1, false>(*p, lds, stream);
 }
 
 }  // namespace
@@ -226,8 +281,30 @@ extern "C" int32_t qgtc_aggregate_reads_map(const qgtc_bits* A, int32_t x_cols) 
   return agg_reads_map(p, sp) ? 1 : 0;
 }
 
-extern "C" qgtc_status qgtc_aggregate(const qgtc_bits* A, const qgtc_tile_map* map, const qgtc_bits* X,
-                                      const qgtc_epilogue* ep, void* out, int64_t ld_out, void* stream) {
+static int64_t codes_bytes(const AggParams& p, const AggSplit& sp) { return codes_group_bytes(p.x_kwords, sp.lt) * cdiv(p.cols, 16 * sp.lt); }
+
+// Whether the features are turned into codes by a launch of their own (3 us) instead of by every workgroup, for
+// whom a stage of planes goes through registers, whose wait is also one for the stage's words of A: from
+// nine stages of K on.  Planes and codes, us:
+//   stages of two chunks: 2048 rows per block (eight stages), 64 columns 19.1 and 17.8, 128 columns 22.8 and 24.2;
+//   3072 x 256 (twelve) 19.8 and 17.8; 8192 x 300 71 and 51; 16384 x 256 112 and 90
+//   of eight, which four waves share: 4096 x 64 (four) 10.4 and 10.7; 8192 x 64 (eight) 18.9 and 18.7, and with
+//   the launch from a script 17.1 and 17.5; 12288 x 16 (twelve) 22.4 and 17.8; 256 x 65536 x 64 94 and 65
+// A codes' column group is addressed with 32 bits; features beyond 256 MiB of codes stay as planes.
+static bool aggregate_from_codes(const AggParams& p, const AggSplit& sp) {
+  return p.s <= 8 && p.a_words > 4 * 8 * sp.chunks() && codes_bytes(p, sp) <= (int64_t)256 << 20;
+}
+
+extern "C" size_t qgtc_aggregate_workspace_bytes(const qgtc_bits* A, const qgtc_bits* X) {
+  AggParams p{};
+  if (!A || !X || A->rows == 0 || X->cols == 0 || agg_fill_params(A, nullptr, X, &p) != QGTC_OK) return 0;
+  const AggSplit sp = aggregate_split(A->rows, X->cols, p.a_words, A->ld_words);
+  return aggregate_from_codes(p, sp) ? (size_t)codes_bytes(p, sp) : 0;
+}
+
+extern "C" qgtc_status qgtc_aggregate_ws(const qgtc_bits* A, const qgtc_tile_map* map, const qgtc_bits* X,
+                                         const qgtc_epilogue* ep, void* workspace, size_t workspace_bytes, void* out,
+                                         int64_t ld_out, void* stream) {
   if (!A || !X || !ep) return QGTC_ERR_NULL;
   AggParams p{};
   qgtc_status st = agg_fill_params(A, map, X, &p);
@@ -244,7 +321,19 @@ extern "C" qgtc_status qgtc_aggregate(const qgtc_bits* A, const qgtc_tile_map* m
   const size_t lds = agg_set_shape(&p, sp, cdiv(X->cols, sp.group()), ep->tuning ? ep->tuning->agg_xcd_run : 0);
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   ProfScope prof(QGTC_KERNEL_AGGREGATE, s);
+  if (workspace && aggregate_from_codes(p, sp)) {
+    if (((uintptr_t)workspace & 15u) != 0) return QGTC_ERR_ALIGN;
+    if (workspace_bytes < (size_t)codes_bytes(p, sp)) return QGTC_ERR_WORKSPACE;
+    if (sp.ct == 2) return launch_codes<2, 2, 1>(&p, X, workspace, lds, s);
+    if (sp.ways == 2) return launch_codes<1, 2, 1>(&p, X, workspace, lds, s);
+    return sp.ks == 4 ? launch_codes<1, 1, 4>(&p, X, workspace, lds, s) : launch_codes<1, 1, 1>(&p, X, workspace, lds, s);
+  }
   if (sp.ct == 2) return launch<2, 2, 1>(p, lds, s);
   if (sp.ways == 2) return launch<1, 2, 1>(p, lds, s);
   return sp.ks == 4 ? launch<1, 1, 4>(p, lds, s) : launch<1, 1, 1>(p, lds, s);
+}
+
+extern "C" qgtc_status qgtc_aggregate(const qgtc_bits* A, const qgtc_tile_map* map, const qgtc_bits* X,
+                                      const qgtc_epilogue* ep, void* out, int64_t ld_out, void* stream) {
+  return qgtc_aggregate_ws(A, map, X, ep, nullptr, 0, out, ld_out, stream);
 }

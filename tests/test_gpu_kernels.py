@@ -873,3 +873,54 @@ def test_aggregate_and_update_on_random_shapes(seed):
     z_inv = qgnn.inv_scale(0.0, float(max(1, qgnn.as_signed(Z).max())), out_bits)
     got = q.qgtc_update(Yb, Wb, q.Epilogue(mode=q.OUT_BITS, rq_nbits=out_bits, rq_lo=0, rq_inv_scale=float(z_inv)))
     assert (words_np(got) == bp.pack(qgnn.requantize(Z, 0, z_inv, out_bits), out_bits, bp.RIGHT)).all(), tag
+
+
+# ------------------------------------------------------------------ long rows: features as codes
+@pytest.mark.parametrize("n,k,d,s,block,density,codes", [
+    (8200, 2049, 257, 8, 0, 0.3, True),        # 17 chunks of K, the last one of a column; two waves of 32 columns
+    (8200, 2048, 257, 8, 0, 0.3, False),
+    (16400, 2500, 33, 3, 0, 0.01, True),       # two waves of 16
+    (8200, 2561, 70, 8, 0, 0.01, True),        # one
+    (700, 8193, 17, 8, 0, 0.3, True),          # four waves share a stage
+    (65, 8192, 1, 1, 0, 0.5, False),
+    (65, 11000, 1, 1, 0, 0.5, True),
+    (4 * 2560 + 100, 2560, 100, 8, 2560, 0.002, True),
+])
+@pytest.mark.parametrize("with_map", [False, True])
+def test_aggregation_of_long_rows(n, k, d, s, block, density, codes, with_map):
+    """Against int64 products of the same integers (below 2^31), and planes against codes for packed results."""
+    import ctypes as C
+    import paper_2111_09547_amd.binding as B
+    gen = torch.Generator(device="cuda").manual_seed(n + k)
+    a = (torch.rand((n, k), generator=gen, device="cuda") < density).to(torch.uint8)
+    a[:, k // 3:k // 3 + 700] = 0                                  # chunks without a bit
+    if block:
+        a[n // block * block:, n % block:] = 0
+    x = torch.randint(0, 1 << s, (n if block else k, d), generator=gen, device="cuda", dtype=torch.int32)
+    A, X = q.qgtc_pack_bits(a, 1, q.LEFT, block_rows=block), q.qgtc_pack_bits(x, s, q.RIGHT)
+    tmap = q.qgtc_build_tile_map(A, 16, 128) if with_map else None
+    assert (B.lib().qgtc_aggregate_workspace_bytes(C.byref(A.c), C.byref(X.c)) > 0) == codes
+    parts = [slice(r, min(r + block, n)) for r in range(0, n, block)] if block else [slice(0, n)]
+    want = torch.cat([a[p, :p.stop - p.start if block else k].double() @ (x[p] if block else x).double() for p in parts]).to(torch.int32)
+    square = block > 0
+    if square:
+        self_ep = q.Epilogue(mode=q.OUT_I32, self_term=True)
+        assert torch.equal(q.qgtc_aggregate(A, tmap, X, self_ep), want + x)
+    assert torch.equal(q.qgtc_aggregate(A, tmap, X, q.Epilogue(mode=q.OUT_I32)), want)
+    ep = q.Epilogue(mode=q.OUT_BITS, rq_nbits=s, rq_lo=0, rq_inv_scale=qgnn.inv_scale(0.0, float(want.max()) + 1, s))
+    got, planes = q.qgtc_aggregate(A, tmap, X, ep), B.alloc_bits(n, d, s, q.LEFT)
+    e = ep.to_c()
+    B._check(B.lib().qgtc_aggregate(C.byref(A.c), C.byref(tmap.c) if tmap else None, C.byref(X.c), C.byref(e), C.byref(planes.c), 0,
+                                    B._stream()), "qgtc_aggregate")
+    assert torch.equal(q.qgtc_unpack_bits(got), q.qgtc_unpack_bits(planes))
+    if with_map:                                                   # the room is the graph's
+        out = torch.empty_like(want)
+        graph = torch.cuda.CUDAGraph()
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph):
+            q.qgtc_aggregate(A, tmap, X, q.Epilogue(mode=q.OUT_I32), out=out)
+        for _ in range(3):
+            out.zero_()
+            graph.replay()
+            assert torch.equal(q.qgtc_aggregate(A, tmap, X, q.Epilogue(mode=q.OUT_I32)), want)
+            assert torch.equal(out, want)
