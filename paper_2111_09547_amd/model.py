@@ -81,7 +81,8 @@ class QuantGNN:
         assert not (update_first and any(b is not None for b in self.batchnorm))
         self._bn_cache = {}
         # update_first: every layer computes A.(X.W) instead of (A.X).W (Section 6.1: GIN
-        # updates before it aggregates); it runs as qgtc_update + qgtc_aggregate on planes
+        # updates before it aggregates); it runs as qgtc_update + qgtc_aggregate on planes, over neighbour
+        # lists as one native call
         self.update_first = update_first
         if update_first:
             weights_as_bytes = False
@@ -233,9 +234,12 @@ class QuantGNN:
         """The packed weights as the layers by themselves take them (pack_static() of a network whose codes are
         two bytes has not made them)."""
         if self._wide:
-            for W, r, dst in zip(self.Ws, self.w_ranges, self._W_ops):
-                B.qgtc_pack_bits(W, self.t, B.RIGHT, quant=r, out=dst)
+            self._pack_w_planes()
         return self._W_ops
+
+    def _pack_w_planes(self):
+        for W, r, dst in zip(self.Ws, self.w_ranges, self._W_ops):
+            B.qgtc_pack_bits(W, self.t, B.RIGHT, quant=r, out=dst)
 
     def _pack_codes(self, X, x_range):
         if self._wide:
@@ -470,7 +474,8 @@ class QuantGNN:
         the drain of one run's kernels overlap with the other runs' work.  A list gives the
         number of subgraphs of each run instead ([48, 16]: the first 48, then 16); "auto"
         takes auto_runs() (resolve it before recording a graph: it reads the tile map back).
-        Everything else is one run, whose launches fill the device by themselves.
+        Everything else is one run, whose launches fill the device by themselves.  (9 to 16 bits over neighbour
+        lists: one run is one native call, which is the faster one; "auto" takes it.)
         x_packed: the features are already packed (pack_static(X, x_range)).
         x_bits: the features as packed planes that live elsewhere (a SubgraphPacket's,
         packed on the host with the same x_range); X is then not read (single run only)."""
@@ -486,27 +491,40 @@ class QuantGNN:
                 return out
             return self._forward_update_first(X, x_range, ranges, out, want_int)
         # (planes of another width than the network's go layer by layer: their first layer is another one)
-        if (self._fused or self._wide) and (x_bits.nbits == self.s if x_bits is not None else x_packed or X.dtype == torch.float32):
+        whole = x_bits.nbits == self.s if x_bits is not None else x_packed or X.dtype == torch.float32
+        if self._fused and whole:
             # one run whatever `streams` says
             if not isinstance(streams, int) and self.A.c.block_rows > 0:
                 assert sum(streams) >= -(-n // self.A.c.block_rows)
             assert x_bits is None or (isinstance(streams, int) and streams <= 1)
             stack = self._stack(x_range, ranges, want_int)
-            run = B.qgtc_wide_forward if self._wide else B.qgtc_stack_forward
             if x_bits is not None:
-                run(stack, out, X=x_bits)
+                B.qgtc_stack_forward(stack, out, X=x_bits)
             elif x_packed:
-                run(stack, out, X=self._x_view(0, self.dims[0][0]) if self._x_form == "planes" else None)
+                B.qgtc_stack_forward(stack, out, X=self._x_view(0, self.dims[0][0]) if self._x_form == "planes" else None)
             else:
                 self._x_form = "codes"
-                run(stack, out, src=X, quant=x_range)
+                B.qgtc_stack_forward(stack, out, src=X, quant=x_range)
             return out
+        one = (isinstance(streams, int) and streams <= 1) or self.A.c.block_rows == 0
+        if self._wide:
+            # One run is one native call as well; runs that the caller asks for go layer by layer on planes, unless
+            # the features are packed as codes already.  The integers are the same.
+            if whole and (one or (x_packed and x_bits is None and self._x_form == "codes")):
+                assert x_bits is None or (isinstance(streams, int) and streams <= 1)
+                if x_bits is None and x_packed:
+                    x = self._x_view(0, self.dims[0][0]) if self._x_form == "planes" else None
+                else:
+                    x = X if x_bits is None else x_bits
+                self._run_layers(0, n, self.A, self.map, self.deg, x, x_range, ranges, out, want_int, None)
+                return out
+            self._pack_w_planes()
         if x_bits is not None:
             assert isinstance(streams, int) and streams <= 1
             xb = x_bits
         else:
             xb = self._x_view(0, X.shape[1]) if x_packed else self.pack_input(X, x_range)
-        if (isinstance(streams, int) and streams <= 1) or self.A.c.block_rows == 0:
+        if one:
             self._run_layers(0, n, self.A, self.map, self.deg, xb, x_range, ranges, out, want_int,
                              self.workspace)
             return out
@@ -572,7 +590,7 @@ class QuantGNN:
             return self._auto_runs
         runs = 1
         br = self.A.c.block_rows
-        if br > 0 and br % 32 == 0 and self.map is not None and not self.update_first:
+        if br > 0 and br % 32 == 0 and not self._wide and self.map is not None and not self.update_first:
             n_blocks = -(-self.A.rows // br)
             votes = {1: 0, 2: 0}
             for l, (d, _) in enumerate(self.dims):
@@ -653,8 +671,15 @@ class QuantGNN:
         return out
 
     def _run_layers(self, r0, r1, A, tmap, deg, xb, x_range, ranges, out, want_int, workspace):
-        """All layers on rows [r0, r1) (whole subgraphs), on the current stream."""
-        for l, (W, (first, second)) in enumerate(zip(self.W, self._epilogues(x_range, ranges, want_int))):
+        """All layers on rows [r0, r1) (whole subgraphs), on the current stream; without a workspace as one
+        native call on codes of two bytes (all rows; xb: planes, fp32 features, or None where the codes are in place)."""
+        if workspace is None:
+            src = xb if isinstance(xb, torch.Tensor) else None
+            if src is not None:
+                self._x_form = "codes"
+            B.qgtc_wide_forward(self._stack(x_range, ranges, want_int), out, src=src, quant=x_range, X=xb if src is None else None)
+            return
+        for l, (W, (first, second)) in enumerate(zip(self._W_ops, self._epilogues(x_range, ranges, want_int))):
             if l < len(self.dims) - 1:
                 xb = B.qgtc_layer(A, tmap, xb, W, first, second, workspace,
                                   out=self._x_rows((l + 1) & 1, self.dims[l][1], r0, r1))
