@@ -486,6 +486,11 @@ qgtc_status qgtc_stack_input(const float* src, int32_t rows, int32_t cols, int64
                              const qgtc_quant* q, void* buffer, size_t buffer_bytes, void* stream);
 qgtc_status qgtc_stack_input_rows(const float* src, int32_t rows, int32_t cols, int64_t ld_src,
                                   const qgtc_quant* q, void* buffer, size_t buffer_bytes, void* stream);
+/* qgtc_stack_input_rows and qgtc_pack_weights in one call, and one launch where that is possible. */
+qgtc_status qgtc_stack_input_and_weights(const float* src, int32_t rows, int32_t cols, int64_t ld_src,
+                                         const qgtc_quant* q, void* buffer, size_t buffer_bytes,
+                                         const qgtc_weight_source* ws, int32_t n, int32_t sums_of,
+                                         int32_t* col_sums, void* stream);
 qgtc_status qgtc_stack_forward(const qgtc_stack* stack, const float* src, int64_t ld_src,
                                const qgtc_quant* q, const qgtc_bits* X, void* out, int64_t ld_out,
                                void* stream);

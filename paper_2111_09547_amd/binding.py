@@ -178,6 +178,7 @@ def lib():
         "qgtc_stack_input": (C.c_int, [vp, i32, i32, i64, P(_QuantC), vp, sz, vp]),
         "qgtc_stack_input_rows": (C.c_int, [vp, i32, i32, i64, P(_QuantC), vp, sz, vp]),
         "qgtc_stack_forward": (C.c_int, [P(_StackC), vp, i64, P(_QuantC), P(_BitsC), vp, i64, vp]),
+        "qgtc_stack_input_and_weights": (C.c_int, [vp, i32, i32, i64, P(_QuantC), vp, sz, P(_WeightSourceC), i32, i32, vp, vp]),
         "qgtc_stack_forward_update_first": (C.c_int, [P(_StackC), vp, i64, P(_QuantC), vp, i64, vp]),
         "qgtc_wide_input": (C.c_int, [vp, i32, i32, i64, P(_QuantC), vp, sz, vp]),
         "qgtc_wide_forward": (C.c_int, [P(_WideStackC), vp, i64, P(_QuantC), P(_BitsC), vp, i64, vp]),
@@ -551,12 +552,19 @@ class Stack:
                          C.pointer(lists.c) if lists is not None else None)
 
 
-def qgtc_stack_input(src: torch.Tensor, nbits: int, quant, buffer: torch.Tensor, rows_form: bool = False):
+def qgtc_stack_input(src: torch.Tensor, nbits: int, quant, buffer: torch.Tensor, rows_form: bool = False, weights=None):
     """Eq. (2) of fp32 features into an activation buffer; rows_form: of a stack with neighbour lists
-    (qgtc_stack_input_rows)."""
+    (qgtc_stack_input_rows), then also with weights: (sources, sums_of, col_sums) of qgtc_pack_weights."""
     assert src.dim() == 2 and src.dtype == torch.float32 and src.is_cuda and src.stride(1) == 1
     rows, cols = src.shape
     q = _QuantC(float(quant[0]), float(quant[1]), nbits)
+    if weights is not None:
+        assert rows_form
+        sources, sums_of, col_sums = weights
+        _check(lib().qgtc_stack_input_and_weights(
+            src.data_ptr(), rows, cols, src.stride(0) if rows > 1 else max(cols, 1), C.byref(q), buffer.data_ptr(),
+            buffer.numel() * buffer.element_size(), sources.c, len(sources.c), sums_of, col_sums.data_ptr(), _stream()), "qgtc_stack_input_and_weights")
+        return
     fn = lib().qgtc_stack_input_rows if rows_form else lib().qgtc_stack_input
     _check(fn(src.data_ptr(), rows, cols, src.stride(0) if rows > 1 else max(cols, 1), C.byref(q),
               buffer.data_ptr(), buffer.numel() * buffer.element_size(), _stream()), "qgtc_stack_input")

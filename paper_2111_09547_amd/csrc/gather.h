@@ -83,6 +83,9 @@ inline uint32_t row_codes_flip(int nbits) { return nbits == 8 ? 0x80808080u : 0u
 // Features to such rows: Eq. (2) of fp32 (pack.hip), from planes (gather.hip).
 qgtc_status pack_row_codes(const float* src, int64_t ld_src, int rows, int cols, const qgtc_quant* q, uint8_t* dst,
                            hipStream_t stream);
+// The same and, in the same launch where the features are read 16 bytes at a time, qgtc_pack_weights.
+qgtc_status pack_row_codes_and_weights(const qgtc_weight_source* ws, int n, int sums_of, int32_t* col_sums, const float* src, int64_t ld_src,
+                                       int rows, int cols, const qgtc_quant* q, uint8_t* dst, hipStream_t stream);
 qgtc_status planes_to_rows(const qgtc_bits* X, uint8_t* dst, hipStream_t stream);
 
 }  // namespace qgtc

@@ -251,6 +251,15 @@ extern "C" qgtc_status qgtc_stack_input_rows(const float* src, int32_t rows, int
   return pack_row_codes(src, ld_src, rows, cols, q, reinterpret_cast<uint8_t*>(buffer), reinterpret_cast<hipStream_t>(stream));
 }
 
+extern "C" qgtc_status qgtc_stack_input_and_weights(const float* src, int32_t rows, int32_t cols, int64_t ld_src, const qgtc_quant* q,
+                                                    void* buffer, size_t buffer_bytes, const qgtc_weight_source* ws, int32_t n,
+                                                    int32_t sums_of, int32_t* col_sums, void* stream) {
+  const qgtc_status st = check_input(src, rows, cols, ld_src, q, buffer, buffer_bytes);
+  if (st != QGTC_OK) return st;
+  return pack_row_codes_and_weights(ws, n, sums_of, col_sums, src, ld_src, rows, cols, q, reinterpret_cast<uint8_t*>(buffer),
+                                    reinterpret_cast<hipStream_t>(stream));
+}
+
 extern "C" qgtc_status qgtc_stack_forward(const qgtc_stack* st, const float* src, int64_t ld_src, const qgtc_quant* q,
                                           const qgtc_bits* X, void* out, int64_t ld_out, void* stream) {
   if (!st || !st->A || !st->layers || !st->buffer[0] || !st->buffer[1]) return QGTC_ERR_NULL;

@@ -212,8 +212,14 @@ class QuantGNN:
             if getattr(self, "_w_sources", (None,))[0] != key:
                 self._w_sources = (key, B.WeightSources(self.Ws, self.w_ranges, self._W_ops))
             # only the last layer dequantizes, so only its column sums are needed
-            B.qgtc_pack_weights(self._w_sources[1], len(self.dims) - 1, self._w_colsum_buf)
+            weights = (self._w_sources[1], len(self.dims) - 1, self._w_colsum_buf)
             self.w_colsum = [None] * (len(self.dims) - 1) + [self._w_colsum_buf]
+            if X is not None and self._fused and self.lists is not None and X.dtype == torch.float32:
+                assert tuple(X.shape) == (self.A.rows, self.dims[0][0])
+                B.qgtc_stack_input(X, self.s, x_range, self._codes[0], rows_form=True, weights=weights)
+                self._x_form = "codes"
+                return
+            B.qgtc_pack_weights(*weights)
         else:
             for W, r, dst, lay in zip(self.Ws, self.w_ranges, self._W_ops, self.w_layout):
                 B.qgtc_pack_bits(W, self.t, lay, quant=r, out=dst)

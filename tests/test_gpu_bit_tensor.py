@@ -131,3 +131,22 @@ def test_weights_of_a_stack_in_one_launch(t, shapes):
     B.qgtc_pack_weights(sources)
     with pytest.raises(q.QgtcError):
         B.qgtc_pack_weights(sources, len(Ws), sums)
+
+
+@pytest.mark.parametrize("n,d,pitch,layers", [(1, 4, 4, 1), (129, 64, 64, 3), (1000, 128, 132, 16), (77, 100, 101, 2), (77, 101, 101, 2), (300, 64, 64, 17)])
+@pytest.mark.parametrize("t", [3, 8])
+def test_features_and_weights_in_one_launch(n, d, pitch, layers, t):
+    """As the two calls, where one launch takes both and where it does not (odd columns or pitch, many weights)."""
+    rng = np.random.default_rng(n + d)
+    x = torch.from_numpy(rng.uniform(-1, 1, (n, pitch)).astype(np.float32)).cuda()[:, :d]
+    Ws = [torch.from_numpy(rng.uniform(-0.5, 0.5, (d + i, 16 + i)).astype(np.float32)).cuda() for i in range(layers)]
+    ranges = [(-0.4, 0.45 + 0.01 * i) for i in range(layers)]
+    outs = [[B.alloc_bits(*W.shape, t, q.RIGHT_BYTES) for W in Ws] for _ in range(2)]
+    buffers = [torch.full((B.lib().qgtc_stack_buffer_bytes(n, d) // 4,), 5, dtype=torch.int32, device="cuda") for _ in range(2)]
+    sums = [torch.full((Ws[-1].shape[1] + 3,), -7, dtype=torch.int32, device="cuda") for _ in range(2)]
+    B.qgtc_pack_weights(B.WeightSources(Ws, ranges, outs[0]), layers - 1, sums[0])
+    B.qgtc_stack_input(x, t, (-0.9, 0.8), buffers[0], rows_form=True)
+    B.qgtc_stack_input(x, t, (-0.9, 0.8), buffers[1], rows_form=True, weights=(B.WeightSources(Ws, ranges, outs[1]), layers - 1, sums[1]))
+    assert torch.equal(*buffers) and torch.equal(*sums)
+    for a, b in zip(*outs):
+        assert torch.equal(a.words, b.words)
