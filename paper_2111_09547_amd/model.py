@@ -155,7 +155,7 @@ class QuantGNN:
             # (update first aggregates the outputs of each layer, and the last one has no further product)
             dims = [(h, h) for _, h in self.dims] if update_first else self.dims
             if lists or B.qgtc_neighbours_pay(self.A, int(built.deg.sum(dtype=torch.int64)), dims):
-                self.lists, self._lists_of = built, self.A
+                self.lists = built
         self._wide = wide and self.lists is not None
         if self._wide:
             nbytes = max(2 * n * 16 * (-(-d // 16)) for d, _ in self.dims)
@@ -188,14 +188,38 @@ class QuantGNN:
         if self.lists is not None:
             if self.use_map and self.map is None:
                 self.map = B._alloc_tile_map(self.A, 16, self.tile_kbits)
-            B.qgtc_build_neighbours(self.A, self.lists, self.map)
-            self._lists_of = self.A
+            self._build_lists(self.map)
             self.deg = self.map.deg if self.use_map else self.lists.deg
+            self._made = (self.map, self.deg)
         elif self.use_map:
             self.map = B.qgtc_build_tile_map(self.A, 16, self.tile_kbits, out=self.map)
             self.deg = self.map.deg
         else:
             self.deg = B.qgtc_row_sums(self.A)
+
+    def _build_lists(self, tmap):
+        """Lists of the adjacency as it is now, with tmap's tiles and degrees in the same pass."""
+        A, c = self.A, self.lists.c
+        same = (c.rows, c.cols, c.block_rows) == (A.rows, A.cols, A.c.block_rows)
+        self.lists = B.qgtc_build_neighbours(A, self.lists if same else None, tmap)
+        if not torch.cuda.is_current_stream_capturing():     # (what is recorded has not run)
+            self._lists_of = A
+
+    def _follow_adjacency(self):
+        """Over lists: an adjacency that was replaced and not packed since gets its own, and so do the map and the
+        degrees unless the caller replaced those as well."""
+        if self.lists is None or self._lists_of is self.A:
+            return
+        tmap, deg = self._made                   # pack_static()'s
+        ours = self.use_map and self.map is tmap
+        if ours and (tmap.rows != self.A.rows or tmap.c.n_tile_cols != -(-self.A.cols // self.tile_kbits)):
+            tmap = B._alloc_tile_map(self.A, 16, self.tile_kbits)
+        self._build_lists(tmap if ours else None)
+        if ours:
+            self.map = tmap
+        if self.deg is deg:
+            self.deg = deg = tmap.deg if ours else self.lists.deg
+        self._made = (tmap, deg)
 
     def _pack_weights_and(self, X, x_range):
         if self._wide:
@@ -285,7 +309,7 @@ class QuantGNN:
         per run the row range, a view of A and a view of the tile map.  Subgraphs share
         no edge (Section 4.1), so the runs are independent from the first layer to the
         last and can be issued on different streams."""
-        key = (str(n_chunks), self.map.c.row_cnt if self.map is not None else 0)
+        key = (str(n_chunks), self.A.c.data, self.A.rows, self.map.c.row_cnt if self.map is not None else 0)
         if getattr(self, "_chunk_cache", (None, None))[0] == key:
             return self._chunk_cache[1]
         br = self.A.c.block_rows
@@ -421,6 +445,7 @@ class QuantGNN:
     def calibrate(self, X: torch.Tensor, x_range):
         """Runs the stack once with int32 outputs and returns LayerRanges per
         layer (range = [0, max observed accumulator], at least 1)."""
+        self._follow_adjacency()
         if self.update_first:
             return self._forward_update_first(X, x_range, None, None, False)
         ranges = []
@@ -485,6 +510,7 @@ class QuantGNN:
         x_packed: the features are already packed (pack_static(X, x_range)).
         x_bits: the features as packed planes that live elsewhere (a SubgraphPacket's,
         packed on the host with the same x_range); X is then not read (single run only)."""
+        self._follow_adjacency()
         n = self.A.rows
         if streams == "auto":
             streams = self.auto_runs()
@@ -571,6 +597,7 @@ class QuantGNN:
                          x_packed=with_static and not self.update_first)
 
         self._ready_planes(X)
+        self._follow_adjacency()
         if any(bn is not None for bn in self.batchnorm):
             self._epilogues(x_range, ranges, want_int)       # folds them, on the caller's stream
         cur = torch.cuda.current_stream()
@@ -631,9 +658,6 @@ class QuantGNN:
         key = (float(x_range[0]), float(x_range[1]), bool(want_int), tuple(vars(self.tuning).values()) if self.tuning else None, *self.w_ranges,
                self.self_term, id(self.A), id(self.map), id(self.lists), self.deg.data_ptr(), *map(id, self._W_ops), *map(id, self.batchnorm),
                *[(r.agg_hi, r.out_hi) for r in ranges])
-        if self.lists is not None and self._lists_of is not self.A:      # (replaced, and not packed since)
-            B.qgtc_build_neighbours(self.A, self.lists)
-            self._lists_of = self.A
         stack = self._stacks.get(key)
         if stack is None:
             Ws = self._W_bytes if self.update_first else self._W_ops

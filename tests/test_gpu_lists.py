@@ -141,6 +141,41 @@ def test_lists_follow_the_adjacency():
     assert net.A is not first and torch.equal(net.forward(x, (-3.0, 3.0), ranges, want_int=True), want)
 
 
+@pytest.mark.parametrize("s", [4, 16])
+@pytest.mark.parametrize("use_map", [True, False])
+@pytest.mark.parametrize("replaced", ["A", "A and its map and degrees", "A of fewer subgraphs"])
+def test_fp32_output_follows_a_replaced_adjacency(s, use_map, replaced):
+    """The degrees, which only the fp32 output reads (times the range's lower end), belong to the new adjacency,
+    also in runs on planes and in calibrate()."""
+    rng = np.random.default_rng(6)
+    small, large = block_graph(rng, 5, 96, 0, 4.0)[0], block_graph(rng, 5, 96, 0, 30.0)[0]
+    if replaced == "A of fewer subgraphs":          
+        small, large = large, small[:288].copy()
+    W, xr = dev(rng.uniform(-1, 1, (20, 9)).astype(np.float32)), (-3.0, 3.0)
+    net, other = (QuantGNN(dev(g), [W], s, s, False, block_rows=96, lists=True, use_map=use_map) for g in (small, large))
+    x = dev(rng.standard_normal((large.shape[0], 20)).astype(np.float32))
+    plain = QuantGNN(dev(large), [W], s, s, False, block_rows=96, lists=False, use_map=use_map)
+    ranges = plain.calibrate(x, xr)
+    want = plain.forward(x, xr, ranges)
+    net.forward(dev(rng.standard_normal((small.shape[0], 20)).astype(np.float32)), xr, ranges)
+    net.A = other.A
+    if replaced == "A and its map and degrees":
+        net.map, net.deg = other.map, other.deg
+    mine = (net.map, net.deg)
+    assert torch.equal(net.forward(x, xr, ranges), want)
+    if replaced == "A and its map and degrees":
+        assert net.map is mine[0] and net.deg is mine[1]
+    assert torch.equal(net.forward(x, xr, ranges, streams=2), want)
+    assert net.calibrate(x, xr) == ranges
+    out = torch.empty_like(want)
+    graph = net.capture(x, xr, ranges, out)
+    for _ in range(3):
+        out.zero_()
+        graph.replay()
+        assert torch.equal(net.forward(x, xr, ranges), want)
+        assert torch.equal(out, want)
+
+
 @pytest.mark.parametrize("blocks,block,short,dims,s,t,gin", [
     (3, 96, 5, "12-16-5", 8, 8, True),               # a quarter of a wave per row, one output tile
     (3, 96, 5, "13-40-70", 3, 5, False),             # rows that are no multiple of 16 bytes, several tiles, two groups of them
