@@ -157,6 +157,7 @@ class QuantGNN:
             if lists or B.qgtc_neighbours_pay(self.A, int(built.deg.sum(dtype=torch.int64)), dims):
                 self.lists = built
         self._wide = wide and self.lists is not None
+        self._planes_kept = False
         if self._wide:
             nbytes = max(2 * n * 16 * (-(-d // 16)) for d, _ in self.dims)
             self._codes = [torch.empty(max(nbytes // 4, 4), dtype=torch.int32, device=self.A.words.device) for _ in range(2)]
@@ -231,6 +232,9 @@ class QuantGNN:
                                                         [0] * len(self.Ws) + [8] * len(high)))
             B.qgtc_pack_weights(self._w_sources[1], len(self.dims) - 1, self._w_colsum_buf)
             self.w_colsum = [None] * (len(self.dims) - 1) + [self._w_colsum_buf]
+            if self._planes_kept:
+                for W, r, dst in zip(self.Ws, self.w_ranges, self._W_ops):
+                    B.qgtc_pack_bits(W, self.t, B.RIGHT, quant=r, out=dst)
         elif all(lay == B.RIGHT_BYTES for lay in self.w_layout) and all(W.dtype == torch.float32 and W.is_contiguous() for W in self.Ws):
             key = [(W.data_ptr(), o.c.data, *r) for W, o, r in zip(self.Ws, self._W_ops, self.w_ranges)]
             if getattr(self, "_w_sources", (None,))[0] != key:
@@ -261,15 +265,21 @@ class QuantGNN:
     # -- helpers -----------------------------------------------------------------
     @property
     def W(self):
-        """The packed weights as the layers by themselves take them (pack_static() of a network whose codes are
-        two bytes has not made them)."""
-        if self._wide:
-            self._pack_w_planes()
+        """The packed weights as the layers by themselves take them."""
+        self._ready_w_planes()
         return self._W_ops
 
-    def _pack_w_planes(self):
-        for W, r, dst in zip(self.Ws, self.w_ranges, self._W_ops):
-            B.qgtc_pack_bits(W, self.t, B.RIGHT, quant=r, out=dst)
+    def _ready_w_planes(self):
+        """Planes of the weights of a network whose passes read them as two bytes: made from those when first needed,
+        from then on by pack_static()."""
+        if not self._wide or self._planes_kept:
+            return
+        for low, high, dst in zip(self._W_low, self._W_high, self._W_ops):
+            codes = B.qgtc_unpack_bits(low)
+            if high is not None:
+                codes += B.qgtc_unpack_bits(high) << 8
+            B.qgtc_pack_bits(codes, self.t, B.RIGHT, out=dst)
+        self._planes_kept = not torch.cuda.is_current_stream_capturing()    # (what is recorded has not run)
 
     def _pack_codes(self, X, x_range):
         if self._wide:
@@ -550,7 +560,7 @@ class QuantGNN:
                     x = X if x_bits is None else x_bits
                 self._run_layers(0, n, self.A, self.map, self.deg, x, x_range, ranges, out, want_int, None)
                 return out
-            self._pack_w_planes()
+            self._ready_w_planes()
         if x_bits is not None:
             assert isinstance(streams, int) and streams <= 1
             xb = x_bits

@@ -267,3 +267,36 @@ def test_codes_of_two_bytes_over_lists(blocks, block, short, dims, s, t, gin):
         graph.replay()
         assert torch.equal(net.forward(x, xr, ranges), want)
         assert torch.equal(out, want)
+
+
+@pytest.mark.parametrize("t", [7, 16])
+def test_planes_of_weights_are_packed_by_pack_static(monkeypatch, t):
+    """Two-byte codes over lists, run by run on planes: no pass packs the weights, eager and recorded ones have
+    those of the last pack_static()."""
+    rng = np.random.default_rng(t)
+    a, _ = block_graph(rng, 5, 96, 31, 6.0)
+    Ws = [rng.uniform(-1, 1, dh).astype(np.float32) for dh in ((20, 24), (24, 9))]
+    net, plain = (QuantGNN(dev(a), [dev(W) for W in Ws], 16, t, False, block_rows=96, lists=lists) for lists in (True, False))
+    x, xr = dev(rng.standard_normal((a.shape[0], 20)).astype(np.float32)), (-3.0, 3.0)
+    ranges = plain.calibrate(x, xr)
+    want = plain.forward(x, xr, ranges)
+    net.Ws[0].neg_()                                 # not packed yet
+    assert torch.equal(net.forward(x, xr, ranges, streams=2), want)
+    out = torch.empty_like(want)
+    graph = net.capture(x, xr, ranges, out, streams=2)
+    packed, real = [], B.qgtc_pack_bits
+    monkeypatch.setattr(B, "qgtc_pack_bits", lambda src, *args, **k: packed.append(tuple(src.shape)) or real(src, *args, **k))
+    assert torch.equal(net.forward(x, xr, ranges, streams=2), want)
+    assert packed == [tuple(x.shape)]
+    plain.Ws[0].neg_()
+    for pack in (False, True):
+        if pack:
+            net.pack_static()
+            plain.pack_static()
+            want = plain.forward(x, xr, ranges)
+        for _ in range(2):
+            out.zero_()
+            graph.replay()
+            assert torch.equal(net.forward(x, xr, ranges), want)
+            assert torch.equal(net.forward(x, xr, ranges, streams=2), want)
+            assert torch.equal(out, want)
