@@ -157,16 +157,15 @@ class QuantGNN:
             if lists or B.qgtc_neighbours_pay(self.A, int(built.deg.sum(dtype=torch.int64)), dims):
                 self.lists = built
         self._wide = wide and self.lists is not None
-        self._planes_kept = False
+        # the weights as passes over lists read them where that is not W's form: per layer its bytes (_byte_ops)
+        self._W_bytes = [self._byte_ops(l, t) for l in range(len(self.dims))] if self.lists is not None and not self._fused else None
+        self._planes_kept = self._w_asked = False
         if self._wide:
             nbytes = max(2 * n * 16 * (-(-d // 16)) for d, _ in self.dims)
             self._codes = [torch.empty(max(nbytes // 4, 4), dtype=torch.int32, device=self.A.words.device) for _ in range(2)]
-            self._W_low = [B.alloc_bits(d, h, min(t, 8), B.RIGHT_BYTES) for d, h in self.dims]
-            self._W_high = [B.alloc_bits(d, h, t - 8, B.RIGHT_BYTES) if t > 8 else None for d, h in self.dims]
         if update_first and self.lists is not None:
             nbytes = max(B.lib().qgtc_stack_buffer_bytes(n, h) for _, h in self.dims)
             self._codes = [torch.empty(max(nbytes // 4, 4), dtype=torch.int32, device=self.A.words.device) for _ in range(2)]
-            self._W_bytes = [B.alloc_bits(d, h, t, B.RIGHT_BYTES) for d, h in self.dims]
         if update_first:                 # activations between layers as left operands of the update
             self.xl_bufs = [B.alloc_bits(n, max(dmax, hmax), s, B.LEFT) for _ in range(2)]
         self.pack_static()
@@ -209,8 +208,6 @@ class QuantGNN:
     def _follow_adjacency(self):
         """Over lists: an adjacency that was replaced and not packed since gets its own, and so do the map and the
         degrees unless the caller replaced those as well."""
-        if self.lists is None or self._lists_of is self.A:
-            return
         tmap, deg = self._made                   # pack_static()'s
         ours = self.use_map and self.map is tmap
         if ours and (tmap.rows != self.A.rows or tmap.c.n_tile_cols != -(-self.A.cols // self.tile_kbits)):
@@ -224,11 +221,11 @@ class QuantGNN:
 
     def _pack_weights_and(self, X, x_range):
         if self._wide:
-            high = [W for W in self._W_high if W is not None]
+            low, high = [ops[0] for ops in self._W_bytes], [op for ops in self._W_bytes for op in ops[1:]]
             key = [(W.data_ptr(), *r) for W, r in zip(self.Ws, self.w_ranges)]
             if getattr(self, "_w_sources", (None,))[0] != key:
                 twice = 2 if high else 1
-                self._w_sources = (key, B.WeightSources(self.Ws * twice, self.w_ranges * twice, self._W_low + high, self.t,
+                self._w_sources = (key, B.WeightSources(self.Ws * twice, self.w_ranges * twice, low + high, self.t,
                                                         [0] * len(self.Ws) + [8] * len(high)))
             B.qgtc_pack_weights(self._w_sources[1], len(self.dims) - 1, self._w_colsum_buf)
             self.w_colsum = [None] * (len(self.dims) - 1) + [self._w_colsum_buf]
@@ -253,7 +250,7 @@ class QuantGNN:
                 B.qgtc_pack_bits(W, self.t, lay, quant=r, out=dst)
             self.w_colsum = [None] * (len(self.dims) - 1) + [B.qgtc_col_sums(self._W_ops[-1], out=self._w_colsum_buf)]
         if self.update_first and self.lists is not None:
-            for W, r, dst in zip(self.Ws, self.w_ranges, self._W_bytes):
+            for W, r, (dst,) in zip(self.Ws, self.w_ranges, self._W_bytes):
                 B.qgtc_pack_bits(W, self.t, B.RIGHT_BYTES, quant=r, out=dst)
         if X is not None and not self.update_first:
             if (self._fused or self._wide) and X.dtype == torch.float32:
@@ -265,19 +262,44 @@ class QuantGNN:
     # -- helpers -----------------------------------------------------------------
     @property
     def W(self):
-        """The packed weights as the layers by themselves take them."""
+        """The packed weights, an operand per layer: passes follow what is replaced here or packed into one.  Over
+        neighbour lists, where they read bytes that pack_static() makes beside these, every pass forms those anew
+        once the operands have been asked for; a graph recorded before has pack_static()'s."""
         self._ready_w_planes()
+        self._w_asked = True
         return self._W_ops
+
+    @W.setter
+    def W(self, ops):
+        self._W_ops = list(ops)
+        self._planes_kept = self._w_asked = True
+
+    def _byte_ops(self, l, nbits):
+        """Room for weights of layer l as passes over lists read them: their low and, above 8 bits, high bytes."""
+        d, h = self.dims[l]
+        return [B.alloc_bits(d, h, min(nbits, 8), B.RIGHT_BYTES)] + ([B.alloc_bits(d, h, nbits - 8, B.RIGHT_BYTES)] if nbits > 8 else [])
+
+    def _follow_weights(self):
+        if not self._w_asked or self._W_bytes is None:
+            return
+        for l, W in enumerate(self._W_ops):
+            if W.nbits > (16 if self._wide else 8):
+                raise ValueError(f"weights of {W.nbits} bits in a network of {self.t}")
+            if W.nbits != sum(op.nbits for op in self._W_bytes[l]):
+                self._W_bytes[l] = self._byte_ops(l, W.nbits)
+            codes = B.qgtc_unpack_bits(W)
+            for i, op in enumerate(self._W_bytes[l]):
+                B.qgtc_pack_bits(codes >> 8 if i else codes, op.nbits, B.RIGHT_BYTES, out=op)
 
     def _ready_w_planes(self):
         """Planes of the weights of a network whose passes read them as two bytes: made from those when first needed,
         from then on by pack_static()."""
         if not self._wide or self._planes_kept:
             return
-        for low, high, dst in zip(self._W_low, self._W_high, self._W_ops):
+        for (low, *high), dst in zip(self._W_bytes, self._W_ops):
             codes = B.qgtc_unpack_bits(low)
-            if high is not None:
-                codes += B.qgtc_unpack_bits(high) << 8
+            for op in high:
+                codes += B.qgtc_unpack_bits(op) << 8
             B.qgtc_pack_bits(codes, self.t, B.RIGHT, out=dst)
         self._planes_kept = not torch.cuda.is_current_stream_capturing()    # (what is recorded has not run)
 
@@ -404,7 +426,7 @@ class QuantGNN:
             xl = B.qgtc_pack_bits(X, self.s, B.LEFT, quant=x_range, out=self._xl_view(0, X.shape[1]))
         n_layers = len(self.dims)
         x_scale = (float(x_range[1]) - float(x_range[0])) / float(2 ** self.s)
-        for l, W in enumerate(self.W):
+        for l, W in enumerate(self._W_ops):
             d, h = self.dims[l]
             last = l == n_layers - 1
             if calibrating:
@@ -455,7 +477,8 @@ class QuantGNN:
     def calibrate(self, X: torch.Tensor, x_range):
         """Runs the stack once with int32 outputs and returns LayerRanges per
         layer (range = [0, max observed accumulator], at least 1)."""
-        self._follow_adjacency()
+        if self.lists is not None and self._lists_of is not self.A:
+            self._follow_adjacency()
         if self.update_first:
             return self._forward_update_first(X, x_range, None, None, False)
         ranges = []
@@ -520,7 +543,8 @@ class QuantGNN:
         x_packed: the features are already packed (pack_static(X, x_range)).
         x_bits: the features as packed planes that live elsewhere (a SubgraphPacket's,
         packed on the host with the same x_range); X is then not read (single run only)."""
-        self._follow_adjacency()
+        if self.lists is not None and self._lists_of is not self.A:
+            self._follow_adjacency()
         n = self.A.rows
         if streams == "auto":
             streams = self.auto_runs()
@@ -607,7 +631,9 @@ class QuantGNN:
                          x_packed=with_static and not self.update_first)
 
         self._ready_planes(X)
-        self._follow_adjacency()
+        if self.lists is not None and self._lists_of is not self.A:
+            self._follow_adjacency()
+        self._follow_weights()
         if any(bn is not None for bn in self.batchnorm):
             self._epilogues(x_range, ranges, want_int)       # folds them, on the caller's stream
         cur = torch.cuda.current_stream()
@@ -665,18 +691,21 @@ class QuantGNN:
     def _stack(self, x_range, ranges, want_int) -> "B.Stack":
         """The prepared native call for these ranges (a caller's handful of them is kept).  An entry
         holds on to the operands that its key names, so that none of them can be another one by now."""
+        if self._w_asked:
+            self._follow_weights()
+        ops = self._W_ops if self._W_bytes is None else [*[op for ops in self._W_bytes for op in ops], self.w_colsum[-1]]
         key = (float(x_range[0]), float(x_range[1]), bool(want_int), tuple(vars(self.tuning).values()) if self.tuning else None, *self.w_ranges,
-               self.self_term, id(self.A), id(self.map), id(self.lists), self.deg.data_ptr(), *map(id, self._W_ops), *map(id, self.batchnorm),
+               self.self_term, id(self.A), id(self.map), id(self.lists), self.deg.data_ptr(), *map(id, ops), *map(id, self.batchnorm),
                *[(r.agg_hi, r.out_hi) for r in ranges])
         stack = self._stacks.get(key)
         if stack is None:
-            Ws = self._W_bytes if self.update_first else self._W_ops
-            layers = [(W, first, second) for W, (first, second) in zip(Ws, self._epilogues(x_range, ranges, want_int))]
+            eps = self._epilogues(x_range, ranges, want_int)
             if self._wide:
-                stack = B.WideStack(self.A, [((lo, hi), f, sec) for lo, hi, (_, f, sec) in zip(self._W_low, self._W_high, layers)],
+                stack = B.WideStack(self.A, [((W[0], W[1] if len(W) > 1 else None), *ep) for W, ep in zip(self._W_bytes, eps)],
                                     self.s, self._codes, self.lists)
             else:
-                stack = B.Stack(self.A, self.map, layers, self.s, self._codes, self.lists)
+                Ws = self._W_ops if self._W_bytes is None else [W for W, in self._W_bytes]
+                stack = B.Stack(self.A, self.map, [(W, *ep) for W, ep in zip(Ws, eps)], self.s, self._codes, self.lists)
             if len(self._stacks) >= 8:
                 self._stacks.pop(next(iter(self._stacks)), None)
             self._stacks[key] = stack

@@ -300,3 +300,46 @@ def test_planes_of_weights_are_packed_by_pack_static(monkeypatch, t):
             assert torch.equal(net.forward(x, xr, ranges), want)
             assert torch.equal(net.forward(x, xr, ranges, streams=2), want)
             assert torch.equal(out, want)
+
+
+@pytest.mark.parametrize("s,t,update_first", [(4, 4, False), (8, 8, True), (4, 3, True), (16, 7, False), (12, 16, False)])
+def test_passes_follow_replaced_weights(s, t, update_first):
+    """W[l] replaced, all of W replaced, and other weights packed into an operand: what a network without lists computes
+    from the same operands, eager and recorded."""
+    rng = np.random.default_rng(s + t)
+    a, _ = block_graph(rng, 5, 96, 31, 6.0)
+    shapes = ((20, 24), (24, 9))
+    sets = [[dev(rng.uniform(-1, 1, dh).astype(np.float32)) for dh in shapes] for _ in range(4)]
+    nets = [QuantGNN(dev(a), sets[0], s, t, False, block_rows=96, lists=lists, update_first=update_first) for lists in (True, False)]
+    assert nets[0].lists is not None and nets[1].lists is None
+    x, xr = dev(rng.standard_normal((a.shape[0], 20)).astype(np.float32)), (-3.0, 3.0)
+    ranges = nets[1].calibrate(x, xr)
+
+    def operand(W, layout):
+        return q.qgtc_pack_bits(W, t, layout, quant=(-1.0, 1.0))
+
+    outs = []
+    for step in ("first", "one", "one of them in place", "all", "none"):
+        for net in nets:
+            if step == "one":
+                net.W[1] = operand(sets[1][1], net.w_layout[1])
+            elif step == "one of them in place":
+                q.qgtc_pack_bits(sets[2][0], t, net.w_layout[0], quant=(-1.0, 1.0), out=net.W[0])
+            elif step == "all":
+                net.W = [operand(W, lay) for W, lay in zip(sets[3], net.w_layout)]
+            elif step == "none":
+                net.pack_static()
+        want = nets[1].forward(x, xr, ranges, want_int=True)
+        assert torch.equal(want, outs[0]) if step == "none" else not any(torch.equal(want, o) for o in outs)
+        assert torch.equal(nets[0].forward(x, xr, ranges, want_int=True), want)
+        if not update_first:
+            assert torch.equal(nets[0].forward(x, xr, ranges, want_int=True, streams=2), want)
+        assert torch.equal(nets[0].forward(x, xr, ranges), nets[1].forward(x, xr, ranges))
+        out = torch.empty_like(want)
+        graph = nets[0].capture(x, xr, ranges, out, want_int=True)
+        for _ in range(2):
+            out.zero_()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(out, want)
+        outs.append(want)
