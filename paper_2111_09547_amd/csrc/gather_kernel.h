@@ -25,6 +25,7 @@
 // Adding bytes up on the vector ALUs instead: 64 -> 64 11.0 us.  Heavy rows in the tiles' own waves: 512 -> 16
 // on the power-law graph 232 us.
 #pragma once
+#include "gather_shape.h"
 #include "gather_update.h"
 
 namespace qgtc {
@@ -34,16 +35,6 @@ namespace {
 // sums at the loop's head two wait states after it, where the instruction needs seven, and the copy is
 // then of the old values.
 __device__ __forceinline__ void settle(v4i& sum) { asm volatile("s_nop 7" : "+v"(sum)); }
-
-// The dimensions of an instance; PARTS = 2: codes of 9 to 16 bits, a low and a high byte each.
-template <int LP, int WPT, int PARTS>
-struct GatherShape {
-  static constexpr int P = 1 << LP;
-  static constexpr int PS = P < 16 ? P : 16;         // pieces of a unit: 16 slots
-  static constexpr int RC = 16 / PS, HV = P / PS;    // rows of a unit; P > 16: parts of 256 columns
-  static constexpr int UNITS = 16 / WPT / RC;        // units of a wave per part
-  static constexpr int W = UNITS * PARTS < 4 ? UNITS * PARTS : 4;   // sums at a time: parts of units
-};
 
 // A[m][16 g + b] = (b == m), which adds up the bytes of the four lanes of a slot.
 __device__ __forceinline__ v4i adder(int ln) {
@@ -289,9 +280,10 @@ __global__ __launch_bounds__(256, 4) void gather_layer_kernel(const GatherParams
   const v4i ident = adder(ln);
   const Rq q = make_rq(p.agg_lo, p.agg_relu, p.agg_inv, p.agg_nbits);
   const Neighbours nb(p, row0, PARTS);
-  const __amdgpu_buffer_rsrc_t r_own = uniform_rsrc(p.X + (int64_t)row0 * ldx, here * (uint32_t)ldx);
-  constexpr int LR = LP < 4 ? LP : 4;
-  const uint32_t v_own = (uint32_t)((ln >> LR) * ldx + 16 * (ln & (PS - 1)) + 4 * g);
+  const uint32_t own_size = here * (uint32_t)ldx;
+  const __amdgpu_buffer_rsrc_t r_own = uniform_rsrc(p.X + (int64_t)row0 * ldx, own_size);
+  constexpr int LR = Sh::LR;
+  const uint32_t v_own = own_lane_offset<Sh>(ln, g, (uint32_t)ldx);
   const int first_row = WPT == 1 ? 0 : wave * (16 / WPT);   // of the wave in the tile
   const bool row_sums = p.split_w || (MODE == kGatherRows && p.want_rowsum);
   v4i z[LT], rs = {0, 0, 0, 0};
@@ -324,7 +316,8 @@ __global__ __launch_bounds__(256, 4) void gather_layer_kernel(const GatherParams
         most = max(most, n[j]);
         own[j] = 0u;
         if (self)
-          own[j] = __builtin_amdgcn_raw_buffer_load_b32(r_own, v_own, (uint32_t)(first_row + (u0 + j / PARTS) * RC) * (uint32_t)ldx + hv * 256u + j % PARTS * nb.part, 0);
+          own[j] = __builtin_amdgcn_raw_buffer_load_b32(
+              r_own, v_own, own_unit_offset((uint32_t)(first_row + (u0 + j / PARTS) * RC), hv * 256u + j % PARTS * nb.part, (uint32_t)ldx, own_size), 0);
       }
       // The first block in up to three steps, each with all of its loads in flight: wide rows are few
       // neighbours of many bytes from HBM, narrow ones more neighbours from the caches.

@@ -343,3 +343,21 @@ def test_passes_follow_replaced_weights(s, t, update_first):
             torch.cuda.synchronize()
             assert torch.equal(out, want)
         outs.append(want)
+
+
+@pytest.mark.parametrize("n", [1, 17, 31, 33, 64 + 15])
+@pytest.mark.parametrize("dims", ["3-2", "70-20", "130-64", "300-9", "512-16"])
+@pytest.mark.parametrize("s", [8, 16])
+def test_last_tile_of_few_rows_with_a_self_term(n, dims, s):
+    """Units behind the last row, for every split of a tile: the layers of whole tiles' results."""
+    rng = np.random.default_rng(n + s)
+    block = 64
+    blocks = -(-n // block)
+    a, _ = block_graph(rng, blocks, block, blocks * block - n, 6.0)
+    d = [int(v) for v in dims.split("-")]
+    W, xr = dev(rng.uniform(-1, 1, d).astype(np.float32)), (-3.0, 3.0)
+    x = dev(rng.standard_normal((n, d[0])).astype(np.float32))
+    nets = [QuantGNN(dev(a), [W], s, s, True, block_rows=block, lists=lists) for lists in (True, False)]
+    ranges = nets[1].calibrate(x, xr)
+    for ints in (True, False):
+        assert torch.equal(*[net.forward(x, xr, ranges, want_int=ints) for net in nets])
