@@ -416,6 +416,8 @@ qgtc_status qgtc_layer_static(const qgtc_bits* A, const qgtc_tile_map* map,
  *   qgtc_build_neighbours   fills deg (bits per row) and the lists; with a map (16 x 32, 64 or 128)
  *                           its row_cnt, col_idx and deg as qgtc_build_tile_map does, in the same
  *                           pass over A, but not its nnz_tiles (qgtc_tile_map_total)
+ * The fields are qgtc_neighbours_carve's.  One that points elsewhere has the same alignment (first, rest and
+ * heavy_cnt 16 bytes, heavy 8, deg 4, else QGTC_ERR_ALIGN) and room: heavy_cnt is read in whole pieces of 16.
  */
 typedef struct qgtc_neighbours {
   int32_t rows, cols, block_rows;     /* of A */

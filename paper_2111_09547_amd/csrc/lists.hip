@@ -11,7 +11,7 @@ struct ListParams {
   int64_t lda;
   int32_t rows;
   int32_t n128;              // 128-bit pieces of a row
-  int32_t cols, rest_cap;
+  int32_t rest_cap;
   uint16_t* first;
   uint16_t* rest;
   uint8_t* heavy_cnt;
@@ -124,7 +124,9 @@ qgtc_status check_neighbours(const qgtc_neighbours* n, const qgtc_bits* A) {
   if (!lists_cover(A)) return QGTC_ERR_UNSUPPORTED;
   if (n->rows != A->rows || n->cols != A->cols || n->block_rows != A->block_rows || n->rest_cap != rest_cap_of(A->cols))
     return QGTC_ERR_SHAPE;
-  if ((((uintptr_t)n->first | (uintptr_t)n->rest) & 15u) != 0) return QGTC_ERR_ALIGN;
+  // as wide as the kernels read them
+  if ((((uintptr_t)n->first | (uintptr_t)n->rest | (uintptr_t)n->heavy_cnt) & 15u) != 0) return QGTC_ERR_ALIGN;
+  if (((uintptr_t)n->heavy & 7u) != 0 || ((uintptr_t)n->deg & 3u) != 0) return QGTC_ERR_ALIGN;
   return QGTC_OK;
 }
 
@@ -185,7 +187,6 @@ extern "C" qgtc_status qgtc_build_neighbours(const qgtc_bits* A, const qgtc_neig
   p.lda = A->ld_words;
   p.rows = A->rows;
   p.n128 = cdiv(A->cols, 128);
-  p.cols = A->cols;
   p.rest_cap = n->rest_cap;
   p.first = n->first;
   p.rest = n->rest;

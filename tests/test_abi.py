@@ -397,3 +397,14 @@ def test_neighbour_lists_on_the_host():
         type("A", (), {"c": _fake_bits(b, rows, block or rows, 1, b.LEFT, block_rows=block)}), int(rows * deg), list(zip(widths[:-1], widths[1:])))
     assert pay(65536, 1024, 8, 128, 64, 64) and pay(262144, 2048, 3.3, 512, 16, 16) and pay(8192, 0, 10, 64, 64)
     assert not pay(65536, 256, 24, 64, 64) and not pay(65536, 1024, 100, 64, 64) and not pay(70000, 0, 3, 64, 64)
+
+
+@pytest.mark.parametrize("field,align", [("first", 16), ("rest", 16), ("heavy_cnt", 16), ("heavy", 8), ("deg", 4)])
+def test_neighbour_lists_of_another_alignment_are_refused(field, align):
+    import paper_2111_09547_amd.binding as b
+    A, n = _fake_bits(b, 4096, 64, 1, b.LEFT, block_rows=64), b._NeighboursC()
+    assert b.lib().qgtc_neighbours_carve(C.byref(n), 0x10000, C.byref(A)) == 0
+    at = getattr(n, field)
+    for off in {1, align // 2}:
+        setattr(n, field, at + off)
+        assert b.lib().qgtc_build_neighbours(C.byref(A), C.byref(n), None, None) == 4, off
