@@ -452,15 +452,25 @@ __global__ __launch_bounds__(256) void col_sums_kernel(const UnpackParams p, int
 template <int SRC>
 qgtc_status launch_pack(const PackParams& p, int layout, hipStream_t s) {
   if (layout == QGTC_LEFT_BYTES) {
-    if constexpr (SRC != QGTC_SRC_U8) {
-      if (left_bytes_wide(p)) {
-        hipLaunchKernelGGL((pack_left_bytes_wide_kernel<SRC>), dim3(left_bytes_wide_groups(p)), dim3(256), 0, s, p, (int)(256 / p.ld),
-                           (int)(256 % p.ld));
-        return launch_status();
+    const int64_t most = ((1ll << 31) - 1) / p.ld;   // rows of a launch, which has a thread per word and fewer than 2^32
+    for (int64_t r0 = 0; r0 < p.rows; r0 += most) {
+      PackParams part = p;
+      part.rows = (int32_t)(p.rows - r0 < most ? p.rows - r0 : most);
+      part.src = reinterpret_cast<const typename src_type<SRC>::type*>(p.src) + r0 * p.ld_src;
+      part.dst = p.dst + r0 * p.ld;
+      bool wide = false;
+      if constexpr (SRC != QGTC_SRC_U8) {
+        wide = left_bytes_wide(part);
+        if (wide)
+          hipLaunchKernelGGL((pack_left_bytes_wide_kernel<SRC>), dim3(left_bytes_wide_groups(part)), dim3(256), 0, s, part,
+                             (int)(256 / p.ld), (int)(256 % p.ld));
       }
+      if (!wide)
+        hipLaunchKernelGGL((pack_left_bytes_kernel<SRC>), dim3((unsigned)cdiv((int64_t)part.rows * p.ld, 256)), dim3(256), 0, s, part);
+      const qgtc_status st = launch_status();
+      if (st != QGTC_OK) return st;
     }
-    hipLaunchKernelGGL((pack_left_bytes_kernel<SRC>), dim3((unsigned)cdiv((int64_t)p.rows * p.ld, 256)), dim3(256),
-                       0, s, p);
+    return QGTC_OK;
   } else if (layout == QGTC_RIGHT_BYTES) {
     const int n_nt = cdiv(p.cols, 16), n_ks = cdiv(p.rows, 64);
     hipLaunchKernelGGL((pack_bytes_kernel<SRC>), dim3((unsigned)cdiv((int64_t)n_nt * n_ks * 64, 256)), dim3(256),

@@ -361,3 +361,23 @@ def test_last_tile_of_few_rows_with_a_self_term(n, dims, s):
     ranges = nets[1].calibrate(x, xr)
     for ints in (True, False):
         assert torch.equal(*[net.forward(x, xr, ranges, want_int=ints) for net in nets])
+
+
+def test_features_of_more_words_than_a_launch_has_threads():
+    """2^24 rows of 1009 columns (64 GiB), read element by element: the codes are those of the same rows by themselves."""
+    n, d, xr = (1 << 24) + 50, 1009, (-1.0, 1.0)
+    if torch.cuda.mem_get_info()[0] < 100 << 30:
+        pytest.skip("needs 100 GiB")
+    x = torch.empty((n, d), device="cuda")
+    buf = torch.zeros(int(B.lib().qgtc_stack_buffer_bytes(n, d)) // 4, dtype=torch.int32, device="cuda")
+    cut = ((1 << 31) - 1) // 256                     # rows of the first launch
+    at = [(0, 40), (cut - 20, cut + 20), (2 * cut - 20, 2 * cut + 20), (n - 40, n)]
+    for r0, r1 in at:
+        x[r0:r1] = torch.rand((r1 - r0, d), device="cuda") * 2 - 1
+    B.qgtc_stack_input(x, 8, xr, buf, rows_form=True)
+    part = torch.zeros(1 << 20, dtype=torch.int32, device="cuda")
+    for r0, r1 in at:
+        B.qgtc_stack_input(x[r0:r1].clone(), 8, xr, part, rows_form=True)
+        assert torch.equal(buf[r0 * 256:r1 * 256], part[:(r1 - r0) * 256]) and len(part[:(r1 - r0) * 256].unique()) > 1000
+    del x, buf
+    torch.cuda.empty_cache()
