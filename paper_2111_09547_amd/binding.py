@@ -237,6 +237,7 @@ class TileMap:
     c: _TileMapC
     rows: int
     totals: bool = True       # nnz_tiles is filled in by whoever fills the rest
+    builds: int = 0           # qgtc_build_tile_map calls on it
 
     def _view(self, ptr, n):
         off = (ptr - self.buffer.data_ptr()) // 4
@@ -429,6 +430,7 @@ def qgtc_build_tile_map(A: Bits, tile_rows: int = 16, tile_kbits: int = 128,
     if out is None:
         out = _alloc_tile_map(A, tile_rows, tile_kbits)
     out.totals = True
+    out.builds += 1
     _check(lib().qgtc_build_tile_map(C.byref(A.c), C.byref(out.c), _stream()),
            "qgtc_build_tile_map")
     return out

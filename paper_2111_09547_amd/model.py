@@ -140,7 +140,8 @@ class QuantGNN:
             nbytes = max(B.lib().qgtc_stack_buffer_bytes(n, d) for d, _ in self.dims)
             self._codes = [torch.empty(max(nbytes // 4, 4), dtype=torch.int32, device=self.A.words.device) for _ in range(2)]
         # Neighbour lists in place of products with whole tiles of A where they pay (lists=None; the bits of A
-        # are counted once), or as the caller says.  The results are the same.
+        # are counted once), or as the caller says.  The results are the same.  Without a map only as the caller says:
+        # nothing would tell a pass that other bits were packed into A.
         self.lists = None
         # 9 to 16 bits over lists: codes as two bytes, where lists pay for bytes (planes lose more there: an
         # aggregation reads s of them, an update multiplies s * t; 64 -> 64 on 8192 rows, 16 bits: 54 us, and 18)
@@ -148,7 +149,7 @@ class QuantGNN:
             (self.tuning is None or self.tuning.layer_path == B.LAYER_FUSED) and all(W.dtype == torch.float32 for W in self.Ws)
         whole = self._fused or wide or (update_first and all(fused_layer_applies(d, h, s, t) for d, h in self.dims) and
                                 (self.tuning is None or self.tuning.layer_path == B.LAYER_FUSED))
-        if whole and lists is not False and (lists or self.plan is not None) and B.neighbours_bytes(self.A) > 0:
+        if whole and lists is not False and (lists or (self.plan is not None and use_map)) and B.neighbours_bytes(self.A) > 0:
             if self.plan is None and self.A_src is not None:
                 B.qgtc_pack_bits(self.A_src, 1, B.LEFT, out=self.A)
             built = B.qgtc_build_neighbours(self.A)
@@ -173,7 +174,9 @@ class QuantGNN:
     def pack_static(self, X: torch.Tensor | None = None, x_range=None):
         """Everything that does not depend on the features: pack A, build its
         zero-tile map, quantize and pack the weights (the paper caches these
-        across layers and subgraphs, end of Section 3.2).  With X: the input features
+        across layers and subgraphs, end of Section 3.2).  To be called again when any of them
+        has changed.  (Passes that are not recorded also follow an adjacency that was replaced, or
+        packed into A and its map built again or replaced.)  With X: the input features
         of the coming forward pass are quantized and packed as well (forward(..., x_packed=True)
         then skips that step)."""
         if X is not None:
@@ -203,18 +206,24 @@ class QuantGNN:
         same = (c.rows, c.cols, c.block_rows) == (A.rows, A.cols, A.c.block_rows)
         self.lists = B.qgtc_build_neighbours(A, self.lists if same else None, tmap)
         if not torch.cuda.is_current_stream_capturing():     # (what is recorded has not run)
-            self._lists_of = A
+            # (other bits packed into A itself have a map of their own, or one that was built again)
+            self._lists_of = (self.A, self.map, self.map.builds if self.map is not None else 0)
 
     def _follow_adjacency(self):
-        """Over lists: an adjacency that was replaced and not packed since gets its own, and so do the map and the
-        degrees unless the caller replaced those as well."""
+        """Over lists: an adjacency that was replaced, or whose map was, and not packed since gets its own, and so do the
+        map and the degrees unless the caller made those as well."""
+        if self.lists is None:
+            return
+        A, tmap, builds = self._lists_of
+        if A is self.A and tmap is self.map and (tmap is None or tmap.builds == builds):
+            return
         tmap, deg = self._made                   # pack_static()'s
-        ours = self.use_map and self.map is tmap
+        ours = self.use_map and self.map is tmap and A is not self.A
         if ours and (tmap.rows != self.A.rows or tmap.c.n_tile_cols != -(-self.A.cols // self.tile_kbits)):
             tmap = B._alloc_tile_map(self.A, 16, self.tile_kbits)
-        self._build_lists(tmap if ours else None)
         if ours:
             self.map = tmap
+        self._build_lists(tmap if ours else None)
         if self.deg is deg:
             self.deg = deg = tmap.deg if ours else self.lists.deg
         self._made = (tmap, deg)
@@ -477,8 +486,7 @@ class QuantGNN:
     def calibrate(self, X: torch.Tensor, x_range):
         """Runs the stack once with int32 outputs and returns LayerRanges per
         layer (range = [0, max observed accumulator], at least 1)."""
-        if self.lists is not None and self._lists_of is not self.A:
-            self._follow_adjacency()
+        self._follow_adjacency()
         if self.update_first:
             return self._forward_update_first(X, x_range, None, None, False)
         ranges = []
@@ -543,8 +551,7 @@ class QuantGNN:
         x_packed: the features are already packed (pack_static(X, x_range)).
         x_bits: the features as packed planes that live elsewhere (a SubgraphPacket's,
         packed on the host with the same x_range); X is then not read (single run only)."""
-        if self.lists is not None and self._lists_of is not self.A:
-            self._follow_adjacency()
+        self._follow_adjacency()
         n = self.A.rows
         if streams == "auto":
             streams = self.auto_runs()
@@ -631,8 +638,7 @@ class QuantGNN:
                          x_packed=with_static and not self.update_first)
 
         self._ready_planes(X)
-        if self.lists is not None and self._lists_of is not self.A:
-            self._follow_adjacency()
+        self._follow_adjacency()
         self._follow_weights()
         if any(bn is not None for bn in self.batchnorm):
             self._epilogues(x_range, ranges, want_int)       # folds them, on the caller's stream

@@ -141,6 +141,42 @@ def test_lists_follow_the_adjacency():
     assert net.A is not first and torch.equal(net.forward(x, (-3.0, 3.0), ranges, want_int=True), want)
 
 
+@pytest.mark.parametrize("s,update_first", [(4, False), (16, False), (8, True)])
+@pytest.mark.parametrize("tmap", ["built again", "replaced", "none"])
+def test_passes_follow_an_adjacency_that_is_packed_in_place(s, update_first, tmap):
+    """Other bits in A, and their map built where the old one was, or in place of it: passes are over the new adjacency.
+    Without a map A is all there is to follow: lists are then used on request only."""
+    rng = np.random.default_rng(7)
+    graphs = [dev(block_graph(rng, 5, 96, 0, deg)[0]) for deg in (4.0, 30.0, 6.0)]
+    W, xr = dev(rng.uniform(-1, 1, (20, 9)).astype(np.float32)), (-3.0, 3.0)
+    x = dev(rng.standard_normal((480, 20)).astype(np.float32))
+    net = QuantGNN(graphs[0], [W], s, s, False, block_rows=96, use_map=tmap != "none", update_first=update_first,
+                   lists=None if tmap == "none" else True)
+    assert (net.lists is None) == (tmap == "none")
+    for g in graphs[1:] + graphs[:1]:
+        plain = QuantGNN(g, [W], s, s, False, block_rows=96, lists=False, update_first=update_first)
+        ranges = plain.calibrate(x, xr)
+        q.qgtc_pack_bits(g, 1, q.LEFT, out=net.A)
+        if tmap == "built again":
+            q.qgtc_build_tile_map(net.A, 16, net.tile_kbits, out=net.map)
+        elif tmap == "replaced":
+            net.map = q.qgtc_build_tile_map(net.A, 16, net.tile_kbits)
+            net.deg = net.map.deg
+        want = plain.forward(x, xr, ranges, want_int=True)
+        assert torch.equal(net.forward(x, xr, ranges, want_int=True), want)
+        assert net.calibrate(x, xr) == ranges
+        if tmap != "none":                           # (the degrees are the map's)
+            want = plain.forward(x, xr, ranges)
+            assert torch.equal(net.forward(x, xr, ranges), want)
+            out = torch.empty_like(want)
+            graph = net.capture(x, xr, ranges, out)
+            for _ in range(3):
+                out.zero_()
+                graph.replay()
+                assert torch.equal(net.forward(x, xr, ranges), want)
+                assert torch.equal(out, want)
+
+
 @pytest.mark.parametrize("s", [4, 16])
 @pytest.mark.parametrize("use_map", [True, False])
 @pytest.mark.parametrize("replaced", ["A", "A and its map and degrees", "A of fewer subgraphs"])
