@@ -229,9 +229,10 @@ class QuantGNN:
         self._made = (tmap, deg)
 
     def _pack_weights_and(self, X, x_range):
-        if self._wide:
+        plain = all(W.dtype == torch.float32 and W.is_contiguous() for W in self.Ws)
+        if self._wide or (self._W_bytes is not None and plain):
             low, high = [ops[0] for ops in self._W_bytes], [op for ops in self._W_bytes for op in ops[1:]]
-            key = [(W.data_ptr(), *r) for W, r in zip(self.Ws, self.w_ranges)]
+            key = [(W.data_ptr(), *r) for W, r in zip(self.Ws, self.w_ranges)] + [op.c.data for op in low + high]
             if getattr(self, "_w_sources", (None,))[0] != key:
                 twice = 2 if high else 1
                 self._w_sources = (key, B.WeightSources(self.Ws * twice, self.w_ranges * twice, low + high, self.t,
@@ -241,7 +242,7 @@ class QuantGNN:
             if self._planes_kept:
                 for W, r, dst in zip(self.Ws, self.w_ranges, self._W_ops):
                     B.qgtc_pack_bits(W, self.t, B.RIGHT, quant=r, out=dst)
-        elif all(lay == B.RIGHT_BYTES for lay in self.w_layout) and all(W.dtype == torch.float32 and W.is_contiguous() for W in self.Ws):
+        elif all(lay == B.RIGHT_BYTES for lay in self.w_layout) and plain:
             key = [(W.data_ptr(), o.c.data, *r) for W, o, r in zip(self.Ws, self._W_ops, self.w_ranges)]
             if getattr(self, "_w_sources", (None,))[0] != key:
                 self._w_sources = (key, B.WeightSources(self.Ws, self.w_ranges, self._W_ops))
@@ -258,8 +259,7 @@ class QuantGNN:
             for W, r, dst, lay in zip(self.Ws, self.w_ranges, self._W_ops, self.w_layout):
                 B.qgtc_pack_bits(W, self.t, lay, quant=r, out=dst)
             self.w_colsum = [None] * (len(self.dims) - 1) + [B.qgtc_col_sums(self._W_ops[-1], out=self._w_colsum_buf)]
-        if self.update_first and self.lists is not None:
-            for W, r, (dst,) in zip(self.Ws, self.w_ranges, self._W_bytes):
+            for W, r, (dst,) in zip(self.Ws, self.w_ranges, self._W_bytes or []):
                 B.qgtc_pack_bits(W, self.t, B.RIGHT_BYTES, quant=r, out=dst)
         if X is not None and not self.update_first:
             if (self._fused or self._wide) and X.dtype == torch.float32:
@@ -301,9 +301,9 @@ class QuantGNN:
                 B.qgtc_pack_bits(codes >> 8 if i else codes, op.nbits, B.RIGHT_BYTES, out=op)
 
     def _ready_w_planes(self):
-        """Planes of the weights of a network whose passes read them as two bytes: made from those when first needed,
-        from then on by pack_static()."""
-        if not self._wide or self._planes_kept:
+        """Planes of the weights of a network whose passes read them as bytes: made from those when first needed, from
+        then on by pack_static()."""
+        if self._W_bytes is None or self._planes_kept:
             return
         for (low, *high), dst in zip(self._W_bytes, self._W_ops):
             codes = B.qgtc_unpack_bits(low)
@@ -426,6 +426,7 @@ class QuantGNN:
         collected on the way and returned as LayerRanges (agg_hi: range of P)."""
         calibrating = ranges is None
         found = []
+        self._ready_w_planes()
         if self.s <= 8 and self.t <= 8:
             # the input goes straight to the int8 matrix cores: codes as bytes, no bit planes
             if getattr(self, "_x_bytes", None) is None:

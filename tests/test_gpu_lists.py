@@ -338,6 +338,44 @@ def test_planes_of_weights_are_packed_by_pack_static(monkeypatch, t):
             assert torch.equal(out, want)
 
 
+@pytest.mark.parametrize("t", [3, 8])
+def test_update_first_over_lists_packs_the_weights_once(monkeypatch, t):
+    """All of them in one launch; planes, which other features than fp32 and calibrate() take, from when those first need
+    them on, eager and recorded."""
+    rng = np.random.default_rng(t)
+    a, _ = block_graph(rng, 5, 96, 31, 6.0)
+    Ws = [rng.uniform(-1, 1, dh).astype(np.float32) for dh in ((20, 24), (24, 9))]
+    calls, real_bits, real_weights = [], B.qgtc_pack_bits, B.qgtc_pack_weights
+    monkeypatch.setattr(B, "qgtc_pack_bits", lambda src, *args, **k: calls.append(tuple(src.shape)) or real_bits(src, *args, **k))
+    monkeypatch.setattr(B, "qgtc_pack_weights", lambda *args, **k: calls.append("weights") or real_weights(*args, **k))
+    net, plain = (QuantGNN(dev(a), [dev(W) for W in Ws], 8, t, False, block_rows=96, lists=lists, update_first=True) for lists in (True, False))
+    x, xr = dev(rng.standard_normal((a.shape[0], 20)).astype(np.float32)), (-3.0, 3.0)
+    codes = dev(rng.integers(0, 256, (a.shape[0], 20)).astype(np.int32))
+    ranges = plain.calibrate(x, xr)
+    packed = lambda: [c for c in calls if c in ("weights", (20, 24), (24, 9))]
+    calls.clear()
+    net.pack_static()
+    assert packed() == ["weights"]
+    assert torch.equal(net.forward(x, xr, ranges), plain.forward(x, xr, ranges))
+    assert net.calibrate(x, xr) == ranges
+    out = torch.empty((a.shape[0], 9), device="cuda")
+    graph = net.capture(codes, xr, ranges, out)
+    for changed in (False, True):
+        if changed:
+            for one in (net, plain):
+                one.Ws[0].neg_()
+                calls.clear()
+                one.pack_static()
+            calls.clear()
+        want = plain.forward(codes, xr, ranges)
+        for _ in range(2):
+            out.zero_()
+            graph.replay()
+            assert torch.equal(net.forward(codes, xr, ranges), want) and torch.equal(out, want)
+        assert torch.equal(net.forward(x, xr, ranges), plain.forward(x, xr, ranges))
+    assert not packed()
+
+
 @pytest.mark.parametrize("s,t,update_first", [(4, 4, False), (8, 8, True), (4, 3, True), (16, 7, False), (12, 16, False)])
 def test_passes_follow_replaced_weights(s, t, update_first):
     """W[l] replaced, all of W replaced, and other weights packed into an operand: what a network without lists computes
