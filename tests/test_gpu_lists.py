@@ -103,7 +103,7 @@ def test_layers_over_lists_equal_the_oracle(blocks, block, short, dims, s, t, gi
 
 
 def test_rows_that_are_all_hubs():
-    """Every row has more neighbours than a list holds, without blocks, and negative requantization bounds."""
+    """Every row has more neighbours than a list holds, without blocks."""
     rng = np.random.default_rng(3)
     n, dims = 900, [40, 48, 9]
     a = (rng.random((n, n), dtype=np.float32) < 0.4).astype(np.uint8)
@@ -119,6 +119,75 @@ def test_rows_that_are_all_hubs():
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(outs[0], outs[1])
+
+
+@pytest.mark.parametrize("form,s,t", [("stack", 8, 8), ("stack", 5, 3), ("two bytes", 16, 16), ("two bytes", 11, 7),
+                                      ("update first", 8, 8), ("update first", 4, 6)])
+@pytest.mark.parametrize("relu", [False, True])
+@pytest.mark.parametrize("below", [False, True])
+@pytest.mark.parametrize("dims", ["70-20-33-9", "300-130-70"])
+def test_lower_bounds_of_requantization(form, s, t, relu, below, dims):
+    """Epilogues with a lower bound under (below) or in the middle of the results, behind affine maps of the columns too:
+    every code against the oracle, in rows of a ragged last tile and of 65, 256 and more neighbours."""
+    rng = np.random.default_rng(s + t)
+    d, block, short = [int(v) for v in dims.split("-")], 320, 41
+    a, csr = block_graph(rng, 3, block, short, 7.0)
+    n = a.shape[0]
+    csr = csr.tolil()
+    for r, many in ((0, 65), (n // 2, 256), (n - 1, 279), (1, 300)):
+        r0 = r // block * block
+        cols = rng.choice(min(block, n - r0), min(many, min(block, n - r0)), replace=False)
+        a[r, cols] = 1
+        csr[r, r0 + cols] = 1
+    csr = csr.tocsr()
+    X = rng.standard_normal((n, d[0])).astype(np.float32)
+    codes = qgnn.quantize(X, -3.0, 3.0, s)
+    A = q.qgtc_pack_bits(dev(a), 1, q.LEFT, block_rows=block)
+    lists = B.qgtc_build_neighbours(A)
+
+    def bits(c, affine=None):
+        """An epilogue that requantizes such results, and what it makes of them."""
+        v = qgnn.as_signed(c).astype(np.float64) if affine is None else qgnn.as_signed(c) * affine[0][None].astype(np.float64) + affine[1][None]
+        v = np.maximum(v, 0) if relu else v
+        # (rq_lo is 32 bits; sums modulo 2^32 span all of them)
+        lo = max(int(v.min() - (v.max() - v.min()) / 3 - 2 if below else np.quantile(v, 0.4)) + 1, -1 << 31)
+        inv = qgnn.inv_scale(float(lo), float(max(v.max(), lo + 1)), s)
+        ep = q.Epilogue(mode=q.OUT_BITS, relu=relu, rq_nbits=s, rq_lo=lo, rq_inv_scale=float(inv))
+        if affine is None:
+            return ep, qgnn.requantize(c, lo, inv, s, relu)
+        ep.col_scale, ep.col_shift = dev(affine[0]), dev(affine[1])
+        return ep, qgnn.requantize_affine(c, *affine, lo, inv, s, relu)
+
+    for affine in (False, True)[:1 if form == "update first" else 2]:
+        layers, x = [], codes
+        for l, (di, h) in enumerate(zip(d[:-1], d[1:])):
+            last = l == len(d) - 2
+            w = rng.integers(0, 1 << t, (di, h)).astype(np.uint32)
+            product = lambda v: qgnn.update(v, w)
+            around = lambda v: qgnn.aggregate(csr, v, True)
+            steps = [product, around] if form == "update first" else [around, product]
+            first, y = bits(steps[0](x))
+            z = steps[1](y)
+            if last:
+                second = q.Epilogue(mode=q.OUT_I32, relu=relu)
+            else:
+                maps = (rng.uniform(0.5, 1.5, h).astype(np.float32), rng.uniform(-9.0, 9.0, h).astype(np.float32)) if affine else None
+                second, x = bits(z, maps)
+            (second if form == "update first" else first).self_term = True
+            part = lambda v, k: q.qgtc_pack_bits(dev(v.astype(np.int32)), k, q.RIGHT_BYTES)
+            W = part(w & 255, min(t, 8))
+            layers.append(((W, part(w >> 8, t - 8) if t > 8 else None) if form == "two bytes" else W, first, second))
+        buffers = [torch.zeros(int(B.lib().qgtc_stack_buffer_bytes(n, max(d))) // (2 if s > 8 else 4) + 4, dtype=torch.int32, device="cuda")
+                   for _ in range(2)]
+        out = torch.zeros((n, d[-1]), dtype=torch.int32, device="cuda")
+        if form == "two bytes":
+            B.qgtc_wide_forward(B.WideStack(A, layers, s, buffers, lists), out, src=dev(X), quant=(-3.0, 3.0))
+        elif form == "update first":
+            B.qgtc_stack_forward_update_first(B.Stack(A, None, layers, s, buffers, lists), out, dev(X), (-3.0, 3.0))
+        else:
+            B.qgtc_stack_forward(B.Stack(A, None, layers, s, buffers, lists), out, src=dev(X), quant=(-3.0, 3.0))
+        assert (out.cpu().numpy() == qgnn.int_output(z, relu)).all()
+        assert len(np.unique(x)) > 2 and len(torch.unique(out)) > 2
 
 
 def test_lists_follow_the_adjacency():
