@@ -248,14 +248,14 @@ struct HostJob {
     // A thread takes as long to start as 4 MiB of a vectorized loop (16 MiB of adjacency and 8 MiB of features: one
     // thread 510 us, two 328, four 176, eight 189, sixteen 347), or 512 KiB of another.
     const bool fast = pack.nbits <= 8 && (is_left ? pack.src_dtype == QGTC_SRC_U8 && pack.nbits == 1 : pack.src_dtype == QGTC_SRC_F32);
-    worth += 16 * items[n] * row / (fast ? 4 << 20 : 512 << 10);
+    worth += 16 * row * items[n] / (fast ? 4 << 20 : 512 << 10);
     ++n;
   }
   int all() const { return pieces[0] + (n > 1 ? pieces[1] : 0); }
   void work() {
     for (int k; (k = next.fetch_add(1, std::memory_order_relaxed)) < all();) {
       const int o = k < pieces[0] ? 0 : 1, at = (o == 0 ? k : k - pieces[0]) * step[o];
-      pack_range(p[o], left[o], at, std::min(items[o], at + step[o]));
+      pack_range(p[o], left[o], at, at + std::min(step[o], items[o] - at));
     }
   }
   // Threads [a, b): the first is this one, which starts the others with half of what is left each (a thread

@@ -1,6 +1,8 @@
 """Host-side packing (Section 4.6): qgtc_pack_bits_host against the oracle's packing and
 quantizer, the compound-buffer layout, argument checks.  No GPU needed."""
 import ctypes as C
+import os
+import threading
 
 import numpy as np
 import pytest
@@ -173,3 +175,27 @@ def test_two_operands_by_the_same_threads():
     assert fn(None, 2, 1) == 1 and fn((b._HostOperandC * 1)(oa), 0, 1) == 2 and fn((b._HostOperandC * 2)(oa, ox), 2, -1) == 2
     bad = b._HostOperandC(x.ctypes.data, b.SRC_F32, 700, 40, 0, 39, C.pointer(q), C.pointer(dx))
     assert fn((b._HostOperandC * 2)(oa, bad), 2, 1) == 2
+
+
+def test_more_than_2_to_27_rows_are_shared_by_the_threads():
+    """16 times as many rows are no 32-bit number."""
+    b = _b()
+    rows = (1 << 27) + 3
+    a, words = np.zeros(rows, np.uint8), np.full(rows, 7, np.uint32)
+    a[::1000] = 1
+    d = b._BitsC.from_buffer_copy(b.describe(rows, 1, 1, b.LEFT)[0])
+    d.data, d.ld_words = words.ctypes.data, 1
+    seen, done = [], threading.Event()
+
+    def watch():
+        while not done.is_set():
+            seen.append(len(os.listdir("/proc/self/task")))
+
+    watcher = threading.Thread(target=watch)
+    watcher.start()
+    before = len(os.listdir("/proc/self/task"))
+    st = b.lib().qgtc_pack_bits_host(C.c_void_p(a.ctypes.data), b.SRC_U8, rows, 1, 1, None, C.byref(d), 4)
+    done.set()
+    watcher.join()
+    assert st == 0 and (words == a).all()
+    assert max(seen) >= before + 3
