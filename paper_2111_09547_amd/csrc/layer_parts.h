@@ -1,4 +1,4 @@
-// What the two fused layer kernels (layer_kernel.h, gather.hip) share: requantization of the
+// What the two fused layer kernels (layer_kernel.h, gather_kernel.h) share: requantization of the
 // aggregated sums to bytes, the weights as operands of the matrix instruction.
 #pragma once
 #include "agg_mfma.h"

@@ -252,7 +252,10 @@ __device__ __forceinline__ void pack_weights_of(const WeightsParams& jobs) {
 }
 __global__ __launch_bounds__(256) void pack_weights_kernel(const WeightsParams jobs) { pack_weights_of(jobs); }
 
-// LEFT_BYTES: one code per byte, row-major; a thread writes 4 consecutive bytes.
+// LEFT_BYTES: one code per byte, row-major; a thread writes 4 consecutive bytes.  Bound by its 4-byte loads: features of
+// a width that is no multiple of four run at 4 to 5 TB/s.  The quantizer to the order of whole tiles, which those took
+// before they were rows, and this one, us: 65536 x 101 10.6 and 8.9, 262144 x 101 33 and 27, x 301 101 and 82,
+// x 513 171 and 141.
 template <int SRC>
 __global__ __launch_bounds__(256) void pack_left_bytes_kernel(const PackParams p) {
   const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;   // dword index
@@ -503,7 +506,8 @@ UnpackParams unpack_params(const qgtc_bits* m) {
 }
 
 // Codes of 9 to 16 bits as rows of low bytes and behind them of high bytes, all minus 128: a thread has
-// four columns.
+// four columns.  Bound by HBM and its 4-byte loads; planes of 16 bits (pack_right_kernel) and this one, us: 65536 x 64 8.2 and
+// 8.0, 262144 x 64 18.9 and 19.2, x 101 40 and 28, x 300 125 and 88, x 512 164 and 144 (805 MB in and out: 5.6 TB/s).
 __global__ __launch_bounds__(256) void pack_wide_rows_kernel(const PackParams p, int quads) {
   const unsigned idx = blockIdx.x * 256u + threadIdx.x;
   const int r = (int)(idx / (unsigned)quads), c0 = 4 * (int)(idx % (unsigned)quads);
@@ -614,18 +618,8 @@ qgtc_status pack_row_codes_and_weights(const qgtc_weight_source* ws, int n, int 
 }
 
 qgtc_status pack_wide_rows(const float* src, int64_t ld_src, int rows, int cols, const qgtc_quant* q, uint8_t* dst, hipStream_t stream) {
-  PackParams p{};
-  p.src = src;
-  p.ld_src = ld_src;
-  p.rows = rows;
-  p.cols = cols;
-  p.nbits = q->nbits;
-  p.dst = reinterpret_cast<uint32_t*>(dst);
-  p.ld = row_codes_ld(cols) / 2;                     // words of both bytes
-  p.qmax = (1u << q->nbits) - 1u;
-  p.qmaxf = (float)p.qmax;
-  p.lo = (float)q->lo;
-  p.inv = qgtc_quant_inv_scale(q->lo, q->hi, q->nbits);
+  PackParams p = row_codes_params(src, ld_src, rows, cols, q, dst);
+  p.ld *= 2;                                         // words of both bytes
   const int quads = (int)(p.ld / 2);
   ProfScope prof(QGTC_KERNEL_PACK, stream);
   hipLaunchKernelGGL(pack_wide_rows_kernel, dim3((unsigned)cdiv((int64_t)rows * quads, 256)), dim3(256), 0, stream, p, quads);
