@@ -120,15 +120,16 @@ def kernel_events(fn, steps):
 
 
 def dominant_kernel(net, w, prof, steps, agg_ops):
-    """The kernel that carries the aggregation: the fused layer kernel where it applies,
-    else the aggregation kernel.  Returns (name, achieved bit-op/s, avg launch ms, launches)."""
+    """The kernel that carries the aggregation: the fused layer kernel, over neighbour lists or
+    whole tiles, where it applies, else the aggregation kernel.  Returns (name, achieved bit-op/s, avg launch ms, launches)."""
     from paper_2111_09547_amd.model import fused_layer_applies
     fused = prof["layer"][1] > 0
     dom_ms, dom_n = prof["layer"] if fused else prof["aggregate"]
-    fused_layers = [fused_layer_applies(d, h, w.s, w.t) for d, h in net.dims]
+    lists = net.lists is not None              # (all layers of the network, of 9 to 16 bits as well)
+    fused_layers = [lists or fused_layer_applies(d, h, w.s, w.t) for d, h in net.dims]
     dom_ops = sum(o for o, f in zip(agg_ops, fused_layers) if f == fused)
     rate = dom_ops * steps / (dom_ms * 1e-3) if dom_ms > 0 else 0.0
-    return ("layer_kernel" if fused else "aggregate_kernel"), rate, dom_ms / max(dom_n, 1), dom_n
+    return ("gather_layer_kernel" if fused and lists else "layer_kernel" if fused else "aggregate_kernel"), rate, dom_ms / max(dom_n, 1), dom_n
 
 
 def ratio_8x128(net):
@@ -318,7 +319,7 @@ def main():
     # The counter runs are child processes of their own (rocprofv3 around this script); they
     # come first, before this process touches the GPU.
     traffic, traffic_note = (None, "skipped")
-    dom_guess = "layer_kernel" if args.bits <= 8 else "aggregate_kernel"
+    dom_guess = "layer_kernel" if args.bits <= 16 else "aggregate_kernel"    # (over lists or not)
     if not (args.no_traffic or args.traffic_child or args.copy_calibration):
         traffic, traffic_note = measure_traffic(args.config, args.bits, dom_guess, tile_kbits=args.tile_kbits)
 
@@ -435,7 +436,7 @@ def main():
                       for d, h in net.dims)
     tile_kbits = net.map.c.tile_kbits
 
-    if dom_name != dom_guess:
+    if dom_guess not in dom_name:
         traffic, traffic_note = None, f"counter runs looked for {dom_guess}, the step ran {dom_name}"
 
     rec = {
@@ -452,10 +453,11 @@ def main():
                    "nonzero_tiles": nnz,
                    "nonzero_tile_ratio": nnz / float(net.map.c.n_tile_rows * net.map.c.n_tile_cols),
                    "nonzero_tile_ratio_8x128": ratio_8x128(net),
-                   "step": "pack A + tile map + pack W + pack X + all layers"},
+                   "step": "pack A + neighbour lists and tile map + pack W + pack X + all layers"},
         "value_counts": "aggregation: AND + popcount bit-ops of the tiles the zero-tile map keeps "
                         "(value_popcount_executed: of their non-zero words only); update: nominal 2 N D H s t; "
-                        "both execute as int8 multiply-accumulates on the matrix cores",
+                        "both execute on the int8 matrix cores, the aggregation of a sparse graph as sums of its "
+                        "neighbours' codes",
         "value_popcount_kept_tiles": sum(agg_ops) / (ms_step * 1e-3) / 1e12,
         "value_popcount_executed": sum(visited) / (ms_step * 1e-3) / 1e12,
         "zero_word_jumping": visited != agg_ops,
@@ -480,7 +482,7 @@ def main():
                      "avg_launch_ms": dom_avg_ms, "launches": dom_n,
                      "counted": "AND + popcount bit-ops of the non-zero words of the aggregation, the method's work, "
                                 "against the vector-ALU ceiling of that form; the kernel itself takes all planes at "
-                                "once on the int8 matrix cores, so this is a rate and no utilisation (it can pass 1); "
+                                "once on the int8 matrix cores and, over neighbour lists, only the bits that are set, so this is a rate and no utilisation (it can pass 1); "
                                 "launch durations are taken with the launches one after the other on one stream",
                      "frac_in_step": sum(visited) / (ms_layers * 1e-3) / PEAK_BITOPS,
                      # the bit-ops of the kept tiles over the same launch time: a rate as well, above 1
