@@ -5,7 +5,8 @@
            as full-precision-equivalent TFLOP/s = 2 N^2 D / t (the paper's unit)
   config3  one layer per bit width (s = t in 1..8, 16, 32) on the 8 x 1024 batch
   config5  the 2-layer GCN on the power-law graph for s = t in {1, 2, 4, 8}, with 128-, 64- and
-           32-bit tiles, and in the update-first order A.(X.W)
+           32-bit tiles in the map (which layers over neighbour lists do not read), and in the
+           update-first order A.(X.W)
 
   sizes    the 1-bit x 1-bit aggregation over N in {128 .. 32768} and D in {16 .. 1024}
            (the paper's adjacency-matrix-size study, Fig. 9), every tile non-zero
@@ -22,8 +23,8 @@
   streaming the HBM-bound kernels one at a time at the shapes of configs 4 and 5: packing the
            adjacency and the features, the zero-tile map and statistics, the update on the
            matrix cores from planes and from bytes; achieved TB/s of algorithmic bytes
-  tiles    cost of an adjacency bit by tile width (16 x 32 / 64 / 128) on configs 4 and 5:
-           the measurement behind the selector's tile-width rule
+  tiles    cost of an adjacency bit by tile width (16 x 32 / 64 / 128) on configs 4 and 5, with
+           layers that read whole tiles: the measurement behind the selector's tile-width rule
 
 Run:  python -m paper_2111_09547_amd.sweeps [table3|config3|config5|sizes|reuse|transfer|gate|streaming|tiles ...]
 Prints one JSON line per measurement and a markdown table per sweep."""
@@ -393,7 +394,7 @@ def tiles():
         xr = (float(w.X.min()), float(w.X.max()))
         base = None
         for kb in (128, 64, 32):
-            net = QuantGNN(a_src, ws, w.s, w.t, w.model == "gin", tile_kbits=kb, block_rows=g.block)
+            net = QuantGNN(a_src, ws, w.s, w.t, w.model == "gin", tile_kbits=kb, block_rows=g.block, lists=False)
             ranges = net.calibrate(x, xr)
             out = torch.empty((g.n_nodes, net.dims[-1][1]), dtype=torch.float32, device="cuda")
             t = _kernel_us(lambda: net.forward(x, xr, ranges, out=out), q.KERNEL_LAYER, n=5, warm=2) * len(net.dims)
