@@ -144,7 +144,7 @@ class QuantGNN:
         # nothing would tell a pass that other bits were packed into A.
         self.lists = None
         # 9 to 16 bits over lists: codes as two bytes, where lists pay for bytes (planes lose more there: an
-        # aggregation reads s of them, an update multiplies s * t; 64 -> 64 on 8192 rows, 16 bits: 54 us, and 18)
+        # aggregation reads s of them, an update multiplies s * t; 64 -> 64 on 8192 rows, 16 bits: 54 us, and 16 to 20)
         wide = not update_first and n < 1 << 24 and self.A.c.ld_words < 1 << 24 and 9 <= s <= 16 and t <= 16 and all(d <= 512 and h <= 256 for d, h in self.dims) and \
             (self.tuning is None or self.tuning.layer_path == B.LAYER_FUSED) and all(W.dtype == torch.float32 for W in self.Ws)
         whole = self._fused or wide or (update_first and all(fused_layer_applies(d, h, s, t) for d, h in self.dims) and
@@ -230,9 +230,9 @@ class QuantGNN:
 
     def _pack_weights_and(self, X, x_range):
         plain = all(W.dtype == torch.float32 and W.is_contiguous() for W in self.Ws)
-        if self._wide or (self._W_bytes is not None and plain):
+        if self._W_bytes is not None and plain:
             low, high = [ops[0] for ops in self._W_bytes], [op for ops in self._W_bytes for op in ops[1:]]
-            key = [(W.data_ptr(), *r) for W, r in zip(self.Ws, self.w_ranges)] + [op.c.data for op in low + high]
+            key = [(W.data_ptr(), W.shape, *r) for W, r in zip(self.Ws, self.w_ranges)] + [op.c.data for op in low + high]
             if getattr(self, "_w_sources", (None,))[0] != key:
                 twice = 2 if high else 1
                 self._w_sources = (key, B.WeightSources(self.Ws * twice, self.w_ranges * twice, low + high, self.t,
@@ -243,7 +243,7 @@ class QuantGNN:
                 for W, r, dst in zip(self.Ws, self.w_ranges, self._W_ops):
                     B.qgtc_pack_bits(W, self.t, B.RIGHT, quant=r, out=dst)
         elif all(lay == B.RIGHT_BYTES for lay in self.w_layout) and plain:
-            key = [(W.data_ptr(), o.c.data, *r) for W, o, r in zip(self.Ws, self._W_ops, self.w_ranges)]
+            key = [(W.data_ptr(), W.shape, o.c.data, *r) for W, o, r in zip(self.Ws, self._W_ops, self.w_ranges)]
             if getattr(self, "_w_sources", (None,))[0] != key:
                 self._w_sources = (key, B.WeightSources(self.Ws, self.w_ranges, self._W_ops))
             # only the last layer dequantizes, so only its column sums are needed
@@ -259,8 +259,7 @@ class QuantGNN:
             for W, r, dst, lay in zip(self.Ws, self.w_ranges, self._W_ops, self.w_layout):
                 B.qgtc_pack_bits(W, self.t, lay, quant=r, out=dst)
             self.w_colsum = [None] * (len(self.dims) - 1) + [B.qgtc_col_sums(self._W_ops[-1], out=self._w_colsum_buf)]
-            for W, r, (dst,) in zip(self.Ws, self.w_ranges, self._W_bytes or []):
-                B.qgtc_pack_bits(W, self.t, B.RIGHT_BYTES, quant=r, out=dst)
+            self._pack_w_bytes()
         if X is not None and not self.update_first:
             if (self._fused or self._wide) and X.dtype == torch.float32:
                 assert tuple(X.shape) == (self.A.rows, self.dims[0][0])
@@ -289,9 +288,12 @@ class QuantGNN:
         return [B.alloc_bits(d, h, min(nbits, 8), B.RIGHT_BYTES)] + ([B.alloc_bits(d, h, nbits - 8, B.RIGHT_BYTES)] if nbits > 8 else [])
 
     def _follow_weights(self):
-        if not self._w_asked or self._W_bytes is None:
-            return
-        for l, W in enumerate(self._W_ops):
+        if self._w_asked:
+            self._pack_w_bytes()
+
+    def _pack_w_bytes(self):
+        """The weights as passes over lists read them from the operands of W, where that is another form."""
+        for l, W in enumerate(self._W_ops if self._W_bytes is not None else ()):
             if W.nbits > (16 if self._wide else 8):
                 raise ValueError(f"weights of {W.nbits} bits in a network of {self.t}")
             if W.nbits != sum(op.nbits for op in self._W_bytes[l]):

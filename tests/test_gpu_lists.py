@@ -445,6 +445,36 @@ def test_update_first_over_lists_packs_the_weights_once(monkeypatch, t):
     assert not packed()
 
 
+@pytest.mark.parametrize("s,t,update_first", [(4, 4, False), (8, 7, True), (16, 7, False), (12, 16, False)])
+def test_weights_of_another_kind_are_packed(s, t, update_first):
+    """pack_static() of weights that were replaced by integers, by rows of a wider matrix, or where the old ones were."""
+    rng = np.random.default_rng(s + t)
+    a, _ = block_graph(rng, 5, 96, 31, 6.0)
+    shapes = ((20, 24), (24, 9))
+    Ws = [dev(rng.uniform(-1, 1, dh).astype(np.float32)) for dh in shapes]
+    nets = [QuantGNN(dev(a), Ws, s, t, False, block_rows=96, lists=lists, update_first=update_first) for lists in (True, False)]
+    assert nets[0].lists is not None and nets[1].lists is None
+    x, xr = dev(rng.standard_normal((a.shape[0], 20)).astype(np.float32)), (-3.0, 3.0)
+    ranges = nets[1].calibrate(x, xr)
+    outs = []
+    for W in (dev(rng.integers(0, 1 << t, shapes[0]).astype(np.int32)), dev(rng.uniform(-1, 1, (20, 31)).astype(np.float32))[:, 3:27],
+              dev(rng.integers(0, 1 << min(t, 8), shapes[0]).astype(np.uint8)), Ws[0].clone()):
+        for net in nets:
+            net.Ws[0] = W
+            net.pack_static()
+        want = nets[1].forward(x, xr, ranges)
+        assert not any(torch.equal(want, o) for o in outs)
+        assert torch.equal(nets[0].forward(x, xr, ranges), want)
+        assert torch.equal(nets[0].forward(x, xr, ranges, want_int=True), nets[1].forward(x, xr, ranges, want_int=True))
+        if not update_first:
+            assert torch.equal(nets[0].forward(x, xr, ranges, streams=2), want)
+        outs.append(want)
+    for net in nets:
+        net.Ws[0] = net.Ws[0].view(24, 20)
+        with pytest.raises((q.QgtcError, AssertionError)):
+            net.pack_static()
+
+
 @pytest.mark.parametrize("s,t,update_first", [(4, 4, False), (8, 8, True), (4, 3, True), (16, 7, False), (12, 16, False)])
 def test_passes_follow_replaced_weights(s, t, update_first):
     """W[l] replaced, all of W replaced, and other weights packed into an operand: what a network without lists computes
