@@ -418,6 +418,7 @@ qgtc_status qgtc_layer_static(const qgtc_bits* A, const qgtc_tile_map* map,
  *                           pass over A, but not its nnz_tiles (qgtc_tile_map_total)
  * The fields are qgtc_neighbours_carve's.  One that points elsewhere has the same alignment (first, rest and
  * heavy_cnt 16 bytes, heavy 8, deg 4, else QGTC_ERR_ALIGN) and room: heavy_cnt is read in whole pieces of 16.
+ * Lists take 2 bytes per column of a row, up to 512 a row, whatever its degree.
  */
 typedef struct qgtc_neighbours {
   int32_t rows, cols, block_rows;     /* of A */

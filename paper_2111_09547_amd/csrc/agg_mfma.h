@@ -5,8 +5,8 @@
 // with the codes of X, so one v_mfma_i32_16x16x64_i8 takes 16 rows x 16 columns x 64 K
 // positions of ALL planes at once.  What is left to do is to bring both operands into bytes:
 //   A  one adjacency word w becomes eight operand registers (w >> b) & 0x01010101, b = 0..7
-//      (15 vector instructions, ~36 cycles, per 32 K positions of 16 rows; the matrix cores
-//      take 32 CT cycles for them); register b holds K positions b, b + 8, b + 16, b + 24.
+//      (a word per lane is 16 rows by 128 K positions: 15 vector instructions, ~36 cycles, and
+//      2 CT matrix instructions of 16); register b holds K positions b, b + 8, b + 16, b + 24.
 //   X  the eight plane words of 32 rows of a column are transposed as 8 x 8 bit matrices
 //      (planes_word_to_codes): code word r holds rows r, r + 8, r + 16, r + 24 - the same
 //      order.  This is done once per workgroup while X is staged into LDS; between the
@@ -35,6 +35,9 @@
 // Pipeline.  X in operand order and the words of A go to LDS without passing through registers
 // (4 to 16 KiB of X and SWC KiB of A per unit and stage), two stages ahead, through three slots with
 // one barrier per stage; the matrix cores' time per stage is 256 to 512 cycles per wave.
+// What bounds it is a stage's latency and its barrier: 16384 x 16384 x 256 at 4 bits, 96 us, is two waves per SIMD, whose
+// vector instructions take 38 us and matrix instructions 31, and which wait a third of their time; 8192 x 8192 x 64 at 2 bits,
+// 18 us, 6.4 and 2 us, and half of the time.
 #pragma once
 #include <type_traits>
 

@@ -17,8 +17,9 @@
 //      the weights of 64 columns are dealt to four tiles so that a lane has 16 columns side by side.
 // WPT = 1: a wave has a tile, and waits for nobody but the weights.  WPT = 4: four waves share a tile, where
 // there are few.  LT: 16-column output tiles at a time.
-// What bounds it: narrow rows the vector ALUs (some 500 instructions per tile and wave) and the latency of
-// four dependent loads behind a launch of 2.4 us; wide rows HBM and latency.  Whole tiles and lists, us:
+// What bounds it at every width: latency, of four dependent loads behind a launch of 2.4 us and, in wide rows, of the
+// 4 KiB that a wave has in flight.  Waves wait 57 to 71 % of their time; the vector ALUs' 320 to 450 instructions per
+// wave are a third of the time of 64 -> 64 on 65536 rows, and 512 -> 16 reads at 2.1 TB/s.  Whole tiles and lists, us:
 // 65536 rows in blocks of 1024, 9 neighbours, 64 -> 64 13.2 and 9.0, 128 -> 128 19.5 and 15.0; 8192 rows,
 // 64 -> 64 8.6 and 4.1; 262144 rows of a power-law graph, 512 -> 16 159 and 85 (134 MB of codes: 27 at the
 // rate of a copy), 1024 -> 64 on 65536 rows 168 and 95; without heavy rows 512 -> 16 320 and 64.
