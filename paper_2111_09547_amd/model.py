@@ -143,6 +143,7 @@ class QuantGNN:
         # are counted once), or as the caller says.  The results are the same.  Without a map only as the caller says:
         # nothing would tell a pass that other bits were packed into A.
         self.lists = None
+        self._lists_of, self._map_deg = (None, None, 0), (None, None)
         # 9 to 16 bits over lists: codes as two bytes, where lists pay for bytes (planes lose more there: an
         # aggregation reads s of them, an update multiplies s * t; 64 -> 64 on 8192 rows, 16 bits: 54 us, and 16 to 20)
         wide = not update_first and n < 1 << 24 and self.A.c.ld_words < 1 << 24 and 9 <= s <= 16 and t <= 16 and all(d <= 512 and h <= 256 for d, h in self.dims) and \
@@ -192,7 +193,9 @@ class QuantGNN:
             if self.use_map and self.map is None:
                 self.map = B._alloc_tile_map(self.A, 16, self.tile_kbits)
             self._build_lists(self.map)
-            self.deg = self.map.deg if self.use_map else self.lists.deg
+            if self.use_map and self._map_deg[0] is not self.map:
+                self._map_deg = (self.map, self.map.deg)
+            self.deg = self._map_deg[1] if self.use_map else self.lists.deg
             self._made = (self.map, self.deg)
         elif self.use_map:
             self.map = B.qgtc_build_tile_map(self.A, 16, self.tile_kbits, out=self.map)
@@ -202,6 +205,9 @@ class QuantGNN:
 
     def _build_lists(self, tmap):
         """Lists of the adjacency as it is now, with tmap's tiles and degrees in the same pass."""
+        if self._lists_current():
+            B.qgtc_build_neighbours(self.A, self.lists, tmap)
+            return
         A, c = self.A, self.lists.c
         same = (c.rows, c.cols, c.block_rows) == (A.rows, A.cols, A.c.block_rows)
         self.lists = B.qgtc_build_neighbours(A, self.lists if same else None, tmap)
@@ -209,16 +215,17 @@ class QuantGNN:
             # (other bits packed into A itself have a map of their own, or one that was built again)
             self._lists_of = (self.A, self.map, self.map.builds if self.map is not None else 0)
 
+    def _lists_current(self):
+        A, tmap, builds = self._lists_of
+        return A is self.A and tmap is self.map and (tmap is None or tmap.builds == builds)
+
     def _follow_adjacency(self):
         """Over lists: an adjacency that was replaced, or whose map was, and not packed since gets its own, and so do the
         map and the degrees unless the caller made those as well."""
-        if self.lists is None:
-            return
-        A, tmap, builds = self._lists_of
-        if A is self.A and tmap is self.map and (tmap is None or tmap.builds == builds):
+        if self.lists is None or self._lists_current():
             return
         tmap, deg = self._made                   # pack_static()'s
-        ours = self.use_map and self.map is tmap and A is not self.A
+        ours = self.use_map and self.map is tmap and self._lists_of[0] is not self.A
         if ours and (tmap.rows != self.A.rows or tmap.c.n_tile_cols != -(-self.A.cols // self.tile_kbits)):
             tmap = B._alloc_tile_map(self.A, 16, self.tile_kbits)
         if ours:
