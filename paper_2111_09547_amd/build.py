@@ -14,7 +14,7 @@ LIB_PATH = os.path.join(LIB_DIR, "libqgtc.so")
 OBJ_DIR = os.path.join(PKG, "_build")
 
 SOURCES = ["api.hip", "plan.hip", "pack.hip", "host_pack.hip", "tilemap.hip", "lists.hip", "gather.hip",
-           "gather_m0.hip", "gather_m1.hip", "gather_m2.hip", "gather_m3.hip", "gather_wide.hip", "first_product.hip", "aggregate.hip", "layer.hip",
+           "gather_m0.hip", "gather_m1.hip", "gather_m2.hip", "gather_m3.hip", "gather_wide.hip", "first_product.hip", "aggregate.hip", "agg_dense.hip", "layer.hip",
            "layer_n0.hip", "layer_n1.hip", "layer_n4.hip", "layer_n16.hip", "stack.hip", "update.hip", "update_mfma.hip", "probe.hip"]
 
 HIPCC_FLAGS = [

@@ -2,7 +2,7 @@
 // non-zero tile reuse, Sections 4.3 and 4.4 of the paper): the product of agg_mfma.h with
 // the output epilogues.  X of more than eight planes is taken eight planes at a time and
 // the partial results are shifted and added (modulo 2^32).
-#include "agg_mfma.h"
+#include "agg_dense.h"
 
 namespace qgtc {
 namespace {
@@ -283,9 +283,14 @@ extern "C" int32_t qgtc_aggregate_reads_map(const qgtc_bits* A, int32_t x_cols) 
 
 static int64_t codes_bytes(const AggParams& p, const AggSplit& sp) { return codes_group_bytes(p.x_kwords, sp.lt) * cdiv(p.cols, 16 * sp.lt); }
 
+// Where the features become operands of 4- or 6-bit floats (agg_dense.hip) instead of bytes: wherever the sums are exact
+// there, but not 5 to 8 bits of 16 or fewer columns, half of whose 32-column tiles would be empty (12288 x 12288 x 16:
+// bytes 17.9, two 6-bit parts 20.1 us; at 2 bits 17.6 and 13.3).
+static bool takes_floats(const AggParams& p) { return dense_applies(p) && !(p.cols <= 16 && p.s > 4); }
+
 // Whether the features are turned into codes by a launch of their own (3 us) instead of by every workgroup, for
 // whom a stage of planes goes through registers, whose wait is also one for the stage's words of A: from
-// nine stages of K on.  Planes and codes, us:
+// nine stages of K on.  Planes and codes as bytes, us:
 //   stages of two chunks: 2048 rows per block (eight stages), 64 columns 19.1 and 17.8, 128 columns 22.8 and 24.2;
 //   3072 x 256 (twelve) 19.8 and 17.8; 8192 x 300 71 and 51; 16384 x 256 112 and 90
 //   of eight, which four waves share: 4096 x 64 (four) 10.4 and 10.7; 8192 x 64 (eight) 18.9 and 18.7, and with
@@ -299,7 +304,8 @@ extern "C" size_t qgtc_aggregate_workspace_bytes(const qgtc_bits* A, const qgtc_
   AggParams p{};
   if (!A || !X || A->rows == 0 || X->cols == 0 || agg_fill_params(A, nullptr, X, &p) != QGTC_OK) return 0;
   const AggSplit sp = aggregate_split(A->rows, X->cols, p.a_words, A->ld_words);
-  return aggregate_from_codes(p, sp) ? (size_t)codes_bytes(p, sp) : 0;
+  if (!aggregate_from_codes(p, sp)) return 0;
+  return (size_t)(takes_floats(p) ? dense_bytes(p) : codes_bytes(p, sp));
 }
 
 extern "C" qgtc_status qgtc_aggregate_ws(const qgtc_bits* A, const qgtc_tile_map* map, const qgtc_bits* X,
@@ -323,6 +329,10 @@ extern "C" qgtc_status qgtc_aggregate_ws(const qgtc_bits* A, const qgtc_tile_map
   ProfScope prof(QGTC_KERNEL_AGGREGATE, s);
   if (workspace && aggregate_from_codes(p, sp)) {
     if (((uintptr_t)workspace & 15u) != 0) return QGTC_ERR_ALIGN;
+    if (takes_floats(p)) {
+      if (workspace_bytes < (size_t)dense_bytes(p)) return QGTC_ERR_WORKSPACE;
+      return dense_aggregate(p, workspace, ep->tuning ? ep->tuning->agg_xcd_run : 0, s);
+    }
     if (workspace_bytes < (size_t)codes_bytes(p, sp)) return QGTC_ERR_WORKSPACE;
     if (sp.ct == 2) return launch_codes<2, 2, 1>(&p, X, workspace, lds, s);
     if (sp.ways == 2) return launch_codes<1, 2, 1>(&p, X, workspace, lds, s);

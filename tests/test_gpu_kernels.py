@@ -924,3 +924,37 @@ def test_aggregation_of_long_rows(n, k, d, s, block, density, codes, with_map):
             graph.replay()
             assert torch.equal(q.qgtc_aggregate(A, tmap, X, q.Epilogue(mode=q.OUT_I32)), want)
             assert torch.equal(out, want)
+
+
+@pytest.mark.parametrize("n,k,d,block", [
+    (1030, 8193, 65, 0),           # 65 chunks, the last one of a column; three column groups, the last one of a column
+    (1024, 65664, 33, 0),          # sums up to the last exact ones at 8 bits
+    (1025, 65792, 17, 0),
+    (40 * 256 + 1, 8300, 250, 0),  # 256 rows per workgroup, 128 and 64 below
+    (20 * 256 - 31, 8300, 130, 0),
+    (20 * 256 - 31, 8300, 40, 0),
+    (2 * 8224 + 33, 8224, 70, 8224),   # diagonal blocks, the last one of two words of rows
+])
+@pytest.mark.parametrize("s", [1, 2, 3, 4, 5, 8])
+def test_aggregation_on_small_floats_is_exact(n, k, d, block, s):
+    """Products of 4- and 6-bit floats against float64: whole tiles of ones and of the largest code, rows and chunks of
+    zeros, the self term, with and without a map that leaves chunks out."""
+    import ctypes as C
+    import paper_2111_09547_amd.binding as B
+    gen = torch.Generator(device="cuda").manual_seed(n + s)
+    a = (torch.rand((n, k), generator=gen, device="cuda") < 0.4).to(torch.uint8)
+    a[:40] = 1
+    a[100:140] = 0
+    a[64:, k // 2:k // 2 + 1100] = 0
+    if block:
+        a[n // block * block:, n % block:] = 0
+    x = torch.randint(0, 1 << s, (n if block else k, d), generator=gen, device="cuda", dtype=torch.int32)
+    x[:, :9] = (1 << s) - 1
+    A, X = q.qgtc_pack_bits(a, 1, q.LEFT, block_rows=block), q.qgtc_pack_bits(x, s, q.RIGHT)
+    assert B.lib().qgtc_aggregate_workspace_bytes(C.byref(A.c), C.byref(X.c)) == -(-x.shape[0] // 32) * -(-d // 32) * 32 * (16 if s <= 2 else (24 if s <= 4 else 48))
+    parts = [slice(r, min(r + block, n)) for r in range(0, n, block)] if block else [slice(0, n)]
+    want = torch.cat([a[p, :p.stop - p.start if block else k].double() @ (x[p] if block else x).double() for p in parts]).to(torch.int32)
+    for tmap in (None, q.qgtc_build_tile_map(A, 16, 128)):
+        assert torch.equal(q.qgtc_aggregate(A, tmap, X, q.Epilogue(mode=q.OUT_I32)), want)
+        if block:
+            assert torch.equal(q.qgtc_aggregate(A, tmap, X, q.Epilogue(mode=q.OUT_I32, self_term=True)), want + x)
