@@ -494,6 +494,13 @@ qgtc_status qgtc_stack_input_and_weights(const float* src, int32_t rows, int32_t
                                          const qgtc_quant* q, void* buffer, size_t buffer_bytes,
                                          const qgtc_weight_source* ws, int32_t n, int32_t sums_of,
                                          int32_t* col_sums, void* stream);
+/* What a mini-batch brings, in one call, and one launch where that is possible: the adjacency packed from 0/1 bytes
+ * (bit 0 of each, as qgtc_pack_bits) with its neighbour lists and, unless NULL, map (as qgtc_build_neighbours), the weights
+ * (qgtc_pack_weights) and, unless x is NULL, the features (qgtc_stack_input_rows).  The same results as those calls. */
+qgtc_status qgtc_pack_batch(const uint8_t* a_src, int64_t ld_a, const qgtc_bits* A, const qgtc_neighbours* lists,
+                            const qgtc_tile_map* map, const qgtc_weight_source* ws, int32_t n, int32_t sums_of,
+                            int32_t* col_sums, const float* x, int32_t x_cols, int64_t ld_x, const qgtc_quant* q,
+                            void* buffer, size_t buffer_bytes, void* stream);
 qgtc_status qgtc_stack_forward(const qgtc_stack* stack, const float* src, int64_t ld_src,
                                const qgtc_quant* q, const qgtc_bits* X, void* out, int64_t ld_out,
                                void* stream);

@@ -179,6 +179,8 @@ def lib():
         "qgtc_stack_input_rows": (C.c_int, [vp, i32, i32, i64, P(_QuantC), vp, sz, vp]),
         "qgtc_stack_forward": (C.c_int, [P(_StackC), vp, i64, P(_QuantC), P(_BitsC), vp, i64, vp]),
         "qgtc_stack_input_and_weights": (C.c_int, [vp, i32, i32, i64, P(_QuantC), vp, sz, P(_WeightSourceC), i32, i32, vp, vp]),
+        "qgtc_pack_batch": (C.c_int, [vp, i64, P(_BitsC), P(_NeighboursC), P(_TileMapC), P(_WeightSourceC), i32, i32, vp,
+                                      vp, i32, i64, P(_QuantC), vp, sz, vp]),
         "qgtc_stack_forward_update_first": (C.c_int, [P(_StackC), vp, i64, P(_QuantC), vp, i64, vp]),
         "qgtc_wide_input": (C.c_int, [vp, i32, i32, i64, P(_QuantC), vp, sz, vp]),
         "qgtc_wide_forward": (C.c_int, [P(_WideStackC), vp, i64, P(_QuantC), P(_BitsC), vp, i64, vp]),
@@ -570,6 +572,26 @@ def qgtc_stack_input(src: torch.Tensor, nbits: int, quant, buffer: torch.Tensor,
     fn = lib().qgtc_stack_input_rows if rows_form else lib().qgtc_stack_input
     _check(fn(src.data_ptr(), rows, cols, src.stride(0) if rows > 1 else max(cols, 1), C.byref(q),
               buffer.data_ptr(), buffer.numel() * buffer.element_size(), _stream()), "qgtc_stack_input")
+
+
+def qgtc_pack_batch(A_src: torch.Tensor, A: Bits, lists: Neighbours, tmap: TileMap | None, weights, src: torch.Tensor | None = None,
+                    nbits: int = 0, quant=None, buffer: torch.Tensor | None = None):
+    """An adjacency from uint8 with its lists and map, weights as (sources, sums_of, col_sums) of qgtc_pack_weights
+    and, unless None, fp32 features into `buffer` (qgtc_stack_input, rows_form)."""
+    assert A_src.dim() == 2 and A_src.dtype == torch.uint8 and A_src.is_cuda and A_src.stride(1) == 1 and tuple(A_src.shape) == (A.rows, A.cols)
+    sources, sums_of, col_sums = weights
+    q = x = buf = None
+    cols = ld = nbytes = 0
+    if src is not None:
+        assert src.dim() == 2 and src.dtype == torch.float32 and src.is_cuda and src.stride(1) == 1 and src.shape[0] == A.rows
+        q, x, cols = C.byref(_QuantC(float(quant[0]), float(quant[1]), nbits)), src.data_ptr(), src.shape[1]
+        ld = src.stride(0) if src.shape[0] > 1 else max(cols, 1)
+        buf, nbytes = buffer.data_ptr(), buffer.numel() * buffer.element_size()
+    if tmap is not None:
+        tmap.totals = False
+    _check(lib().qgtc_pack_batch(A_src.data_ptr(), A_src.stride(0) if A.rows > 1 else max(A.cols, 1), C.byref(A.c), C.byref(lists.c),
+                                 C.byref(tmap.c) if tmap is not None else None, sources.c, len(sources.c), sums_of,
+                                 col_sums.data_ptr() if col_sums is not None else None, x, cols, ld, q, buf, nbytes, _stream()), "qgtc_pack_batch")
 
 
 def qgtc_stack_forward(stack: Stack, out: torch.Tensor, src: torch.Tensor | None = None, quant=None,

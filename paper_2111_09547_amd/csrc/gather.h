@@ -86,6 +86,8 @@ qgtc_status pack_row_codes(const float* src, int64_t ld_src, int rows, int cols,
 // The same and, in the same launch where the features are read 16 bytes at a time, qgtc_pack_weights.
 qgtc_status pack_row_codes_and_weights(const qgtc_weight_source* ws, int n, int sums_of, int32_t* col_sums, const float* src, int64_t ld_src,
                                        int rows, int cols, const qgtc_quant* q, uint8_t* dst, hipStream_t stream);
+// Checks of features that are quantized into a buffer of a stack.
+qgtc_status check_row_codes(const float* src, int rows, int cols, int64_t ld_src, const qgtc_quant* q, const void* buffer, size_t buffer_bytes);
 qgtc_status planes_to_rows(const qgtc_bits* X, uint8_t* dst, hipStream_t stream);
 
 }  // namespace qgtc

@@ -1,111 +1,20 @@
 // Neighbour lists of a packed adjacency: zero-tile jumping (Section 4.3 of the paper) down to the
 // single entry, for graphs of a few neighbours per node.  Like the tile map, they are laid out once
 // per adjacency and read by every layer; one pass over A makes both, and the degrees.
-#include "lists.h"
+#include "lists_of.h"
 
 namespace qgtc {
 namespace {
 
-struct ListParams {
-  const uint32_t* A;
-  int64_t lda;
-  int32_t rows;
-  int32_t n128;              // 128-bit pieces of a row
-  int32_t rest_cap;
-  uint16_t* first;
-  uint16_t* rest;
-  uint8_t* heavy_cnt;
-  uint64_t* heavy;
-  int32_t* deg;
-  int32_t* map_deg;          // the tile map's part (NULL: none)
-  int32_t* row_cnt;
-  int32_t* col_idx;
-  int32_t n_tile_cols, tile_shift;   // tiles per 128-bit piece: 1 << tile_shift
-};
-
-__device__ __forceinline__ int list_at(int e) { return (e & ~15) + 4 * (e & 3) + ((e >> 2) & 3); }
-
-// A wave per 16 rows, lane <-> (row = lane % 16, one of four 128-bit pieces = lane / 16).  A row is read
-// once, 16 pieces of it in flight together; each lane puts the positions of its bits into the row's
-// list in LDS, behind those of the lanes in front of it.  What bounds it is the latency of its
-// loads and the loops over the bits; 8 MiB of A (65536 rows of 1024 bits, 8 bits each) are read once.
+// A wave per 16 rows reads them from A.  What bounds it is the latency of its loads and the loops over the bits; 8 MiB of A
+// (65536 rows of 1024 bits, 8 bits each) are read once.
 __global__ __launch_bounds__(256) void lists_kernel(const ListParams p) {
   __shared__ __attribute__((aligned(16))) uint16_t lists[4][16][kListMax];
-  __shared__ uint32_t heavy[4];                      // the waves' heavy rows
+  __shared__ uint32_t heavy[4];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int tr = blockIdx.x * 4 + wave;
-  const int r = tr * 16 + (lane & 15), g = lane >> 4;
-  const bool r_ok = r < p.rows;
-  const uint32_t* row = p.A + (int64_t)(r_ok ? r : 0) * p.lda;
-  uint16_t* const list = lists[wave][lane & 15];
-  int count = 0, tiles = 0;                          // entries of the row so far; tiles of the map
-  for (int c0 = 0; c0 < p.n128; c0 += 16) {
-    uint4 v[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int c = c0 + 4 * u + g;
-      v[u] = make_uint4(0u, 0u, 0u, 0u);
-      if (r_ok && c < p.n128) v[u] = *reinterpret_cast<const uint4*>(row + 4 * c);
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      if (c0 + 4 * u >= p.n128) continue;            // (uniform)
-      const uint32_t w[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
-      const int mine = __builtin_popcount(w[0]) + __builtin_popcount(w[1]) + __builtin_popcount(w[2]) + __builtin_popcount(w[3]);
-      const int s1 = __shfl_up(mine, 16, 64), s2 = __shfl_up(mine, 32, 64), s3 = __shfl_up(mine, 48, 64);
-      int at = count + (g > 0 ? s1 : 0) + (g > 1 ? s2 : 0) + (g > 2 ? s3 : 0);
-      count = __shfl(at + mine, 48 + (lane & 15), 64);
-      const int k0 = (c0 + 4 * u + g) * 128;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        uint32_t m = w[i];
-        while (m) {
-          if (at < kListMax) list[list_at(at)] = (uint16_t)(k0 + 32 * i + __builtin_ctz(m));
-          ++at;
-          m &= m - 1u;
-        }
-      }
-      if (p.row_cnt) {                               // (uniform) the tile map's list of the 16 rows
-        unsigned long long b[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) b[i] = __builtin_amdgcn_ballot_w64(w[i] != 0u);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          uint32_t bits = 0u;                        // words of the piece that hold a bit
-#pragma unroll
-          for (int i = 0; i < 4; ++i) bits |= ((b[i] >> (16 * k)) & 0xffffull) != 0ull ? 1u << i : 0u;
-          const int sub = 4 >> p.tile_shift;         // words per tile
-          for (int c = 0; c < 1 << p.tile_shift; ++c) {
-            const int tile = ((c0 + 4 * u + k) << p.tile_shift) + c;
-            if (((bits >> (c * sub)) & ((1u << sub) - 1u)) != 0u && tile < p.n_tile_cols) {
-              if (lane == 0) p.col_idx[(int64_t)tr * p.n_tile_cols + tiles] = tile;
-              ++tiles;
-            }
-          }
-        }
-      }
-    }
-  }
-  if (p.row_cnt && lane == 0 && tr * 16 < p.rows) p.row_cnt[tr] = tiles;
-  const uint32_t many = (uint32_t)__builtin_amdgcn_ballot_w64(count > kListLight) & 0xffffu;
-  if (lane == 0) heavy[wave] = many;
-  const int whole = min((max(count, 1) + kListBlock - 1) / kListBlock * kListBlock, kListMax);   // whole blocks
-  for (int e = count + g; e < whole; e += 4) list[list_at(e)] = kListNone;
-  __syncthreads();                                   // (the lanes of a row also read each other's entries)
-  if (threadIdx.x == 0) {
-    const uint64_t m = (uint64_t)heavy[0] | (uint64_t)heavy[1] << 16 | (uint64_t)heavy[2] << 32 | (uint64_t)heavy[3] << 48;
-    p.heavy[blockIdx.x] = m;
-    p.heavy_cnt[blockIdx.x] = (uint8_t)__builtin_popcountll(m);
-  }
-  if (!r_ok) return;
-  if (g == 0) {
-    p.deg[r] = count;
-    if (p.map_deg) p.map_deg[r] = count;
-  }
-  if (g < 2) *reinterpret_cast<uint4*>(p.first + (int64_t)r * kListBlock + 8 * g) = *reinterpret_cast<const uint4*>(list + 8 * g);
-  const int kept = min(whole, kListBlock + p.rest_cap);
-  for (int e = kListBlock + 8 * g; e < kept; e += 32)
-    *reinterpret_cast<uint4*>(p.rest + (int64_t)r * p.rest_cap + (e - kListBlock)) = *reinterpret_cast<const uint4*>(list + e);
+  const int r = ((int)blockIdx.x * 4 + wave) * 16 + (lane & 15);
+  const uint32_t* const row = p.A + (int64_t)(r < p.rows ? r : 0) * p.lda;
+  lists_of(p, blockIdx.x, lists[wave], heavy, [&](int c) { return r < p.rows ? *reinterpret_cast<const uint4*>(row + 4 * c) : make_uint4(0u, 0u, 0u, 0u); });
 }
 
 int rest_cap_of(int cols) {
@@ -165,7 +74,8 @@ extern "C" qgtc_status qgtc_neighbours_carve(qgtc_neighbours* n, void* buffer, c
   return QGTC_OK;
 }
 
-extern "C" qgtc_status qgtc_build_neighbours(const qgtc_bits* A, const qgtc_neighbours* n, const qgtc_tile_map* map, void* stream) {
+namespace qgtc {
+qgtc_status list_params(const qgtc_bits* A, const qgtc_neighbours* n, const qgtc_tile_map* map, ListParams* to) {
   if (!A || !n) return QGTC_ERR_NULL;
   qgtc_status st = check_adjacency(A);
   if (st != QGTC_OK) return st;
@@ -182,7 +92,6 @@ extern "C" qgtc_status qgtc_build_neighbours(const qgtc_bits* A, const qgtc_neig
     p.n_tile_cols = map->n_tile_cols;
     p.tile_shift = map->tile_kbits == 128 ? 0 : (map->tile_kbits == 64 ? 1 : 2);
   }
-  if (A->rows == 0) return QGTC_OK;
   p.A = A->data;
   p.lda = A->ld_words;
   p.rows = A->rows;
@@ -193,6 +102,15 @@ extern "C" qgtc_status qgtc_build_neighbours(const qgtc_bits* A, const qgtc_neig
   p.heavy = n->heavy;
   p.heavy_cnt = n->heavy_cnt;
   p.deg = n->deg;
+  *to = p;
+  return QGTC_OK;
+}
+}  // namespace qgtc
+
+extern "C" qgtc_status qgtc_build_neighbours(const qgtc_bits* A, const qgtc_neighbours* n, const qgtc_tile_map* map, void* stream) {
+  ListParams p;
+  const qgtc_status st = list_params(A, n, map, &p);
+  if (st != QGTC_OK || A->rows == 0) return st;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   ProfScope prof(QGTC_KERNEL_TILE_MAP, s);
   hipLaunchKernelGGL(lists_kernel, dim3((unsigned)cdiv(A->rows, 64)), dim3(256), 0, s, p);

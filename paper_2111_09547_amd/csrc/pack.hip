@@ -3,6 +3,7 @@
 // compression of Section 4.2 of the paper, for gfx950.  All of these are
 // streaming kernels bound by HBM bandwidth.
 #include "gather.h"
+#include "lists_of.h"
 
 namespace qgtc {
 namespace {
@@ -232,13 +233,13 @@ struct WeightsParams {
   int32_t sums_of;           // job whose column sums are wanted, by the workgroups behind the last job (-1: none)
   int32_t* sums;
 };
-__device__ __forceinline__ void pack_weights_of(const WeightsParams& jobs) {
+__device__ __forceinline__ void pack_weights_of(const WeightsParams& jobs, int block) {
   int j = 0;
-  while (j < jobs.n && (int)blockIdx.x >= jobs.end[j]) ++j;
+  while (j < jobs.n && block >= jobs.end[j]) ++j;
   const int lane = threadIdx.x & 63;
   if (j == jobs.n) {                                 // a wave has 16 columns, a quarter of the rows per lane
     const PackParams& p = jobs.w[jobs.sums_of];
-    const int c0 = (((int)blockIdx.x - jobs.end[jobs.n - 1]) * 4 + (int)(threadIdx.x >> 6)) * 16, col = c0 + (lane & 15);
+    const int c0 = ((block - jobs.end[jobs.n - 1]) * 4 + (int)(threadIdx.x >> 6)) * 16, col = c0 + (lane & 15);
     if (c0 >= p.cols) return;
     uint32_t sum = 0u;
 #pragma unroll 8
@@ -248,9 +249,9 @@ __device__ __forceinline__ void pack_weights_of(const WeightsParams& jobs) {
     if (lane < 16 && col < p.cols) jobs.sums[col] = (int32_t)sum;
     return;
   }
-  pack_bytes_of<QGTC_SRC_F32>(jobs.w[j], jobs.n_nt[j], jobs.n_ks[j], ((int)blockIdx.x - (j > 0 ? jobs.end[j - 1] : 0)) * 256 + (int)threadIdx.x);
+  pack_bytes_of<QGTC_SRC_F32>(jobs.w[j], jobs.n_nt[j], jobs.n_ks[j], (block - (j > 0 ? jobs.end[j - 1] : 0)) * 256 + (int)threadIdx.x);
 }
-__global__ __launch_bounds__(256) void pack_weights_kernel(const WeightsParams jobs) { pack_weights_of(jobs); }
+__global__ __launch_bounds__(256) void pack_weights_kernel(const WeightsParams jobs) { pack_weights_of(jobs, (int)blockIdx.x); }
 
 // LEFT_BYTES: one code per byte, row-major; a thread writes 4 consecutive bytes.  Bound by its 4-byte loads: features of
 // a width that is no multiple of four run at 4 to 5 TB/s.  The quantizer to the order of whole tiles, which those took
@@ -329,7 +330,7 @@ __global__ __launch_bounds__(256) void pack_left_bytes_wide_kernel(const PackPar
 // recorded step on 65536 nodes (five layers) 97.7 -> 92.8 us, launched one by one on 8192 nodes 58 -> 53.
 __global__ __launch_bounds__(256) void pack_codes_and_weights_kernel(const WeightsParams jobs, unsigned groups, const PackParams p, int step_r,
                                                                      int step_w) {
-  if (blockIdx.x < groups) pack_weights_of(jobs);
+  if (blockIdx.x < groups) pack_weights_of(jobs, (int)blockIdx.x);
   else pack_left_bytes_wide_of<QGTC_SRC_F32>(p, step_r, step_w, blockIdx.x - groups);
 }
 
@@ -338,6 +339,74 @@ bool left_bytes_wide(const PackParams& p) {
   return (p.cols & 3) == 0 && (p.ld_src & 3) == 0 && ((uintptr_t)p.src & 15u) == 0 && (int64_t)p.rows * p.ld < (int64_t)1 << 31;
 }
 unsigned left_bytes_wide_groups(const PackParams& p) { return (unsigned)cdiv((int64_t)p.rows * p.ld, 256 * kByteWords); }
+
+// A mini-batch in one launch: the adjacency from bytes with its neighbour lists and map, the weights, and the features as
+// row-major codes.  Bound by HBM: 65536 rows of 1024 bytes and of 128 features, 115 MB in and out, 25.6 us = 4.5 TB/s, of
+// which the lists take 4.5 beside the loads; three launches, of which the second reads back what the first wrote, 10, 13 and 8
+// and their gaps (the whole step 90.4 and 83.7 us, eager batches of 8192 rows, whose launches the host bounds, 53.8 and 42.3).
+// Workgroups of the lists in front: they are the longer ones (behind the features 86.3 us, among them 89.9).
+struct BatchParams {
+  PackParams a;              // bytes of the adjacency; a.dst: its words
+  int32_t pieces;            // 16-byte pieces of a row, padding to 128 columns included
+  uint32_t pieces_magic;
+  ListParams lists;
+  unsigned list_groups, weight_groups;
+  PackParams x;
+  int32_t x_step_r, x_step_w;
+  WeightsParams jobs;
+};
+
+// A wave has 16 rows, whose bytes become words in LDS, kBatchLoads loads of 1 KiB in flight (4 or 16: level); the words go to memory and, from
+// where they are, into the lists.
+constexpr int kBatchPieces = 128;                    // of a row: 2048 columns
+constexpr int kBatchLoads = 8;
+__device__ __forceinline__ void pack_lists_of(const BatchParams& p, unsigned block, uint16_t (*lists)[16][kListMax], uint32_t* heavy) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int row0 = ((int)block * 4 + wave) * 16;
+  const int n_rows = min(p.a.rows - row0, 16);       // (none for a wave behind the last row)
+  // a row's words, and 16 bytes that spread the rows over the banks
+  const int stride = 2 * p.pieces + 16;
+  static_assert(16 * (2 * kBatchPieces + 16) <= 16 * kListMax * 2, "the words lie where the lists will");
+  uint8_t* const words = reinterpret_cast<uint8_t*>(lists[wave]);
+  const uint8_t* const src = reinterpret_cast<const uint8_t*>(p.a.src) + (int64_t)row0 * p.a.ld_src;
+  const int n = n_rows * p.pieces;
+#pragma unroll 1
+  for (int i0 = lane; i0 < n; i0 += 64 * kBatchLoads) {
+    uint4 v[kBatchLoads];
+    int at[kBatchLoads];
+#pragma unroll
+    for (int k = 0; k < kBatchLoads; ++k) {
+      const unsigned i = (unsigned)min(i0 + 64 * k, n - 1);
+      const int r = (int)div_by(i, (unsigned)p.pieces, p.pieces_magic), c = (int)i - r * p.pieces;
+      at[k] = r * stride + 2 * c;
+      v[k] = make_uint4(0u, 0u, 0u, 0u);
+      if (16 * c < p.a.cols) v[k] = *reinterpret_cast<const uint4*>(src + (int64_t)r * p.a.ld_src + 16 * c);
+    }
+#pragma unroll
+    for (int k = 0; k < kBatchLoads; ++k) {
+      const uint32_t h = squeeze4(v[k].x) | (squeeze4(v[k].y) << 4) | (squeeze4(v[k].z) << 8) | (squeeze4(v[k].w) << 12);
+      *reinterpret_cast<uint16_t*>(words + at[k]) = (uint16_t)h;   // (the last piece maybe several times)
+    }
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the lanes read each other's halves
+  const int ld4 = (int)p.a.ld >> 2, n128 = p.lists.n128;
+  for (int i = lane; i < n_rows * ld4; i += 64) {
+    const int r = i / ld4, c = i - r * ld4;
+    const uint4 v = c < n128 ? *reinterpret_cast<const uint4*>(words + r * stride + 16 * c) : make_uint4(0u, 0u, 0u, 0u);
+    *reinterpret_cast<uint4*>(p.a.dst + (int64_t)(row0 + r) * p.a.ld + 4 * c) = v;
+  }
+  const int mine = lane & 15;
+  lists_of(p.lists, block, lists[wave], heavy,
+           [&](int c) { return mine < n_rows ? *reinterpret_cast<const uint4*>(words + mine * stride + 16 * c) : make_uint4(0u, 0u, 0u, 0u); });
+}
+
+__global__ __launch_bounds__(256) void pack_batch_kernel(const BatchParams p) {
+  __shared__ __attribute__((aligned(16))) uint16_t lists[4][16][kListMax];
+  __shared__ uint32_t heavy[4];
+  if (blockIdx.x < p.list_groups) pack_lists_of(p, blockIdx.x, lists, heavy);
+  else if (blockIdx.x < p.list_groups + p.weight_groups) pack_weights_of(p.jobs, (int)(blockIdx.x - p.list_groups));
+  else pack_left_bytes_wide_of<QGTC_SRC_F32>(p.x, p.x_step_r, p.x_step_w, blockIdx.x - p.list_groups - p.weight_groups);
+}
 
 struct UnpackParams {
   const uint32_t* src;
@@ -684,6 +753,55 @@ extern "C" qgtc_status qgtc_pack_weights(const qgtc_weight_source* ws, int32_t n
     if (launch_status() != QGTC_OK) return QGTC_ERR_HIP;
   }
   return QGTC_OK;
+}
+
+extern "C" qgtc_status qgtc_pack_batch(const uint8_t* a_src, int64_t ld_a, const qgtc_bits* A, const qgtc_neighbours* lists,
+                                       const qgtc_tile_map* map, const qgtc_weight_source* ws, int32_t n, int32_t sums_of,
+                                       int32_t* col_sums, const float* x, int32_t x_cols, int64_t ld_x, const qgtc_quant* q, void* buffer,
+                                       size_t buffer_bytes, void* stream) {
+  if (!a_src || !A) return QGTC_ERR_NULL;
+  BatchParams b{};
+  qgtc_status st = list_params(A, lists, map, &b.lists);
+  if (st != QGTC_OK) return st;
+  if (ld_a < A->cols) return QGTC_ERR_SHAPE;
+  st = check_weights(ws, n, sums_of, col_sums);
+  if (st != QGTC_OK) return st;
+  if (x) {
+    st = check_row_codes(x, A->rows, x_cols, ld_x, q, buffer, buffer_bytes);
+    if (st != QGTC_OK) return st;
+  }
+  const int rows = A->rows;
+  if (x) b.x = row_codes_params(x, ld_x, rows, x_cols, q, reinterpret_cast<uint8_t*>(buffer));
+  // One launch where the bytes are read 16 at a time, a row's words fit its list, and the features are read 16 bytes at a time;
+  // else one each.
+  const bool one = rows > 0 && (A->cols & 15) == 0 && A->cols <= 16 * kBatchPieces && (ld_a & 15) == 0 && ((uintptr_t)a_src & 15u) == 0 &&
+                   n <= kWeightJobs && (!x || (x_cols > 0 && left_bytes_wide(b.x)));
+  if (!one) {
+    if (x) st = qgtc_stack_input_and_weights(x, rows, x_cols, ld_x, q, buffer, buffer_bytes, ws, n, sums_of, col_sums, stream);
+    else st = qgtc_pack_weights(ws, n, sums_of, col_sums, stream);
+    if (st == QGTC_OK) st = qgtc_pack_bits(a_src, QGTC_SRC_U8, rows, A->cols, ld_a, nullptr, A, stream);
+    return st == QGTC_OK ? qgtc_build_neighbours(A, lists, map, stream) : st;
+  }
+  b.a.src = a_src;
+  b.a.ld_src = ld_a;
+  b.a.rows = rows;
+  b.a.cols = A->cols;
+  b.a.dst = A->data;
+  b.a.ld = A->ld_words;
+  b.pieces = 8 * b.lists.n128;
+  b.pieces_magic = div_magic(b.pieces);
+  b.list_groups = (unsigned)cdiv(rows, 64);
+  b.weight_groups = (unsigned)weight_jobs(ws, n, 0, sums_of, col_sums, &b.jobs);
+  unsigned groups = b.list_groups + b.weight_groups;
+  if (x) {
+    b.x_step_r = (int32_t)(256 / b.x.ld);
+    b.x_step_w = (int32_t)(256 % b.x.ld);
+    groups += left_bytes_wide_groups(b.x);
+  }
+  hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+  ProfScope prof(QGTC_KERNEL_PACK, s);
+  hipLaunchKernelGGL(pack_batch_kernel, dim3(groups), dim3(256), 0, s, b);
+  return launch_status();
 }
 
 extern "C" qgtc_status qgtc_unpack_bits(const qgtc_bits* src, uint32_t* dst, int64_t ld_dst, void* stream) {

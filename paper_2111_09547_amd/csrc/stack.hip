@@ -227,8 +227,8 @@ extern "C" size_t qgtc_stack_buffer_bytes(int32_t rows, int32_t cols) {
   return (size_t)cdiv(cols, 16 * ct) * (size_t)codes_cg_bytes(rows, ct);
 }
 
-static qgtc_status check_input(const float* src, int32_t rows, int32_t cols, int64_t ld_src, const qgtc_quant* q, const void* buffer,
-                               size_t buffer_bytes) {
+qgtc_status qgtc::check_row_codes(const float* src, int rows, int cols, int64_t ld_src, const qgtc_quant* q, const void* buffer,
+                                  size_t buffer_bytes) {
   if (!src || !q || !buffer) return QGTC_ERR_NULL;
   if (rows < 0 || cols < 0 || ld_src < cols || !(q->hi > q->lo)) return QGTC_ERR_SHAPE;
   if (q->nbits < 1 || q->nbits > 8) return QGTC_ERR_BITWIDTH;
@@ -239,14 +239,14 @@ static qgtc_status check_input(const float* src, int32_t rows, int32_t cols, int
 
 extern "C" qgtc_status qgtc_stack_input(const float* src, int32_t rows, int32_t cols, int64_t ld_src, const qgtc_quant* q,
                                         void* buffer, size_t buffer_bytes, void* stream) {
-  const qgtc_status st = check_input(src, rows, cols, ld_src, q, buffer, buffer_bytes);
+  const qgtc_status st = check_row_codes(src, rows, cols, ld_src, q, buffer, buffer_bytes);
   if (st != QGTC_OK || rows == 0 || cols == 0) return st;
   return pack_codes(src, ld_src, rows, cols, q, reinterpret_cast<uint8_t*>(buffer), reinterpret_cast<hipStream_t>(stream));
 }
 
 extern "C" qgtc_status qgtc_stack_input_rows(const float* src, int32_t rows, int32_t cols, int64_t ld_src, const qgtc_quant* q,
                                              void* buffer, size_t buffer_bytes, void* stream) {
-  const qgtc_status st = check_input(src, rows, cols, ld_src, q, buffer, buffer_bytes);
+  const qgtc_status st = check_row_codes(src, rows, cols, ld_src, q, buffer, buffer_bytes);
   if (st != QGTC_OK || rows == 0 || cols == 0) return st;
   return pack_row_codes(src, ld_src, rows, cols, q, reinterpret_cast<uint8_t*>(buffer), reinterpret_cast<hipStream_t>(stream));
 }
@@ -254,7 +254,7 @@ extern "C" qgtc_status qgtc_stack_input_rows(const float* src, int32_t rows, int
 extern "C" qgtc_status qgtc_stack_input_and_weights(const float* src, int32_t rows, int32_t cols, int64_t ld_src, const qgtc_quant* q,
                                                     void* buffer, size_t buffer_bytes, const qgtc_weight_source* ws, int32_t n,
                                                     int32_t sums_of, int32_t* col_sums, void* stream) {
-  const qgtc_status st = check_input(src, rows, cols, ld_src, q, buffer, buffer_bytes);
+  const qgtc_status st = check_row_codes(src, rows, cols, ld_src, q, buffer, buffer_bytes);
   if (st != QGTC_OK) return st;
   return pack_row_codes_and_weights(ws, n, sums_of, col_sums, src, ld_src, rows, cols, q, reinterpret_cast<uint8_t*>(buffer),
                                     reinterpret_cast<hipStream_t>(stream));

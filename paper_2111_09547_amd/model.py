@@ -186,22 +186,40 @@ class QuantGNN:
         # step on 65536 nodes 102.2 and 98.3 us, and launched one by one they wait for the host)
         if getattr(self, "_w_colsum_buf", None) is None:
             self._w_colsum_buf = torch.empty(self.dims[-1][1], dtype=torch.int32, device=self.A.words.device)
-        self._pack_weights_and(X, x_range)
-        if self.A_src is not None:
-            B.qgtc_pack_bits(self.A_src, 1, B.LEFT, out=self.A)
+        weights = self._plain_weights()
+        src = self.A_src
+        if self.lists is not None and self.use_map and self.map is None:
+            self.map = B._alloc_tile_map(self.A, 16, self.tile_kbits)
+        if weights is not None and self._fused and self.lists is not None and src is not None and src.dtype == torch.uint8 and src.is_cuda and \
+                src.stride(1) == 1 and tuple(src.shape) == (self.A.rows, self.A.cols) and self._lists_current():
+            x = X if X is not None and X.dtype == torch.float32 else None
+            assert x is None or tuple(x.shape) == (self.A.rows, self.dims[0][0])
+            B.qgtc_pack_batch(src, self.A, self.lists, self.map if self.use_map else None, weights, x, self.s, x_range,
+                              self._codes[0] if x is not None else None)
+            self._packed_weights()
+            if x is not None:
+                self._x_form = "codes"
+            else:
+                self._pack_x(X, x_range)
+            self._made_lists()
+            return
+        self._pack_weights_and(weights, X, x_range)
+        if src is not None:
+            B.qgtc_pack_bits(src, 1, B.LEFT, out=self.A)
         if self.lists is not None:
-            if self.use_map and self.map is None:
-                self.map = B._alloc_tile_map(self.A, 16, self.tile_kbits)
             self._build_lists(self.map)
-            if self.use_map and self._map_deg[0] is not self.map:
-                self._map_deg = (self.map, self.map.deg)
-            self.deg = self._map_deg[1] if self.use_map else self.lists.deg
-            self._made = (self.map, self.deg)
+            self._made_lists()
         elif self.use_map:
             self.map = B.qgtc_build_tile_map(self.A, 16, self.tile_kbits, out=self.map)
             self.deg = self.map.deg
         else:
             self.deg = B.qgtc_row_sums(self.A)
+
+    def _made_lists(self):
+        if self.use_map and self._map_deg[0] is not self.map:
+            self._map_deg = (self.map, self.map.deg)
+        self.deg = self._map_deg[1] if self.use_map else self.lists.deg
+        self._made = (self.map, self.deg)
 
     def _build_lists(self, tmap):
         """Lists of the adjacency as it is now, with tmap's tiles and degrees in the same pass."""
@@ -235,38 +253,52 @@ class QuantGNN:
             self.deg = deg = tmap.deg if ours else self.lists.deg
         self._made = (tmap, deg)
 
-    def _pack_weights_and(self, X, x_range):
-        plain = all(W.dtype == torch.float32 and W.is_contiguous() for W in self.Ws)
-        if self._W_bytes is not None and plain:
+    def _plain_weights(self):
+        """The weights as qgtc_pack_weights takes them, with the column sums of the last layer's (only that one
+        dequantizes); None where they are packed one by one."""
+        if not all(W.dtype == torch.float32 and W.is_contiguous() for W in self.Ws):
+            return None
+        if self._W_bytes is not None:
             low, high = [ops[0] for ops in self._W_bytes], [op for ops in self._W_bytes for op in ops[1:]]
             key = [(W.data_ptr(), W.shape, *r) for W, r in zip(self.Ws, self.w_ranges)] + [op.c.data for op in low + high]
             if getattr(self, "_w_sources", (None,))[0] != key:
                 twice = 2 if high else 1
                 self._w_sources = (key, B.WeightSources(self.Ws * twice, self.w_ranges * twice, low + high, self.t,
                                                         [0] * len(self.Ws) + [8] * len(high)))
-            B.qgtc_pack_weights(self._w_sources[1], len(self.dims) - 1, self._w_colsum_buf)
-            self.w_colsum = [None] * (len(self.dims) - 1) + [self._w_colsum_buf]
-            if self._planes_kept:
-                for W, r, dst in zip(self.Ws, self.w_ranges, self._W_ops):
-                    B.qgtc_pack_bits(W, self.t, B.RIGHT, quant=r, out=dst)
-        elif all(lay == B.RIGHT_BYTES for lay in self.w_layout) and plain:
+        elif all(lay == B.RIGHT_BYTES for lay in self.w_layout):
             key = [(W.data_ptr(), W.shape, o.c.data, *r) for W, o, r in zip(self.Ws, self._W_ops, self.w_ranges)]
             if getattr(self, "_w_sources", (None,))[0] != key:
                 self._w_sources = (key, B.WeightSources(self.Ws, self.w_ranges, self._W_ops))
-            # only the last layer dequantizes, so only its column sums are needed
-            weights = (self._w_sources[1], len(self.dims) - 1, self._w_colsum_buf)
-            self.w_colsum = [None] * (len(self.dims) - 1) + [self._w_colsum_buf]
-            if X is not None and self._fused and self.lists is not None and X.dtype == torch.float32:
+        else:
+            return None
+        return self._w_sources[1], len(self.dims) - 1, self._w_colsum_buf
+
+    def _packed_weights(self):
+        self.w_colsum = [None] * (len(self.dims) - 1) + [self._w_colsum_buf]
+        if self._W_bytes is not None and self._planes_kept:
+            for W, r, dst in zip(self.Ws, self.w_ranges, self._W_ops):
+                B.qgtc_pack_bits(W, self.t, B.RIGHT, quant=r, out=dst)
+
+    def _pack_weights_and(self, weights, X, x_range):
+        if weights is not None:
+            with_x = X is not None and self._fused and self.lists is not None and X.dtype == torch.float32
+            if with_x:
                 assert tuple(X.shape) == (self.A.rows, self.dims[0][0])
                 B.qgtc_stack_input(X, self.s, x_range, self._codes[0], rows_form=True, weights=weights)
                 self._x_form = "codes"
+            else:
+                B.qgtc_pack_weights(*weights)
+            self._packed_weights()
+            if with_x:
                 return
-            B.qgtc_pack_weights(*weights)
         else:
             for W, r, dst, lay in zip(self.Ws, self.w_ranges, self._W_ops, self.w_layout):
                 B.qgtc_pack_bits(W, self.t, lay, quant=r, out=dst)
             self.w_colsum = [None] * (len(self.dims) - 1) + [B.qgtc_col_sums(self._W_ops[-1], out=self._w_colsum_buf)]
             self._pack_w_bytes()
+        self._pack_x(X, x_range)
+
+    def _pack_x(self, X, x_range):
         if X is not None and not self.update_first:
             if (self._fused or self._wide) and X.dtype == torch.float32:
                 assert tuple(X.shape) == (self.A.rows, self.dims[0][0])

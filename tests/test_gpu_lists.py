@@ -554,3 +554,54 @@ def test_features_of_more_words_than_a_launch_has_threads():
         assert torch.equal(buf[r0 * 256:r1 * 256], part[:(r1 - r0) * 256]) and len(part[:(r1 - r0) * 256].unique()) > 1000
     del x, buf
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("rows,cols,block,extra,d", [
+    (1, 32, 32, 0, 4),
+    (65, 64, 64, 0, 12),           # a wave with one row, one word of a row
+    (1000, 416, 416, 16, 100),     # pieces that are no whole words, a stride
+    (130, 2048, 2048, 0, 64),      # the longest rows of one launch, lists of 256 entries and more
+    (2000, 2000, 0, 0, 8),         # one block
+    (300, 2080, 2080, 0, 8),       # too long: a launch each
+    (100, 100, 0, 1, 8),           # no whole pieces
+    (128, 128, 128, 0, 7),         # features of a width that is not
+])
+@pytest.mark.parametrize("with_map,with_x", [(True, True), (False, True), (True, False)])
+def test_a_batch_is_packed_like_its_parts(rows, cols, block, extra, d, with_map, with_x):
+    import paper_2111_09547_amd.binding as B
+    cols = min(cols, block) if block else cols
+    gen = torch.Generator(device="cuda").manual_seed(rows + cols)
+    wide = (torch.rand((rows, cols + extra), generator=gen, device="cuda") < torch.rand((rows, 1), generator=gen, device="cuda") ** 4).to(torch.uint8)
+    wide += 2 * torch.randint(0, 2, wide.shape, generator=gen, device="cuda", dtype=torch.uint8)    # (bit 0 counts)
+    src = wide[:, :cols]
+    x = torch.randn((rows, d), generator=gen, device="cuda")
+    Ws = [torch.rand(s, generator=gen, device="cuda") for s in ((d, 64), (64, 17))]
+    ranges = [(float(W.min()), float(W.max())) for W in Ws]
+    got = []
+    for together in (False, True):
+        A = B.alloc_bits(rows, cols, 1, B.LEFT, block)
+        lists = B.qgtc_build_neighbours(B.qgtc_pack_bits(torch.zeros_like(src), 1, B.LEFT, out=A))
+        lists.buffer.fill_(-1)                                     # (what is not an entry of a list is not read)
+        tmap = B._alloc_tile_map(A, 16, 32) if with_map else None
+        A.words.fill_(-1)
+        ops = [B.alloc_bits(*W.shape, t, B.RIGHT_BYTES) for W, t in zip(Ws, (8, 3))]
+        for op in ops:
+            op.words.zero_()
+        sums = torch.zeros(17, dtype=torch.int32, device="cuda")
+        codes = torch.zeros(B.lib().qgtc_stack_buffer_bytes(rows, d) // 4 + 4, dtype=torch.int32, device="cuda")
+        weights = (B.WeightSources(Ws, ranges, ops), 1, sums)
+        if together:
+            B.qgtc_pack_batch(src, A, lists, tmap, weights, x if with_x else None, 8, (-2.0, 2.0), codes)
+        else:
+            B.qgtc_pack_weights(*weights)
+            if with_x:
+                B.qgtc_stack_input(x, 8, (-2.0, 2.0), codes, rows_form=True)
+            B.qgtc_pack_bits(src, 1, B.LEFT, out=A)
+            B.qgtc_build_neighbours(A, lists, tmap)
+        got.append([A.words, lists.buffer, sums, codes, *[op.words for op in ops]] + ([tmap.row_cnt, tmap.deg] if with_map else []))
+        if with_map:
+            cnt = tmap.row_cnt
+            used = torch.arange(tmap.c.n_tile_cols, device="cuda")[None, :] < cnt[:, None]
+            got[-1].append(torch.where(used, tmap.col_idx, -1))
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
