@@ -958,3 +958,18 @@ def test_aggregation_on_small_floats_is_exact(n, k, d, block, s):
         assert torch.equal(q.qgtc_aggregate(A, tmap, X, q.Epilogue(mode=q.OUT_I32)), want)
         if block:
             assert torch.equal(q.qgtc_aggregate(A, tmap, X, q.Epilogue(mode=q.OUT_I32, self_term=True)), want + x)
+
+
+@pytest.mark.parametrize("s", [1, 3, 4, 5, 8])
+@pytest.mark.parametrize("n,d", [(1, 1), (3, 33), (300, 64), (70000, 31), (33000, 132)])
+def test_left_planes_are_decoded_four_columns_at_a_time(n, d, s):
+    """Into rows of whole and of odd widths, one and four items per thread."""
+    import ctypes as C
+    import paper_2111_09547_amd.binding as B
+    v = torch.randint(0, 1 << s, (n, d), device="cuda", dtype=torch.int32)
+    bits = q.qgtc_pack_bits(v, s, q.LEFT)
+    assert torch.equal(q.qgtc_unpack_bits(bits), v)
+    ld = -(-d // 4) * 4 + 4
+    wide = torch.full((n, ld), -1, device="cuda", dtype=torch.int32)
+    B._check(B.lib().qgtc_unpack_bits(C.byref(bits.c), C.c_void_p(wide.data_ptr()), ld, B._stream()), "qgtc_unpack_bits")
+    assert torch.equal(wide[:, :d], v) and bool((wide[:, d:] == -1).all())
