@@ -211,8 +211,14 @@ def _check(status: int, where: str):
         raise QgtcError(status, where)
 
 
-def _stream() -> C.c_void_p:
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+# The current stream's handle.  (torch.cuda.current_stream() makes a Stream object on the way, 2.9 us of the 8 to 13
+# that a call costs the host; the handle by itself 0.2.)
+if hasattr(torch._C, "_cuda_getCurrentRawStream") and hasattr(torch._C, "_cuda_getDevice"):
+    def _stream() -> int:
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+else:
+    def _stream() -> int:
+        return torch.cuda.current_stream().cuda_stream
 
 
 # ---------------------------------------------------------------- descriptors
