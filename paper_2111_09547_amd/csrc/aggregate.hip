@@ -295,9 +295,18 @@ static bool takes_floats(const AggParams& p) { return dense_applies(p) && !(p.co
 //   3072 x 256 (twelve) 19.8 and 17.8; 8192 x 300 71 and 51; 16384 x 256 112 and 90
 //   of eight, which four waves share: 4096 x 64 (four) 10.4 and 10.7; 8192 x 64 (eight) 18.9 and 18.7, and with
 //   the launch from a script 17.1 and 17.5; 12288 x 16 (twelve) 22.4 and 17.8; 256 x 65536 x 64 94 and 65
+// Floats, which are faster, earlier where rows are not few: of more than 4608 columns of A, of 7168 for 32 columns of X or
+// fewer.  Planes and floats, called one by one from a script, where the second launch and its room are 4 us of the host's
+// 13: 4700 x 4700 x 64 at 2 bits 13.4 and 13.3, 5000 x 5000 x 64 at 8 14.5 and 13.6, 8192 x 8192 x 64 at 2 16.9 and 13.5 (in a
+// graph 17.1 and 11.8), 5000 x 5000 x 32 11.6 and 13.3, 6000 x 6000 x 16 at 3 12.6 and 13.4, 8192 x 8192 x 20 15.5 and 13.2.
 // A codes' column group is addressed with 32 bits; features beyond 256 MiB of codes stay as planes.
 static bool aggregate_from_codes(const AggParams& p, const AggSplit& sp) {
-  return p.s <= 8 && p.a_words > 4 * 8 * sp.chunks() && codes_bytes(p, sp) <= (int64_t)256 << 20;
+  int enough = 8 * sp.chunks();
+  if (takes_floats(p) && p.rows >= 1024) {
+    const int floats = p.cols > 32 ? 36 : 56;
+    if (floats < enough) enough = floats;
+  }
+  return p.s <= 8 && p.a_words > 4 * enough && codes_bytes(p, sp) <= (int64_t)256 << 20;
 }
 
 extern "C" size_t qgtc_aggregate_workspace_bytes(const qgtc_bits* A, const qgtc_bits* X) {

@@ -928,6 +928,8 @@ def test_aggregation_of_long_rows(n, k, d, s, block, density, codes, with_map):
 
 @pytest.mark.parametrize("n,k,d,block", [
     (1030, 8193, 65, 0),           # 65 chunks, the last one of a column; three column groups, the last one of a column
+    (1024, 4609, 64, 0),           # where floats begin
+    (1024, 7169, 20, 0),
     (1024, 65664, 33, 0),          # sums up to the last exact ones at 8 bits
     (1025, 65792, 17, 0),
     (40 * 256 + 1, 8300, 250, 0),  # 256 rows per workgroup, 128 and 64 below
