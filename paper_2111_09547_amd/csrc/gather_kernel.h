@@ -81,7 +81,11 @@ __device__ __forceinline__ void emit_sums(const GatherParams& p, int row, int co
   }
 }
 
-// The heavy rows, one after the other, by all n_heavy_wg workgroups.
+// The heavy rows, one after the other, by all n_heavy_wg workgroups.  A chain of round trips per row, three rows per workgroup
+// in the largest graphs: which row, its degree, its list or words, the codes.  A row is found by a wave's lanes at once and
+// words are taken up to eight at a time, us with both one by one and here: 512-16-16 on 262144 rows of a power-law graph
+// (1540 heavy rows, 236 of them from words) 199.9 and 196.4, update first 131.0 and 126.9, 128-32-32-16 on 131072 72.8 and 69.4
+// (without heavy rows 172, 110 and 54).
 template <int LP, int LT, int MODE, int PARTS>
 __device__ __forceinline__ void heavy_rows(const GatherParams& p, uint8_t* lds, int wave, int lane) {
   using Sh = GatherShape<LP, 1, PARTS>;
@@ -135,14 +139,40 @@ __device__ __forceinline__ void heavy_rows(const GatherParams& p, uint8_t* lds, 
 #pragma unroll 1
   for (uint32_t tile = blockIdx.x; tile < all; tile += (uint32_t)p.n_heavy_wg) {
     __syncthreads();                                 // what the last row left has been read
-    const uint32_t k = tile - before[threadIdx.x];
-    if (tile >= before[threadIdx.x] && k < before[256 + threadIdx.x]) {
-      int at = (int)threadIdx.x * per;
-      uint32_t rest = k;
-      while (rest >= p.heavy_cnt[at]) rest -= p.heavy_cnt[at++];
+    // Heavy row number `tile`: the thread whose groups have it, then the group, by all of a wave's lanes at once.
+    if (wave == 0) {
+      int at = 0;
+      uint32_t left = 0u;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const uint32_t k = tile - before[64 * i + lane];
+        const unsigned long long has = __builtin_amdgcn_ballot_w64(tile >= before[64 * i + lane] && k < before[256 + 64 * i + lane]);
+        if (has) {
+          const int l = __builtin_ctzll(has);
+          at = (64 * i + l) * per;
+          left = (uint32_t)__builtin_amdgcn_readlane((int)k, l);
+        }
+      }
+      for (;; at += 64) {                            // (`per` counts hold it)
+        const uint32_t c = at + lane < p.n_groups ? p.heavy_cnt[at + lane] : 0u;
+        uint32_t upto = c;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+          const uint32_t up = (uint32_t)__shfl_up((int)upto, d, 64);
+          if (lane >= d) upto += up;
+        }
+        const unsigned long long past = __builtin_amdgcn_ballot_w64(upto > left);
+        if (past || at + 64 >= p.n_groups) {
+          const int l = past ? __builtin_ctzll(past) : 63;
+          left -= (uint32_t)__builtin_amdgcn_readlane((int)(upto - c), l);
+          at = min(at + l, p.n_groups - 1);
+          break;
+        }
+        left -= (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
+      }
       uint64_t m = p.heavy[at];
-      for (; rest > 0u; --rest) m &= m - 1u;
-      taken[0] = at * kListGroup + __builtin_ctzll(m);
+      for (; left > 0u; --left) m &= m - 1u;
+      if (lane == 0) taken[0] = min(at * kListGroup + (m ? __builtin_ctzll(m) : 0), p.rows - 1);
     }
     for (int i = (int)threadIdx.x; i < P * 16 * PARTS; i += 256) sums[i] = 0u;
     __syncthreads();
@@ -179,19 +209,23 @@ __device__ __forceinline__ void heavy_rows(const GatherParams& p, uint8_t* lds, 
           unsigned long long some = __builtin_amdgcn_ballot_w64(word != 0u);
 #pragma unroll 1
           while (some) {
-            const int l = __builtin_ctzll(some);
-            some &= some - 1ull;
-            const uint32_t wd = (uint32_t)__builtin_amdgcn_readlane((int)word, l);
-            const uint32_t col = (uint32_t)(k0 + 4 * l + wave) * 32u;
-            constexpr int STEPS = RC < 8 ? 8 / RC : 1, HB = STEPS < 8 ? STEPS : 8;
-            v4i y[HB];
+            // several words at a time: a word's loads are up to eight, and a round trip
+            constexpr int STEPS = RC < 8 ? 8 / RC : 1, NB = 8 / STEPS;
+            v4i y[NB * STEPS];
 #pragma unroll
-            for (int s = 0; s < HB; ++s) {
-              const uint32_t bit = (uint32_t)((s * RC + rs) * 4 + g);
-              y[s] = nb.load(bit < 32u && ((wd >> (bit & 31u)) & 1u) ? col + bit : (uint32_t)kListNone, pofs);
+            for (int b = 0; b < NB; ++b) {
+              const int l = some ? __builtin_ctzll(some) : 0;
+              const uint32_t wd = some ? (uint32_t)__builtin_amdgcn_readlane((int)word, l) : 0u;
+              some &= some - 1ull;
+              const uint32_t col = (uint32_t)(k0 + 4 * l + wave) * 32u;
+#pragma unroll
+              for (int s = 0; s < STEPS; ++s) {
+                const uint32_t bit = (uint32_t)((s * RC + rs) * 4 + g);
+                y[b * STEPS + s] = nb.load(bit < 32u && ((wd >> (bit & 31u)) & 1u) ? col + bit : (uint32_t)kListNone, pofs);
+              }
             }
 #pragma unroll
-            for (int s = 0; s < HB; ++s) h = mfma_i8(ident, y[s], h);
+            for (int s = 0; s < NB * STEPS; ++s) h = mfma_i8(ident, y[s], h);
             settle(h);
           }
         }
