@@ -27,7 +27,8 @@
 // agree, so a lane of the Y side owns LW consecutive 16-bit pieces of its row per
 // "super-step":
 //   LW = 1: half a word   (K up to 64: the whole contraction is one step)
-//   LW = 2: one word      (rows of up to 32 bytes)
+//   LW = 2: one word      (rows that are not 16-byte aligned; as bytes)
+//   LW = 4: two words     (rows of up to 32 bytes: the whole contraction is one super-step)
 //   LW = 8: four words    (one 16-byte load per plane and lane; a wave reads the 16
 //                          rows x 64 bytes of a tile and plane as 1 KiB in one piece)
 // and runs LW steps on what it has loaded.
@@ -47,6 +48,7 @@ namespace qgtc {
 namespace {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
+typedef unsigned int v2u __attribute__((ext_vector_type(2)));
 typedef unsigned int v4u __attribute__((ext_vector_type(4)));
 
 constexpr int kRowsPerGroup = 32;
@@ -54,7 +56,7 @@ constexpr int kPad = 16;   // bytes of padding per LDS row of W
 constexpr uint32_t kOutOfRange = 0x80000000u;   // buffer offset past any operand: the load returns 0
 
 // SPLIT_Y / SPLIT_W: the operand has 8 planes and is taken as code - 128 (see the top);
-// NTC: 16-column tiles per workgroup (1 or 4); LW: see above (1, 2 or 8).
+// NTC: 16-column tiles per workgroup (1 or 4); LW: see above (1, 2, 4 or 8).
 template <bool SPLIT_Y, bool SPLIT_W, int NTC, int LW>
 __global__ __launch_bounds__(256) void update_mfma_kernel(const UpdParams p) {
   extern __shared__ uint32_t wl_words[];            // W bytes: [part][col][kpad + kPad]
@@ -73,6 +75,53 @@ __global__ __launch_bounds__(256) void update_mfma_kernel(const UpdParams p) {
   const int kpad = n_ss * SSW * 32;                 // K positions per column in LDS, one byte each
   const int wstride = kpad + kPad;
   int32_t* colsum = reinterpret_cast<int32_t*>(wl + CC * wstride);   // [CC], sum of the codes of a column
+
+  // Y through buffer loads: what lies outside (rows past the last, words past the end of a
+  // row) gets an offset beyond the buffer and reads as zero, with no branch around the load
+  const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc((void*)p.Y, 0, (int)p.y_span_bytes, 0x00020000);
+  const uint32_t ldy4 = (uint32_t)p.ldy * 4u, psy4 = (uint32_t)p.psy * 4u;
+
+  // This lane's part of tile mt (16 rows) of row group rg for super-step ss, all loads issued
+  // together.  planes: word k of plane pl at [pl * WPL + k]; bytes: dword c of step j at [4 * j + c]
+  static_assert(4 * LW <= 8 * WPL, "the byte form fits into the registers of the plane form");
+  auto load_tile = [&](int rg, int ss, int mt, uint32_t (&raw)[8 * WPL]) {
+    const int row = rg * kRowsPerGroup + mt * 16 + ln;
+    if (p.y_bytes) {
+#pragma unroll
+      for (int j = 0; j < LW; ++j) {
+        const uint32_t kb = (uint32_t)((ss * LW + j) * 64 + g * 16);
+        const uint32_t off = (row < p.rows && kb < ldy4) ? (uint32_t)row * ldy4 + kb : kOutOfRange;
+        const v4u v = __builtin_amdgcn_raw_buffer_load_b128(ry, off, 0, 0);
+        raw[4 * j] = v.x; raw[4 * j + 1] = v.y; raw[4 * j + 2] = v.z; raw[4 * j + 3] = v.w;
+      }
+    } else {
+      // words up to the leading dimension are data or zero padding; beyond it the next row begins
+      const int w0 = LW == 1 ? ss * 2 + (g >> 1) : ss * SSW + g * WPL;
+      const uint32_t off = (row < p.rows && w0 < p.ldy) ? (uint32_t)row * ldy4 + (uint32_t)w0 * 4u : kOutOfRange;
+      static_assert(WPL == 4 || WPL == 2 || WPL == 1, "one word, two or four per lane");
+#pragma unroll
+      for (int pl = 0; pl < 8; ++pl) {
+        if (WPL == 4) {                             // the host picks LW = 8 only for 16-byte aligned rows
+          v4u v = {0u, 0u, 0u, 0u};
+          if (pl < p.s) v = __builtin_amdgcn_raw_buffer_load_b128(ry, off, (uint32_t)pl * psy4, 0);
+          raw[pl * WPL] = v.x; raw[pl * WPL + 1] = v.y; raw[pl * WPL + 2] = v.z; raw[pl * WPL + WPL - 1] = v.w;
+        } else if (WPL == 2) {
+          v2u v = {0u, 0u};
+          if (pl < p.s) v = __builtin_amdgcn_raw_buffer_load_b64(ry, off, (uint32_t)pl * psy4, 0);
+          raw[pl * WPL] = v.x; raw[pl * WPL + WPL - 1] = v.y;
+        } else {
+          raw[pl] = 0u;
+          if (pl < p.s) raw[pl] = __builtin_amdgcn_raw_buffer_load_b32(ry, off, (uint32_t)pl * psy4, 0);
+        }
+      }
+    }
+  };
+
+  // The first tile is requested in front of the staging of W, which takes as long as its loads.
+  const int rg_step = (int)gridDim.x * 4;
+  int rg = blockIdx.x * 4 + wave, ss = 0;
+  uint32_t buf0[8 * WPL], buf1[8 * WPL];
+  load_tile(rg, 0, 0, buf0);                        // (zeros for a wave without a group)
 
   // ---- stage W[.][c0 .. c0+CC) in LDS as bytes ------------------------------------
   // one thread turns one word (32 K positions) of one column, all planes, into 32 bytes
@@ -125,43 +174,6 @@ __global__ __launch_bounds__(256) void update_mfma_kernel(const UpdParams p) {
   const int qbits = e.rq_nbits;
   const uint32_t qmax = qbits >= 32 ? 0xffffffffu : ((1u << qbits) - 1u);
   const float qmaxf = (float)qmax;
-  // Y through buffer loads: what lies outside (rows past the last, words past the end of a
-  // row) gets an offset beyond the buffer and reads as zero, with no branch around the load
-  const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc((void*)p.Y, 0, (int)p.y_span_bytes, 0x00020000);
-  const uint32_t ldy4 = (uint32_t)p.ldy * 4u, psy4 = (uint32_t)p.psy * 4u;
-
-  // This lane's part of tile mt (16 rows) of row group rg for super-step ss, all loads issued
-  // together.  planes: word k of plane pl at [pl * WPL + k]; bytes: dword c of step j at [4 * j + c]
-  static_assert(4 * LW <= 8 * WPL, "the byte form fits into the registers of the plane form");
-  auto load_tile = [&](int rg, int ss, int mt, uint32_t (&raw)[8 * WPL]) {
-    const int row = rg * kRowsPerGroup + mt * 16 + ln;
-    if (p.y_bytes) {
-#pragma unroll
-      for (int j = 0; j < LW; ++j) {
-        const uint32_t kb = (uint32_t)((ss * LW + j) * 64 + g * 16);
-        const uint32_t off = (row < p.rows && kb < ldy4) ? (uint32_t)row * ldy4 + kb : kOutOfRange;
-        const v4u v = __builtin_amdgcn_raw_buffer_load_b128(ry, off, 0, 0);
-        raw[4 * j] = v.x; raw[4 * j + 1] = v.y; raw[4 * j + 2] = v.z; raw[4 * j + 3] = v.w;
-      }
-    } else {
-      // words up to the leading dimension are data or zero padding; beyond it the next row begins
-      const int w0 = LW == 1 ? ss * 2 + (g >> 1) : ss * SSW + g * WPL;
-      const uint32_t off = (row < p.rows && w0 < p.ldy) ? (uint32_t)row * ldy4 + (uint32_t)w0 * 4u : kOutOfRange;
-      static_assert(WPL == 4 || WPL == 1, "one word or four per lane");
-#pragma unroll
-      for (int pl = 0; pl < 8; ++pl) {
-        if (WPL == 4) {                             // the host picks LW = 8 only for 16-byte aligned rows
-          v4u v = {0u, 0u, 0u, 0u};
-          if (pl < p.s) v = __builtin_amdgcn_raw_buffer_load_b128(ry, off, (uint32_t)pl * psy4, 0);
-          raw[pl * WPL] = v.x; raw[pl * WPL + 1] = v.y; raw[pl * WPL + 2] = v.z; raw[pl * WPL + WPL - 1] = v.w;
-        } else {
-          raw[pl] = 0u;
-          if (pl < p.s) raw[pl] = __builtin_amdgcn_raw_buffer_load_b32(ry, off, (uint32_t)pl * psy4, 0);
-        }
-      }
-    }
-  };
-
   v4i acc[2][NTC], rsum[2];                          // products; row sums of Y (8-bit W only)
 
   // LW steps on the matrix cores for one tile: two per loaded word (one for LW = 1).  A
@@ -212,11 +224,7 @@ __global__ __launch_bounds__(256) void update_mfma_kernel(const UpdParams p) {
 
   // Items (row group, super-step) of this wave, one after the other, each as two tiles;
   // while one tile is on the matrix cores the loads of the next one are in flight.
-  const int rg_step = (int)gridDim.x * 4;
-  int rg = blockIdx.x * 4 + wave, ss = 0;
   if (rg >= n_groups) return;                       // whole wave; no barrier follows
-  uint32_t buf0[8 * WPL], buf1[8 * WPL];
-  load_tile(rg, 0, 0, buf0);
   while (true) {
     load_tile(rg, ss, 1, buf1);
     const int row0 = rg * kRowsPerGroup;
@@ -313,7 +321,9 @@ int pick_lw(const UpdParams& p) {
   if (p.y_bytes) return p.ldy * 4 <= 64 ? 1 : (p.ldy * 4 <= 128 ? 2 : 8);
   // four words per lane and plane are one 16-byte load: rows, planes and base at multiples of 16 bytes
   const bool vec = (p.ldy & 3) == 0 && (p.psy & 3) == 0 && ((uintptr_t)p.Y & 15u) == 0;
-  return p.kwords <= 2 ? 1 : ((p.kwords <= 8 || !vec) ? 2 : 8);
+  // up to 8 words: both words of a lane's part by one load and the whole row as one super-step, 16384 x 256 -> 64 with
+  // one word at a time 9.4 and 8.6 us (4 bits), 11.9 and 10.3 (8)
+  return p.kwords <= 2 ? 1 : ((p.kwords <= 4 || !vec) ? 2 : (p.kwords <= 8 ? 4 : 8));
 }
 
 size_t lds_bytes(const UpdParams& p, int ntc, int lw) {
@@ -364,13 +374,19 @@ qgtc_status dispatch_lw(const UpdParams& p, hipStream_t stream) {
   switch (pick_lw(p)) {
     case 1: return launch<SY, SW, NTC, 1>(p, stream);
     case 2: return launch<SY, SW, NTC, 2>(p, stream);
+    case 4: return launch<SY, SW, NTC, 4>(p, stream);
     default: return launch<SY, SW, NTC, 8>(p, stream);
   }
 }
 
 template <bool SY, bool SW>
 qgtc_status dispatch_n(const UpdParams& p, hipStream_t stream) {
-  switch (pick_ntc(p)) {
+  const int ntc = pick_ntc(p);
+  // Rows that leave compute units without a workgroup: 16 columns per workgroup, which all read Y (from the caches).
+  // 64 and 16 columns, us: 16384 x 256 -> 64 of 4 bits 8.6 and 7.0, of 8 bits 10.3 and 8.2, 4096 x 256 -> 128 8.2 and 6.0,
+  // 2048 x 512 -> 64 10.5 and 6.7, 1000 x 160 -> 33 7.6 and 5.6.
+  const bool few = (int64_t)cdiv(cdiv(p.rows, kRowsPerGroup), 4) * cdiv(p.cols, 64) < device_compute_units();
+  switch (ntc == 4 && few ? 1 : ntc) {
     case 4: return dispatch_lw<SY, SW, 4>(p, stream);
     case 1: return dispatch_lw<SY, SW, 1>(p, stream);
     default: return QGTC_ERR_UNSUPPORTED;

@@ -711,6 +711,25 @@ def test_update_matrix_core_path_equals_popcount_and_oracle(st, shape):
         assert_fp32_close(f, ref, str(path))
 
 
+@pytest.mark.parametrize("st", [(4, 4), (8, 8), (3, 8)])
+@pytest.mark.parametrize("shape", [(33, 129, 17), (31, 256, 64), (500, 160, 130), (32800, 200, 64), (32768, 256, 33)])
+def test_update_of_five_to_eight_words_in_slices_of_16_and_64_columns(st, shape):
+    """Rows of 5 to 8 words are one super-step; few rows have a workgroup per 16 columns, many one per 64."""
+    s, t = st
+    n, d, h = shape
+    rng = np.random.default_rng([12, s, t, n, h])
+    Yq = rng.integers(0, 2 ** s, size=(n, d), dtype=np.uint64).astype(np.uint32)
+    Wq = rng.integers(0, 2 ** t, size=(d, h), dtype=np.uint64).astype(np.uint32)
+    Yb = q.qgtc_pack_bits(dev(Yq.view(np.int32)), s, q.LEFT)
+    Wb = q.qgtc_pack_bits(dev(Wq.view(np.int32)), t, q.RIGHT)
+    Z = qgnn.update(Yq, Wq)
+    tn = q.Tuning(update_path=q.UPDATE_MATRIX_CORES)
+    assert (as_u32(q.qgtc_update(Yb, Wb, q.Epilogue(mode=q.OUT_I32, tuning=tn))) == Z).all()
+    inv = qgnn.inv_scale(0.0, float(Z.max()), 4)
+    bits = q.qgtc_update(Yb, Wb, q.Epilogue(mode=q.OUT_BITS, rq_nbits=4, rq_lo=0, rq_inv_scale=float(inv), tuning=tn))
+    assert (words_np(bits) == bp.pack(qgnn.requantize(Z, 0, inv, 4), 4, bp.RIGHT)).all()
+
+
 # ------------------------------------------------------------ zero-word jumping
 @pytest.mark.parametrize("s", [3, 4, 8, 11])
 @pytest.mark.parametrize("shape,p_edge", [((300, 64), 0.01), ((300, 64), 0.6), ((130, 20), 0.03), ((257, 130), 0.002),
