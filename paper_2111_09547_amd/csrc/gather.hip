@@ -97,9 +97,11 @@ void set_grid(GatherParams* gp, int tiles) {
   if (run > (int64_t)p.nblocks / 8) run = p.nblocks / 8;
   p.run_shift = 0;
   while (((int64_t)2 << p.run_shift) <= run && p.run_shift < 24) ++p.run_shift;
-  // 1543 of them in 262144 rows, 16 -> 16: 256 workgroups 29.9, 512 19.2, 1024 15.4 us; without any, 64 -> 64 on 65536
-  // rows, 8.8, 8.8 and 9.6.
-  p.n_heavy_wg = p.block > kListLight ? (p.n_groups < 2 * cus ? (p.n_groups + 7) / 8 * 8 : 2 * cus / 8 * 8) : 0;
+  // Their number grows with the rows.  1543 of them in 262144 rows, 16 -> 16: 256 workgroups 29.9, 512 17.7, 1024 15.9 us;
+  // without any, 64 -> 64 on 65536 rows, 8.8, 8.8 and 9.6; 512 columns, whose rows a workgroup takes as long as the
+  // caches deliver them, on 262144 rows 75, 1024 workgroups 82.
+  const int most = (p.ldx <= 128 && p.n_groups >= 16 * cus ? 4 : 2) * cus;
+  p.n_heavy_wg = p.block > kListLight ? (p.n_groups < most ? (p.n_groups + 7) / 8 * 8 : most / 8 * 8) : 0;
 }
 
 }  // namespace

@@ -45,6 +45,14 @@ __device__ __forceinline__ v4i adder(int ln) {
 }
 __device__ __forceinline__ uint32_t list_entry(const v2u& idx, int k) { return k & 1 ? idx[k >> 1] >> 16 : idx[k >> 1] & 0xffffu; }
 
+// Keeps the compiler from moving loads behind products that could wait for them, for fewer registers than a wave may
+// have.  us with and without: 64 -> 64 on 65536 rows 8.8 and 9.6, fp32 out 12.4 and 12.9; 300 columns on 15221 rows,
+// 14 neighbours, 22.6 and 24.8 (all 16 entries at once), but 512 -> 16 on 262144 rows of a power-law graph 88 and 75.
+template <bool ON>
+__device__ __forceinline__ void all_in_flight() {
+  if constexpr (ON) __builtin_amdgcn_sched_barrier(0);
+}
+
 // Rows of X that a row of A can have as neighbours: its diagonal block's.
 struct Neighbours {
   __amdgpu_buffer_rsrc_t rx;
@@ -355,10 +363,11 @@ __global__ __launch_bounds__(256, 4) void gather_layer_kernel(const GatherParams
               r_own, v_own, own_unit_offset((uint32_t)(first_row + (u0 + j / PARTS) * RC), hv * 256u + j % PARTS * nb.part, (uint32_t)ldx, own_size), 0);
       }
       // The first block in up to three steps, each with all of its loads in flight: wide rows are few
-      // neighbours of many bytes from HBM, narrow ones more neighbours from the caches.
-      constexpr int K1 = P >= 16 ? 1 : 2;            // 4 K1 entries of every row, then up to 8, then all 16
-      v4i acc[W], x[W][2];
-      const bool five = K1 == 1 && __builtin_amdgcn_ballot_w64(most > 4) != 0ull, nine = __builtin_amdgcn_ballot_w64(most > 8) != 0ull;
+      // neighbours of many bytes from HBM, narrow ones more neighbours from the caches, few tiles all of them at once.
+      constexpr int K1 = WPT == 4 && P >= 16 ? 4 : P >= 16 ? 1 : 2;   // 4 K1 entries of every row, then up to 8, then all 16
+      constexpr int XK = K1 == 4 ? 4 : 2;
+      v4i acc[W], x[W][XK];
+      const bool five = K1 == 1 && __builtin_amdgcn_ballot_w64(most > 4) != 0ull, nine = K1 < 4 && __builtin_amdgcn_ballot_w64(most > 8) != 0ull;
 #pragma unroll
       for (int k = 0; k < K1; ++k)
 #pragma unroll
@@ -367,6 +376,7 @@ __global__ __launch_bounds__(256, 4) void gather_layer_kernel(const GatherParams
 #pragma unroll
         for (int j = 0; j < W; ++j) x[j][1] = nb.load(list_entry(idx[j], 1), pofs + j % PARTS * nb.part);
       }
+      all_in_flight<K1 != 1>();
       // (the own row, and 128 for every code that is code - 128)
 #pragma unroll
       for (int j = 0; j < W; ++j) {
@@ -387,6 +397,7 @@ __global__ __launch_bounds__(256, 4) void gather_layer_kernel(const GatherParams
         for (int k = 0; k < 2; ++k)
 #pragma unroll
           for (int j = 0; j < W; ++j) x[j][k] = nb.load(list_entry(idx[j], 2 + k), pofs + j % PARTS * nb.part);
+        all_in_flight<K1 != 1>();
 #pragma unroll
         for (int k = 0; k < 2; ++k)
 #pragma unroll
@@ -412,6 +423,7 @@ __global__ __launch_bounds__(256, 4) void gather_layer_kernel(const GatherParams
 #pragma unroll
               for (int j = 0; j < W; ++j) x[j][k] = nb.load(list_entry(idx[j], 2 * h + k), pofs + j % PARTS * nb.part);
             if (h == 1) more(base + kListBlock);
+            all_in_flight<K1 != 1>();
 #pragma unroll
             for (int k = 0; k < 2; ++k)
 #pragma unroll

@@ -605,3 +605,17 @@ def test_a_batch_is_packed_like_its_parts(rows, cols, block, extra, d, with_map,
             got[-1].append(torch.where(used, tmap.col_idx, -1))
     for a, b in zip(*got):
         assert torch.equal(a, b)
+
+
+def test_heavy_rows_of_a_large_graph_in_narrow_layers():
+    """262144 rows and more, of which more than the workgroups that take heavy rows have more neighbours than a tile's waves take."""
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    n, block = 262144 + 70, 128
+    a = (torch.rand((n, block), generator=gen, device="cuda") < 0.02).to(torch.uint8)
+    a[::41] = 1
+    a[n // block * block:, n % block:] = 0
+    x = torch.randn((n, 20), generator=gen, device="cuda")
+    Ws = [torch.rand((d, h), generator=gen, device="cuda") - 0.5 for d, h in ((20, 16), (16, 5))]
+    nets = [QuantGNN(a, Ws, 8, 8, True, block_rows=block, lists=lists) for lists in (True, False)]
+    ranges = nets[1].calibrate(x, (-3.0, 3.0))
+    assert torch.equal(*[net.forward(x, (-3.0, 3.0), ranges) for net in nets])
