@@ -43,6 +43,7 @@ __device__ __forceinline__ void lists_of(const ListParams& p, unsigned block, ui
   int count = 0, tiles = 0;                          // entries of the row so far; tiles of the map
   for (int c0 = 0; c0 < p.n128; c0 += 16) {
     uint4 v[4];
+    unsigned long long words = 0ull;
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const int c = c0 + 4 * u + g;
@@ -68,25 +69,29 @@ __device__ __forceinline__ void lists_of(const ListParams& p, unsigned block, ui
           m &= m - 1u;
         }
       }
-      if (p.row_cnt) {                               // (uniform) the tile map's list of the 16 rows
-        unsigned long long b[4];
+      if (p.row_cnt) {                               // (uniform) bit 16 u + j: word j of the four pieces holds a bit
+        unsigned long long some = 0ull;              // four words of a piece at bits 16 piece ..
 #pragma unroll
-        for (int i = 0; i < 4; ++i) b[i] = __builtin_amdgcn_ballot_w64(w[i] != 0u);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          uint32_t bits = 0u;                        // words of the piece that hold a bit
-#pragma unroll
-          for (int i = 0; i < 4; ++i) bits |= ((b[i] >> (16 * k)) & 0xffffull) != 0ull ? 1u << i : 0u;
-          const int sub = 4 >> p.tile_shift;         // words per tile
-          for (int c = 0; c < 1 << p.tile_shift; ++c) {
-            const int tile = ((c0 + 4 * u + k) << p.tile_shift) + c;
-            if (((bits >> (c * sub)) & ((1u << sub) - 1u)) != 0u && tile < p.n_tile_cols) {
-              if (lane == 0) p.col_idx[(int64_t)tr * p.n_tile_cols + tiles] = tile;
-              ++tiles;
-            }
-          }
+        for (int i = 0; i < 4; ++i) {
+          unsigned long long b = __builtin_amdgcn_ballot_w64(w[i] != 0u);
+          b |= b >> 8;
+          b |= b >> 4;
+          b |= b >> 2;
+          b |= b >> 1;
+          some |= (b & 0x0001000100010001ull) << i;
         }
+        words |= ((some | some >> 12 | some >> 24 | some >> 36) & 0xffffull) << (16 * u);
       }
+    }
+    if (p.row_cnt) {
+      // the tile map's list of the 16 rows: a lane per word, the first of a tile writes it
+      if (p.tile_shift < 2) words |= words >> 1;
+      if (p.tile_shift < 1) words |= words >> 2;
+      const int sub = 4 >> p.tile_shift, tile = (c0 * 4 + lane) / sub;   // words per tile
+      const bool kept = (words >> lane & 1ull) != 0ull && (lane & (sub - 1)) == 0 && tile < p.n_tile_cols;
+      const unsigned long long all = __builtin_amdgcn_ballot_w64(kept);
+      if (kept) p.col_idx[(int64_t)tr * p.n_tile_cols + tiles + __builtin_popcountll(all & ((1ull << lane) - 1ull))] = tile;
+      tiles += __builtin_popcountll(all);
     }
   }
   if (p.row_cnt && lane == 0 && tr * 16 < p.rows) p.row_cnt[tr] = tiles;
