@@ -23,6 +23,7 @@
 // 65536 rows in blocks of 1024, 9 neighbours, 64 -> 64 13.2 and 9.0, 128 -> 128 19.5 and 15.0; 8192 rows,
 // 64 -> 64 8.6 and 4.1; 262144 rows of a power-law graph, 512 -> 16 159 and 85 (134 MB of codes: 27 at the
 // rate of a copy), 1024 -> 64 on 65536 rows 168 and 95; without heavy rows 512 -> 16 320 and 64.
+// Waves in flight decide in wide rows: 512 -> 16 has five per SIMD (95 registers) and takes 79 us, with four 88, with three 102.
 // Adding bytes up on the vector ALUs instead: 64 -> 64 11.0 us.  Heavy rows in the tiles' own waves: 512 -> 16
 // on the power-law graph 232 us.
 #pragma once

@@ -60,7 +60,9 @@ def test_lists_and_the_map_of_one_pass(n, k, block, kbits):
     (3, 160, 33, "64-65-47", 8, 8, True),            # whole groups of columns and one more
     (2, 1024, 1, "130-129-7", 8, 4, False),          # sixteen pieces, seven of them empty
     (2, 512, 0, "256-200-64", 7, 8, True),
-    (2, 288, 3, "300-101-5", 8, 8, False),  # two parts of 256 columns
+    (2, 288, 3, "300-101-5", 8, 8, False),  # two parts of 256 columns, the second of few pieces
+    (3, 288, 7, "370-40-2", 8, 5, True),            # ... of up to eight
+    (130, 256, 0, "384-16", 8, 8, True),
     (1, 640, 40, "1024-256-16", 8, 8, True),         # four parts, more weights than LDS keeps
     (130, 256, 77, "64-64-12", 8, 8, True),          # a tile per wave: one, four and more output tiles
     (130, 256, 0, "300-16-100", 8, 8, False),
