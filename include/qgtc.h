@@ -341,8 +341,10 @@ qgtc_status qgtc_aggregate(const qgtc_bits* A, const qgtc_tile_map* map,
                            const qgtc_bits* X, const qgtc_epilogue* ep,
                            void* out, int64_t ld_out, void* stream);
 
-/* The same with room for X as codes, which long rows are faster with: qgtc_aggregate_workspace_bytes (0: not used)
- * of them, 16-byte aligned, written on `stream`.  workspace == NULL: qgtc_aggregate. */
+/* The same with room for X as operands of the product (bytes, or floats of 4 or 6 bits), which long rows are faster
+ * with: qgtc_aggregate_workspace_bytes (0: not used) of them, 16-byte aligned, written on `stream`.  Room that is too
+ * small for the form that is asked for is used for bytes where it holds those, refused (QGTC_ERR_WORKSPACE) where
+ * bytes would be taken too, and else not used.  workspace == NULL: qgtc_aggregate. */
 size_t qgtc_aggregate_workspace_bytes(const qgtc_bits* A, const qgtc_bits* X);
 qgtc_status qgtc_aggregate_ws(const qgtc_bits* A, const qgtc_tile_map* map,
                               const qgtc_bits* X, const qgtc_epilogue* ep, void* workspace,

@@ -281,6 +281,8 @@ extern "C" int32_t qgtc_aggregate_reads_map(const qgtc_bits* A, int32_t x_cols) 
   return agg_reads_map(p, sp) ? 1 : 0;
 }
 
+// A codes' column group is addressed with 32 bits; features of more codes stay as planes.
+constexpr int64_t kMostCodes = (int64_t)256 << 20;
 static int64_t codes_bytes(const AggParams& p, const AggSplit& sp) { return codes_group_bytes(p.x_kwords, sp.lt) * cdiv(p.cols, 16 * sp.lt); }
 
 // Where the features become operands of 4- or 6-bit floats (agg_dense.hip) instead of bytes: wherever the sums are exact
@@ -299,22 +301,21 @@ static bool takes_floats(const AggParams& p) { return dense_applies(p) && !(p.co
 // fewer.  Planes and floats, called one by one from a script, where the second launch and its room are 4 us of the host's
 // 13: 4700 x 4700 x 64 at 2 bits 13.4 and 13.3, 5000 x 5000 x 64 at 8 14.5 and 13.6, 8192 x 8192 x 64 at 2 16.9 and 13.5 (in a
 // graph 17.1 and 11.8), 5000 x 5000 x 32 11.6 and 13.3, 6000 x 6000 x 16 at 3 12.6 and 13.4, 8192 x 8192 x 20 15.5 and 13.2.
-// A codes' column group is addressed with 32 bits; features beyond 256 MiB of codes stay as planes.
+static bool aggregate_from_floats(const AggParams& p, const AggSplit& sp) {
+  return takes_floats(p) && codes_bytes(p, sp) <= kMostCodes &&
+         (p.a_words > 32 * sp.chunks() || (p.rows >= 1024 && p.a_words > (p.cols > 32 ? 144 : 224)));
+}
+// (as bytes)
 static bool aggregate_from_codes(const AggParams& p, const AggSplit& sp) {
-  int enough = 8 * sp.chunks();
-  if (takes_floats(p) && p.rows >= 1024) {
-    const int floats = p.cols > 32 ? 36 : 56;
-    if (floats < enough) enough = floats;
-  }
-  return p.s <= 8 && p.a_words > 4 * enough && codes_bytes(p, sp) <= (int64_t)256 << 20;
+  return p.s <= 8 && p.a_words > 32 * sp.chunks() && codes_bytes(p, sp) <= kMostCodes;
 }
 
 extern "C" size_t qgtc_aggregate_workspace_bytes(const qgtc_bits* A, const qgtc_bits* X) {
   AggParams p{};
   if (!A || !X || A->rows == 0 || X->cols == 0 || agg_fill_params(A, nullptr, X, &p) != QGTC_OK) return 0;
   const AggSplit sp = aggregate_split(A->rows, X->cols, p.a_words, A->ld_words);
-  if (!aggregate_from_codes(p, sp)) return 0;
-  return (size_t)(takes_floats(p) ? dense_bytes(p) : codes_bytes(p, sp));
+  if (aggregate_from_floats(p, sp)) return (size_t)dense_bytes(p);
+  return aggregate_from_codes(p, sp) ? (size_t)codes_bytes(p, sp) : 0;
 }
 
 extern "C" qgtc_status qgtc_aggregate_ws(const qgtc_bits* A, const qgtc_tile_map* map, const qgtc_bits* X,
@@ -336,12 +337,11 @@ extern "C" qgtc_status qgtc_aggregate_ws(const qgtc_bits* A, const qgtc_tile_map
   const size_t lds = agg_set_shape(&p, sp, cdiv(X->cols, sp.group()), ep->tuning ? ep->tuning->agg_xcd_run : 0);
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   ProfScope prof(QGTC_KERNEL_AGGREGATE, s);
+  // (room that is no room for floats may still be enough for bytes, and is not needed for planes)
+  if (workspace && aggregate_from_floats(p, sp) && ((uintptr_t)workspace & 15u) == 0 && workspace_bytes >= (size_t)dense_bytes(p))
+    return dense_aggregate(p, workspace, ep->tuning ? ep->tuning->agg_xcd_run : 0, s);
   if (workspace && aggregate_from_codes(p, sp)) {
     if (((uintptr_t)workspace & 15u) != 0) return QGTC_ERR_ALIGN;
-    if (takes_floats(p)) {
-      if (workspace_bytes < (size_t)dense_bytes(p)) return QGTC_ERR_WORKSPACE;
-      return dense_aggregate(p, workspace, ep->tuning ? ep->tuning->agg_xcd_run : 0, s);
-    }
     if (workspace_bytes < (size_t)codes_bytes(p, sp)) return QGTC_ERR_WORKSPACE;
     if (sp.ct == 2) return launch_codes<2, 2, 1>(&p, X, workspace, lds, s);
     if (sp.ways == 2) return launch_codes<1, 2, 1>(&p, X, workspace, lds, s);

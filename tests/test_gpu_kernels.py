@@ -981,6 +981,32 @@ def test_aggregation_on_small_floats_is_exact(n, k, d, block, s):
             assert torch.equal(q.qgtc_aggregate(A, tmap, X, q.Epilogue(mode=q.OUT_I32, self_term=True)), want + x)
 
 
+def test_aggregation_with_less_room_than_it_asks_for():
+    """Room for X as bytes is enough where floats would be taken, and room that nothing fits in is not used where the
+    product goes without; too little for bytes, or misaligned, stays refused where bytes are what room is for."""
+    import ctypes as C
+    import paper_2111_09547_amd.binding as B
+    OK, ALIGN, WORKSPACE = 0, 4, 6
+    room = torch.empty(1 << 21, dtype=torch.uint8, device="cuda")
+    as_bytes = 257 * 512 * 5                                       # (700, 8193, 65) in groups of 16 columns
+    for n, k, d, s, calls in [
+        (700, 8193, 65, 8, [(as_bytes, 0, OK), (as_bytes - 1, 0, WORKSPACE), (1 << 20, 4, ALIGN)]),
+        (1024, 4609, 64, 2, [(16, 0, OK), (1 << 20, 4, OK)]),
+        (1024, 7169, 20, 5, [(1 << 15, 0, OK)]),
+    ]:
+        gen = torch.Generator(device="cuda").manual_seed(n + k)
+        a = (torch.rand((n, k), generator=gen, device="cuda") < 0.4).to(torch.uint8)
+        x = torch.randint(0, 1 << s, (k, d), generator=gen, device="cuda", dtype=torch.int32)
+        A, X = q.qgtc_pack_bits(a, 1, q.LEFT), q.qgtc_pack_bits(x, s, q.RIGHT)
+        want = (a.double() @ x.double()).to(torch.int32)
+        ep = q.Epilogue(mode=q.OUT_I32).to_c()
+        for nbytes, offset, status in calls:
+            out = torch.full((n, d), -1, dtype=torch.int32, device="cuda")
+            got = B.lib().qgtc_aggregate_ws(C.byref(A.c), None, C.byref(X.c), C.byref(ep), room.data_ptr() + offset, nbytes, out.data_ptr(), d, B._stream())
+            assert got == status, (n, k, d, s, nbytes, offset)
+            assert status != OK or torch.equal(out, want)
+
+
 @pytest.mark.parametrize("s", [1, 3, 4, 5, 8])
 @pytest.mark.parametrize("n,d", [(1, 1), (3, 33), (300, 64), (70000, 31), (33000, 132)])
 def test_left_planes_are_decoded_four_columns_at_a_time(n, d, s):
