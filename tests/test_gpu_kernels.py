@@ -981,6 +981,78 @@ def test_aggregation_on_small_floats_is_exact(n, k, d, block, s):
             assert torch.equal(q.qgtc_aggregate(A, tmap, X, q.Epilogue(mode=q.OUT_I32, self_term=True)), want + x)
 
 
+@pytest.mark.parametrize("n,k,d,s,block", [
+    (1030, 8193, 65, 2, 0),        # 4-bit floats, the last columns alone, a row of workgroups of six rows
+    (8300, 4700, 42, 4, 0),        # 6-bit floats
+    (16500, 2100, 30, 8, 0),       # two parts of 6 bits
+    (8210, 8210, 44, 3, 0),        # square, no multiple of 32, with the self term
+    (4 * 2304 + 40, 2304, 72, 1, 2304),
+])
+def test_outputs_of_long_rows(n, k, d, s, block):
+    """Every output of the products of floats against the same call without room, which takes planes: int32, fp32 with all
+    row and column terms, into whole and into odd strides, and codes of 12 bits with padding to be cleared.  Both form the
+    same expression of the same integers, so that the results are the same bits."""
+    import ctypes as C
+    import paper_2111_09547_amd.binding as B
+    gen = torch.Generator(device="cuda").manual_seed(n + d)
+    a = (torch.rand((n, k), generator=gen, device="cuda") < 0.1).to(torch.uint8)
+    a[:, k // 3:k // 3 + 900] = 0
+    if block:
+        a[n // block * block:, n % block:] = 0
+    x = torch.randint(0, 1 << s, (n if block else k, d), generator=gen, device="cuda", dtype=torch.int32)
+    A, X = q.qgtc_pack_bits(a, 1, q.LEFT, block_rows=block), q.qgtc_pack_bits(x, s, q.RIGHT)
+    nbytes = B.lib().qgtc_aggregate_workspace_bytes(C.byref(A.c), C.byref(X.c))
+    assert nbytes == -(-x.shape[0] // 32) * -(-d // 32) * 32 * (16 if s <= 2 else (24 if s <= 4 else 48))
+    room = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+    tmap = q.qgtc_build_tile_map(A, 16, 128)
+
+    def both(ep, made):
+        """made: a fresh output, as (what to compare, pointer, leading dimension)"""
+        out = []
+        for ws, size in ((None, 0), (room.data_ptr(), nbytes)):
+            res, ptr, ld = made()
+            B._check(B.lib().qgtc_aggregate_ws(C.byref(A.c), C.byref(tmap.c), C.byref(X.c), C.byref(ep.to_c()), ws, size, ptr, ld, B._stream()),
+                     "qgtc_aggregate_ws")
+            out.append(res)
+        assert torch.equal(*out)
+        return out[1]
+
+    def strided(ld, first):
+        def made():
+            res = torch.full((n, ld), -7, dtype=torch.int32, device="cuda")
+            return res, res.data_ptr() + 4 * first, ld
+        return made
+
+    ints = lambda m: torch.randint(0, 1000, (m,), generator=gen, device="cuda", dtype=torch.int32)
+    reals = lambda m: torch.randn(m, generator=gen, device="cuda")
+    square = block > 0 or n == k
+    whole = -(-d // 4) * 4 + 4
+    for self_term in (False, True) if square else (False,):
+        got = both(q.Epilogue(mode=q.OUT_I32, self_term=self_term), strided(d + 3, 1))
+        want = torch.cat([a[r:r + (block or n), :min(block, n - r) if block else k].double() @ (x[r:r + block] if block else x).double()
+                          for r in range(0, n, block or n)])
+        assert torch.equal(got[:, 1:1 + d], want.to(torch.int32) + (x if self_term else 0)) and bool((got[:, 0] == -7).all())
+        both(q.Epilogue(mode=q.OUT_I32, relu=True, self_term=self_term), strided(whole, 0))
+        terms = dict(cc=0.013, rs=-0.7, l0a=0.25, l0b=0.5, ck=3.0, cs=0.125, row_i=ints(n), row_l=ints(n), col_i=ints(d))
+        affine = dict(col_scale=reals(d), col_shift=reals(d))
+        for extra in ({}, terms, {**terms, **affine, "relu": True}):
+            for made in (strided(whole, 0), strided(d + 1 + (d & 1), 0), strided(whole, 3)):
+                got = both(q.Epilogue(mode=q.OUT_F32, self_term=self_term, **{"cc": 0.013, **extra}), made)
+                assert len(got.unique()) > 20
+        words = -(-d // 32)
+
+        def planes(nbits, ld):
+            def made():
+                res = B.alloc_bits(n, d, nbits, q.LEFT, ld_words=ld)
+                res.words.fill_(-1)
+                made.keep = res                                     # (its descriptor is read by the call)
+                return res.words, C.cast(C.pointer(res.c), C.c_void_p), 0
+            return made
+        inv = qgnn.inv_scale(0.0, float(want.max()) + (1 << s), 12)
+        for nbits, ld in ((12, words + 3), (16, words), (8, words + 1)):
+            both(q.Epilogue(mode=q.OUT_BITS, self_term=self_term, relu=True, rq_nbits=nbits, rq_lo=2, rq_inv_scale=inv, **affine), planes(nbits, ld))
+
+
 def test_aggregation_with_less_room_than_it_asks_for():
     """Room for X as bytes is enough where floats would be taken, and room that nothing fits in is not used where the
     product goes without; too little for bytes, or misaligned, stays refused where bytes are what room is for."""
