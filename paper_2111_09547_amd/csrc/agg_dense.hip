@@ -134,17 +134,26 @@ struct DenseParams {
   EpiParams ep;
 };
 
-// The workgroup's chunks from the tile map (its rows are tile rows tr0 .. tr0 + n_tr - 1): their number.
+// Whether the workgroup (its rows are tile rows tr0 .. tr0 + n_tr - 1, MOST at most) takes all chunks: a list that leaves out
+// less than an eighth of them costs more than it saves (65536 x 256 columns in blocks of 4096 with 0.1 % of the bits, at 8
+// bits: 138 us with such lists, 117), and one such row is enough.  Scalar loads, which need not wait for the stages that are
+// on their way.
+typedef const __attribute__((address_space(4))) int32_t* ScalarInts;
+template <int MOST>
+__device__ __forceinline__ bool dense_all_chunks(const DenseParams& p, int tr0, int n_tr) {
+  const ScalarInts cnt = (ScalarInts)(uintptr_t)(p.row_cnt + (int)uniform((uint32_t)tr0));
+  int most = 0;
+#pragma unroll
+  for (int t = 0; t < MOST; ++t) most = max(most, cnt[min(t, n_tr - 1)]);
+  return most > p.n_tile_cols - p.n_tile_cols / 8 - 1;
+}
+
+// The workgroup's chunks from the tile map, and their number.
 __device__ __forceinline__ int dense_list(const DenseParams& p, uint8_t* lds, int tr0, int n_tr, int n_waves) {
   uint16_t* const list = reinterpret_cast<uint16_t*>(lds + p.list_off);
   const int mw = (p.n_chunks + 31) >> 5, tid = (int)threadIdx.x, wave = tid >> 6, lane = tid & 63;
   uint32_t* const mask = reinterpret_cast<uint32_t*>(lds + p.list_off + (2 * p.n_chunks + 3) / 4 * 4);
   uint32_t* const count = mask + mw;
-  // a full list is not read, and one such row is enough
-  bool all = false;
-  for (int t0 = 0; t0 < n_tr; t0 += 64)
-    all = all || __builtin_amdgcn_ballot_w64(t0 + lane < n_tr && p.row_cnt[tr0 + min(t0 + lane, n_tr - 1)] >= p.n_tile_cols) != 0ull;
-  if (all) return p.n_chunks;                        // (the same in every wave)
   for (int i = tid; i < mw; i += 64 * n_waves) mask[i] = 0u;
   __syncthreads();
   for (int t = wave; t < n_tr; t += n_waves) {
@@ -441,18 +450,25 @@ __global__ __launch_bounds__(64 * RWV * KS) void dense_kernel(const DenseParams 
 
   // ---- the pipeline: a stage's operands go to registers beside the products of the one in front, and its slot is
   // then loaded again ----
-  auto load_first = [&] {
+  auto load_first = [&](int from, int slots) {
 #pragma unroll 1
-    for (int i = 0; i < min(Sh::SLOTS, (n_list + KS - 1) / KS); ++i) load(i, lds0 + (uint32_t)(i * Sh::SLOT));
+    for (int i = from; i < min(slots, (n_list + KS - 1) / KS); ++i) load(i, lds0 + (uint32_t)(i * Sh::SLOT));
   };
-  load_first();
-  if (p.list_off) {                                  // (beside the loads of all chunks, which most lists turn out to be)
-    n_list = dense_list(p, lds, (block0 + lrow_wg) >> 4, (rows_wg + 15) >> 4, Sh::NW);
-    if (n_list < p.n_chunks) {
+  // Of all chunks first, while the lengths of the lists come: two stages, which most lists turn out to want; more are in the way
+  // of a short list's (8192 x 8192 x 64 with 8 full blocks on the diagonal, at 2 bits: all slots 9.8 us, two 9.4; 32768 x 32768
+  // x 128 with blocks of 1024, at 8 bits 32.1 and 30.2).
+  const int ahead = p.list_off ? 2 : Sh::SLOTS;
+  load_first(0, ahead);
+  if (p.list_off) {
+    const int tr0 = (block0 + lrow_wg) >> 4, n_tr = (rows_wg + 15) >> 4;
+    if (dense_all_chunks<ROWS / 16>(p, tr0, n_tr)) {
+      load_first(ahead, Sh::SLOTS);
+    } else {
+      n_list = dense_list(p, lds, tr0, n_tr, Sh::NW);
       list = reinterpret_cast<const uint16_t*>(lds + p.list_off);
       dense_wait<0, 0>(0);
       __syncthreads();
-      load_first();
+      load_first(0, Sh::SLOTS);
     }
   }
   const int n_st = (n_list + KS - 1) / KS;
