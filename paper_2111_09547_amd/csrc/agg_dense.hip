@@ -231,12 +231,12 @@ __device__ __forceinline__ void dense_emit(const DenseParams& p, int row0, int r
     }
     // Rows that are not whole 16 bytes: through LDS, so that a store is 32 columns of two rows instead of one of 64 (8200 x 2049
     // x 257 at 8 bits, us: one by one 38.7, here 25.8; at 2 bits 29.8 and 18.6).
-    if (!vec) {
+    if (__builtin_expect(!vec, 0)) {
 #pragma unroll
       for (int k = 0; k < 16; ++k) room[32 * n + ((16 * kh + k) ^ n)] = y[k];   // (rows spread over the banks)
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       uint32_t* const to = reinterpret_cast<uint32_t*>(e.out) + (int64_t)row0 * e.ld_out + 32 * cg + n;
-#pragma unroll
+#pragma unroll 4
       for (int k = 0; k < 16; ++k) {
         const int r = 2 * k + kh;
         const uint32_t v = room[32 * r + (n ^ r)];
@@ -450,26 +450,25 @@ __global__ __launch_bounds__(64 * RWV * KS) void dense_kernel(const DenseParams 
 
   // ---- the pipeline: a stage's operands go to registers beside the products of the one in front, and its slot is
   // then loaded again ----
-  auto load_first = [&](int from, int slots) {
+  auto load_first = [&](int from, int upto) {
 #pragma unroll 1
-    for (int i = from; i < min(slots, (n_list + KS - 1) / KS); ++i) load(i, lds0 + (uint32_t)(i * Sh::SLOT));
+    for (int i = from; i < min(upto, (n_list + KS - 1) / KS); ++i) load(i, lds0 + (uint32_t)(i * Sh::SLOT));
   };
   // Of all chunks first, while the lengths of the lists come: two stages, which most lists turn out to want; more are in the way
   // of a short list's (8192 x 8192 x 64 with 8 full blocks on the diagonal, at 2 bits: all slots 9.8 us, two 9.4; 32768 x 32768
   // x 128 with blocks of 1024, at 8 bits 32.1 and 30.2).
-  const int ahead = p.list_off ? 2 : Sh::SLOTS;
-  load_first(0, ahead);
+  int from = p.list_off ? 2 : Sh::SLOTS;
+  load_first(0, from);
   if (p.list_off) {
     const int tr0 = (block0 + lrow_wg) >> 4, n_tr = (rows_wg + 15) >> 4;
-    if (dense_all_chunks<ROWS / 16>(p, tr0, n_tr)) {
-      load_first(ahead, Sh::SLOTS);
-    } else {
+    if (!dense_all_chunks<ROWS / 16>(p, tr0, n_tr)) {
       n_list = dense_list(p, lds, tr0, n_tr, Sh::NW);
       list = reinterpret_cast<const uint16_t*>(lds + p.list_off);
       dense_wait<0, 0>(0);
       __syncthreads();
-      load_first(0, Sh::SLOTS);
+      from = 0;
     }
+    load_first(from, Sh::SLOTS);
   }
   const int n_st = (n_list + KS - 1) / KS;
   uint32_t slot = 0;                                 // of the stage in front
