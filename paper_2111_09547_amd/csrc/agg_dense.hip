@@ -582,18 +582,26 @@ qgtc_status launch(DenseParams* dp, int xcd_run, hipStream_t stream) {
 }
 
 template <int FMT, int CT>
-qgtc_status launch_rows(DenseParams* p, int xcd_run, hipStream_t stream) {
-  const int n_sub = p->block_rows > 0 ? cdiv(p->rows, p->block_rows) : 1;
-  const int64_t wide = cdiv(p->cols, 32 * CT), half = device_compute_units() / 2;
-  // The most rows that give half of the compute units a workgroup: more of them read X more often, and take turns.
-  // 256, 128, 64 and 32 rows, us: 12000 x 12000 x 100 at 8 bits (188, 376, .. workgroups) 35.8, 44.5, 65.5, 107; 5000 x 5000 x
-  // 100 at 5 (80, 160, ..) 19.5, 16.0, 22.6, 34.0; 12288 x 12288 x 16 at 2 (48, 96, 192, ..) 21.1, 15.8, 13.3, 14.6; 8192 x
-  // 8192 x 64 at 2 (32, 64, 128, 256) 22.7, 16.1, 13.2, 11.8.
-  auto groups = [&](int rows) { return (int64_t)n_sub * cdiv(p->eff_rows, rows) * wide; };
-  if (groups(256) > half) return launch<FMT, 4, CT, 2, 4>(p, xcd_run, stream);
-  if (groups(128) > half) return launch<FMT, 2, CT, 2, 4>(p, xcd_run, stream);
-  if (groups(64) > half) return launch<FMT, 1, CT, 2, 4>(p, xcd_run, stream);
-  return launch<FMT, 1, CT, 1, 4>(p, xcd_run, stream);
+qgtc_status launch_rows(DenseParams* p, int rows, int xcd_run, hipStream_t stream) {
+  if (rows == 256) return launch<FMT, 4, CT, 2, 4>(p, xcd_run, stream);
+  // (5 to 8 bits come here only where rows are many: aggregate_from_floats)
+  if (FMT == kTwoSixBits || rows == 128) return launch<FMT, 2, CT, 2, 4>(p, xcd_run, stream);
+  if constexpr (FMT != kTwoSixBits) {
+    if (rows == 64) return launch<FMT, 1, CT, 2, 4>(p, xcd_run, stream);
+    return launch<FMT, 1, CT, 1, 4>(p, xcd_run, stream);
+  }
+}
+
+bool one_tile(const AggParams& p) { return p.cols <= 32 || dense_format(p.s) == kTwoSixBits; }   // of columns per workgroup
+
+// The most rows of a workgroup that give half of the compute units one: more of them read X more often, and take turns.
+// 256, 128, 64 and 32 rows, us: 12000 x 12000 x 100 at 8 bits (188, 376, .. workgroups) 35.8, 44.5, 65.5, 107; 12288 x 12288 x
+// 16 at 2 (48, 96, 192, ..) 21.1, 15.8, 13.3, 14.6; 8192 x 8192 x 64 at 2 (32, 64, 128, 256) 22.7, 16.1, 13.2, 11.8.
+int dense_rows(const AggParams& p) {
+  const int64_t half = device_compute_units() / 2;
+  for (int rows = 256; rows > 32; rows >>= 1)
+    if (dense_groups(p, rows) > half) return rows;
+  return 32;
 }
 
 }  // namespace
@@ -601,6 +609,11 @@ qgtc_status launch_rows(DenseParams* p, int xcd_run, hipStream_t stream) {
 // Sums, which may include the row itself, below 2^24: of 8 bits up to 65792 columns of A.
 bool dense_applies(const AggParams& p) {
   return p.s <= 8 && p.lda < (int64_t)1 << 21 && (((int64_t)1 << p.s) - 1) * ((int64_t)p.a_words * 32 + 1) < (int64_t)1 << 24;
+}
+
+int64_t dense_groups(const AggParams& p, int rows) {
+  const int eff = p.eff_rows < p.rows ? p.eff_rows : p.rows;
+  return (int64_t)(p.block_rows > 0 ? cdiv(p.rows, p.block_rows) : 1) * cdiv(eff, rows) * cdiv(p.cols, one_tile(p) ? 32 : 64);
 }
 
 static int64_t dense_group_bytes(const AggParams& p) { return (int64_t)p.x_kwords * dense_word_bytes(dense_format(p.s)); }
@@ -640,10 +653,10 @@ qgtc_status dense_aggregate(const AggParams& a, void* workspace, int xcd_run, hi
   p.row_cnt = a.row_cnt;
   p.col_idx = a.col_idx;
   p.ep = a.ep;
-  const bool narrow = a.cols <= 32;
-  if (fmt == kNibbles) return narrow ? launch_rows<kNibbles, 1>(&p, xcd_run, stream) : launch_rows<kNibbles, 2>(&p, xcd_run, stream);
-  if (fmt == kSixBits) return narrow ? launch_rows<kSixBits, 1>(&p, xcd_run, stream) : launch_rows<kSixBits, 2>(&p, xcd_run, stream);
-  return launch_rows<kTwoSixBits, 1>(&p, xcd_run, stream);
+  const int rows = dense_rows(a);
+  if (fmt == kTwoSixBits) return launch_rows<kTwoSixBits, 1>(&p, rows, xcd_run, stream);
+  if (one_tile(a)) return fmt == kNibbles ? launch_rows<kNibbles, 1>(&p, rows, xcd_run, stream) : launch_rows<kSixBits, 1>(&p, rows, xcd_run, stream);
+  return fmt == kNibbles ? launch_rows<kNibbles, 2>(&p, rows, xcd_run, stream) : launch_rows<kSixBits, 2>(&p, rows, xcd_run, stream);
 }
 
 }  // namespace qgtc

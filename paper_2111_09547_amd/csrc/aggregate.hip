@@ -285,11 +285,6 @@ extern "C" int32_t qgtc_aggregate_reads_map(const qgtc_bits* A, int32_t x_cols) 
 constexpr int64_t kMostCodes = (int64_t)256 << 20;
 static int64_t codes_bytes(const AggParams& p, const AggSplit& sp) { return codes_group_bytes(p.x_kwords, sp.lt) * cdiv(p.cols, 16 * sp.lt); }
 
-// Where the features become operands of 4- or 6-bit floats (agg_dense.hip) instead of bytes: wherever the sums are exact
-// there, but not 5 to 8 bits of 16 or fewer columns, half of whose 32-column tiles would be empty (12288 x 12288 x 16:
-// bytes 17.9, two 6-bit parts 20.1 us; at 2 bits 17.6 and 13.3).
-static bool takes_floats(const AggParams& p) { return dense_applies(p) && !(p.cols <= 16 && p.s > 4); }
-
 // Whether the features are turned into codes by a launch of their own (3 us) instead of by every workgroup, for
 // whom a stage of planes goes through registers, whose wait is also one for the stage's words of A: from
 // nine stages of K on.  Planes and codes as bytes, us:
@@ -297,24 +292,50 @@ static bool takes_floats(const AggParams& p) { return dense_applies(p) && !(p.co
 //   3072 x 256 (twelve) 19.8 and 17.8; 8192 x 300 71 and 51; 16384 x 256 112 and 90
 //   of eight, which four waves share: 4096 x 64 (four) 10.4 and 10.7; 8192 x 64 (eight) 18.9 and 18.7, and with
 //   the launch from a script 17.1 and 17.5; 12288 x 16 (twelve) 22.4 and 17.8; 256 x 65536 x 64 94 and 65
-// Floats, which are faster, earlier where rows are not few: of more than 4608 columns of A, of 7168 for 32 columns of X or
-// fewer.  Planes and floats, called one by one from a script, where the second launch and its room are 4 us of the host's
-// 13: 4700 x 4700 x 64 at 2 bits 13.4 and 13.3, 5000 x 5000 x 64 at 8 14.5 and 13.6, 8192 x 8192 x 64 at 2 16.9 and 13.5 (in a
-// graph 17.1 and 11.8), 5000 x 5000 x 32 11.6 and 13.3, 6000 x 6000 x 16 at 3 12.6 and 13.4, 8192 x 8192 x 20 15.5 and 13.2.
-static bool aggregate_from_floats(const AggParams& p, const AggSplit& sp) {
-  return takes_floats(p) && codes_bytes(p, sp) <= kMostCodes &&
-         (p.a_words > 32 * sp.chunks() || (p.rows >= 1024 && p.a_words > (p.cols > 32 ? 144 : 224)));
-}
-// (as bytes)
 static bool aggregate_from_codes(const AggParams& p, const AggSplit& sp) {
   return p.s <= 8 && p.a_words > 32 * sp.chunks() && codes_bytes(p, sp) <= kMostCodes;
+}
+
+// Whether they become operands of 4- or 6-bit floats (agg_dense.hip) instead, where the sums are exact there.  odd: rows of
+// the output that are not whole 16 bytes.  Measured over 300 drawn shapes of 200 to 60000 rows, 2100 to 30000 columns of A and 4 to
+// 600 of X, every tile occupied; bytes (or planes) and floats, us:
+//   1 to 4 bits, one product per word: from nine stages on wherever rows fill the chip with undivided stages (16384 x 16384 x 256 at
+//   4 bits 89 and 46, 16400 x 2500 x 64 15.6 and 12.5).  Diagonal blocks of up to 3072 rows that are more than two rounds of
+//   workgroups are not: X is as long as A and its operands are written once more (81920 x 256 at 4 bits 102 and 119).
+//   Where four waves share a unit's stages, 1 and 2 bits and up to 32 columns of 3 and 4 as before (1161 x 21479 x 32 23.7 and
+//   17.1), wider rows of 3 and 4 bits where workgroups of 32 rows and 64 columns fill half of the chip (7889 x 15121 x 47
+//   24.1 and 21.2; 1350 x 6699 x 46, 43 workgroups, 12.8 and 13.7).  That many have floats earlier too, of more than 4608
+//   columns of A instead of 8192 (5000 x 5000 x 64 at 2 bits 12.5 and 10.1; 1603 x 4608 x 58 10.1 and 10.4), and up to 32
+//   columns of 1024 rows and more from 7168 (1024 x 7200 x 32 13.4 and 10.4).
+//   5 to 8 bits, two products per word and 32 columns per workgroup: undivided stages in one round of workgroups (16384 x 16384 x 64 at 8
+//   55.6 and 30.1; 13932 x 2760 x 384, 2.6 rounds, 44.6 and 53.9), with odd rows, whose stores cost bytes more (16551 x 3077 x 574,
+//   4.6 rounds, 124 and 101), or of more than 10240 columns without a map (16384 x 16384 x 256 90 and 78; with one of blocks of 256
+//   17815 x 17815 x 556 38.8 and 78.9); divided ones are level at best (461 x 8274 x 433 15.5 and 20.6).  Not 16 or fewer
+//   columns, half of whose tiles of 32 would be empty (12288 x 12288 x 16 17.9 and 20.1).
+// With a map that leaves most tiles out floats lose some: the launch in front, and more rows per list (8192 x 8192 x 64 at 2
+// bits with eight full blocks on the diagonal 6.9 and 9.2, sixteen in 16384 x 16384 x 256 at 4 19.1 and 21.0; with every
+// tile 15.6 and 11.8, 89 and 46).  How full a map is only the device knows.
+static bool aggregate_from_floats(const AggParams& p, const AggSplit& sp, bool odd) {
+  if (!dense_applies(p) || codes_bytes(p, sp) > kMostCodes || (p.cols <= 16 && p.s > 4)) return false;
+  const bool long_rows = p.a_words > 32 * sp.chunks();
+  const int64_t cus = device_compute_units();
+  if (sp.ks == 1) {
+    if (!long_rows) return false;
+    const int64_t rounds = cdiv(dense_groups(p, 256), cus);
+    return p.s > 4 ? rounds == 1 || odd || (!p.row_cnt && p.a_words > 320) : !(p.block_rows > 0 && p.a_words <= 96 && rounds > 2);
+  }
+  if (p.s > 4) return false;
+  if (p.cols <= 32) return long_rows || (p.rows >= 1024 && p.a_words > 224);
+  const bool many = dense_groups(p, 32) > cus / 2;
+  return (long_rows && (many || p.s <= 2)) || (many && p.a_words > 144);
 }
 
 extern "C" size_t qgtc_aggregate_workspace_bytes(const qgtc_bits* A, const qgtc_bits* X) {
   AggParams p{};
   if (!A || !X || A->rows == 0 || X->cols == 0 || agg_fill_params(A, nullptr, X, &p) != QGTC_OK) return 0;
   const AggSplit sp = aggregate_split(A->rows, X->cols, p.a_words, A->ld_words);
-  if (aggregate_from_floats(p, sp)) return (size_t)dense_bytes(p);
+  // (where the output decides, bytes need less)
+  if (aggregate_from_floats(p, sp, true)) return (size_t)dense_bytes(p);
   return aggregate_from_codes(p, sp) ? (size_t)codes_bytes(p, sp) : 0;
 }
 
@@ -338,7 +359,8 @@ extern "C" qgtc_status qgtc_aggregate_ws(const qgtc_bits* A, const qgtc_tile_map
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   ProfScope prof(QGTC_KERNEL_AGGREGATE, s);
   // (room that is no room for floats may still be enough for bytes, and is not needed for planes)
-  if (workspace && aggregate_from_floats(p, sp) && ((uintptr_t)workspace & 15u) == 0 && workspace_bytes >= (size_t)dense_bytes(p))
+  const bool odd = ep->mode != QGTC_OUT_BITS && ((ld_out & 3) != 0 || ((uintptr_t)out & 15u) != 0);
+  if (workspace && aggregate_from_floats(p, sp, odd) && ((uintptr_t)workspace & 15u) == 0 && workspace_bytes >= (size_t)dense_bytes(p))
     return dense_aggregate(p, workspace, ep->tuning ? ep->tuning->agg_xcd_run : 0, s);
   if (workspace && aggregate_from_codes(p, sp)) {
     if (((uintptr_t)workspace & 15u) != 0) return QGTC_ERR_ALIGN;

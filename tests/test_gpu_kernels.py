@@ -896,14 +896,19 @@ def test_aggregate_and_update_on_random_shapes(seed):
 
 # ------------------------------------------------------------------ long rows: features as codes
 @pytest.mark.parametrize("n,k,d,s,block,density,codes", [
-    (8200, 2049, 257, 8, 0, 0.3, True),        # 17 chunks of K, the last one of a column; two waves of 32 columns
+    (8200, 2049, 257, 8, 0, 0.3, True),        # floats: 17 chunks of K, the last one of a column; odd rows
     (8200, 2048, 257, 8, 0, 0.3, False),
-    (16400, 2500, 33, 3, 0, 0.01, True),       # two waves of 16
-    (8200, 2561, 70, 8, 0, 0.01, True),        # one
-    (700, 8193, 17, 8, 0, 0.3, True),          # four waves share a stage
+    (16400, 2500, 33, 3, 0, 0.01, True),       # floats
+    (8200, 2561, 70, 8, 0, 0.01, True),        # floats
+    (700, 8193, 17, 8, 0, 0.3, True),          # bytes: four waves share a stage
     (65, 8192, 1, 1, 0, 0.5, False),
-    (65, 11000, 1, 1, 0, 0.5, True),
-    (4 * 2560 + 100, 2560, 100, 8, 2560, 0.002, True),
+    (65, 11000, 1, 1, 0, 0.5, True),           # floats
+    (4 * 2560 + 100, 2560, 100, 8, 2560, 0.002, True),   # floats
+    (700, 8193, 16, 8, 0, 0.3, 257 * 512),     # bytes (their room): four waves share a stage
+    (65, 11000, 5, 5, 0, 0.5, 344 * 512),
+    (33000, 2561, 16, 8, 0, 0.05, 81 * 512),   # one wave of 16 columns
+    (6600, 65900, 150, 8, 0, 0.01, 2060 * 512 * 10),     # two of them; sums of 2^24 and more
+    (8200, 2500, 256, 8, 0, 0.01, True),       # two of 32; more than a round of workgroups of floats
 ])
 @pytest.mark.parametrize("with_map", [False, True])
 def test_aggregation_of_long_rows(n, k, d, s, block, density, codes, with_map):
@@ -918,7 +923,8 @@ def test_aggregation_of_long_rows(n, k, d, s, block, density, codes, with_map):
     x = torch.randint(0, 1 << s, (n if block else k, d), generator=gen, device="cuda", dtype=torch.int32)
     A, X = q.qgtc_pack_bits(a, 1, q.LEFT, block_rows=block), q.qgtc_pack_bits(x, s, q.RIGHT)
     tmap = q.qgtc_build_tile_map(A, 16, 128) if with_map else None
-    assert (B.lib().qgtc_aggregate_workspace_bytes(C.byref(A.c), C.byref(X.c)) > 0) == codes
+    nbytes = B.lib().qgtc_aggregate_workspace_bytes(C.byref(A.c), C.byref(X.c))
+    assert (nbytes > 0) == codes if isinstance(codes, bool) else nbytes == codes
     parts = [slice(r, min(r + block, n)) for r in range(0, n, block)] if block else [slice(0, n)]
     want = torch.cat([a[p, :p.stop - p.start if block else k].double() @ (x[p] if block else x).double() for p in parts]).to(torch.int32)
     square = block > 0
@@ -945,19 +951,30 @@ def test_aggregation_of_long_rows(n, k, d, s, block, density, codes, with_map):
             assert torch.equal(out, want)
 
 
-@pytest.mark.parametrize("n,k,d,block", [
-    (1030, 8193, 65, 0),           # 65 chunks, the last one of a column; three column groups, the last one of a column
-    (1024, 4609, 64, 0),           # where floats begin
-    (1024, 7169, 20, 0),
-    (1024, 65664, 33, 0),          # sums up to the last exact ones at 8 bits
-    (1025, 65792, 17, 0),
-    (40 * 256 + 1, 8300, 250, 0),  # 256 rows per workgroup, 128 and 64 below
-    (20 * 256 - 31, 8300, 130, 0),
-    (20 * 256 - 31, 8300, 40, 0),
-    (2 * 8224 + 33, 8224, 70, 8224),   # diagonal blocks, the last one of two words of rows
+@pytest.mark.parametrize("n,k,d,block,forms", [
+    # forms of X at 1 and 2, 3 and 4, 5 to 8 bits: floats, bytes, planes
+    (1030, 8193, 65, 0, "fbb"),    # 65 chunks, the last one of a column; three column groups, the last one of a column
+    (1024, 4609, 64, 0, "ppp"),    # few workgroups
+    (1024, 7169, 20, 0, "ffp"),    # 32 rows per workgroup
+    (1024, 65664, 33, 0, "fbb"),
+    (1025, 65792, 17, 0, "ffb"),
+    (2065, 65792, 500, 0, "fff"),  # sums up to the last exact ones at 8 bits
+    (40 * 256 + 1, 8300, 250, 0, "fff"),
+    (20 * 256 - 31, 8300, 130, 0, "fff"),
+    (20 * 256 - 31, 8300, 40, 0, "ffb"),
+    # up to 32 columns: 64, 128 and 256 rows per workgroup (5 to 8 bits: 128, 256)
+    (8300, 7200, 20, 0, "ffp"),
+    (16500, 2100, 20, 0, "fff"),
+    (33000, 2100, 30, 0, "fff"),
+    # more: 32, 64, 128 and 256 rows (5 to 8 bits: 256 at 16500 rows, and room for floats where aligned rows take bytes)
+    (7000, 4700, 40, 0, "ffp"),
+    (8300, 4700, 40, 0, "ffp"),
+    (16500, 4700, 40, 0, "fff"),
+    (33000, 2100, 40, 0, "fff"),
+    (2 * 8224 + 33, 8224, 70, 8224, "fff"),   # diagonal blocks, the last one of two words of rows
 ])
 @pytest.mark.parametrize("s", [1, 2, 3, 4, 5, 8])
-def test_aggregation_on_small_floats_is_exact(n, k, d, block, s):
+def test_aggregation_on_small_floats_is_exact(n, k, d, block, forms, s):
     """Products of 4- and 6-bit floats against float64: whole tiles of ones and of the largest code, rows and chunks of
     zeros, the self term, with and without a map that leaves chunks out."""
     import ctypes as C
@@ -972,7 +989,9 @@ def test_aggregation_on_small_floats_is_exact(n, k, d, block, s):
     x = torch.randint(0, 1 << s, (n if block else k, d), generator=gen, device="cuda", dtype=torch.int32)
     x[:, :9] = (1 << s) - 1
     A, X = q.qgtc_pack_bits(a, 1, q.LEFT, block_rows=block), q.qgtc_pack_bits(x, s, q.RIGHT)
-    assert B.lib().qgtc_aggregate_workspace_bytes(C.byref(A.c), C.byref(X.c)) == -(-x.shape[0] // 32) * -(-d // 32) * 32 * (16 if s <= 2 else (24 if s <= 4 else 48))
+    words, form = -(-x.shape[0] // 32), forms[0 if s <= 2 else 1 if s <= 4 else 2]
+    room = {"f": words * -(-d // 32) * 32 * (16 if s <= 2 else (24 if s <= 4 else 48)), "b": words * -(-d // 16) * 512, "p": 0}[form]
+    assert B.lib().qgtc_aggregate_workspace_bytes(C.byref(A.c), C.byref(X.c)) == room
     parts = [slice(r, min(r + block, n)) for r in range(0, n, block)] if block else [slice(0, n)]
     want = torch.cat([a[p, :p.stop - p.start if block else k].double() @ (x[p] if block else x).double() for p in parts]).to(torch.int32)
     for tmap in (None, q.qgtc_build_tile_map(A, 16, 128)):
@@ -1059,12 +1078,12 @@ def test_aggregation_with_less_room_than_it_asks_for():
     import ctypes as C
     import paper_2111_09547_amd.binding as B
     OK, ALIGN, WORKSPACE = 0, 4, 6
-    room = torch.empty(1 << 21, dtype=torch.uint8, device="cuda")
-    as_bytes = 257 * 512 * 5                                       # (700, 8193, 65) in groups of 16 columns
+    room = torch.empty((1 << 21) + 16, dtype=torch.uint8, device="cuda")
+    as_bytes = 260 * 512 * 9                                       # (5089, 8300, 130) in groups of 16 columns
     for n, k, d, s, calls in [
-        (700, 8193, 65, 8, [(as_bytes, 0, OK), (as_bytes - 1, 0, WORKSPACE), (1 << 20, 4, ALIGN)]),
-        (1024, 4609, 64, 2, [(16, 0, OK), (1 << 20, 4, OK)]),
-        (1024, 7169, 20, 5, [(1 << 15, 0, OK)]),
+        (5089, 8300, 130, 8, [(as_bytes, 0, OK), (as_bytes - 1, 0, WORKSPACE), (1 << 21, 4, ALIGN)]),
+        (7000, 4700, 40, 2, [(16, 0, OK), (1 << 20, 4, OK)]),
+        (1024, 7169, 20, 4, [(1 << 15, 0, OK)]),
     ]:
         gen = torch.Generator(device="cuda").manual_seed(n + k)
         a = (torch.rand((n, k), generator=gen, device="cuda") < 0.4).to(torch.uint8)
@@ -1072,6 +1091,7 @@ def test_aggregation_with_less_room_than_it_asks_for():
         A, X = q.qgtc_pack_bits(a, 1, q.LEFT), q.qgtc_pack_bits(x, s, q.RIGHT)
         want = (a.double() @ x.double()).to(torch.int32)
         ep = q.Epilogue(mode=q.OUT_I32).to_c()
+        assert B.lib().qgtc_aggregate_workspace_bytes(C.byref(A.c), C.byref(X.c)) > calls[0][0]
         for nbytes, offset, status in calls:
             out = torch.full((n, d), -1, dtype=torch.int32, device="cuda")
             got = B.lib().qgtc_aggregate_ws(C.byref(A.c), None, C.byref(X.c), C.byref(ep), room.data_ptr() + offset, nbytes, out.data_ptr(), d, B._stream())
