@@ -117,11 +117,12 @@ __global__ __launch_bounds__(256) void update_mfma_kernel(const UpdParams p) {
     }
   };
 
-  // The first tile is requested in front of the staging of W, which takes as long as its loads.
   const int rg_step = (int)gridDim.x * 4;
   int rg = blockIdx.x * 4 + wave, ss = 0;
   uint32_t buf0[8 * WPL], buf1[8 * WPL];
-  load_tile(rg, 0, 0, buf0);                        // (zeros for a wave without a group)
+  // One super-step: its first tile is requested in front of the staging of W, which takes as long.  (Elsewhere the registers
+  // and the code in front cost more: 1000 x 1024 -> 256 at 8 bits 10.5 us, with it 11.0; 30000 x 64 -> 256 14.2 and 15.8.)
+  if constexpr (LW == 4) load_tile(rg, 0, 0, buf0); // (zeros for a wave without a group)
 
   // ---- stage W[.][c0 .. c0+CC) in LDS as bytes ------------------------------------
   // one thread turns one word (32 K positions) of one column, all planes, into 32 bytes
@@ -225,6 +226,7 @@ __global__ __launch_bounds__(256) void update_mfma_kernel(const UpdParams p) {
   // Items (row group, super-step) of this wave, one after the other, each as two tiles;
   // while one tile is on the matrix cores the loads of the next one are in flight.
   if (rg >= n_groups) return;                       // whole wave; no barrier follows
+  if constexpr (LW != 4) load_tile(rg, 0, 0, buf0);
   while (true) {
     load_tile(rg, ss, 1, buf1);
     const int row0 = rg * kRowsPerGroup;
