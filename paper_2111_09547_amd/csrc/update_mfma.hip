@@ -319,6 +319,9 @@ __global__ __launch_bounds__(256) void update_mfma_kernel(const UpdParams p) {
   }
 }
 
+// Workgroups along the rows, each wave with a group of them.
+int64_t row_workgroups(const UpdParams& p) { return cdiv(cdiv(p.rows, kRowsPerGroup), 4); }
+
 int pick_lw(const UpdParams& p) {
   if (p.y_bytes) return p.ldy * 4 <= 64 ? 1 : (p.ldy * 4 <= 128 ? 2 : 8);
   // four words per lane and plane are one 16-byte load: rows, planes and base at multiples of 16 bytes
@@ -386,8 +389,13 @@ qgtc_status dispatch_n(const UpdParams& p, hipStream_t stream) {
   const int ntc = pick_ntc(p);
   // Rows that leave compute units without a workgroup: 16 columns per workgroup, which all read Y (from the caches).
   // 64 and 16 columns, us: 16384 x 256 -> 64 of 4 bits 8.6 and 7.0, of 8 bits 10.3 and 8.2, 4096 x 256 -> 128 8.2 and 6.0,
-  // 2048 x 512 -> 64 10.5 and 6.7, 1000 x 160 -> 33 7.6 and 5.6.
-  const bool few = (int64_t)cdiv(cdiv(p.rows, kRowsPerGroup), 4) * cdiv(p.cols, 64) < device_compute_units();
+  // 2048 x 512 -> 64 10.5 and 6.7, 1000 x 160 -> 33 7.6 and 5.6.  But not more of them than are on the device at once, three per
+  // compute unit, two of long rows of 8 bits: 24000 x 64 -> 64 of 8 bits (752) 7.7 and 7.5, 30000 (940) 7.7 and 9.0; 24000 x 512 -> 64
+  // of 4 bits (752) 10.5 and 9.5, 30000 10.8 and 12.1; 16384 x 512 -> 64 of 8 bits (512) 10.8 and 8.7, 20000 (628) 11.1 and
+  // 13.4.  (129 to 256 columns gain up to the end: 30000 x 256 -> 64 of 8 bits 11.2 and 10.8.)
+  const int lw = pick_lw(p), cus = device_compute_units();
+  const bool few = row_workgroups(p) * cdiv(p.cols, 64) < cus &&
+                   (lw == 4 || row_workgroups(p) * cdiv(p.cols, 16) <= (lw == 8 && p.s == 8 ? 2 : 3) * cus);
   switch (ntc == 4 && few ? 1 : ntc) {
     case 4: return dispatch_lw<SY, SW, 4>(p, stream);
     case 1: return dispatch_lw<SY, SW, 1>(p, stream);

@@ -712,7 +712,8 @@ def test_update_matrix_core_path_equals_popcount_and_oracle(st, shape):
 
 
 @pytest.mark.parametrize("st", [(4, 4), (8, 8), (3, 8)])
-@pytest.mark.parametrize("shape", [(33, 129, 17), (31, 256, 64), (500, 160, 130), (32800, 200, 64), (32768, 256, 33)])
+@pytest.mark.parametrize("shape", [(33, 129, 17), (31, 256, 64), (500, 160, 130), (32800, 200, 64), (32768, 256, 33),
+                                   (30000, 70, 40), (27000, 500, 33), (17000, 300, 64)])   # 16 columns each, and too many of them
 def test_update_of_five_to_eight_words_in_slices_of_16_and_64_columns(st, shape):
     """Rows of 5 to 8 words are one super-step; few rows have a workgroup per 16 columns, many one per 64."""
     s, t = st
