@@ -27,8 +27,8 @@
 // agree, so a lane of the Y side owns LW consecutive 16-bit pieces of its row per
 // "super-step":
 //   LW = 1: half a word   (K up to 64: the whole contraction is one step)
-//   LW = 2: one word      (rows that are not 16-byte aligned; as bytes)
-//   LW = 4: two words     (rows of up to 32 bytes: the whole contraction is one super-step)
+//   LW = 2: one word      (rows of 3 and 4 words, many rows of up to 8, rows that are not 16-byte aligned, bytes)
+//   LW = 4: two words     (aligned rows of 5 to 8 words: the whole contraction is one super-step)
 //   LW = 8: four words    (one 16-byte load per plane and lane; a wave reads the 16
 //                          rows x 64 bytes of a tile and plane as 1 KiB in one piece)
 // and runs LW steps on what it has loaded.
@@ -326,9 +326,15 @@ int pick_lw(const UpdParams& p) {
   if (p.y_bytes) return p.ldy * 4 <= 64 ? 1 : (p.ldy * 4 <= 128 ? 2 : 8);
   // four words per lane and plane are one 16-byte load: rows, planes and base at multiples of 16 bytes
   const bool vec = (p.ldy & 3) == 0 && (p.psy & 3) == 0 && ((uintptr_t)p.Y & 15u) == 0;
-  // up to 8 words: both words of a lane's part by one load and the whole row as one super-step, 16384 x 256 -> 64 with
-  // one word at a time 9.4 and 8.6 us (4 bits), 11.9 and 10.3 (8)
-  return p.kwords <= 2 ? 1 : ((p.kwords <= 4 || !vec) ? 2 : (p.kwords <= 8 ? 4 : 8));
+  if (p.kwords <= 2) return 1;
+  if (p.kwords <= 4 || !vec) return 2;
+  if (p.kwords > 8) return 8;
+  // 5 to 8 words: both words of a lane's part by one load and the whole row as one super-step, 16384 x 256 -> 64 with one
+  // word at a time 9.4 and 8.6 us (4 bits), 11.9 and 10.3 (8); 262144 x 256 -> 64 at 8 bits 40.4 and 32.2.  Below 8 bits it
+  // has two waves per SIMD instead of three, which rows of more than four workgroups per compute unit want back: 65536 x 256
+  // -> 128 at 4 bits 19.4 and 17.8, 100000 25.2 and 27.9, 262144 46.1 and 49.2.
+  const bool many = p.s < 8 && p.cols > 16 && row_workgroups(p) * cdiv(p.cols, 64) > 4 * device_compute_units();
+  return many ? 2 : 4;
 }
 
 size_t lds_bytes(const UpdParams& p, int ntc, int lw) {

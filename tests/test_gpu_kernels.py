@@ -713,9 +713,11 @@ def test_update_matrix_core_path_equals_popcount_and_oracle(st, shape):
 
 @pytest.mark.parametrize("st", [(4, 4), (8, 8), (3, 8)])
 @pytest.mark.parametrize("shape", [(33, 129, 17), (31, 256, 64), (500, 160, 130), (32800, 200, 64), (32768, 256, 33),
+                                   (131201, 150, 50), (131073, 256, 64),   # four workgroups per compute unit and more
                                    (30000, 70, 40), (27000, 500, 33), (17000, 300, 64)])   # 16 columns each, and too many of them
 def test_update_of_five_to_eight_words_in_slices_of_16_and_64_columns(st, shape):
-    """Rows of 5 to 8 words are one super-step; few rows have a workgroup per 16 columns, many one per 64."""
+    """Rows of 5 to 8 words are one super-step, up to a number of rows that depends on the bits; few rows have a workgroup
+    per 16 columns, many one per 64."""
     s, t = st
     n, d, h = shape
     rng = np.random.default_rng([12, s, t, n, h])
