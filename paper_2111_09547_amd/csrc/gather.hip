@@ -97,10 +97,13 @@ void set_grid(GatherParams* gp, int tiles) {
   if (run > (int64_t)p.nblocks / 8) run = p.nblocks / 8;
   p.run_shift = 0;
   while (((int64_t)2 << p.run_shift) <= run && p.run_shift < 24) ++p.run_shift;
-  // Their number grows with the rows.  1543 of them in 262144 rows, 16 -> 16: 256 workgroups 29.9, 512 17.7, 1024 15.9 us;
-  // without any, 64 -> 64 on 65536 rows, 8.8, 8.8 and 9.6; 512 columns, whose rows a workgroup takes as long as the
-  // caches deliver them, on 262144 rows 75, 1024 workgroups 82.
-  const int most = (p.ldx <= 128 && p.n_groups >= 16 * cus ? 4 : 2) * cus;
+  // Two per compute unit.  A visit for nothing costs the tiles more than half a microsecond per 512 of them (65536 rows, 16 -> 16 ->
+  // 16, without heavy rows: 20.1 us, with 1024 of them 20.9), and rows of more columns take as long as the caches deliver them
+  // (with 512 and 1024, us: 64 -> 64 -> 64 on 262144 rows of a power-law graph 80.0 and 82.9, 524288 130 and 133; 48 columns
+  // 66.8 and 69.6, 32 59.0 and 61.4; 512 -> 16 on 262144 75 and 82).  Of 16 columns, whose rows are round trips and
+  // little else, four from 262144 rows on: sums of 16 at 4 bits, twice, behind 512 -> 16 127.9 and 121.4, 16 -> 16 -> 16 47.1 and
+  // 44.4 (1540 heavy rows; with smaller blocks and fewer of them 39.3 and 40.8, without any 36.5 and 37.1).
+  const int most = (p.ldx <= 16 && p.n_groups >= 16 * cus ? 4 : 2) * cus;
   p.n_heavy_wg = p.block > kListLight ? (p.n_groups < most ? (p.n_groups + 7) / 8 * 8 : most / 8 * 8) : 0;
 }
 
