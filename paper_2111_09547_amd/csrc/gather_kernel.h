@@ -277,8 +277,8 @@ __device__ __forceinline__ void heavy_rows(const GatherParams& p, uint8_t* lds, 
   }
 }
 
-template <int LP, int WPT, int LT, int MODE, int PARTS>
-__global__ __launch_bounds__(256, 4) void gather_layer_kernel(const GatherParams p) {
+template <int LP, int WPT, int LT, int MODE, int PARTS, int WAVES>
+__global__ __launch_bounds__(256, WAVES) void gather_layer_kernel(const GatherParams p) {
   extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
   using Sh = GatherShape<LP, WPT, PARTS>;
   constexpr int P = Sh::P, PS = Sh::PS, RC = Sh::RC, HV = Sh::HV, UNITS = Sh::UNITS, W = Sh::W;
@@ -490,11 +490,19 @@ __global__ __launch_bounds__(256, 4) void gather_layer_kernel(const GatherParams
   else finish_tile<LT, MODE>(p, lds, yb, row0, out_ok, WPT == 1 ? 0 : wave, WPT == 1 ? LT : 4, rl, lane);
 }
 
-template <int LP, int WPT, int LT, int MODE, int PARTS>
+// WAVES: per SIMD, at least, which bounds the registers of a wave.  49 to 64 columns have 97 or 98 with all of their loads in
+// flight, which is four waves, and 96 with five; the others have as many waves either way, or lose with fewer registers
+// (256 -> 64 -> 64 on 65536 rows 51.2 us, with 96 registers 52.9).  Five where there are more workgroups than four waves hold.
+// Four and five, us, five layers of 64: 65536 rows (1024 workgroups) 55.4 and 59.7, 98304 75.6 and 75.1, 131072 88.9 and 88.1;
+// of a power-law graph, 131072 rows 94.4 and 92.5, 262144 148.8 and 135, 524288 248 and 225.
+template <int LP, int WPT, int LT, int MODE, int PARTS, int WAVES = 4>
 qgtc_status launch_one(const GatherParams& p, size_t lds, hipStream_t stream) {
+  if constexpr (LP == 2 && WPT == 1 && PARTS == 1 && WAVES == 4) {
+    if (p.nblocks > 4u * (unsigned)device_compute_units()) return launch_one<LP, WPT, LT, MODE, PARTS, 5>(p, lds, stream);
+  }
   static OncePerDevice once;
-  if (!allow_lds(once, reinterpret_cast<const void*>(&gather_layer_kernel<LP, WPT, LT, MODE, PARTS>), lds)) return QGTC_ERR_HIP;
-  hipLaunchKernelGGL((gather_layer_kernel<LP, WPT, LT, MODE, PARTS>), dim3((unsigned)p.n_heavy_wg + xcd_deal_grid(p.nblocks, p.run_shift)), dim3(256),
+  if (!allow_lds(once, reinterpret_cast<const void*>(&gather_layer_kernel<LP, WPT, LT, MODE, PARTS, WAVES>), lds)) return QGTC_ERR_HIP;
+  hipLaunchKernelGGL((gather_layer_kernel<LP, WPT, LT, MODE, PARTS, WAVES>), dim3((unsigned)p.n_heavy_wg + xcd_deal_grid(p.nblocks, p.run_shift)), dim3(256),
                      lds, stream, p);
   return launch_status();
 }

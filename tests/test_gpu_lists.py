@@ -621,3 +621,29 @@ def test_heavy_rows_of_a_large_graph_in_narrow_layers():
     nets = [QuantGNN(a, Ws, 8, 8, True, block_rows=block, lists=lists) for lists in (True, False)]
     ranges = nets[1].calibrate(x, (-3.0, 3.0))
     assert torch.equal(*[net.forward(x, (-3.0, 3.0), ranges) for net in nets])
+
+
+@pytest.mark.parametrize("dims,bn,update_first", [
+    ("64-50-64-12", False, False),                   # codes and fp32 from four output tiles, and from one
+    ("49-64-16-48-3", True, False),                  # behind an affine map
+    ("70-64-49", False, True),                       # sums of 49 and 64 columns
+])
+def test_layers_of_49_to_64_columns_with_more_workgroups_than_four_waves_per_simd_hold(dims, bn, update_first):
+    """65606 rows: more than four workgroups per compute unit, whose kernels have fewer registers.  Against layers of whole tiles."""
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    n, block = 65536 + 70, 128
+    a = (torch.rand((n, block), generator=gen, device="cuda") < 0.1).to(torch.uint8)
+    a[::301] = 1
+    a[n // block * block:, n % block:] = 0
+    d = [int(v) for v in dims.split("-")]
+    x = torch.randn((n, d[0]), generator=gen, device="cuda")
+    Ws = [torch.rand(dh, generator=gen, device="cuda") - 0.5 for dh in zip(d[:-1], d[1:])]
+    rng = np.random.default_rng(2)
+    norms = [BatchNorm(*(rng.uniform(lo, hi, h).tolist() for lo, hi in ((0.5, 1.5), (-0.3, 0.6), (-0.02, 0.04), (0.01, 0.04)))) for h in d[1:-1]] + [None]
+    nets = [QuantGNN(a, Ws, 8, 8, True, block_rows=block, lists=lists, update_first=update_first, batchnorm=norms if bn else None)
+            for lists in (True, False)]
+    assert nets[0].lists is not None and nets[1].lists is None
+    ranges = nets[1].calibrate(x, (-3.0, 3.0))
+    for ints in (True, False):
+        got, want = [net.forward(x, (-3.0, 3.0), ranges, want_int=ints) for net in nets]
+        assert torch.equal(got, want) and len(want.unique()) > 1000
