@@ -95,6 +95,10 @@ __device__ __forceinline__ void emit_sums(const GatherParams& p, int row, int co
 // words are taken up to eight at a time, us with both one by one and here: 512-16-16 on 262144 rows of a power-law graph
 // (1540 heavy rows, 236 of them from words) 199.9 and 196.4, update first 131.0 and 126.9, 128-32-32-16 on 131072 72.8 and 69.4
 // (without heavy rows 172, 110 and 54).
+// From 65 columns on the loads of a row's step are kept in front of its products: the compiler otherwise gives them one or
+// two registers in turn, a round trip per product.  On power-law graphs, us without and with: 454 -> 64 on 8192 rows 50.8
+// and 30.3, 700 -> 64 51.3 and 37.3, 200 -> 64 26.2 and 21.1, 128 -> 128 -> 64 29.6 and 26.9.  Narrower rows have several in a step
+// anyway, and more registers cost their tiles a wave (16 -> 16 -> 16 on 262144 rows 44.4 and 46.1).
 template <int LP, int LT, int MODE, int PARTS>
 __device__ __forceinline__ void heavy_rows(const GatherParams& p, uint8_t* lds, int wave, int lane) {
   using Sh = GatherShape<LP, 1, PARTS>;
@@ -205,6 +209,7 @@ __device__ __forceinline__ void heavy_rows(const GatherParams& p, uint8_t* lds, 
           v4i y[4];
 #pragma unroll
           for (int k = 0; k < 4; ++k) y[k] = nb.load(list_entry(idx, k), pofs);
+          all_in_flight<RC <= 2>();
 #pragma unroll
           for (int k = 0; k < 4; ++k) h = mfma_i8(ident, y[k], h);
           settle(h);
@@ -233,6 +238,7 @@ __device__ __forceinline__ void heavy_rows(const GatherParams& p, uint8_t* lds, 
                 y[b * STEPS + s] = nb.load(bit < 32u && ((wd >> (bit & 31u)) & 1u) ? col + bit : (uint32_t)kListNone, pofs);
               }
             }
+            all_in_flight<RC <= 2>();
 #pragma unroll
             for (int s = 0; s < NB * STEPS; ++s) h = mfma_i8(ident, y[s], h);
             settle(h);
