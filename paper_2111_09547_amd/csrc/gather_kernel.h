@@ -370,20 +370,33 @@ __global__ __launch_bounds__(256, WAVES) void gather_layer_kernel(const GatherPa
               r_own, v_own, own_unit_offset((uint32_t)(first_row + (u0 + j / PARTS) * RC), hv * 256u + j % PARTS * nb.part, (uint32_t)ldx, own_size), 0);
       }
       // The first block in up to three steps, each with all of its loads in flight: wide rows are few
-      // neighbours of many bytes from HBM, narrow ones more neighbours from the caches, few tiles all of them at once.
-      constexpr int K1 = WPT == 4 && P >= 16 ? 4 : P >= 16 ? 1 : 2;   // 4 K1 entries of every row, then up to 8, then all 16
-      constexpr int XK = K1 == 4 ? 4 : 2;
+      // neighbours of many bytes from HBM, narrow ones more neighbours from the caches.  Few tiles of wide rows are bound by the
+      // round trips instead and request at once what any row of the unit has, 4, 8 or 16 entries.  us, in steps, here, and always
+      // all 16: 300 columns on 15221 rows, 14 neighbours, in front of two layers 44.5, 43.0 and 42.8; 700 on 24576 rows
+      // of a power-law graph 66.4, 65.2 and 68.7, 2 neighbours 53.7, 52.6 and 56.5.  129 to 256 columns: launch_one().
+      constexpr int K1 = P >= 16 ? 1 : 2;            // 4 K1 entries of every row, then up to 8, then all 16
+      constexpr bool ONE = WPT == 4 && MODE != kGatherSums && (P >= 32 || (P >= 16 && WAVES == 4));
+      constexpr int XK = ONE ? 4 : 2;
       v4i acc[W], x[W][XK];
-      const bool five = K1 == 1 && __builtin_amdgcn_ballot_w64(most > 4) != 0ull, nine = K1 < 4 && __builtin_amdgcn_ballot_w64(most > 8) != 0ull;
+      const bool five = K1 == 1 && __builtin_amdgcn_ballot_w64(most > 4) != 0ull, nine = __builtin_amdgcn_ballot_w64(most > 8) != 0ull;
+      auto entries = [&](int k, int to) {
 #pragma unroll
-      for (int k = 0; k < K1; ++k)
+        for (int j = 0; j < W; ++j) x[j][to] = nb.load(list_entry(idx[j], k), pofs + j % PARTS * nb.part);
+      };
+      auto add = [&](int k) {
 #pragma unroll
-        for (int j = 0; j < W; ++j) x[j][k] = nb.load(list_entry(idx[j], k), pofs + j % PARTS * nb.part);
-      if (five) {
+        for (int j = 0; j < W; ++j) acc[j] = mfma_i8(ident, x[j][k], acc[j]);
+      };
 #pragma unroll
-        for (int j = 0; j < W; ++j) x[j][1] = nb.load(list_entry(idx[j], 1), pofs + j % PARTS * nb.part);
+      for (int k = 0; k < K1; ++k) entries(k, k);
+      if (five) entries(1, 1);
+      if constexpr (ONE) {
+        if (nine) {
+          entries(2, 2);
+          entries(3, 3);
+        }
       }
-      all_in_flight<K1 != 1>();
+      all_in_flight<K1 != 1 || ONE>();
       // (the own row, and 128 for every code that is code - 128)
 #pragma unroll
       for (int j = 0; j < W; ++j) {
@@ -392,23 +405,16 @@ __global__ __launch_bounds__(256, WAVES) void gather_layer_kernel(const GatherPa
         for (int r = 0; r < 4; ++r) acc[j][r] = bias + (int)(int8_t)(own[j] >> (8 * r));
       }
 #pragma unroll
-      for (int k = 0; k < K1; ++k)
-#pragma unroll
-        for (int j = 0; j < W; ++j) acc[j] = mfma_i8(ident, x[j][k], acc[j]);
-      if (five) {
-#pragma unroll
-        for (int j = 0; j < W; ++j) acc[j] = mfma_i8(ident, x[j][1], acc[j]);
-      }
+      for (int k = 0; k < K1; ++k) add(k);
+      if (five) add(1);
       if (nine) {
-#pragma unroll
-        for (int k = 0; k < 2; ++k)
-#pragma unroll
-          for (int j = 0; j < W; ++j) x[j][k] = nb.load(list_entry(idx[j], 2 + k), pofs + j % PARTS * nb.part);
-        all_in_flight<K1 != 1>();
-#pragma unroll
-        for (int k = 0; k < 2; ++k)
-#pragma unroll
-          for (int j = 0; j < W; ++j) acc[j] = mfma_i8(ident, x[j][k], acc[j]);
+        if constexpr (!ONE) {
+          entries(2, 0);
+          entries(3, 1);
+          all_in_flight<K1 != 1>();
+        }
+        add(XK - 2);
+        add(XK - 1);
       }
       // further blocks, a block's entries requested beside the products of the one in front
       if (__builtin_amdgcn_ballot_w64(most > kListBlock) != 0ull) {
@@ -430,7 +436,7 @@ __global__ __launch_bounds__(256, WAVES) void gather_layer_kernel(const GatherPa
 #pragma unroll
               for (int j = 0; j < W; ++j) x[j][k] = nb.load(list_entry(idx[j], 2 * h + k), pofs + j % PARTS * nb.part);
             if (h == 1) more(base + kListBlock);
-            all_in_flight<K1 != 1>();
+            all_in_flight<K1 != 1 || ONE>();
 #pragma unroll
             for (int k = 0; k < 2; ++k)
 #pragma unroll
@@ -501,10 +507,14 @@ __global__ __launch_bounds__(256, WAVES) void gather_layer_kernel(const GatherPa
 // (256 -> 64 -> 64 on 65536 rows 51.2 us, with 96 registers 52.9).  Five where there are more workgroups than four waves hold.
 // Four and five, us, five layers of 64: 65536 rows (1024 workgroups) 55.4 and 59.7, 98304 75.6 and 75.1, 131072 88.9 and 88.1;
 // of a power-law graph, 131072 rows 94.4 and 92.5, 262144 148.8 and 135, 524288 248 and 225.
+// 129 to 256 columns of which four waves share a tile: the whole first block at once and four waves up to three workgroups per
+// compute unit, in steps with 80 registers and six waves beyond.  200 -> 200 -> 64, 2 and 14 neighbours, us: 3584 rows (224
+// workgroups) in steps 25.4 and 28.1, at once 25.5 and 27.4; 12288 (768) 28.1 and 32.4, at once 28.3 and 32.2; 16384 (1024)
+// 31.5 and 36.2, at once 31.3 and 36.5; 24576 (1536) 38.1 and 45.6, at once 47.3 and 52.6.
 template <int LP, int WPT, int LT, int MODE, int PARTS, int WAVES = 4>
 qgtc_status launch_one(const GatherParams& p, size_t lds, hipStream_t stream) {
-  if constexpr (LP == 2 && WPT == 1 && PARTS == 1 && WAVES == 4) {
-    if (p.nblocks > 4u * (unsigned)device_compute_units()) return launch_one<LP, WPT, LT, MODE, PARTS, 5>(p, lds, stream);
+  if constexpr (PARTS == 1 && WAVES == 4 && (WPT == 1 ? LP == 2 : LP == 4 && MODE != kGatherSums)) {
+    if (p.nblocks > (WPT == 1 ? 4u : 3u) * (unsigned)device_compute_units()) return launch_one<LP, WPT, LT, MODE, PARTS, WPT == 1 ? 5 : 6>(p, lds, stream);
   }
   static OncePerDevice once;
   if (!allow_lds(once, reinterpret_cast<const void*>(&gather_layer_kernel<LP, WPT, LT, MODE, PARTS, WAVES>), lds)) return QGTC_ERR_HIP;

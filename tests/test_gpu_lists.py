@@ -623,16 +623,20 @@ def test_heavy_rows_of_a_large_graph_in_narrow_layers():
     assert torch.equal(*[net.forward(x, (-3.0, 3.0), ranges) for net in nets])
 
 
-@pytest.mark.parametrize("dims,bn,update_first", [
-    ("64-50-64-12", False, False),                   # codes and fp32 from four output tiles, and from one
-    ("49-64-16-48-3", True, False),                  # behind an affine map
-    ("70-64-49", False, True),                       # sums of 49 and 64 columns
+@pytest.mark.parametrize("n,block,dims,bn,update_first", [
+    # 49 to 64 columns, a wave per tile, more than four workgroups per compute unit
+    (65536 + 70, 128, "64-50-64-12", False, False),  # codes and fp32 from four output tiles, and from one
+    (65536 + 70, 128, "49-64-16-48-3", True, False), # behind an affine map
+    (65536 + 70, 128, "70-64-49", False, True),      # sums of 49 and 64 columns
+    # 129 to 256 columns, four waves per tile, more than three
+    (12288 + 35, 512, "129-200-256-70", False, False),
+    (12288 + 35, 512, "256-130-160-5", True, False),
 ])
-def test_layers_of_49_to_64_columns_with_more_workgroups_than_four_waves_per_simd_hold(dims, bn, update_first):
-    """65606 rows: more than four workgroups per compute unit, whose kernels have fewer registers.  Against layers of whole tiles."""
+@pytest.mark.parametrize("degree", [2.0, 12.0])
+def test_layers_of_more_workgroups_have_kernels_of_fewer_registers(n, block, dims, bn, update_first, degree):
+    """Against layers of whole tiles."""
     gen = torch.Generator(device="cuda").manual_seed(7)
-    n, block = 65536 + 70, 128
-    a = (torch.rand((n, block), generator=gen, device="cuda") < 0.1).to(torch.uint8)
+    a = (torch.rand((n, block), generator=gen, device="cuda") < degree / block).to(torch.uint8)
     a[::301] = 1
     a[n // block * block:, n % block:] = 0
     d = [int(v) for v in dims.split("-")]
@@ -646,4 +650,4 @@ def test_layers_of_49_to_64_columns_with_more_workgroups_than_four_waves_per_sim
     ranges = nets[1].calibrate(x, (-3.0, 3.0))
     for ints in (True, False):
         got, want = [net.forward(x, (-3.0, 3.0), ranges, want_int=ints) for net in nets]
-        assert torch.equal(got, want) and len(want.unique()) > 1000
+        assert torch.equal(got, want) and len(want.unique()) > 100     # (sums of two 8-bit codes alone take more)
