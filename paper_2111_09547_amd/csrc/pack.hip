@@ -815,8 +815,19 @@ extern "C" qgtc_status qgtc_pack_batch(const uint8_t* a_src, int64_t ld_a, const
   if (x) b.x = row_codes_params(x, ld_x, rows, x_cols, q, reinterpret_cast<uint8_t*>(buffer));
   // One launch where the bytes are read 16 at a time, a row's words fit its list, and the features are read 16 bytes at a time;
   // else one each.
-  const bool one = rows > 0 && (A->cols & 15) == 0 && A->cols <= 16 * kBatchPieces && (ld_a & 15) == 0 && ((uintptr_t)a_src & 15u) == 0 &&
+  bool one = rows > 0 && (A->cols & 15) == 0 && A->cols <= 16 * kBatchPieces && (ld_a & 15) == 0 && ((uintptr_t)a_src & 15u) == 0 &&
                    n <= kWeightJobs && (!x || (x_cols > 0 && left_bytes_wide(b.x)));
+  // Recorded, where a launch costs the host nothing, few long rows are split over more workgroups by launches of their own: the
+  // 64 rows of a workgroup are 96 KiB and more here, which one compute unit reads, and others idle.  New inputs at every
+  // replay, 20 columns of features, us of a step in one launch and in three: 8192 rows of 2048 36.7 and 31.0, 7680 of
+  // 1536 32.3 and 28.5, 16384 of 2048 38.5 and 35.0, 32768 43.9 and 43.9; 8192 of 1024 25.9 and 26.1.  With 128 columns, whose
+  // codes are beside the rows, 8192 of 2048 37.8 and 38.8; not recorded 31.7 and 36.6.
+  hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+  if (one && A->cols > 1024 && cdiv(rows, 64) <= device_compute_units() && (!x || 16 * (int64_t)x_cols < A->cols)) {
+    hipStreamCaptureStatus recorded = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &recorded) != hipSuccess) (void)hipGetLastError();
+    one = recorded == hipStreamCaptureStatusNone;
+  }
   if (!one) {
     if (x) st = qgtc_stack_input_and_weights(x, rows, x_cols, ld_x, q, buffer, buffer_bytes, ws, n, sums_of, col_sums, stream);
     else st = qgtc_pack_weights(ws, n, sums_of, col_sums, stream);
@@ -839,7 +850,6 @@ extern "C" qgtc_status qgtc_pack_batch(const uint8_t* a_src, int64_t ld_a, const
     b.x_step_w = (int32_t)(256 % b.x.ld);
     groups += left_bytes_wide_groups(b.x);
   }
-  hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   ProfScope prof(QGTC_KERNEL_PACK, s);
   hipLaunchKernelGGL(pack_batch_kernel, dim3(groups), dim3(256), 0, s, b);
   return launch_status();

@@ -609,6 +609,42 @@ def test_a_batch_is_packed_like_its_parts(rows, cols, block, extra, d, with_map,
         assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("rows,cols,d", [(130, 2048, 20), (700, 1056, 8), (100, 1024, 4), (200, 1536, 128)])
+@pytest.mark.parametrize("with_map", [True, False])
+def test_a_recorded_batch_is_packed_like_one_that_is_not(rows, cols, d, with_map):
+    """Few long rows go in launches of their own where they are recorded: every replay, on new inputs, against the call itself."""
+    gen = torch.Generator(device="cuda").manual_seed(rows + cols)
+    src, x = torch.zeros((rows, cols), dtype=torch.uint8, device="cuda"), torch.zeros((rows, d), device="cuda")
+    W = torch.rand((d, 17), generator=gen, device="cuda")
+    made = []
+    for _ in range(2):
+        A = B.alloc_bits(rows, cols, 1, B.LEFT, cols)
+        lists = B.qgtc_build_neighbours(B.qgtc_pack_bits(src, 1, B.LEFT, out=A))
+        lists.buffer.fill_(-1)
+        tmap = B._alloc_tile_map(A, 16, 32) if with_map else None
+        op = B.alloc_bits(d, 17, 8, B.RIGHT_BYTES)
+        sums = torch.zeros(17, dtype=torch.int32, device="cuda")
+        codes = torch.zeros(B.lib().qgtc_stack_buffer_bytes(rows, d) // 4 + 4, dtype=torch.int32, device="cuda")
+        weights = (B.WeightSources([W], [(0.0, 1.0)], [op]), 0, sums)
+        made.append(((src, A, lists, tmap, weights, x, 8, (-2.0, 2.0), codes),
+                     [A.words, lists.deg, lists.buffer, op.words, sums, codes] + ([tmap.row_cnt, tmap.deg] if with_map else [])))
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        B.qgtc_pack_batch(*made[0][0])
+    for _ in range(3):
+        src.copy_(torch.rand((rows, cols), generator=gen, device="cuda") < torch.rand((rows, 1), generator=gen, device="cuda") ** 4)
+        x.normal_(generator=gen)
+        for _, outs in made:
+            for out in outs:
+                out.zero_()
+        graph.replay()
+        B.qgtc_pack_batch(*made[1][0])
+        for got, want in zip(made[0][1], made[1][1]):
+            assert torch.equal(got, want)
+        assert len(made[0][1][0].unique()) > 20
+
+
 def test_heavy_rows_of_a_large_graph_in_narrow_layers():
     """262144 rows and more, of which more than the workgroups that take heavy rows have more neighbours than a tile's waves take."""
     gen = torch.Generator(device="cuda").manual_seed(5)
