@@ -1,7 +1,7 @@
 // Aggregation of long rows, C = A.X with A binary and X of at most 8 bits, on v_mfma_scale_f32_32x32x64_f8f6f4.
 //
-// The instruction takes 4-bit (E2M1) and 6-bit (E2M3) floats at one and a half times the rate of bytes (7.0 against
-// 4.4 POP/s from registers), and small integers are exact in both, as are fp32 sums below 2^24, which the rule in
+// The instruction takes 4-bit (E2M1) and 6-bit (E2M3) floats at twice the rate of bytes (8.2 to 9.6 against
+// 3.5 to 4.2 POP/s from registers, four sums per wave), and small integers are exact in both, as are fp32 sums below 2^24, which the rule in
 // dense_applies() keeps to.  What it saves more of is the way there:
 //   A  a word w of 32 bits is the 4-bit operand after five instructions instead of fifteen and in half the
 //      registers: w & 0x11111111, w & 0x22222222, w & 0x44444444 and (w >> 3) & 0x11111111, whose nibbles are

@@ -21,9 +21,9 @@
 // 4 KiB that a wave has in flight.  Waves wait 57 to 71 % of their time; the vector ALUs' 320 to 450 instructions per
 // wave are a third of the time of 64 -> 64 on 65536 rows, and 512 -> 16 reads at 2.1 TB/s.  Whole tiles and lists, us:
 // 65536 rows in blocks of 1024, 9 neighbours, 64 -> 64 13.2 and 9.0, 128 -> 128 19.5 and 15.0; 8192 rows,
-// 64 -> 64 8.6 and 4.1; 262144 rows of a power-law graph, 512 -> 16 159 and 85 (134 MB of codes: 27 at the
+// 64 -> 64 8.6 and 4.1; 262144 rows of a power-law graph, 512 -> 16 159 and 72 (134 MB of codes: 27 at the
 // rate of a copy), 1024 -> 64 on 65536 rows 168 and 95; without heavy rows 512 -> 16 320 and 64.
-// Waves in flight decide in wide rows: 512 -> 16 has five per SIMD (95 registers) and takes 79 us, with four 88, with three 102.
+// Waves in flight decide in wide rows: 512 -> 16 has five per SIMD (95 registers); with four and three it took 9 and 23 us longer.
 // Adding bytes up on the vector ALUs instead: 64 -> 64 11.0 us.  Heavy rows in the tiles' own waves: 512 -> 16
 // on the power-law graph 232 us.
 #pragma once
@@ -48,7 +48,7 @@ __device__ __forceinline__ uint32_t list_entry(const v2u& idx, int k) { return k
 
 // Keeps the compiler from moving loads behind products that could wait for them, for fewer registers than a wave may
 // have.  us with and without: 64 -> 64 on 65536 rows 8.8 and 9.6, fp32 out 12.4 and 12.9; 300 columns on 15221 rows,
-// 14 neighbours, 22.6 and 24.8 (all 16 entries at once), but 512 -> 16 on 262144 rows of a power-law graph 88 and 75.
+// 14 neighbours, 22.6 and 24.8 (all 16 entries at once), but 512 -> 16 on 262144 rows of a power-law graph 13 us more (four waves per SIMD).
 template <bool ON>
 __device__ __forceinline__ void all_in_flight() {
   if constexpr (ON) __builtin_amdgcn_sched_barrier(0);
