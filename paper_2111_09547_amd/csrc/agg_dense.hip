@@ -584,12 +584,9 @@ qgtc_status launch(DenseParams* dp, int xcd_run, hipStream_t stream) {
 template <int FMT, int CT>
 qgtc_status launch_rows(DenseParams* p, int rows, int xcd_run, hipStream_t stream) {
   if (rows == 256) return launch<FMT, 4, CT, 2, 4>(p, xcd_run, stream);
-  // (5 to 8 bits come here only where rows are many: aggregate_from_floats)
-  if (FMT == kTwoSixBits || rows == 128) return launch<FMT, 2, CT, 2, 4>(p, xcd_run, stream);
-  if constexpr (FMT != kTwoSixBits) {
-    if (rows == 64) return launch<FMT, 1, CT, 2, 4>(p, xcd_run, stream);
-    return launch<FMT, 1, CT, 1, 4>(p, xcd_run, stream);
-  }
+  if (rows == 128) return launch<FMT, 2, CT, 2, 4>(p, xcd_run, stream);
+  if (rows == 64) return launch<FMT, 1, CT, 2, 4>(p, xcd_run, stream);
+  return launch<FMT, 1, CT, 1, 4>(p, xcd_run, stream);
 }
 
 bool one_tile(const AggParams& p) { return p.cols <= 32 || dense_format(p.s) == kTwoSixBits; }   // of columns per workgroup

@@ -310,8 +310,10 @@ static bool aggregate_from_codes(const AggParams& p, const AggSplit& sp) {
 //   5 to 8 bits, two products per word and 32 columns per workgroup: undivided stages in one round of workgroups (16384 x 16384 x 64 at 8
 //   55.6 and 30.1; 13932 x 2760 x 384, 2.6 rounds, 44.6 and 53.9), with odd rows, whose stores cost bytes more (16551 x 3077 x 574,
 //   4.6 rounds, 124 and 101), or of more than 10240 columns without a map (16384 x 16384 x 256 90 and 78; with one of blocks of 256
-//   17815 x 17815 x 556 38.8 and 78.9); divided ones are level at best (461 x 8274 x 433 15.5 and 20.6).  Not 16 or fewer
-//   columns, half of whose tiles of 32 would be empty (12288 x 12288 x 16 17.9 and 20.1).
+//   17815 x 17815 x 556 38.8 and 78.9).  Divided ones up to 64 columns (with a launch beside them, as it is used: 10507 x 10507 x 24
+//   27.4 and 25.1, 16384 x 16384 x 32 34.7 and 31.2, 1000 x 9000 x 64 22.5 and 20.8, 300 x 30000 x 50 40.6 and 37.2; 5000 x 9000 x 40 22.8 and
+//   23.4; a map of blocks of 4096 9500 x 9500 x 32 21.1 and 21.4, 8300 x 8300 x 17 20.4 and 22.3), not more (461 x 8274 x 433 15.5 and 20.6).
+//   Not 16 or fewer columns, half of whose tiles of 32 would be empty (12288 x 12288 x 16 17.9 and 20.1).
 // With a map that leaves most tiles out floats lose some: the launch in front, and more rows per list (8192 x 8192 x 64 at 2
 // bits with eight full blocks on the diagonal 6.9 and 9.2, sixteen in 16384 x 16384 x 256 at 4 19.1 and 21.0; with every
 // tile 15.6 and 11.8, 89 and 46).  How full a map is only the device knows.
@@ -324,7 +326,7 @@ static bool aggregate_from_floats(const AggParams& p, const AggSplit& sp, bool o
     const int64_t rounds = cdiv(dense_groups(p, 256), cus);
     return p.s > 4 ? rounds == 1 || odd || (!p.row_cnt && p.a_words > 320) : !(p.block_rows > 0 && p.a_words <= 96 && rounds > 2);
   }
-  if (p.s > 4) return false;
+  if (p.s > 4) return long_rows && p.cols <= 64;
   if (p.cols <= 32) return long_rows || (p.rows >= 1024 && p.a_words > 224);
   const bool many = dense_groups(p, 32) > cus / 2;
   return (long_rows && (many || p.s <= 2)) || (many && p.a_words > 144);

@@ -959,17 +959,18 @@ def test_aggregation_of_long_rows(n, k, d, s, block, density, codes, with_map):
     (1030, 8193, 65, 0, "fbb"),    # 65 chunks, the last one of a column; three column groups, the last one of a column
     (1024, 4609, 64, 0, "ppp"),    # few workgroups
     (1024, 7169, 20, 0, "ffp"),    # 32 rows per workgroup
-    (1024, 65664, 33, 0, "fbb"),
-    (1025, 65792, 17, 0, "ffb"),
+    (1024, 65664, 33, 0, "fbf"),
+    (1025, 65792, 17, 0, "fff"),
     (2065, 65792, 500, 0, "fff"),  # sums up to the last exact ones at 8 bits
     (40 * 256 + 1, 8300, 250, 0, "fff"),
     (20 * 256 - 31, 8300, 130, 0, "fff"),
-    (20 * 256 - 31, 8300, 40, 0, "ffb"),
-    # up to 32 columns: 64, 128 and 256 rows per workgroup (5 to 8 bits: 128, 256)
+    (20 * 256 - 31, 8300, 40, 0, "fff"),
+    (8300, 8300, 40, 0, "fff"),    # 128 rows per workgroup at 5 to 8 bits
+    # up to 32 columns: 64, 128 and 256 rows per workgroup
     (8300, 7200, 20, 0, "ffp"),
     (16500, 2100, 20, 0, "fff"),
     (33000, 2100, 30, 0, "fff"),
-    # more: 32, 64, 128 and 256 rows (5 to 8 bits: 256 at 16500 rows, and room for floats where aligned rows take bytes)
+    # more: 32, 64, 128 and 256 rows (5 to 8 bits: 256 at 16500 rows)
     (7000, 4700, 40, 0, "ffp"),
     (8300, 4700, 40, 0, "ffp"),
     (16500, 4700, 40, 0, "fff"),
